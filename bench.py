@@ -28,8 +28,8 @@ PEAK_HBM_GBS = 8000.0
 GEMM_KERNEL_NAMES = {
     "qkv_proj": "gemm_bf16_ws_kernel<0> (Q/K/V projection, V as the transposed column range)",
     "qk_proj": "gemm_bf16_ws_kernel<0> (Q/K projection)",
-    "v_proj": "gemm_bf16_fast_kernel<..., true, 0> (V projection, transposed output)",
-    "o_proj": "gemm_bf16_ws_kernel<0> (output projection + residual), or gemm_bf16_fast_kernel on the active rows only",
+    "v_proj": "gemm_bf16_kernel<128, 128, 2, 2, true> (V projection, transposed output)",
+    "o_proj": "gemm_bf16_ws_kernel<0> (output projection + residual), or gemm_pipe_kernel<0> on the active rows only",
     "ffn_up": "gemm_bf16_ws_kernel<1> (FFN up-projection + ReLU)",
     "ffn_down": "gemm_bf16_ws_kernel<0> (FFN down-projection + residual)",
 }

@@ -287,6 +287,7 @@ extern "C" int32_t sf_pruned_ffn_forward(const sf_desc *desc, const sf_compact_l
     if (ly->k_ffn < 1 || ly->k_ffn > D.F) return fail(SF_ERR_INVALID_ARG, "pruned_ffn: k_ffn out of range");
     if (!ly->W1 || !ly->W2T) return fail(SF_ERR_INVALID_ARG, "pruned_ffn: NULL weight pointer");
     if (D.P > 1 && !pattern_id) return fail(SF_ERR_INVALID_ARG, "pruned_ffn: pattern_id required when P > 1");
+    if (D.P == 1) pattern_id = nullptr;
     const int Fp = (int)align_up(ly->k_ffn, D.ffn_pad);
     FfnWs w = ffn_ws(D, Fp, pre_ln != 0, workspace);
     if (!workspace || workspace_bytes < w.bytes || ((uintptr_t)workspace & 255))
@@ -358,6 +359,7 @@ static int32_t encoder_forward_impl(const sf_desc *desc, const sf_compact_layer 
     if (!layers || !X || !Y) return fail(SF_ERR_INVALID_ARG, "encoder: NULL argument");
     if (X == Y) return fail(SF_ERR_INVALID_ARG, "encoder: Y may not alias X");
     if (D.P > 1 && !pattern_id) return fail(SF_ERR_INVALID_ARG, "encoder: pattern_id required when P > 1");
+    if (D.P == 1) pattern_id = nullptr;          // every sample has the one weight set: GEMM tiles may then cross samples
     if ((D.flags & SF_FLAG_FINAL_LN) && (!final_g || !final_b))
         return fail(SF_ERR_INVALID_ARG, "encoder: final LayerNorm parameters missing");
     for (int l = 0; l < D.nl; ++l) {

@@ -26,7 +26,7 @@ struct GemmArgs {
     int act;
     const void *R; int64_t ldr; int r0;                  // residual (NULL = none), first column r0
     void *C; int64_t ldc; int c0;                        // EPI_ROWMAJOR: row stride, first column
-    const int32_t *row_map;                              // large bf16 row-major problems only (gemm_takes_row_map): row i
+    const int32_t *row_map;                              // bf16 row-major problems only (gemm_takes_row_map): row i
                                                          // of sample b reads A row row_map[b*L + i] (all of A within 4 GiB)
     int xcd_rows;                                        // hint: deal 256-row tiles to the 8 XCDs round-robin instead of in
                                                          // contiguous ranges (rows of unequal cost, e.g. n_lim / k_lim)
@@ -36,7 +36,7 @@ struct GemmArgs {
                                                          // elements = bytes), K % 128 == 0
     float out_scale;                                     // f8: factor of the sum of code products (the two tensor scales)
     int c_f8; float c_scale;                             // f8: C receives E4M3 codes of act(value) * c_scale (ldc in bytes)
-    void *VT; int vt_from;                               // large bf16 row-major problems only (gemm_takes_vt_split):
+    void *VT; int vt_from;                               // bf16 row-major problems only (gemm_takes_vt_split):
                                                          // features n >= vt_from go to VT[b, n - vt_from, i] (strides
                                                          // vt_b, vt_n, both % 8 == 0; vt_from % 8 == 0) instead of C
 };
@@ -71,6 +71,14 @@ int32_t proj_fp8_check(const char *who, const Dims &D, const sf_proj_fp8 *p, int
 void quantize_rows_fp8(const void *x, int64_t ld, int64_t rows, int K, int Kp, float inv_scale, uint8_t *codes, hipStream_t st);
 void transpose_v(const void *src, int64_t ld, int col0, int ncols, int B, int L, int Lp, void *vt, hipStream_t st,
                  const int32_t *row0 = nullptr);
+
+// The bf16 GEMM kernels: 256 x 256 tiles (gemm_bf16_ws.hip), 128 x 128 tiles and K slices (gemm_bf16_tile.hip)
+enum GemmKind { GEMM_WS, GEMM_PIPE, GEMM_SLICE4, GEMM_SLICE8 };
+bool gemm_bf16_ws_eligible(const GemmArgs &a);
+int32_t gemm_bf16_ws(const GemmArgs &a, hipStream_t st);
+bool gemm_bf16_tile_eligible(const GemmArgs &a);
+int32_t gemm_bf16_tile(GemmKind kind, const GemmArgs &a, hipStream_t st);
+GemmKind gemm_bf16_choose(const GemmArgs &a, bool ws_ok);
 
 // True when gemm() honours a.row_map for this problem (else it fails with SF_ERR_UNSUPPORTED).
 bool gemm_takes_row_map(int dtype, const GemmArgs &a);

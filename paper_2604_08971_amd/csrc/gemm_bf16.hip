@@ -27,7 +27,7 @@ __device__ __forceinline__ int swz(int row, int chunk) { return row * BK + ((chu
 __device__ __forceinline__ float apply_act(float z, int act)
 {
     if (act == ACT_RELU) return z > 0.f ? z : 0.f;
-    if (act == ACT_GELU) return 0.5f * z * (1.f + erff(z * 0.70710678118654752f));
+    if (act == ACT_GELU) return gelu_erf(z);
     return z;
 }
 
@@ -239,42 +239,39 @@ static int32_t launch_cfg(const GemmArgs &a, hipStream_t st)
     return SF_OK;
 }
 
-int32_t gemm_bf16_fast(const GemmArgs &a, hipStream_t st, bool &done);
-int32_t gemm_bf16_ws(const GemmArgs &a, hipStream_t st, bool &done);
-bool gemm_bf16_ws_eligible(const GemmArgs &a);
-
-bool gemm_takes_row_map(int dtype, const GemmArgs &a) { return dtype == SF_BF16 && gemm_bf16_ws_eligible(a); }
+bool gemm_takes_row_map(int dtype, const GemmArgs &a)
+{
+    return dtype == SF_BF16 && a.epi == EPI_ROWMAJOR && (gemm_bf16_ws_eligible(a) || gemm_bf16_tile_eligible(a));
+}
 bool gemm_takes_vt_split(int dtype, const GemmArgs &a)
 {
-    return dtype == SF_BF16 && gemm_bf16_ws_eligible(a) && a.vt_from > 0 && a.vt_from < a.N && a.vt_from % 8 == 0 &&
-           a.vt_b % 8 == 0 && a.vt_n % 8 == 0 && !a.R && !a.c_f32 && !a.n_lim;
+    return dtype == SF_BF16 && a.epi == EPI_ROWMAJOR && (gemm_bf16_ws_eligible(a) || gemm_bf16_tile_eligible(a)) &&
+           a.vt_from > 0 && a.vt_from < a.N && a.vt_from % 8 == 0 && a.vt_b % 8 == 0 && a.vt_n % 8 == 0 && !a.R &&
+           !a.c_f32 && !a.n_lim;
 }
 
-int32_t gemm_bf16(const GemmArgs &a, hipStream_t st)
+int32_t gemm_bf16(const GemmArgs &a0, hipStream_t st)
 {
+    GemmArgs a = a0;
     if (a.B <= 0 || a.N <= 0) return SF_OK;
-    if (a.VT && !gemm_takes_vt_split(SF_BF16, a)) return fail(SF_ERR_UNSUPPORTED, "gemm(bf16): transposed column range on a problem the large-tile kernel does not take");
-    if (a.row_map && !gemm_bf16_ws_eligible(a)) return fail(SF_ERR_UNSUPPORTED, "gemm(bf16): row_map on a problem the large-tile kernel does not take");
-    {
-        bool done = false;
-        if (int32_t rc = gemm_bf16_ws(a, st, done)) return rc;
-        if (done) return SF_OK;
-        if (int32_t rc = gemm_bf16_fast(a, st, done)) return rc;
-        if (done) return SF_OK;
+    if (a.VT && !gemm_takes_vt_split(SF_BF16, a)) return fail(SF_ERR_UNSUPPORTED, "gemm(bf16): transposed column range on a problem the tiled kernels do not take");
+    if (a.row_map && !gemm_takes_row_map(SF_BF16, a)) return fail(SF_ERR_UNSUPPORTED, "gemm(bf16): row_map on a problem the tiled kernels do not take");
+    // one weight set and row-major output: the samples are one long one, and no tile is cut at a sample's end
+    if (!a.pattern_id && a.epi == EPI_ROWMAJOR && !a.VT && !a.row_map && (int64_t)a.B * a.L * a.lda * 2 < ((int64_t)1 << 32)) {
+        a.L *= a.B;
+        a.B = 1;
+    }
+    const bool ws_ok = gemm_bf16_ws_eligible(a), tile_ok = gemm_bf16_tile_eligible(a);
+    if (ws_ok || tile_ok) {
+        const GemmKind kind = tile_ok ? gemm_bf16_choose(a, ws_ok) : GEMM_WS;
+        return kind == GEMM_WS ? gemm_bf16_ws(a, st) : gemm_bf16_tile(kind, a, st);
     }
     if (a.K % 8 || a.lda % 8 || a.ldw % 8 || a.N % 4 || a.n0 % 4 || (a.R && (a.ldr % 4 || a.r0 % 4)) ||
         (a.epi == EPI_ROWMAJOR && (a.ldc % 4 || a.c0 % 4)))
         return fail(SF_ERR_SHAPE, "gemm(bf16): K, leading dimensions and column origins must be multiples of 8/4");
     const bool swap = a.epi == EPI_VT;
     if (swap && (a.R || a.c_f32)) return fail(SF_ERR_UNSUPPORTED, "gemm(bf16): residual / fp32 output with transposed store");
-    const int64_t rows = (int64_t)a.B * a.L;
-    const bool big = a.L >= 192 && a.N >= 192 && rows * a.N >= (int64_t)256 * 256 * 256;
-    if (swap) {
-        if (big) return launch_cfg<256, 256, 2, 2, true>(a, st);
-        return launch_cfg<128, 128, 2, 2, true>(a, st);
-    }
-    if (big) return launch_cfg<256, 256, 2, 2, false>(a, st);
-    return launch_cfg<128, 128, 2, 2, false>(a, st);
+    return swap ? launch_cfg<128, 128, 2, 2, true>(a, st) : launch_cfg<128, 128, 2, 2, false>(a, st);
 }
 
 }  // namespace sf

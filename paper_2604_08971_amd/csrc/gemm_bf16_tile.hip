@@ -1,0 +1,625 @@
+// bf16 MFMA GEMMs for the launches that do not fill the chip with the 256 x 256 tiles of gemm_bf16_ws.hip (see
+// gemm_bf16.hip for the role of the GEMM and gemm.hpp for the arguments): short batches, short or ragged samples,
+// narrow outputs.  Two kernels share loads, layout and argument handling:
+//
+//  * gemm_pipe_kernel: 128 x 128 tiles, four waves of 64 x 64, two workgroups per compute unit (64 KB of LDS each), so
+//    that one workgroup's epilogue runs under the other's K loop.  What bounds it is LDS: a 64 x 64 wave tile reads
+//    16 KB of fragments per 16 MFMAs, a K tile of a workgroup moves 96 KB through the LDS (768 clocks at 128 B/clk)
+//    for 512 clocks of matrix work, which is why the 256 x 256 kernel (wave tiles of 128 x 64) stays ahead wherever
+//    its tiles fill the chip.  The K loop is software-pipelined by hand: fragments are read two k-steps ahead, also
+//    across the barrier, which therefore sits in the middle of a K tile - there every fragment of the tile is in
+//    registers, so the tile's own slot is free for the loads of the tile after next, and the next tile must have
+//    landed.  (The compiler's own order waits for the fragments right before their MFMAs: 10-15 % slower.)  Three or
+//    four ring slots with one workgroup per compute unit were slower everywhere (15-40 %).
+//  * gemm_slice_kernel: K sliced over the waves of a workgroup, for problems with a tile or two per compute unit: every
+//    wave owns the whole tile and every NWK-th K tile in an LDS region of its own, so there is no barrier and no wait
+//    on another wave until the partial tiles are summed through LDS.  Latency is all there is: 20 K tiles are
+//    20 dependent steps of 0.5 us for the pipelined kernel and three for eight slices.
+//
+// Measured (bf16, us; 256 x 256 kernel / pipe / slice): 512 rows, N 512, K 1280, fp32 residual 32.1 / 14.3 / 6.0;
+// 4096 rows, N 1280, K 512, ReLU 16.4 / 11.9 / 31.6; 24576 rows in samples of 384, N 256, K 192, residual
+// 24.8 / 12.6 / 37; 37777 rows in samples of 1021, N 384, K 960 77 / 47 / 112; 65536 rows, N 2176, K 768
+// 229 / 288 / 1109.
+#include <algorithm>
+#include <atomic>
+
+#include "gemm.hpp"
+
+namespace sf {
+
+namespace {
+
+constexpr int TBK = 64;                 // elements of K per ring slot
+constexpr int N_XCD = 8;
+
+typedef __attribute__((address_space(3))) void lds_void;
+typedef short i16x4 __attribute__((ext_vector_type(4)));
+
+// Element offset of (row, 16-byte chunk) in a [rows][64] tile: 256-byte super-rows of two rows, slot XOR super-row, so
+// that any 16 consecutive rows of one chunk fall into different LDS slots (16 lanes of a ds_read_b128 per cycle).
+__device__ __forceinline__ int lay(int row, int chunk)
+{
+    const int sr = row >> 1;
+    return sr * 128 + ((((row & 1) << 3) | chunk) ^ (sr & 7)) * 8;
+}
+
+template <int ACT>
+__device__ __forceinline__ float activate(float z)
+{
+    // integer max on the bit pattern: one instruction, -0 and negatives give +0
+    if (ACT == ACT_RELU) return __int_as_float(max(__float_as_int(z), 0));
+    if (ACT == ACT_GELU) return gelu_erf(z);
+    return z;
+}
+
+// The output tile of a workgroup.  Tiles are numbered N fastest and each XCD walks a contiguous range of them, so
+// that the workgroups of an XCD share activation rows and weight tiles in its L2.
+struct Tile { int b, m0, nt0, N, p; bool vt; };
+
+__device__ __forceinline__ bool find_tile(const GemmArgs &a, int bm, int bn, int tiles_m, int tiles_n, int total, int per_xcd,
+                                          Tile &t)
+{
+    int w = (blockIdx.x % N_XCD) * per_xcd + blockIdx.x / N_XCD;
+    if (a.xcd_rows) {
+        // rows of tiles of unequal cost: dealt to the XCDs round-robin
+        const int s = blockIdx.x / N_XCD;
+        w = ((s / tiles_n) * N_XCD + blockIdx.x % N_XCD) * tiles_n + s % tiles_n;
+    }
+    if (w >= total) return false;
+    const int tn_i = w % tiles_n, tm_i = w / tiles_n;
+    t.b = tm_i / tiles_m;
+    t.m0 = (tm_i % tiles_m) * bm;
+    t.p = a.pattern_id ? a.pattern_id[t.b] : 0;
+    if (t.p < 0) return false;                                     // sample not in use
+    t.vt = a.epi == EPI_VT;
+    t.nt0 = tn_i * bn;
+    t.N = a.n_lim ? min(a.N, a.n_lim[t.p]) : a.N;
+    if (a.VT) {
+        // two column ranges, each with its own tiles: [0, vt_from) row-major, [vt_from, N) transposed
+        const int ta = (a.vt_from + bn - 1) / bn;
+        t.vt = tn_i >= ta;
+        t.nt0 = t.vt ? a.vt_from + (tn_i - ta) * bn : tn_i * bn;
+        t.N = t.vt ? a.N : a.vt_from;
+    }
+    return t.nt0 < t.N;
+}
+
+// The operands of a tile as buffers: the base is the tile's first row, the scalar offset of a load walks K and a lane's
+// byte offset never changes.  The record count ends the buffer with the operand, so the K tail (K % 64 == 32: the
+// last K tile is half a tile) may request bytes behind a row - those of the next row, never used - but not behind
+// the operand.  Rows beyond the edge are clamped: they only feed outputs that are never stored.
+__device__ __forceinline__ uint32_t records(int64_t rows, int64_t ld, int K)
+{
+    const int64_t n = ((rows - 1) * ld + K) * 2;
+    return n < (int64_t)0xffffffff ? (uint32_t)n : 0xffffffffu;
+}
+
+struct Source { const char *x, *w; uint32_t nx, nw; };
+
+__device__ __forceinline__ Source sources(const GemmArgs &a, const Tile &t)
+{
+    Source s;
+    const int64_t row = (int64_t)t.b * a.L + t.m0;
+    s.x = static_cast<const char *>(a.A) + (a.row_map ? (int64_t)0 : row * a.lda * 2);
+    s.nx = a.row_map ? 0xffffffffu : records((int64_t)a.B * a.L - row, a.lda, a.K);
+    s.w = static_cast<const char *>(a.W) + ((int64_t)t.p * a.w_pstride + (int64_t)(a.n0 + t.nt0) * a.ldw) * 2;
+    s.nw = records(a.N - t.nt0, a.ldw, a.K);
+    return s;
+}
+
+// Byte offset, from the tile's first row, of the 16 bytes lane `lane` brings in for super-rows sr4*4 .. sr4*4+3
+__device__ __forceinline__ uint32_t lane_off(int sr4, int lane, int rows, int64_t ld, const int32_t *rmap)
+{
+    const int sr = sr4 * 4 + (lane >> 4), t = (lane & 15) ^ (sr & 7);
+    const int r = min(sr * 2 + (t >> 3), rows - 1);
+    return (uint32_t)(rmap ? rmap[r] : r) * (uint32_t)ld * 2u + (uint32_t)(t & 7) * 16u;
+}
+
+template <int N> __device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+// a bare barrier: __syncthreads() would wait for every load in flight
+__device__ __forceinline__ void barrier()
+{
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// ------------------------------------------------------------------------------------------------- pipelined tiles
+template <int ACT>
+__global__ __launch_bounds__(256, 2)
+void gemm_pipe_kernel(GemmArgs a, int tiles_m, int tiles_n, int total_tiles, int per_xcd)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int BM = 128, BN = 128, NW = 4;
+    constexpr int LX = BM / 8 / NW, LW = BN / 8 / NW, LPW = LX + LW;       // load instructions per wave and K tile
+    constexpr int STAGE = (BM + BN) * TBK * 2;                             // bytes per ring slot
+    extern __shared__ __attribute__((aligned(16))) char smem[];            // [2][X rows | W rows][128 bytes]
+
+    Tile tl;
+    if (!find_tile(a, BM, BN, tiles_m, tiles_n, total_tiles, per_xcd, tl)) return;
+    const bool vt = tl.vt;
+    const int N = tl.N, K = a.k_lim ? min(a.K, a.k_lim[tl.p]) : a.K;
+    const int nk = K / TBK, nkt = (K + TBK - 1) / TBK;                     // whole K tiles, K tiles with the tail
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int l32 = lane & 31, lhi = lane >> 5;
+
+    const Source src = sources(a, tl);
+    const auto xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(src.x), 0, (int)src.nx, 0x00020000);
+    const auto wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(src.w), 0, (int)src.nw, 0x00020000);
+    uint32_t xoff[LX], woff[LW];
+    {
+        const int32_t *rmap = a.row_map ? a.row_map + (int64_t)tl.b * a.L + tl.m0 : nullptr;
+        const int rows_x = min(BM, a.L - tl.m0), rows_w = min(BN, N - tl.nt0);
+#pragma unroll
+        for (int j = 0; j < LX; ++j) xoff[j] = lane_off(wave + j * NW, lane, rows_x, a.lda, rmap);
+#pragma unroll
+        for (int j = 0; j < LW; ++j) woff[j] = lane_off(wave + j * NW, lane, rows_w, a.ldw, nullptr);
+    }
+    auto issue = [&](int j, int kt, int slot) {
+        char *base = smem + slot * STAGE;
+        if (j < LX)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_void *)(base + (wave + j * NW) * 1024), 16,
+                                                     xoff[j < LX ? j : 0], kt * (TBK * 2), 0, 0);
+        else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, (lds_void *)(base + BM * 128 + (wave + (j - LX) * NW) * 1024), 16,
+                                                     woff[j < LX ? 0 : j - LX], kt * (TBK * 2), 0, 0);
+    };
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+        if (t < nkt) {
+#pragma unroll
+            for (int j = 0; j < LPW; ++j) issue(j, t, t);
+        }
+
+    // The accumulators start at the bias.  acc[i][j]: "A"-side tile i, "B"-side tile j; the A side are the features and
+    // the B side the tokens, exchanged for the transposed range, so that a staged row below is always a B-side row.
+    f32x16 acc[2][2];
+    {
+        const h16 *bias = a.bias ? static_cast<const h16 *>(a.bias) + (int64_t)tl.p * a.bias_pstride + a.n0 : nullptr;
+        if (vt) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const float f = bias ? (float)bias[min(tl.nt0 + wn * 64 + j * 32 + l32, N - 1)] : 0.f;   // clamped: never stored
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[0][j][e] = acc[1][j][e] = f;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    h16x4 bv = {};
+                    if (bias) bv = *reinterpret_cast<const h16x4 *>(bias + min(tl.nt0 + wn * 64 + i * 32 + q * 8 + lhi * 4, N - 4));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[i][0][q * 4 + e] = acc[i][1][q * 4 + e] = (float)bv[e];
+                }
+        }
+    }
+
+    // Byte addresses of this lane's fragments in a slot: tile t adds t * 4096 bytes, k-step s flips bits 5..6
+    const uint32_t abase = (uint32_t)lay((vt ? wm * 64 : BM + wn * 64) + l32, lhi) * 2u;
+    const uint32_t bbase = (uint32_t)lay((vt ? BM + wn * 64 : wm * 64) + l32, lhi) * 2u;
+    h16x8 af[4][2], bf[4][2];
+    auto read = [&](int s, int c, uint32_t slotb) {             // fragment c of k-step s: A0 B0 A1 B1
+        const uint32_t base = ((c & 1) ? bbase : abase) + slotb;
+        const h16x8 v = *reinterpret_cast<const h16x8 *>(smem + ((base ^ ((uint32_t)s << 5)) + (uint32_t)(c >> 1) * 4096u));
+        if (c & 1) bf[s][c >> 1] = v;
+        else af[s][c >> 1] = v;
+    };
+    if (nkt > 1) wait_vmcnt<LPW>();
+    else wait_vmcnt<0>();
+    barrier();
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) read(s, c, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t slotb = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+        const bool more = kt + 2 < nkt;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if (s == 2) {
+                asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+                barrier();
+            }
+            const uint32_t rs = s < 2 ? slotb : slotb ^ (uint32_t)STAGE;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                acc[c & 1][c >> 1] = SF_MFMA16(af[s][c & 1], bf[s][c >> 1], acc[c & 1][c >> 1], 0, 0, 0);
+                read((s + 2) & 3, c, rs);
+                __builtin_amdgcn_sched_barrier(0);              // keep this order: MFMA, read
+            }
+            if (s >= 2 && more) {
+#pragma unroll
+                for (int j = 0; j < LPW / 2; ++j) issue((s - 2) * (LPW / 2) + j, kt + 2, slotb ? 1 : 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        slotb ^= (uint32_t)STAGE;
+    }
+    if (nkt > nk) {                                             // K % 64 == 32: two more k-steps, already in registers
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[c & 1][c >> 1] = SF_MFMA16(af[s][c & 1], bf[s][c >> 1], acc[c & 1][c >> 1], 0, 0, 0);
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    barrier();
+
+    // ---- epilogue: a private 8 KB staging area per wave (64 rows of 128 bytes), whole rows to memory
+    char *stg = smem + wave * 8192;
+    const int64_t grow0 = (int64_t)tl.b * a.L;
+    const int mrow0 = tl.m0 + wm * 64, ncol0 = tl.nt0 + wn * 64;
+    const int er = lane >> 3, ec = lane & 7;                    // 8 lanes x 16 bytes = one row, 8 rows per instruction
+    if (vt || (!a.c_f32 && !a.R)) {
+        // 4 consecutive A-side values of a lane are one 8-byte LDS write; the chunk index only flips address bits 4..6
+        const uint32_t wbase = (uint32_t)lay(l32, 0) * 2u + (uint32_t)lhi * 8u;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    float v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float z = acc[i][j][q * 4 + e];
+                        v[e] = ACT == ACT_RELU ? z : activate<ACT>(z);
+                    }
+                    uint2 pw;
+                    pw.x = pack2_h16(v[0], v[1]);
+                    pw.y = pack2_h16(v[2], v[3]);
+                    i16x4 m = __builtin_bit_cast(i16x4, pw);
+                    if (ACT == ACT_RELU) {                      // on the rounded values: rounding never changes the sign
+                        const i16x4 z = {0, 0, 0, 0};
+                        m = __builtin_elementwise_max(m, z);
+                    }
+                    *reinterpret_cast<uint2 *>(stg + ((wbase ^ ((uint32_t)(i * 4 + q) << 4)) + (uint32_t)j * 4096u)) =
+                        __builtin_bit_cast(uint2, m);
+                }
+        if (vt) {
+            h16 *V = static_cast<h16 *>(a.VT ? a.VT : a.C) + (int64_t)tl.b * a.vt_b;
+            const int vf = a.VT ? a.vt_from : 0;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const h16x8 o = *reinterpret_cast<const h16x8 *>(stg + lay(j * 8 + er, ec) * 2);
+                const int n = ncol0 + j * 8 + er, i = mrow0 + ec * 8;
+                h16 *dst = V + (int64_t)(n - vf) * a.vt_n + i;
+                if (n < N && i + 7 < a.L) {
+                    *reinterpret_cast<h16x8 *>(dst) = o;
+                } else if (n < N) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        if (i + e < a.L) dst[e] = o[e];
+                }
+            }
+        } else {
+            h16 *cp = static_cast<h16 *>(a.C) + (grow0 + mrow0 + er) * a.ldc + a.c0 + ncol0 + ec * 8;
+            const bool col_ok = ncol0 + ec * 8 < N;             // N % 8 == 0: a chunk is all in or all out
+            const int rows_left = a.L - mrow0 - er;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const h16x8 o = *reinterpret_cast<const h16x8 *>(stg + lay(j * 8 + er, ec) * 2);
+                if (col_ok && j * 8 < rows_left) *reinterpret_cast<h16x8 *>(cp + (int64_t)(j * 8) * a.ldc) = o;
+            }
+        }
+        return;
+    }
+    // residual and / or fp32 output: 64 tokens x 32 features of fp32 at a time; the residual of a pass is read before the
+    // staging, so its latency is paid once per pass
+    const uint32_t wbase32 = (uint32_t)lay(l32, lhi) * 2u;
+    const int rows_left = a.L - mrow0 - er;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int n = ncol0 + i * 32 + ec * 4;
+        const bool col_ok = n < N;
+        const int64_t co0 = (grow0 + mrow0 + er) * a.ldc + a.c0 + n;
+        const int64_t ro0 = (grow0 + min(mrow0 + er, a.L - 1)) * a.ldr + a.r0 + min(n, N - 4);     // clamped: never stored
+        auto rrow = [&](int j) { return ro0 + (int64_t)min(j * 8, max(rows_left - 1, 0)) * a.ldr; };
+        f32x4 rr[8];
+        if (a.R && a.r_f32) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) rr[j] = *reinterpret_cast<const f32x4 *>(static_cast<const float *>(a.R) + rrow(j));
+        } else if (a.R) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const h16x4 t = *reinterpret_cast<const h16x4 *>(static_cast<const h16 *>(a.R) + rrow(j));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) rr[j][e] = (float)t[e];
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                f32x4 o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = activate<ACT>(acc[i][j][q * 4 + e]);
+                *reinterpret_cast<f32x4 *>(stg + ((wbase32 ^ ((uint32_t)(q * 2) << 4)) + (uint32_t)j * 4096u)) = o;
+            }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            f32x4 v = *reinterpret_cast<const f32x4 *>(stg + lay(j * 8 + er, ec) * 2);
+            if (a.R) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] += rr[j][e];
+            }
+            if (col_ok && j * 8 < rows_left) {
+                const int64_t co = co0 + (int64_t)(j * 8) * a.ldc;
+                if (a.c_f32) {
+                    *reinterpret_cast<f32x4 *>(static_cast<float *>(a.C) + co) = v;
+                } else {
+                    h16x4 o;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = (h16)v[e];
+                    *reinterpret_cast<h16x4 *>(static_cast<h16 *>(a.C) + co) = o;
+                }
+            }
+        }
+    }
+#endif
+}
+
+// ----------------------------------------------------------------------------------------------------- K slices
+// (TM * 32) x (TN * 32) tile; wave w takes the K tiles w, w + NWK, ... through its own LDS region.
+template <int TM, int TN, int NWK, int ACT>
+__global__ __launch_bounds__(64 * NWK)
+void gemm_slice_kernel(GemmArgs a, int tiles_m, int tiles_n, int total_tiles, int per_xcd)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int BM = TM * 32, BN = TN * 32, LX = BM / 8, LW = BN / 8, BUF = (BM + BN) * TBK * 2;     // bytes
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    Tile tl;
+    if (!find_tile(a, BM, BN, tiles_m, tiles_n, total_tiles, per_xcd, tl)) return;
+    const int N = tl.N, K = a.k_lim ? min(a.K, a.k_lim[tl.p]) : a.K;
+    const int nkt = (K + TBK - 1) / TBK;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, lhi = lane >> 5;
+    char *mine = smem + wave * BUF;
+
+    const Source src = sources(a, tl);
+    const auto xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(src.x), 0, (int)src.nx, 0x00020000);
+    const auto wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(src.w), 0, (int)src.nw, 0x00020000);
+    uint32_t xoff[LX], woff[LW];
+    {
+        const int32_t *rmap = a.row_map ? a.row_map + (int64_t)tl.b * a.L + tl.m0 : nullptr;
+        const int rows_x = min(BM, a.L - tl.m0), rows_w = min(BN, N - tl.nt0);
+#pragma unroll
+        for (int j = 0; j < LX; ++j) xoff[j] = lane_off(j, lane, rows_x, a.lda, rmap);
+#pragma unroll
+        for (int j = 0; j < LW; ++j) woff[j] = lane_off(j, lane, rows_w, a.ldw, nullptr);
+    }
+    f32x16 acc[TN][TM];                                         // [feature tile][token tile]
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    for (int kt = wave; kt < nkt; kt += NWK) {
+#pragma unroll
+        for (int j = 0; j < LX; ++j)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_void *)(mine + j * 1024), 16, xoff[j], kt * (TBK * 2), 0, 0);
+#pragma unroll
+        for (int j = 0; j < LW; ++j)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, (lds_void *)(mine + BM * 128 + j * 1024), 16, woff[j], kt * (TBK * 2), 0, 0);
+        wait_vmcnt<0>();
+        const int steps = min(4, (K - kt * TBK) / 16);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if (s >= steps) break;                              // uniform; only the K tail
+            h16x8 xf[TM], wf[TN];
+            const int chunk = s * 2 + lhi;
+#pragma unroll
+            for (int t = 0; t < TM; ++t) xf[t] = *reinterpret_cast<const h16x8 *>(mine + lay(t * 32 + l32, chunk) * 2);
+#pragma unroll
+            for (int t = 0; t < TN; ++t) wf[t] = *reinterpret_cast<const h16x8 *>(mine + BM * 128 + lay(t * 32 + l32, chunk) * 2);
+#pragma unroll
+            for (int i = 0; i < TN; ++i)
+#pragma unroll
+                for (int j = 0; j < TM; ++j) acc[i][j] = SF_MFMA16(wf[i], xf[j], acc[i][j], 0, 0, 0);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // this wave's fragments are in registers: reuse the region
+    }
+    barrier();
+    // partial tiles: part[wave][token][feature], fp32, 16-byte chunks of a row XOR-ed by the row
+    constexpr int CPR = BN / 4;
+    float *part = reinterpret_cast<float *>(smem);
+    auto po = [](int row, int c) { return row * BN + ((c ^ (row & (CPR - 1))) << 2); };
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                f32x4 o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = acc[i][j][q * 4 + e];
+                *reinterpret_cast<f32x4 *>(part + wave * BM * BN + po(j * 32 + l32, i * 8 + q * 2 + lhi)) = o;
+            }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    barrier();
+    const h16 *bias = a.bias ? static_cast<const h16 *>(a.bias) + (int64_t)tl.p * a.bias_pstride + a.n0 : nullptr;
+    constexpr int NT = 64 * NWK;
+    if (!tl.vt) {
+#pragma unroll 2
+        for (int c = threadIdx.x; c < BM * CPR; c += NT) {      // 4 features of a token per thread
+            const int r = c / CPR, cc = c % CPR, i = tl.m0 + r, n = tl.nt0 + cc * 4;
+            if (i >= a.L || n >= N) continue;
+            const int64_t row = (int64_t)tl.b * a.L + i;
+            f32x4 rv = {}, v = {};
+            if (a.R) {
+                const int64_t ro = row * a.ldr + a.r0 + n;
+                if (a.r_f32) {
+                    rv = *reinterpret_cast<const f32x4 *>(static_cast<const float *>(a.R) + ro);
+                } else {
+                    const h16x4 t = *reinterpret_cast<const h16x4 *>(static_cast<const h16 *>(a.R) + ro);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) rv[e] = (float)t[e];
+                }
+            }
+            if (bias) {
+                const h16x4 t = *reinterpret_cast<const h16x4 *>(bias + n);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = (float)t[e];
+            }
+#pragma unroll
+            for (int k = 0; k < NWK; ++k) {
+                const f32x4 t = *reinterpret_cast<const f32x4 *>(part + k * BM * BN + po(r, cc));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] += t[e];
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = activate<ACT>(v[e]) + rv[e];
+            const int64_t co = row * a.ldc + a.c0 + n;
+            if (a.c_f32) {
+                *reinterpret_cast<f32x4 *>(static_cast<float *>(a.C) + co) = v;
+            } else {
+                h16x4 o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = (h16)v[e];
+                *reinterpret_cast<h16x4 *>(static_cast<h16 *>(a.C) + co) = o;
+            }
+        }
+    } else {
+        h16 *V = static_cast<h16 *>(a.VT ? a.VT : a.C) + (int64_t)tl.b * a.vt_b;
+        const int vf = a.VT ? a.vt_from : 0;
+        for (int c = threadIdx.x; c < BN * (BM / 4); c += NT) {  // one feature of 4 tokens per thread
+            const int f = c / (BM / 4), r0 = (c % (BM / 4)) * 4, n = tl.nt0 + f, i = tl.m0 + r0;
+            if (n >= N) continue;
+            h16 *dst = V + (int64_t)(n - vf) * a.vt_n + i;
+            const float bv = bias ? (float)bias[n] : 0.f;
+            h16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float v = bv;
+#pragma unroll
+                for (int k = 0; k < NWK; ++k) v += part[k * BM * BN + po(r0 + e, f >> 2) + (f & 3)];
+                o[e] = (h16)activate<ACT>(v);
+            }
+            if (i + 3 < a.L) {
+                *reinterpret_cast<h16x4 *>(dst) = o;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (i + e < a.L) dst[e] = o[e];
+            }
+        }
+    }
+#endif
+}
+
+typedef void (*Kernel)(GemmArgs, int, int, int, int);
+
+// `attr_set` belongs to the kernel; setting the attribute twice is harmless
+int32_t launch(Kernel kern, std::atomic<bool> &attr_set, const GemmArgs &a, int bm, int bn, int threads, size_t lds, hipStream_t st)
+{
+    if (!attr_set) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
+            hipSuccess)
+            return fail(SF_ERR_HIP, "gemm: cannot reserve %zu bytes of LDS", lds);
+        attr_set = true;
+    }
+    const int tiles_m = ceil_div(a.L, bm);
+    const int tiles_n = a.VT ? ceil_div(a.vt_from, bn) + ceil_div(a.N - a.vt_from, bn) : ceil_div(a.N, bn);
+    const int total = a.B * tiles_m * tiles_n;
+    const int per_xcd = a.xcd_rows ? ceil_div(a.B * tiles_m, N_XCD) * tiles_n : ceil_div(total, N_XCD);
+    ProfScope prof(SF_KERNEL_GEMM, st);
+    hipLaunchKernelGGL(kern, dim3(per_xcd * N_XCD), dim3(threads), lds, st, a, tiles_m, tiles_n, total, per_xcd);
+    return SF_OK;
+}
+
+template <int ACT>
+int32_t launch_pipe(const GemmArgs &a, hipStream_t st)
+{
+    static std::atomic<bool> set{false};
+    return launch(gemm_pipe_kernel<ACT>, set, a, 128, 128, 256, 2 * 256 * TBK * 2, st);
+}
+
+template <int TM, int TN, int NWK, int ACT>
+int32_t launch_slice(const GemmArgs &a, hipStream_t st)
+{
+    static std::atomic<bool> set{false};
+    constexpr size_t loads = (size_t)NWK * (TM + TN) * 32 * TBK * 2, parts = (size_t)NWK * TM * TN * 1024 * 4;
+    return launch(gemm_slice_kernel<TM, TN, NWK, ACT>, set, a, TM * 32, TN * 32, 64 * NWK, loads > parts ? loads : parts, st);
+}
+
+template <int ACT>
+int32_t launch_kind(GemmKind kind, const GemmArgs &a, hipStream_t st)
+{
+    switch (kind) {
+    case GEMM_SLICE8: return launch_slice<1, 2, 8, ACT>(a, st);
+    case GEMM_SLICE4: return launch_slice<2, 2, 4, ACT>(a, st);
+    default: return launch_pipe<ACT>(a, st);
+    }
+}
+
+}  // namespace
+
+// 16-byte rows and columns, K a multiple of 32 (the K tail is half a tile), offsets within a tile below 4 GiB
+bool gemm_bf16_tile_eligible(const GemmArgs &a)
+{
+    if (a.K % 32 || a.K < TBK || a.N % 8 || a.n0 % 8 || a.lda % 8 || a.ldw % 8) return false;
+    if (a.epi == EPI_VT || a.VT) {
+        if (a.R || a.c_f32 || ((a.vt_b | a.vt_n) & 7)) return false;
+    }
+    if (a.epi == EPI_ROWMAJOR && (a.ldc % 8 || a.c0 % 8 || (a.R && (a.ldr % 8 || a.r0 % 8)))) return false;
+    // 32-bit byte offsets: within a tile, or (row_map) anywhere in A, which the caller keeps below 4 GiB
+    return a.lda < ((int64_t)1 << 23) && a.ldw < ((int64_t)1 << 23);
+}
+
+int32_t gemm_bf16_tile(GemmKind kind, const GemmArgs &a, hipStream_t st)
+{
+    switch (a.act) {
+    case ACT_RELU: return launch_kind<ACT_RELU>(kind, a, st);
+    case ACT_GELU: return launch_kind<ACT_GELU>(kind, a, st);
+    default: return launch_kind<ACT_NONE>(kind, a, st);
+    }
+}
+
+// Which kernel takes a problem: an estimate of each one's time in microseconds.  The constants are a fit to the
+// launches listed at the top of this file and about 40 more between 100 and 123 000 rows (one layer of every workload
+// at batches 1 to 256, K 128 to 2176): fixed cost, cost of a K tile and cost of an epilogue per workgroup and round.
+//   256 x 256: whole rounds of one workgroup per compute unit, 1.35 us per K tile (1.45 with a residual or fp32 output)
+//     and 4.5 us per output tile (15 with GELU), and a part of the HBM time that no other tile's K loop covers: all of
+//     it in a single round, 40 % (60 % with a residual or fp32 output) in many;
+//   128 x 128: a chain of 0.53 us per K tile while there is at most one workgroup per compute unit, 0.45 us per K tile
+//     and 2.6 us per tile and compute unit beyond (0.6 and 4.2, and a seventh of the HBM time, with a residual or fp32
+//     output);
+//   slices: rounds of 256 workgroups (eight slices), dearer from the second on, where the L2 feeds every compute unit
+//     with a tile of few rows; or one round of up to two per compute unit (four slices).
+// On 160 launches of layers drawn at random (10 to 130 000 rows, d 128 to 1024, kept heads and channels at random) the
+// choice is the fastest kernel for all but a few, where two of them are within 10-20 %; the largest gaps between the
+// kernels are factors of 3 to 6.
+GemmKind gemm_bf16_choose(const GemmArgs &a, bool ws_ok)
+{
+    auto tiles = [&](int bm, int bn) {
+        const int64_t n = a.VT ? ceil_div(a.vt_from, bn) + ceil_div(a.N - a.vt_from, bn) : ceil_div(a.N, bn);
+        return (double)(a.B * (int64_t)ceil_div(a.L, bm) * n);
+    };
+    const bool wide = a.R || a.c_f32;
+    const double nk = (a.K + TBK - 1) / TBK, rows = (double)a.B * a.L;
+    const double hbm = rows * (2.0 * a.K + a.N * ((a.c_f32 ? 4.0 : 2.0) + (!a.R ? 0.0 : a.r_f32 ? 4.0 : 2.0))) / 5.2e6;
+    const double rounds = ceil(tiles(256, 256) / 256);
+    const double bare = wide ? 0.6 + 0.4 / (rounds * rounds) : 0.4 + 0.6 / (rounds * rounds);
+    const bool gelu = a.act == ACT_GELU;
+    const double ws = 3.0 + rounds * ((wide ? 1.45 : 1.35) * nk + (gelu ? 15.0 : 4.5)) + bare * hbm;
+    const double q = tiles(128, 128) / 256;
+    const double pipe = 3.3 + (wide ? 0.15 * hbm : 0.0) +
+                        std::max(0.53 * nk + (wide ? 2.5 : 1.0), q * (wide ? 0.6 * nk + 4.2 : 0.45 * nk + (gelu ? 4.1 : 2.6)));
+    const double r8 = ceil(tiles(32, 64) / 256), c8 = ceil(nk / 8);
+    const double s8 = 2.3 + r8 * (r8 > 1 ? 1.9 + 1.35 * c8 : 1.5 + 0.95 * c8);
+    const double s4 = (wide ? 3.6 : 4.4) + std::max(1.0, tiles(64, 64) / 256) * (1.6 + 0.85 * ceil(nk / 4));
+    GemmKind best = GEMM_PIPE;
+    double t = pipe;
+    if (ws_ok && ws < t) { best = GEMM_WS; t = ws; }
+    if (s4 < t) { best = GEMM_SLICE4; t = s4; }
+    if (s8 < t) best = GEMM_SLICE8;
+    return best;
+}
+
+}  // namespace sf

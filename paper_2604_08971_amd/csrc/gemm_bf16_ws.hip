@@ -70,7 +70,7 @@ __device__ __forceinline__ float activate(float z)
 {
     // integer max on the bit pattern: one instruction, -0 and negatives give +0, no canonicalisation pass
     if (ACT == ACT_RELU) return __int_as_float(max(__float_as_int(z), 0));
-    if (ACT == ACT_GELU) return 0.5f * z * (1.f + erff(z * 0.70710678118654752f));
+    if (ACT == ACT_GELU) return gelu_erf(z);
     return z;
 }
 
@@ -645,12 +645,9 @@ bool gemm_bf16_ws_eligible(const GemmArgs &a)
     return true;
 }
 
-// Takes the problem (sets `done`) when it is eligible.
-int32_t gemm_bf16_ws(const GemmArgs &a, hipStream_t st, bool &done)
+// A problem that gemm_bf16_ws_eligible() accepts
+int32_t gemm_bf16_ws(const GemmArgs &a, hipStream_t st)
 {
-    done = false;
-    if (!gemm_bf16_ws_eligible(a)) return SF_OK;
-    done = true;
     switch (a.act) {
     case ACT_RELU: return launch_ws<ACT_RELU, false>(a, st);
     case ACT_GELU: return launch_ws<ACT_GELU, false>(a, st);

@@ -1,0 +1,34 @@
+"""The bf16 GEMM kernels that take what the 256 x 256 tiles do not: K slices (a few tiles) and 128 x 128 tiles, at the
+edges of their tiles and at a K tail of half a K tile, through the pruned FFN and the encoder against the oracle."""
+from __future__ import annotations
+
+import pytest
+
+from paper_2604_08971_amd import binding as sf
+from paper_2604_08971_amd import workloads as W
+from helpers import make_wl
+from test_gpu_parity import _encoder_parity, _ffn_case, _say
+
+pytestmark = pytest.mark.gpu
+
+
+# 32 x 64 and 64 x 64 slices: one row, one row past a tile, K of one tile / one and a half (d = 96) / more tiles than
+# slices; 128 x 128 tiles: one row short of and past a tile, widths that are no multiple of it, K tails
+@pytest.mark.parametrize("act,B,L,d,F,keep", [
+    (0, 1, 1, 64, 64, 1.0), (1, 1, 33, 96, 200, 0.5), (0, 2, 129, 96, 200, 0.7), (0, 1, 65, 640, 1280, 0.6),
+    (1, 4, 512, 512, 1024, 0.6), (0, 30, 127, 320, 1000, 0.64), (1, 30, 129, 352, 1000, 0.64), (0, 300, 1, 64, 136, 1.0),
+])
+def test_ffn_on_small_tiles(act, B, L, d, F, keep):
+    _say(f"small tiles act={act} B={B} L={L} d={d} F={F}")
+    _ffn_case("bf16", act, B, L, d, F, keep)
+
+
+# K = kept heads x 32: an odd number of heads leaves a K tail in the output projection; ragged lengths in the transposed
+# column range of the Q/K/V projection, with slices (B = 2) and 128 x 128 tiles (B = 40)
+@pytest.mark.parametrize("dtype,B,seg,drop", [("bf16", 2, (70, 50, 91), "bernoulli:0.3"), ("bf16", 40, (170, 91), "none"),
+                                              ("f16", 3, (33, 95), "none")])
+def test_encoder_with_an_odd_number_of_heads(dtype, B, seg, drop):
+    _say(f"odd heads {dtype} B={B} seg={seg}")
+    spec = W.small_spec(dtype=dtype, B=B, seg=seg, d=128, Hq=4, Hk=2, dh=32, F=256, head_keep=0.75, nl=2, dropout=drop)
+    with sf.use_half("f16" if dtype == "f16" else "bf16"):
+        _encoder_parity(make_wl(spec))
