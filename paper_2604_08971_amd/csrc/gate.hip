@@ -2,6 +2,8 @@
 // the global threshold that meets a cost budget (Sec. 4.5, the paragraph that introduces the three pruning
 // locations; Sec. 4.2 names the FLOPs / energy budget).  Both are plan-construction steps: tiny next to the
 // encoder forward, so the kernels aim at being exact and launch-cheap, not at a roofline.
+#include <atomic>
+
 #include "common.hpp"
 
 namespace sf {
@@ -76,112 +78,202 @@ __device__ inline float key_score(uint32_t k)
 
 struct BudgetCosts { int64_t head[MAX_LAYERS_BUDGET], group[MAX_LAYERS_BUDGET], ffn[MAX_LAYERS_BUDGET]; };
 
-// One block.  Sizes of the keep set { key(score) >= K } per layer (before the one-unit floor), into LDS.
-// `none` keeps nothing (the one-unit-per-layer network).
-__device__ void count_keep(const float *__restrict__ gh, const float *__restrict__ gf, int64_t lstride_h,
-                           int64_t lstride_f, int nl, int Hq, int Hk, int F, uint32_t K, bool none, int *kh, int *kg,
-                           int *kf, unsigned long long *gmask)
-{
-    const int tid = threadIdx.x, lane = tid & 63;
-    for (int l = tid; l < nl; l += blockDim.x) { kh[l] = 0; kf[l] = 0; gmask[l] = 0ull; }
-    __syncthreads();
-    if (!none) {
-        const int per_group = Hq / Hk;
-        for (int l = 0; l < nl; ++l) {
-            int c = 0;
-            for (int i = tid; i < F; i += blockDim.x) c += score_key(gf[l * lstride_f + i]) >= K;
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
-            if (lane == 0 && c) atomicAdd(&kf[l], c);
-            for (int hd = tid; hd < Hq; hd += blockDim.x)
-                if (score_key(gh[l * lstride_h + hd]) >= K) {
-                    atomicAdd(&kh[l], 1);
-                    atomicOr(&gmask[l], 1ull << (hd / per_group));
-                }
-        }
-    }
-    __syncthreads();
-    for (int l = tid; l < nl; l += blockDim.x) {
-        kg[l] = __popcll(gmask[l]);
-        if (kh[l] == 0) { kh[l] = 1; kg[l] = 1; }                   // the best head stays, with its group
-        if (kf[l] == 0) kf[l] = 1;                                  // the best channel stays
-    }
-    __syncthreads();
-}
+// The cost of a threshold K is a weighted count: c_fixed, plus one head, one K/V group and one channel per layer (which
+// always stay), plus the cost of every other unit whose key is >= K - heads and channels with their own keys, a K/V
+// group with the largest key of its heads, one best unit of each kind and layer left out.  So the threshold is found
+// as a weighted radix select: v, the largest key at which the cost exceeds the budget, eight bits per pass over a
+// histogram of costs (integers: the order of the atomics does not matter); the keep set is { key > v }.
+//
+// One block and latency-bound: the scores are read once (into LDS where they fit) and passed over four times, where a
+// bisection over the key's bits takes 32 passes.  Six layers of 8 heads and 2048 channels: 260 -> 16 us.
+constexpr int BUDGET_NT = 1024;
+constexpr int BUDGET_LDS_KEYS = 32768;                                // channels cached in LDS (128 KB)
 
-__global__ __launch_bounds__(1024) void budget_search_kernel(
+__global__ __launch_bounds__(BUDGET_NT) void budget_search_kernel(
     const float *__restrict__ gh, const float *__restrict__ gf, int64_t lstride_h, int64_t lstride_f, int nl, int Hq,
-    int Hk, int F, BudgetCosts costs, int64_t c_fixed, int64_t budget, float *__restrict__ tau_out,
+    int Hk, int F, int cached, BudgetCosts costs, int64_t c_fixed, int64_t budget, float *__restrict__ tau_out,
     int32_t *__restrict__ k_head_out, int32_t *__restrict__ k_ffn_out, int64_t *__restrict__ cost_out,
     int32_t *__restrict__ feasible_out)
 {
-    __shared__ int kh[MAX_LAYERS_BUDGET], kg[MAX_LAYERS_BUDGET], kf[MAX_LAYERS_BUDGET];
-    __shared__ unsigned long long gmask[MAX_LAYERS_BUDGET];
-    __shared__ uint32_t s_key;
-    __shared__ int s_ok;
-    const int tid = threadIdx.x;
+    extern __shared__ uint32_t fkeys[];                               // [nl][F] when cached
+    __shared__ unsigned long long hist[256];
+    __shared__ uint32_t gkey[MAX_LAYERS_BUDGET * 64];                 // [nl][Hk] largest key of a group's heads
+    __shared__ int best_h[MAX_LAYERS_BUDGET], best_g[MAX_LAYERS_BUDGET], best_f[MAX_LAYERS_BUDGET];
+    __shared__ uint32_t s_max, s_min, s_digit;
+    __shared__ long long s_rest, s_cost;
+    __shared__ int s_found;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int NWAVES = BUDGET_NT / 64;
 
-    auto cost_now = [&]() {                                          // thread 0, after count_keep
-        int64_t c = c_fixed;
-        for (int l = 0; l < nl; ++l) c += kh[l] * costs.head[l] + kg[l] * costs.group[l] + kf[l] * costs.ffn[l];
-        return c;
+    auto key_h = [&](int l, int i) { return score_key(gh[l * lstride_h + i]); };
+    auto key_f = [&](int l, int i) { return cached ? fkeys[l * F + i] : score_key(gf[l * lstride_f + i]); };
+
+    if (tid == 0) { s_max = 0u; s_min = 0xffffffffu; s_cost = 0; }
+    if (cached)
+        for (int l = 0; l < nl; ++l)
+            for (int i = tid; i < F; i += BUDGET_NT) fkeys[l * F + i] = score_key(gf[l * lstride_f + i]);
+    __syncthreads();
+
+    // a wave per layer: the best head, group and channel (first of the largest) and the groups' keys
+    auto first_of_max = [&](uint32_t mk, int mi, int &idx) {          // over the wave
+        uint32_t m = mk;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
+        int at = mk == m ? mi : 0x7fffffff;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) at = min(at, __shfl_xor(at, o));
+        idx = at;
+        return m;
     };
-
-    // the largest score present: the strictest threshold that is a candidate
-    if (tid == 0) s_key = 0u;
-    __syncthreads();
-    {
+    const int per_group = Hq / Hk;
+    for (int l = wave; l < nl; l += NWAVES) {
         uint32_t mk = 0u;
+        int mi = 0x7fffffff, idx;
+        for (int i = lane; i < F; i += 64) {
+            const uint32_t k = key_f(l, i);
+            if (k > mk || mi == 0x7fffffff) { mk = k; mi = i; }
+        }
+        const uint32_t mf = first_of_max(mk, mi, idx);
+        if (lane == 0) best_f[l] = idx;
+        mk = 0u;
+        mi = 0x7fffffff;
+        for (int i = lane; i < Hq; i += 64) {
+            const uint32_t k = key_h(l, i);
+            if (k > mk || mi == 0x7fffffff) { mk = k; mi = i; }
+        }
+        const uint32_t mh = first_of_max(mk, mi, idx);
+        if (lane == 0) {
+            best_h[l] = idx;
+            best_g[l] = idx / per_group;                              // the best head's group
+            atomicMax(&s_max, max(mf, mh));
+        }
+        if (lane < Hk) {
+            uint32_t g = 0u;
+            for (int j = 0; j < per_group; ++j) g = max(g, key_h(l, lane * per_group + j));
+            gkey[l * 64 + lane] = g;
+        }
+    }
+    __syncthreads();
+
+    // every unit but the ones that always stay: visit(key, cost, everyone in the wave has the same cost)
+    auto units = [&](auto visit) {
         for (int l = 0; l < nl; ++l) {
-            for (int i = tid; i < F; i += blockDim.x) mk = max(mk, score_key(gf[l * lstride_f + i]));
-            for (int i = tid; i < Hq; i += blockDim.x) mk = max(mk, score_key(gh[l * lstride_h + i]));
+            const int bf = best_f[l];
+            for (int i0 = 0; i0 < F; i0 += BUDGET_NT) {
+                const int i = i0 + tid;
+                const bool in = i < F && i != bf;
+                visit(in ? key_f(l, i) : 0u, in, costs.ffn[l]);
+            }
         }
-        atomicMax(&s_key, mk);
-    }
-    __syncthreads();
-    const uint32_t max_key = s_key;
-    __syncthreads();
+        for (int t0 = 0; t0 < nl * Hq; t0 += BUDGET_NT) {
+            const int t = t0 + tid, l = t / Hq, i = t % Hq;
+            const bool in = t < nl * Hq && i != best_h[l];
+            visit(in ? key_h(l, i) : 0u, in, in ? costs.head[l] : 0);
+        }
+        for (int t0 = 0; t0 < nl * Hk; t0 += BUDGET_NT) {
+            const int t = t0 + tid, l = t / Hk, i = t % Hk;
+            const bool in = t < nl * Hk && i != best_g[l];
+            visit(in ? gkey[l * 64 + i] : 0u, in, in ? costs.group[l] : 0);
+        }
+    };
+    long long base = c_fixed;
+    for (int l = 0; l < nl; ++l) base += costs.head[l] + costs.group[l] + costs.ffn[l];
 
-    count_keep(gh, gf, lstride_h, lstride_f, nl, Hq, Hk, F, max_key, false, kh, kg, kf, gmask);
-    if (tid == 0) s_ok = cost_now() <= budget;
-    __syncthreads();
-    const bool feasible = s_ok != 0;
-    __syncthreads();
-
-    uint32_t lo = 0u, hi = max_key;                                  // smallest K in [lo, hi] whose keep set fits
-    if (feasible) {
-        while (lo < hi) {                                            // uniform over the block
-            const uint32_t mid = lo + (hi - lo) / 2;
-            count_keep(gh, gf, lstride_h, lstride_f, nl, Hq, Hk, F, mid, false, kh, kg, kf, gmask);
-            if (tid == 0) s_ok = cost_now() <= budget;
+    uint32_t v = 0u, mask = 0u;
+    bool exceeds = budget >= base;                                    // is there a key at which the budget is exceeded?
+    if (tid == 0) s_rest = budget - base;
+    if (exceeds)
+        for (int pass = 0; pass < 4; ++pass) {                        // uniform over the block
+            const int shift = 24 - 8 * pass;
+            for (int j = tid; j < 256; j += BUDGET_NT) hist[j] = 0ull;
+            if (tid == 0) s_found = 0;
             __syncthreads();
-            if (s_ok) hi = mid; else lo = mid + 1;
+            units([&](uint32_t key, bool in, int64_t cost) {
+                const bool use = in && (key & mask) == v;
+                const uint32_t bin = (key >> shift) & 255u;
+                if (pass == 0) {
+                    // scores of one layer share a few exponents: one atomic per wave, bin and cost
+                    unsigned long long left = __ballot(use);
+                    while (left) {
+                        const int src = __ffsll((long long)left) - 1;
+                        const uint32_t b = (uint32_t)__shfl((int)bin, src);
+                        const long long c = __shfl((long long)cost, src);
+                        const unsigned long long same = __ballot(use && bin == b && cost == c) & left;
+                        if (lane == src) atomicAdd(&hist[b], (unsigned long long)c * (unsigned long long)__popcll(same));
+                        left &= ~same;
+                    }
+                } else if (use) {
+                    atomicAdd(&hist[bin], (unsigned long long)cost);
+                }
+            });
+            __syncthreads();
+            if (tid < 64) {
+                // lane owns bins 4*lane .. 4*lane+3: the bin in which the cost from the top passes the rest of the budget
+                long long h[4], local = 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) { h[j] = (long long)hist[4 * lane + j]; local += h[j]; }
+                long long incl = local;
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    const long long t = __shfl_down(incl, o);
+                    if (lane + o < 64) incl += t;
+                }
+                const long long rest = s_rest;
+                long long run = incl - local;                         // cost of the strictly higher bins
+#pragma unroll
+                for (int j = 3; j >= 0; --j) {
+                    if (run <= rest && run + h[j] > rest) { s_digit = (uint32_t)(4 * lane + j); s_cost = rest - run; s_found = 1; }
+                    run += h[j];
+                }
+            }
+            __syncthreads();
+            if (!s_found) { exceeds = false; break; }                 // pass 0 only: everything fits
+            v |= s_digit << shift;
+            mask |= 255u << shift;
+            if (tid == 0) s_rest = s_cost;
             __syncthreads();
         }
-    }
-    // final keep set, its cost, and the threshold as a score value: the smallest score >= K
-    count_keep(gh, gf, lstride_h, lstride_f, nl, Hq, Hk, F, lo, !feasible, kh, kg, kf, gmask);
-    if (tid == 0) s_key = 0xffffffffu;
+    // v: the largest key at which the budget is exceeded.  The strictest threshold is the largest score itself.
+    const bool feasible = budget >= base && !(exceeds && v >= s_max);
+    const uint32_t lo = exceeds ? v + 1u : 0u;                        // keep { key >= lo }; unused when infeasible
     __syncthreads();
-    if (feasible) {
+    if (tid == 0) s_cost = 0;
+    __syncthreads();
+    for (int l = wave; l < nl; l += NWAVES) {
+        int kf = 0, kh = 0, kg = 0;
         uint32_t mk = 0xffffffffu;
-        for (int l = 0; l < nl; ++l) {
-            for (int i = tid; i < F; i += blockDim.x) {
-                const uint32_t k = score_key(gf[l * lstride_f + i]);
-                if (k >= lo) mk = min(mk, k);
+        if (feasible) {
+            for (int i = lane; i < F; i += 64) {
+                const uint32_t k = key_f(l, i);
+                if (k >= lo) { ++kf; mk = min(mk, k); }
             }
-            for (int i = tid; i < Hq; i += blockDim.x) {
-                const uint32_t k = score_key(gh[l * lstride_h + i]);
-                if (k >= lo) mk = min(mk, k);
+            for (int i = lane; i < Hq; i += 64) {
+                const uint32_t k = key_h(l, i);
+                if (k >= lo) { ++kh; mk = min(mk, k); }
             }
+            if (lane < Hk) kg = gkey[l * 64 + lane] >= lo;
         }
-        atomicMin(&s_key, mk);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            kf += __shfl_xor(kf, o);
+            kh += __shfl_xor(kh, o);
+            kg += __shfl_xor(kg, o);
+            mk = min(mk, (uint32_t)__shfl_xor((int)mk, o));
+        }
+        if (lane == 0) {
+            if (kh == 0) { kh = 1; kg = 1; }                          // the best head stays, with its group
+            if (kf == 0) kf = 1;                                      // the best channel stays
+            k_head_out[l] = kh;
+            k_ffn_out[l] = kf;
+            atomicAdd(reinterpret_cast<unsigned long long *>(&s_cost),
+                      (unsigned long long)(kh * costs.head[l] + kg * costs.group[l] + kf * costs.ffn[l]));
+            atomicMin(&s_min, mk);
+        }
     }
     __syncthreads();
-    for (int l = tid; l < nl; l += blockDim.x) { k_head_out[l] = kh[l]; k_ffn_out[l] = kf[l]; }
     if (tid == 0) {
-        *tau_out = feasible ? key_score(s_key) : INFINITY;
-        *cost_out = cost_now();
+        *tau_out = feasible ? key_score(s_min) : INFINITY;            // the smallest score that is kept
+        *cost_out = c_fixed + s_cost;
         *feasible_out = feasible ? 1 : 0;
     }
 }
@@ -233,8 +325,17 @@ extern "C" int32_t sf_budget_search(const sf_desc *desc, const float *g_head, co
             return fail(SF_ERR_INVALID_ARG, "budget_search: negative cost in layer %d", l);
         bc.head[l] = c_head_host[l]; bc.group[l] = c_group_host[l]; bc.ffn[l] = c_ffn_host[l];
     }
-    hipLaunchKernelGGL(budget_search_kernel, dim3(1), dim3(1024), 0, static_cast<hipStream_t>(stream),
+    const bool cached = (int64_t)D.nl * D.F <= BUDGET_LDS_KEYS;
+    const size_t lds = cached ? (size_t)D.nl * D.F * sizeof(uint32_t) : 0;
+    static std::atomic<bool> attr_set{false};     // setting the attribute twice is harmless
+    if (!attr_set) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(budget_search_kernel),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, BUDGET_LDS_KEYS * 4) != hipSuccess)
+            return fail(SF_ERR_HIP, "budget_search: cannot reserve %d bytes of LDS", BUDGET_LDS_KEYS * 4);
+        attr_set = true;
+    }
+    hipLaunchKernelGGL(budget_search_kernel, dim3(1), dim3(BUDGET_NT), lds, static_cast<hipStream_t>(stream),
                        g_head + (int64_t)pattern * D.Hq, g_ffn + (int64_t)pattern * D.F, (int64_t)D.P * D.Hq,
-                       (int64_t)D.P * D.F, D.nl, D.Hq, D.Hk, D.F, bc, c_fixed, budget, tau, k_head, k_ffn, cost, feasible);
+                       (int64_t)D.P * D.F, D.nl, D.Hq, D.Hk, D.F, cached ? 1 : 0, bc, c_fixed, budget, tau, k_head, k_ffn, cost, feasible);
     return check_launch("budget_search");
 }
