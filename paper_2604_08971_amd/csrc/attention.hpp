@@ -49,7 +49,8 @@ __device__ __forceinline__ int64_t sample_row(const int32_t *row0, int b, int L)
 struct AttnPlan {
     int splits;            // key splits of the active pass (1 = write O directly)
     int keys_per_split;    // multiple of 64
-    int stat_chunks;       // partial-sum chunks of the K/V statistics
+    int stat_parts;        // key ranges of the K/V statistics (1 = one launch)
+    int score_parts;       // key ranges of the score stream (1 = the score itself)
     int Upad;              // U rounded up to 32
     int Lp;                // L rounded up to 8 (row length of the transposed V copy)
     int Sp;                // key-sample size rounded up to 64 (0: no sample)
@@ -61,13 +62,17 @@ struct AttnPlan {
 };
 AttnPlan attn_plan(int dtype, const AttnArgs &a, void *ws);
 
+constexpr int SLICE_U = 256;        // fewer active queries per head: the keys are dealt to the waves of a workgroup per head
+
 int32_t attention_forward(int dtype, const AttnArgs &a, hipStream_t st);
 
 // bf16 MFMA kernels (attention_bf16.hip)
 // score [B,scoreH,L]; sel [B,selH,U].  The score is taken over the Lk keys `Kx` (strides skx) with
 // validity key_mask [B,Lk] (NULL: all) and mean-key statistics `stats`; queries use a.key_valid.
+// parts > 1: over `parts` ranges of keys, part p at score + p * B*scoreH*L (-inf where a range has no allowed key).
 int32_t score_bf16(const AttnArgs &a, const void *Kx, sf_strides skx, int Lk, const uint8_t *key_mask,
-                   const float *stats, float *score, int scoreH, hipStream_t st);
+                   const float *stats, float *score, int scoreH, int parts, hipStream_t st);
+int score_bf16_parts(const AttnArgs &a, int Lk);
 int32_t attend_bf16(const AttnArgs &a, const AttnPlan &pl, const void *vt, sf_strides svt,
                     const int32_t *sel, int selH, hipStream_t st);
 
@@ -92,7 +97,5 @@ void lazy_ctx_proj_q8(const float *stats, const int32_t *head_group, int hg_stri
 void lazy_combine_ln(const void *x, bool x_f32, const int32_t *pos_of, const float *Cc, const void *bo, const float *cvec,
                      int B, int L, int capA, const void *gamma, const void *beta, float eps, int d, float *x1, void *xn,
                      float q_inv, hipStream_t st);
-
-constexpr int STAT_CHUNK = 128;     // keys per partial-sum block of the K/V statistics
 
 }  // namespace sf

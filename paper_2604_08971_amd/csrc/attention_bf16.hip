@@ -11,6 +11,9 @@
 // [dh, L] (key-contiguous) layout so that its fragments are plain vector
 // loads too.  K and V^T tiles are staged in LDS once per workgroup and shared
 // by all waves, i.e. by all heads of the K/V group.
+#include <algorithm>
+#include <atomic>
+
 #include "attention.hpp"
 
 namespace sf {
@@ -98,13 +101,16 @@ struct KTile {
 // mostly share the K/V group - run on one XCD and find K in its L2.  K tiles
 // are double-buffered in LDS and the next tile is prefetched into registers
 // while the current one is multiplied, so one barrier per tile suffices.
+// `parts` > 1: an item is also one range of key tiles (launches with few items: one 512-token sample and six heads are 12
+// items that walk eight tiles one after the other, 9.5 us; as 96 items of one tile 5.2 us).
 template <int DH, int QBS>
 __global__ __launch_bounds__(NWAVE * 64) SF_SCORE_OCC void score_bf16_kernel(
     const h16 *__restrict__ Q, sf_strides sq, const h16 *__restrict__ K, sf_strides sk,
     const int32_t *__restrict__ head_group, int hg_stride, const int32_t *__restrict__ pattern_id,
     const uint8_t *__restrict__ query_valid, const uint8_t *__restrict__ key_mask,
     const float *__restrict__ stats, int nH, int nG, int L, int Lk, float *__restrict__ score, int scoreH,
-    int qblocks, int n_items, const int32_t *__restrict__ row0, const int32_t *__restrict__ row0_k)
+    int qblocks, int n_items, int parts, int64_t part_stride, const int32_t *__restrict__ row0,
+    const int32_t *__restrict__ row0_k)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     h16 *Ks = reinterpret_cast<h16 *>(smem);                              // [2][BKEY][DH+PAD]
@@ -115,7 +121,7 @@ __global__ __launch_bounds__(NWAVE * 64) SF_SCORE_OCC void score_bf16_kernel(
 
     const int item = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
     if (item >= n_items) return;                          // uniform
-    const int qblk = item % qblocks, bh = item / qblocks, b = bh / nH, h = bh % nH;
+    const int qblk = item % qblocks, part = (item / qblocks) % parts, bh = item / (qblocks * parts), b = bh / nH, h = bh % nH;
     const int g = head_group[(int64_t)(pattern_id ? pattern_id[b] : 0) * hg_stride + h];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, lhi = lane >> 5;
     const uint8_t *kv = query_valid ? query_valid + (int64_t)b * L : nullptr;
@@ -139,7 +145,8 @@ __global__ __launch_bounds__(NWAVE * 64) SF_SCORE_OCC void score_bf16_kernel(
         rmax[qq] = -INFINITY;
     }
     __syncthreads();
-    build_tile_list(words, nwords, 0, Lk, tiles, &n_tiles);
+    const int kpp = ((Lk + BKEY - 1) / BKEY + parts - 1) / parts * BKEY;            // keys per part
+    build_tile_list(words, nwords, part * kpp, min(Lk, (part + 1) * kpp), tiles, &n_tiles);
     __syncthreads();
     const int nt = n_tiles;
 
@@ -211,7 +218,9 @@ __global__ __launch_bounds__(NWAVE * 64) SF_SCORE_OCC void score_bf16_kernel(
         const int i = q0 + qq * 32 + l32;
         if (lhi == 0 && i < L) {
             const bool ok = !kv || kv[i];
-            score[((int64_t)b * scoreH + h) * L + i] = !ok ? -INFINITY : nt == 0 ? 0.f : (m - dot) * scale;   // no key: 0
+            // no allowed key scores 0 (with parts: decided by the selection, which sees them all)
+            score[part * part_stride + ((int64_t)b * scoreH + h) * L + i] =
+                !ok ? -INFINITY : nt == 0 ? (parts > 1 ? -INFINITY : 0.f) : (m - dot) * scale;
         }
     }
 }
@@ -240,15 +249,9 @@ __device__ __forceinline__ float both_halves_sum(float v)
 // XCD and share its L2, and the items are spread evenly over the XCDs.
 constexpr int AWAVE = 8;
 
-// (139 registers at dh = 64: one workgroup per compute unit.  Capping the allocation at 128 registers so that two fit
-// was faster where the launch has more workgroups than compute units - C5 active pass 40 -> 33.5 us, C3 66 -> 49.5 us -
-// but the build with its eight spilled registers gave wrong rows whenever a pass left waves without a pair, with or
-// without the key groups and with or without a second workgroup on the compute unit; no cause was found in the
-// source, so that build is not used.)
-// NW = waves per workgroup.  Four instead of eight where a (sample, group) has at most four pairs: the same registers
-// per wave then leave room for three workgroups per compute unit, and no wave is without a pair.
-template <int DH, int QB, int NW>
-__global__ __launch_bounds__(NW * 64) void attend_bf16_kernel(
+// Serves head dimension 128 with U >= 256; the other shapes have kernels of their own below.
+template <int DH, int QB>
+__global__ __launch_bounds__(AWAVE * 64) void attend_bf16_kernel(
     const h16 *__restrict__ Q, sf_strides sq, const h16 *__restrict__ K, sf_strides sk,
     const h16 *__restrict__ VT, sf_strides svt, const int32_t *__restrict__ head_group, int hg_stride,
     const int32_t *__restrict__ pattern_id, const uint8_t *__restrict__ key_valid,
@@ -256,7 +259,7 @@ __global__ __launch_bounds__(NW * 64) void attend_bf16_kernel(
     int Upad, int splits, int keys_per_split, h16 *__restrict__ O, int64_t ldo,
     float *__restrict__ part_o, float *__restrict__ part_ml, const int32_t *__restrict__ row0)
 {
-    constexpr int NT = NW * 64;
+    constexpr int NW = AWAVE, NT = NW * 64;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int KT = BKEY * (DH + PAD), VT_ = DH * (BKEY + PAD);          // elements of one K / V^T tile
     h16 *Ks = reinterpret_cast<h16 *>(smem);                         // [2][BKEY][DH+PAD]
@@ -556,6 +559,235 @@ __global__ __launch_bounds__(NW * 64) void attend_bf16_kernel(
             }
         }
         __syncthreads();            // the next pass restages both tile buffers
+    }
+}
+
+// ------------------------------------------------- active pass, few active rows (U < 256)
+// A workgroup serves one (sample, head, block of 32 active queries) with the keys dealt to its waves in tiles of 32: wave w
+// takes every NW-th live tile, reads its K and V^T fragments straight from memory into registers - no LDS, no barrier, no
+// wait on another wave - and keeps a running softmax of its own; the NW partial results are merged through LDS at the
+// end.  U = c * ceil(ln L) gives one or two blocks of 32 queries per head, so K and V of a group are read only a few
+// times (from L2), and what counts is that every wave of every compute unit has loads in flight: staging the tiles in LDS
+// for all heads of a group walked them one after the other in one workgroup per (sample, group).  us, staged (with the
+// merge launch where the keys were split) / sliced: 256 samples of 480 keys, 4 heads 38 / 29; 64 of 384 keys, 6 heads
+// 11.6 / 8.0; 37 of 1021 keys, 8 heads 20 + 7 / 18; 16 of 4096 keys, 8 heads 31 + 6 / 37; 1 of 512 keys, 6 heads 10 + 4 / 8.5;
+// 128 of 512 keys, 6 heads in two groups 19 / 23 (the one case where sharing the tiles over six pairs pays).
+//
+// The keys of a tile are assigned to the rows of S^T so that a lane's 16 scores are two runs of 8 consecutive keys: row
+// 8 a + 4 h + r (a < 4, h < 2, r < 4) holds key 16 (a / 2) + 8 h + 4 (a % 2) + r.  P then meets V^T fragments that are
+// 16 contiguous bytes.
+template <int DH, int QB, int NW>
+__global__ __launch_bounds__(NW * 64, DH == 128 || QB * DH == 128 ? 2 : 3) void attend_slice_bf16_kernel(
+    const h16 *__restrict__ Q, sf_strides sq, const h16 *__restrict__ K, sf_strides sk,
+    const h16 *__restrict__ VT, sf_strides svt, const int32_t *__restrict__ head_group, int hg_stride,
+    const int32_t *__restrict__ pattern_id, const uint8_t *__restrict__ key_valid,
+    const int32_t *__restrict__ sel, int selH, int nH, int nG, int nqb, int n_items, int L, int Lp, int U,
+    h16 *__restrict__ O, int64_t ldo, const int32_t *__restrict__ row0)
+{
+    constexpr int KF = DH / 16, DB = DH / 32, OP = DH + 4;                // fragments of K, dim blocks, row of a partial
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    float *part = reinterpret_cast<float *>(smem);                        // [NW][32][OP], one query block at a time
+    float2 *ml = reinterpret_cast<float2 *>(part + NW * 32 * OP);         // [NW][QB * 32] reference, sum
+    int32_t *rows = reinterpret_cast<int32_t *>(ml + NW * QB * 32);       // [QB * 32] query of a slot
+    uint32_t *words = reinterpret_cast<uint32_t *>(rows + QB * 32);       // [ceil(L/32)] when there is a mask
+
+    const int item = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    if (item >= n_items) return;                                          // uniform
+    const int qb = item % nqb, bh = item / nqb, b = bh / nH, h = bh % nH;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, lhi = lane >> 5;
+    int qidx[QB];
+#pragma unroll
+    for (int qq = 0; qq < QB; ++qq) {
+        const int slot = (qb * QB + qq) * 32 + l32;
+        qidx[qq] = slot < U ? sel[((int64_t)b * selH + h) * U + slot] : -1;
+    }
+    const int g = head_group[(int64_t)(pattern_id ? pattern_id[b] : 0) * hg_stride + h];
+    const int nt = (L + 31) / 32;
+    if (key_valid) build_mask_words(key_valid + (int64_t)b * L, L, words, nt);
+    h16x8 qf[QB][KF];
+#pragma unroll
+    for (int qq = 0; qq < QB; ++qq) {
+        if (threadIdx.x < 32) rows[qq * 32 + threadIdx.x] = qidx[qq];
+        const h16 *qrow = Q + sample_offset(row0, b, sq) + (int64_t)h * sq.h + (int64_t)max(qidx[qq], 0) * sq.l;
+#pragma unroll
+        for (int kk = 0; kk < KF; ++kk) qf[qq][kk] = *reinterpret_cast<const h16x8 *>(qrow + kk * 16 + lhi * 8);
+    }
+    if (key_valid) __syncthreads();
+    if (__builtin_amdgcn_ballot_w64(qidx[0] >= 0) == 0ull) return;        // uniform over the workgroup: no row in these blocks
+
+    const h16 *Kb = K + sample_offset(row0, b, sk) + (int64_t)g * sk.h + lhi * 8;
+    const h16 *Vb = VT + (int64_t)b * svt.b + (int64_t)g * svt.h + (int64_t)l32 * svt.l + lhi * 8;
+    const int krow = 16 * (l32 >> 4) + 8 * ((l32 >> 2) & 1) + 4 * ((l32 >> 3) & 1) + (l32 & 3);
+    const float sc = LOG2E / sqrtf((float)DH);
+    auto word = [&](int t) -> uint32_t {                                  // allowed keys of tile t
+        if (key_valid) return (uint32_t)__builtin_amdgcn_readfirstlane((int)words[t]);
+        return t * 32 + 32 <= L ? 0xffffffffu : (1u << (L - t * 32)) - 1u;
+    };
+    // the wave's next tile: the live ones are dealt round-robin
+    int blk = -64, turn = 0;
+    unsigned long long live = 0ull;
+    auto next = [&]() -> int {
+        for (;;) {
+            while (!live) {
+                blk += 64;
+                if (blk >= nt) return -1;
+                live = __builtin_amdgcn_ballot_w64(blk + lane < nt && (!key_valid || words[blk + lane] != 0u));
+            }
+            const int t = blk + __ffsll((long long)live) - 1;
+            live &= live - 1ull;
+            const bool mine = turn == wave;
+            turn = turn + 1 == NW ? 0 : turn + 1;
+            if (mine) return t;
+        }
+    };
+    struct KV { h16x8 k[KF], v[DB][2]; };
+    auto load = [&](KV &x, int t) {
+        const h16 *kp = Kb + (int64_t)min(t * 32 + krow, L - 1) * sk.l;   // rows beyond L: masked
+#pragma unroll
+        for (int kk = 0; kk < KF; ++kk) x.k[kk] = *reinterpret_cast<const h16x8 *>(kp + kk * 16);
+#pragma unroll
+        for (int d = 0; d < DB; ++d)
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+                x.v[d][p] = *reinterpret_cast<const h16x8 *>(Vb + (int64_t)(d * 32) * svt.l + min(t * 32 + p * 16, Lp - 8 - lhi * 8));
+    };
+    f32x16 o[QB][DB];
+    float m_run[QB], l_run[QB];
+#pragma unroll
+    for (int qq = 0; qq < QB; ++qq) {
+        m_run[qq] = -INFINITY;
+        l_run[qq] = 0.f;
+#pragma unroll
+        for (int d = 0; d < DB; ++d)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) o[qq][d][e] = 0.f;
+    }
+    auto process = [&](KV &x, int t) {
+        f32x16 s[QB];
+#pragma unroll
+        for (int qq = 0; qq < QB; ++qq) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) s[qq][e] = 0.f;
+#pragma unroll
+            for (int kk = 0; kk < KF; ++kk) s[qq] = SF_MFMA16(x.k[kk], qf[qq][kk], s[qq], 0, 0, 0);
+        }
+        const uint32_t w = word(t);
+        if (w != 0xffffffffu) {                                           // scalar branch
+            const uint32_t wl = w >> (lhi * 8);                           // s[e]: key 16 (e / 8) + 8 lhi + e % 8
+#pragma unroll
+            for (int qq = 0; qq < QB; ++qq)
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    if (!((wl >> ((e / 8) * 16 + e % 8)) & 1u)) s[qq][e] = -INFINITY;
+            if (t * 32 + 32 > L) {                                        // V^T beyond L may hold anything
+#pragma unroll
+                for (int d = 0; d < DB; ++d)
+#pragma unroll
+                    for (int p = 0; p < 2; ++p)
+#pragma unroll
+                        for (int i = 0; i < 8; ++i)
+                            if (t * 32 + p * 16 + lhi * 8 + i >= L) x.v[d][p][i] = (h16)0.f;
+            }
+        }
+        h16x8 pf[QB][2];
+#pragma unroll
+        for (int qq = 0; qq < QB; ++qq) {
+            float mt = fmaxf(s[qq][0], s[qq][1]);
+#pragma unroll
+            for (int e = 2; e < 16; e += 2) mt = fmaxf(fmaxf(mt, s[qq][e]), s[qq][e + 1]);
+            mt = both_halves_max(mt) * sc;                                // sc > 0: max and scaling commute
+            // the reference of the exponentials moves only when some query exceeds it by 2^RESCALE_LOG2 (results are
+            // relative to it and do not depend on it)
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(mt > m_run[qq] + RESCALE_LOG2) != 0ull, 0)) {
+                const float m_new = fmaxf(m_run[qq], mt);
+                const float alpha = __builtin_amdgcn_exp2f(m_run[qq] - (m_new == -INFINITY ? 0.f : m_new));
+                m_run[qq] = m_new;
+                l_run[qq] *= alpha;
+#pragma unroll
+                for (int d = 0; d < DB; ++d)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) o[qq][d][e] *= alpha;
+            }
+            const float nm = m_run[qq] == -INFINITY ? 0.f : -m_run[qq];
+            float rs0 = 0.f, rs1 = 0.f;
+#pragma unroll
+            for (int e = 0; e < 16; e += 2) {
+                const float p0 = __builtin_amdgcn_exp2f(fmaf(s[qq][e], sc, nm)), p1 = __builtin_amdgcn_exp2f(fmaf(s[qq][e + 1], sc, nm));
+                rs0 += p0;
+                rs1 += p1;
+                reinterpret_cast<uint32_t *>(&pf[qq][e / 8])[(e % 8) / 2] = pack2_h16(p0, p1);
+            }
+            l_run[qq] += rs0 + rs1;
+        }
+#pragma unroll
+        for (int d = 0; d < DB; ++d)
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int qq = 0; qq < QB; ++qq) o[qq][d] = SF_MFMA16(x.v[d][p], pf[qq][p], o[qq][d], 0, 0, 0);
+    };
+    if constexpr (DH == 128) {                                            // no registers for a second tile
+        KV x;
+        for (int t = next(); t >= 0; t = next()) {
+            load(x, t);
+            process(x, t);
+        }
+    } else {
+        KV x, y;
+        int t = next();
+        if (t >= 0) load(x, t);
+        while (t >= 0) {                                                  // one tile ahead
+            int u = next();
+            if (u >= 0) load(y, u);
+            process(x, t);
+            if (u < 0) break;
+            t = next();
+            if (t >= 0) load(x, t);
+            process(y, u);
+        }
+    }
+    // merge: partial of wave w at part[w][query][dim]; lane owns query l32 and dims d*32 + q*8 + lhi*4 + {0..3}
+#pragma unroll
+    for (int qq = 0; qq < QB; ++qq) {
+        const float l_tot = both_halves_sum(l_run[qq]);
+        if (lhi == 0) ml[(wave * QB + qq) * 32 + l32] = make_float2(m_run[qq], l_tot);
+        if (qq > 0) __syncthreads();                                      // the last block's partials have been read
+        float *mine = part + (wave * 32 + l32) * OP + lhi * 4;
+#pragma unroll
+        for (int d = 0; d < DB; ++d)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                f32x4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = o[qq][d][q * 4 + e];
+                *reinterpret_cast<f32x4 *>(mine + d * 32 + q * 8) = v;
+            }
+        __syncthreads();
+        constexpr int CPR = DH / 4;
+        for (int c = threadIdx.x; c < 32 * CPR; c += NW * 64) {
+            const int q = c / CPR, d4 = (c % CPR) * 4, qi = rows[qq * 32 + q];
+            if (qi < 0) continue;
+            float m = -INFINITY;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) m = fmaxf(m, ml[(w * QB + qq) * 32 + q].x);
+            const float m_safe = m == -INFINITY ? 0.f : m;
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            float den = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const float2 t = ml[(w * QB + qq) * 32 + q];
+                const float wgt = __builtin_amdgcn_exp2f(t.x - m_safe);
+                den += wgt * t.y;
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(part + (w * 32 + q) * OP + d4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] += wgt * v[e];
+            }
+            const float inv = den > 0.f ? 1.0f / den : 0.f;
+            h16x4 out;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) out[e] = (h16)(acc[e] * inv);
+            *reinterpret_cast<h16x4 *>(O + (sample_row(row0, b, L) + qi) * ldo + (int64_t)h * DH + d4) = out;
+        }
     }
 }
 
@@ -895,27 +1127,39 @@ __global__ __launch_bounds__(AWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2
 // ---------------------------------------------------------------- host side
 template <int DH, int QBS>
 static int32_t launch_score(const AttnArgs &a, const void *Kx, sf_strides skx, int Lk, const uint8_t *key_mask,
-                            const float *stats, float *score, int scoreH, hipStream_t st)
+                            const float *stats, float *score, int scoreH, int parts, hipStream_t st)
 {
     const size_t lds = (size_t)2 * BKEY * (DH + PAD) * 2 + DH * 4 + (size_t)ceil_div(Lk, 32) * 4 +
                        (size_t)ceil_div(Lk, BKEY) * 2 + 16;
     const int qblocks = ceil_div(a.L, NWAVE * QBS * 32);
-    const int64_t items = (int64_t)qblocks * a.B * a.nH;
+    const int64_t items = (int64_t)qblocks * a.B * a.nH * parts;
     if (items > (1 << 30)) return fail(SF_ERR_SHAPE, "sparse_gqa(bf16): too many work items");
     dim3 grid((unsigned)align_up(items, 8));
     ProfScope prof(SF_KERNEL_SCORE, st);
     hipLaunchKernelGGL((score_bf16_kernel<DH, QBS>), grid, dim3(NWAVE * 64), lds, st, (const h16 *)a.Q,
                        a.sq, (const h16 *)Kx, skx, a.head_group, a.hg_stride, a.pattern_id, a.key_valid,
-                       key_mask, stats, a.nH, a.nG, a.L, Lk, score, scoreH, qblocks, (int)items, a.row0,
-                       Kx == a.K ? a.row0 : nullptr);
+                       key_mask, stats, a.nH, a.nG, a.L, Lk, score, scoreH, qblocks, (int)items, parts,
+                       (int64_t)a.B * scoreH * a.L, a.row0, Kx == a.K ? a.row0 : nullptr);
     return SF_OK;
 }
 
-int32_t score_bf16(const AttnArgs &a, const void *Kx, sf_strides skx, int Lk, const uint8_t *key_mask,
-                   const float *stats, float *score, int scoreH, hipStream_t st)
+static bool score_wide(const AttnArgs &a) { return a.L >= 1024; }
+
+// With at least a workgroup per compute unit the stream is not split; below that, towards two per compute unit, down
+// to one key tile each, and at most eight ways (the selection reads every part of a score).
+int score_bf16_parts(const AttnArgs &a, int Lk)
 {
-    const bool wide = a.L >= 1024;
-#define SF_SCORE_ARGS a, Kx, skx, Lk, key_mask, stats, score, scoreH, st
+    const int rows = NWAVE * 32 * (a.dh == 128 ? (score_wide(a) ? 2 : 1) : (score_wide(a) ? 4 : 2));      // per workgroup
+    const int64_t items = (int64_t)ceil_div(a.L, rows) * a.B * a.nH;
+    if (items >= 256) return 1;
+    return (int)std::min<int64_t>(std::min(ceil_div(Lk, BKEY), 8), (512 + items - 1) / items);
+}
+
+int32_t score_bf16(const AttnArgs &a, const void *Kx, sf_strides skx, int Lk, const uint8_t *key_mask,
+                   const float *stats, float *score, int scoreH, int parts, hipStream_t st)
+{
+    const bool wide = score_wide(a);
+#define SF_SCORE_ARGS a, Kx, skx, Lk, key_mask, stats, score, scoreH, parts, st
     switch (a.dh) {
     case 32:  return wide ? launch_score<32, 4>(SF_SCORE_ARGS) : launch_score<32, 2>(SF_SCORE_ARGS);
     case 64:  return wide ? launch_score<64, 4>(SF_SCORE_ARGS) : launch_score<64, 2>(SF_SCORE_ARGS);
@@ -934,12 +1178,7 @@ static int32_t launch_attend(const AttnArgs &a, const AttnPlan &pl, const void *
     const int nqb = pl.Upad / 32, BG = a.B * a.nG;
     // pair chunks per (sample, group) for evenly spread heads; a group with more heads takes several passes
     const int pairs = ceil_div(a.nH, a.nG) * nqb;
-    // four waves where the launch has a (sample, group) problem per compute unit or more (no key splits) and at most
-    // four pairs per problem (measured: C3 active pass 66 -> 49 us); with split keys the launch is short of work per
-    // compute unit and eight waves with key groups are faster (C5: 40 against 45 us); dh 128 needs 232 registers
-    // with four waves, i.e. one wave per SIMD
-    const int nw = (QB == 1 && DH <= 64 && pairs <= 4 && pl.splits == 1) ? 4 : AWAVE;
-    const int chunks = ceil_div(pairs, nw * QB);
+    const int chunks = ceil_div(pairs, AWAVE * QB);
     const int64_t items = (int64_t)chunks * BG * pl.splits;
     if (items > (1 << 30)) return fail(SF_ERR_SHAPE, "sparse_gqa(bf16): too many work items");
     dim3 grid((unsigned)align_up(items, 8));
@@ -950,13 +1189,34 @@ static int32_t launch_attend(const AttnArgs &a, const AttnPlan &pl, const void *
                            a.pattern_id, a.key_valid, sel, selH, a.nH, a.nG, BG, chunks, a.L, pl.Lp, a.U, pl.Upad,
                            pl.splits, pl.keys_per_split, (h16 *)a.O, a.ldo, pl.part_o, pl.part_ml, a.row0);
     } else {
-#define SF_ATTEND_ARGS grid, dim3(nw * 64), lds, st, (const h16 *)a.Q, a.sq, (const h16 *)a.K, a.sk, (const h16 *)vt, \
-                       svt, a.head_group, a.hg_stride, a.pattern_id, a.key_valid, sel, selH, a.nH, a.nG, BG, chunks, a.L, \
-                       pl.Lp, a.U, pl.Upad, pl.splits, pl.keys_per_split, (h16 *)a.O, a.ldo, pl.part_o, pl.part_ml, a.row0
-        if (nw == 4) hipLaunchKernelGGL((attend_bf16_kernel<DH, QB, DH <= 64 ? 4 : AWAVE>), SF_ATTEND_ARGS);
-        else hipLaunchKernelGGL((attend_bf16_kernel<DH, QB, AWAVE>), SF_ATTEND_ARGS);
-#undef SF_ATTEND_ARGS
+        hipLaunchKernelGGL((attend_bf16_kernel<DH, QB>), grid, dim3(AWAVE * 64), lds, st, (const h16 *)a.Q, a.sq, (const h16 *)a.K,
+                           a.sk, (const h16 *)vt, svt, a.head_group, a.hg_stride, a.pattern_id, a.key_valid, sel, selH, a.nH,
+                           a.nG, BG, chunks, a.L, pl.Lp, a.U, pl.Upad, pl.splits, pl.keys_per_split, (h16 *)a.O, a.ldo,
+                           pl.part_o, pl.part_ml, a.row0);
     }
+    return SF_OK;
+}
+
+template <int DH, int QB, int NW>
+static int32_t launch_attend_slice(const AttnArgs &a, const AttnPlan &pl, const void *vt, sf_strides svt, const int32_t *sel,
+                                   int selH, hipStream_t st)
+{
+    auto kern = attend_slice_bf16_kernel<DH, QB, NW>;
+    const size_t lds = (size_t)NW * 32 * (DH + 4) * 4 + (size_t)NW * QB * 32 * 8 + QB * 128 + (size_t)ceil_div(a.L, 32) * 4;
+    static std::atomic<bool> attr_set{false};     // setting the attribute twice is harmless
+    if (!attr_set) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) !=
+            hipSuccess)
+            return fail(SF_ERR_HIP, "sparse_gqa: cannot reserve LDS for the active pass");
+        attr_set = true;
+    }
+    const int nqb = ceil_div(pl.Upad / 32, QB);
+    const int64_t items = (int64_t)a.B * a.nH * nqb;
+    if (items > (1 << 30)) return fail(SF_ERR_SHAPE, "sparse_gqa(bf16): too many work items");
+    ProfScope prof(SF_KERNEL_ATTEND, st);
+    hipLaunchKernelGGL(kern, dim3((unsigned)align_up(items, 8)), dim3(NW * 64), lds, st, (const h16 *)a.Q, a.sq, (const h16 *)a.K,
+                       a.sk, (const h16 *)vt, svt, a.head_group, a.hg_stride, a.pattern_id, a.key_valid, sel, selH, a.nH, a.nG,
+                       nqb, (int)items, a.L, pl.Lp, a.U, (h16 *)a.O, a.ldo, a.row0);
     return SF_OK;
 }
 
@@ -964,11 +1224,24 @@ int32_t attend_bf16(const AttnArgs &a, const AttnPlan &pl, const void *vt, sf_st
                     const int32_t *sel, int selH, hipStream_t st)
 {
     if (a.nH > 64) return fail(SF_ERR_SHAPE, "sparse_gqa(bf16): at most 64 heads");
-    const bool many = a.U >= 256;       // dense-like: two query blocks per wave
-    switch (a.dh) {
-    case 32:  return many ? launch_attend<32, 2>(a, pl, vt, svt, sel, selH, st) : launch_attend<32, 1>(a, pl, vt, svt, sel, selH, st);
-    case 64:  return many ? launch_attend<64, 2>(a, pl, vt, svt, sel, selH, st) : launch_attend<64, 1>(a, pl, vt, svt, sel, selH, st);
-    case 128: return launch_attend<128, 1>(a, pl, vt, svt, sel, selH, st);
+    if (a.U >= SLICE_U) {                        // dense-like: two query blocks per wave
+        switch (a.dh) {
+        case 32: return launch_attend<32, 2>(a, pl, vt, svt, sel, selH, st);
+        case 64: return launch_attend<64, 2>(a, pl, vt, svt, sel, selH, st);
+        case 128: return launch_attend<128, 1>(a, pl, vt, svt, sel, selH, st);
+        }
+    } else {
+        // two query blocks per wave halve the reads of K and V (256 samples of 480 keys, 4 heads: 35 -> 29 us) where the
+        // heads alone fill the chip; four waves instead of eight where the items do
+        const int64_t heads = (int64_t)a.B * a.nH, nqb = pl.Upad / 32;
+        const bool two = nqb > 1 && heads >= 256, four = heads * nqb >= 512;
+#define SF_SLICE(DH, QB, NW) launch_attend_slice<DH, QB, NW>(a, pl, vt, svt, sel, selH, st)
+        switch (a.dh) {
+        case 32: return two ? SF_SLICE(32, 2, 4) : four ? SF_SLICE(32, 1, 4) : SF_SLICE(32, 1, 8);
+        case 64: return two ? SF_SLICE(64, 2, 4) : four ? SF_SLICE(64, 1, 4) : SF_SLICE(64, 1, 8);
+        case 128: return four ? SF_SLICE(128, 1, 4) : SF_SLICE(128, 1, 8);
+        }
+#undef SF_SLICE
     }
     return fail(SF_ERR_SHAPE, "sparse_gqa(bf16): dh must be 32, 64 or 128");
 }

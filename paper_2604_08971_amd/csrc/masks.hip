@@ -23,8 +23,7 @@ __device__ void keep_topk_block(const float *__restrict__ g, int n, int lp, int 
     int32_t *ix = idx + (size_t)lp * n;
 
     for (int i = threadIdx.x; i < n; i += NT) keys[i] = sortable_key(gs[i]);
-    __syncthreads();
-    block_topk<NT>(keys, n, k, scratch, [&](int i, bool kept, int pos) {
+    block_topk<NT>(keys, n, k, scratch, false, [&](int i, bool kept, int pos) {
         m[i] = kept ? 1 : 0;
         if (kept) ix[pos] = i;
     });
@@ -62,7 +61,7 @@ __global__ __launch_bounds__(NT) void keep_masks_kernel(
     int32_t *__restrict__ n_groups, int32_t *__restrict__ head_group)
 {
     extern __shared__ uint32_t keys[];
-    __shared__ int scratch[TOPK_SCRATCH];
+    __shared__ __attribute__((aligned(16))) int scratch[TOPK_SCRATCH];
     if ((int)blockIdx.x < n_lp) {
         const int lp = blockIdx.x;
         keep_topk_block<false, NT>(g_ffn, F, lp, kf.k[lp / P], ffn_mask, ffn_idx, 0, nullptr, nullptr, nullptr, keys, scratch);

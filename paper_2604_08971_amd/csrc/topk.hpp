@@ -3,27 +3,43 @@
 // (Sec. 4.5) and for the top-U query choice of SentryAttend (Sec. 4.4).
 //
 // The k-th largest key is found by a 4-pass radix select (8 bits per pass, a
-// 256-bin LDS histogram with integer atomics: the counts, hence the result,
-// do not depend on the order of the atomics).  The kept indices are then
-// emitted in ascending order from contiguous per-thread index ranges with two
-// block-wide prefix sums.
+// 256-bin LDS histogram per pass with integer atomics: the counts, hence the
+// result, do not depend on the order of the atomics).  The kept indices are then
+// emitted in ascending order from contiguous per-thread index ranges with one
+// block-wide prefix sum.  Barriers and cross-lane moves are what it costs on short
+// rows, so there is one barrier per pass (every wave scans the histogram for itself)
+// and two around them: keep sets of 1024 channels 9.1 -> 8.2 us with the launch, 4096
+// query scores 14.6 -> 12.7.
 #pragma once
 
 #include "common.hpp"
 
 namespace sf {
 
-constexpr int TOPK_SCRATCH = 256 + 16 + 2;      // ints of LDS scratch block_topk needs
+constexpr int TOPK_SCRATCH = 4 * 256 + 16;      // ints of LDS scratch block_topk needs (16-byte aligned)
+
+// Inclusive prefix sum over the 64 lanes of a wave, in registers (data-parallel primitives: shifts by 1, 2, 4 and 8 inside
+// a row of 16 lanes, then the last lane of a row added to the rows behind it); six cross-lane moves through the LDS
+// permute path take about 600 clocks one after the other, these about 60.
+__device__ __forceinline__ int wave_incl_scan(int x)
+{
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);      // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);      // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);      // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);      // row_shr:8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);      // row_bcast:15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);      // row_bcast:31 into rows 2 and 3
+    return x;
+}
 
 // Sum of one int per thread over the block; every thread gets the total.
 // `red` is LDS scratch of at least NT/64 ints.
 template <int NT>
 __device__ __forceinline__ int block_sum(int v, int *red)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    v = wave_incl_scan(v);
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = v;
     __syncthreads();
     int t = 0;
 #pragma unroll
@@ -31,93 +47,82 @@ __device__ __forceinline__ int block_sum(int v, int *red)
     return t;
 }
 
-// Exclusive prefix sum of one int per thread in thread order; `total` gets the
-// block total.  `red` is LDS scratch of at least NT/64 ints.
-template <int NT>
-__device__ __forceinline__ int block_excl_scan(int v, int *red, int &total)
-{
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(x, o);
-        if (lane >= o) x += t;
-    }
-    __syncthreads();
-    if (lane == 63) red[w] = x;
-    __syncthreads();
-    int off = 0, t = 0;
-#pragma unroll
-    for (int i = 0; i < NT / 64; ++i) {
-        const int c = red[i];
-        if (i < w) off += c;
-        t += c;
-    }
-    total = t;
-    return off + x - v;
-}
-
-// keys[0..n) in LDS (already synchronised).  Selects the k largest
-// (1 <= k <= n).  For every index i, in ascending order within a thread,
-// calls emit(i, kept, pos) where pos is the rank of i among the kept indices
-// (ascending index order) when kept.  Must be called by all NT threads;
-// `scratch` is LDS of TOPK_SCRATCH ints.
+// keys[0..n) in LDS, n <= 16384; the caller's writes to it need no barrier of their own, but `scratch` must not be in
+// use.  Selects the k largest (1 <= k <= n).  For every index i, in ascending order within a thread, calls
+// emit(i, kept, pos) where pos is the rank of i among the kept indices (ascending index order) when kept; at that point
+// keys[i] is read by nobody else any more.  `positive`: k is the number of keys > 0 (no search).  Must be called by all NT threads; `scratch` is LDS of TOPK_SCRATCH ints.
 template <int NT, class Emit>
-__device__ void block_topk(const uint32_t *keys, int n, int k, int *scratch, Emit emit)
+__device__ void block_topk(uint32_t *keys, int n, int k, int *scratch, bool positive, Emit emit)
 {
-    int *hist = scratch, *red = scratch + 256, *res = scratch + 256 + 16;
-    const int tid = threadIdx.x, lane = tid & 63;
-    __syncthreads();        // nobody may still be reading `scratch` (or writing `keys`) from before the call
+    int *red = scratch + 4 * 256;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    for (int j = tid; j < 4 * 256; j += NT) scratch[j] = 0;
+    __syncthreads();
 
     // k-th largest key T, most significant byte first
     uint32_t prefix = 0, mask = 0;
-    int kk = k;
+    int kk = positive ? 0 : k;
+#pragma unroll
     for (int pass = 0; pass < 4; ++pass) {
+        if (positive) break;
         const int shift = 24 - 8 * pass;
-        for (int j = tid; j < 256; j += NT) hist[j] = 0;
-        __syncthreads();
-        for (int i = tid; i < n; i += NT) {
-            const uint32_t key = keys[i];
-            if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1);
+        int *hist = scratch + pass * 256;
+        for (int i0 = 0; i0 < n; i0 += NT) {                    // the same trip count for every lane of a wave
+            const int i = i0 + tid;
+            const uint32_t key = i < n ? keys[i] : 0u;
+            const int bin = (int)((key >> shift) & 255u);
+            bool use = i < n && (key & mask) == prefix;
+            if (pass == 0) {
+                // the top byte is sign and exponent: most lanes share one or two bins, and a wave's atomics on one
+                // address run one after the other
+#pragma unroll
+                for (int it = 0; it < 2; ++it) {
+                    const unsigned long long left = __ballot(use);
+                    if (!left) break;
+                    const int src = __ffsll((long long)left) - 1;
+                    const int b = __builtin_amdgcn_readlane(bin, src);
+                    const unsigned long long same = __ballot(use && bin == b);
+                    if (lane == src) atomicAdd(&hist[b], __popcll(same));
+                    use = use && bin != b;
+                }
+            }
+            if (use) atomicAdd(&hist[bin], 1);
         }
         __syncthreads();
-        if (tid < 64) {
-            // lane owns bins 4*lane .. 4*lane+3; find the bin holding the kk-th largest candidate
-            int h[4], local = 0;
+        // lane owns bins 252 - 4*lane .. 255 - 4*lane (descending with the lane, so that a prefix sum runs from the top);
+        // find the bin holding the kk-th largest candidate
+        const int4 hv = reinterpret_cast<const int4 *>(hist)[63 - lane];
+        const int h[4] = {hv.x, hv.y, hv.z, hv.w};
+        const int local = h[0] + h[1] + h[2] + h[3];
+        int run = wave_incl_scan(local) - local;        // candidates in strictly higher bins
+        int digit = -1, rest = 0;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) { h[j] = hist[4 * lane + j]; local += h[j]; }
-            int incl = local;                       // becomes the sum over lanes >= lane
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int t = __shfl_down(incl, o);
-                if (lane + o < 64) incl += t;
-            }
-            int run = incl - local;                 // candidates in strictly higher bins
-#pragma unroll
-            for (int j = 3; j >= 0; --j) {
-                if (run < kk && run + h[j] >= kk) { res[0] = 4 * lane + j; res[1] = kk - run; }
-                run += h[j];
-            }
+        for (int j = 3; j >= 0; --j) {
+            if (run < kk && run + h[j] >= kk) { digit = 252 - 4 * lane + j; rest = kk - run; }
+            run += h[j];
         }
-        __syncthreads();
-        prefix |= (uint32_t)res[0] << shift;
+        const int at = __ffsll((long long)__ballot(digit >= 0)) - 1;      // exactly one lane
+        prefix |= (uint32_t)__builtin_amdgcn_readlane(digit, at) << shift;
+        kk = __builtin_amdgcn_readlane(rest, at);
         mask |= 255u << shift;
-        kk = res[1];
-        __syncthreads();                            // res is rewritten in the next pass
     }
     const uint32_t T = prefix;
     const int need = kk;                            // how many keys == T are kept (lowest indices)
 
-    // emit in ascending index order: thread t owns indices [t*E, (t+1)*E)
+    // emit in ascending index order: thread t owns indices [t*E, (t+1)*E).  One prefix sum counts the keys above T (high
+    // half) and those equal to it (low half).
     const int E = (n + NT - 1) / NT;
     const int i0 = min(n, tid * E), i1 = min(n, i0 + E);
-    int c_gt = 0, c_eq = 0;
-    for (int i = i0; i < i1; ++i) { const uint32_t key = keys[i]; c_gt += key > T; c_eq += key == T; }
-    int tot;
-    const int eq_before = block_excl_scan<NT>(c_eq, red, tot);
-    const int eq_kept = max(0, min(c_eq, need - eq_before));
-    int pos = block_excl_scan<NT>(c_gt + eq_kept, red, tot);
-    int eqr = eq_before;
+    int c = 0;
+    for (int i = i0; i < i1; ++i) { const uint32_t key = keys[i]; c += key > T ? 1 << 16 : key == T ? 1 : 0; }
+    const int x = wave_incl_scan(c);
+    if (lane == 63) red[w] = x;
+    __syncthreads();
+    int before = x - c;
+#pragma unroll
+    for (int i = 0; i < NT / 64; ++i) before += i < w ? red[i] : 0;
+    int eqr = before & 0xffff;
+    int pos = (before >> 16) + min(eqr, need);
     for (int i = i0; i < i1; ++i) {
         const uint32_t key = keys[i];
         const bool eq = key == T;

@@ -1,0 +1,38 @@
+"""SentryAttend at the edges of its dispatch: key ranges of the score stream and of the statistics, keys dealt to waves, one
+and two query blocks per wave, head dimension 128, the fill beside the selection, masks that leave whole tiles out."""
+from __future__ import annotations
+
+import pytest
+
+from paper_2604_08971_amd import binding as sf
+from paper_2604_08971_amd import workloads as W
+from helpers import make_wl
+from test_gpu_parity import _encoder_parity, _say, test_sparse_gqa_parity as gqa_case
+
+pytestmark = pytest.mark.gpu
+
+
+# B, heads, groups, length, head dim, U override, mask
+@pytest.mark.parametrize("dtype,B,nH,nG,L,dh,Uo,mask", [
+    ("bf16", 1, 6, 2, 33, 64, -1, True),          # two tiles, the second of one key
+    ("bf16", 1, 1, 1, 1025, 32, -1, False),       # statistics in two launches, score parts, last tile of one key
+    ("bf16", 2, 3, 1, 2047, 64, 33, True),        # one active query beyond a block
+    ("bf16", 130, 2, 2, 97, 64, 33, True),        # two query blocks per wave, four waves
+    ("bf16", 130, 2, 1, 97, 32, 64, False),
+    ("bf16", 3, 5, 5, 515, 128, 40, True),        # head dimension 128
+    ("bf16", 2, 2, 1, 700, 128, 255, False),      # just below the staged kernels
+    ("bf16", 2, 2, 1, 700, 128, 256, True),       # and just there
+    ("bf16", 1, 64, 8, 64, 32, 0, False),         # no active query: every row is filled
+])
+def test_attention_edges(dtype, B, nH, nG, L, dh, Uo, mask):
+    gqa_case(dtype, B, nH, nG, L, dh, Uo, mask)
+
+
+# one sample whose only modality is a few tokens at the end: most key tiles are dead
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_encoder_with_dead_tiles(dtype):
+    _say(f"dead tiles {dtype}")
+    spec = W.small_spec(dtype=dtype, B=7, seg=(600, 40, 7), d=64, Hq=2, Hk=1, dh=32, F=128, nl=1, head_keep=1.0,
+                        dropout="upto:2", c=3)
+    with sf.use_half("f16" if dtype == "f16" else "bf16"):
+        _encoder_parity(make_wl(spec))
