@@ -581,20 +581,19 @@ int32_t gemm_bf16_tile(GemmKind kind, const GemmArgs &a, hipStream_t st)
     }
 }
 
-// Which kernel takes a problem: an estimate of each one's time in microseconds.  The constants are a fit to the
-// launches listed at the top of this file and about 40 more between 100 and 123 000 rows (one layer of every workload
-// at batches 1 to 256, K 128 to 2176): fixed cost, cost of a K tile and cost of an epilogue per workgroup and round.
-//   256 x 256: whole rounds of one workgroup per compute unit, 1.35 us per K tile (1.45 with a residual or fp32 output)
-//     and 4.5 us per output tile (15 with GELU), and a part of the HBM time that no other tile's K loop covers: all of
-//     it in a single round, 40 % (60 % with a residual or fp32 output) in many;
-//   128 x 128: a chain of 0.53 us per K tile while there is at most one workgroup per compute unit, 0.45 us per K tile
-//     and 2.6 us per tile and compute unit beyond (0.6 and 4.2, and a seventh of the HBM time, with a residual or fp32
-//     output);
+// Which kernel takes a problem: an estimate of each one's time in microseconds.  The constants are a fit to 456
+// launches of layers drawn at random (10 to 130 000 rows, d 128 to 1024, K 128 to 4096, kept heads and channels at
+// random), with weights that no cache holds: fixed cost, cost of a K tile and cost of an epilogue per workgroup and
+// round.
+//   256 x 256: whole rounds of one workgroup per compute unit, 1.06 us per K tile (1.12 with a residual or fp32 output)
+//     and 4.9 us per output tile (13.7 with GELU), and the time of the output's own traffic;
+//   128 x 128: a chain of 0.57 us per K tile while there is at most one workgroup per compute unit, 0.47 us per K tile
+//     and 2.1 us per tile and compute unit beyond (0.59 and 2.5, and a sixth of the output's traffic, with a residual or
+//     fp32 output), a last uneven round counted nearly as a whole one;
 //   slices: rounds of 256 workgroups (eight slices), dearer from the second on, where the L2 feeds every compute unit
 //     with a tile of few rows; or one round of up to two per compute unit (four slices).
-// On 160 launches of layers drawn at random (10 to 130 000 rows, d 128 to 1024, kept heads and channels at random) the
-// choice is the fastest kernel for all but a few, where two of them are within 10-20 %; the largest gaps between the
-// kernels are factors of 3 to 6.
+// Over those launches the choice costs 0.4 % over the fastest kernel, 16 % at worst, where the gaps between the kernels
+// are factors of 3 to 6.
 GemmKind gemm_bf16_choose(const GemmArgs &a, bool ws_ok)
 {
     auto tiles = [&](int bm, int bn) {
@@ -603,17 +602,20 @@ GemmKind gemm_bf16_choose(const GemmArgs &a, bool ws_ok)
     };
     const bool wide = a.R || a.c_f32;
     const double nk = (a.K + TBK - 1) / TBK, rows = (double)a.B * a.L;
-    const double hbm = rows * (2.0 * a.K + a.N * ((a.c_f32 ? 4.0 : 2.0) + (!a.R ? 0.0 : a.r_f32 ? 4.0 : 2.0))) / 5.2e6;
-    const double rounds = ceil(tiles(256, 256) / 256);
-    const double bare = wide ? 0.6 + 0.4 / (rounds * rounds) : 0.4 + 0.6 / (rounds * rounds);
     const bool gelu = a.act == ACT_GELU;
-    const double ws = 3.0 + rounds * ((wide ? 1.45 : 1.35) * nk + (gelu ? 15.0 : 4.5)) + bare * hbm;
-    const double q = tiles(128, 128) / 256;
-    const double pipe = 3.3 + (wide ? 0.15 * hbm : 0.0) +
-                        std::max(0.53 * nk + (wide ? 2.5 : 1.0), q * (wide ? 0.6 * nk + 4.2 : 0.45 * nk + (gelu ? 4.1 : 2.6)));
+    // reads and writes of the epilogue at the rate of a large copy; those of A and W hide behind the matrix cores
+    const double out = rows * a.N * ((a.c_f32 ? 4.0 : 2.0) + (!a.R ? 0.0 : a.r_f32 ? 4.0 : 2.0)) / 5.2e6;
+    const double rounds = ceil(tiles(256, 256) / 256);
+    const double bare = wide ? 0.93 : 0.73 + 0.27 / (rounds * rounds);
+    const double ws = 2.3 + rounds * ((wide ? 1.12 : 1.06) * nk + (gelu ? 13.7 : 4.9)) + bare * out;
+    // two workgroups share a compute unit: a last one left alone takes nearly the time of a pair
+    double q = tiles(128, 128) / 256;
+    if (q > 1) q += 0.87 * (ceil(q) - q) / q;
+    const double pipe = 3.8 + (wide ? 0.18 * out : 0.0) +
+                        std::max(0.57 * nk + (wide ? 2.5 : gelu ? 2.8 : 1.0), q * (wide ? 0.59 * nk + 2.5 : 0.47 * nk + (gelu ? 3.2 : 2.1)));
     const double r8 = ceil(tiles(32, 64) / 256), c8 = ceil(nk / 8);
     const double s8 = 2.3 + r8 * (r8 > 1 ? 1.9 + 1.35 * c8 : 1.5 + 0.95 * c8);
-    const double s4 = (wide ? 3.6 : 4.4) + std::max(1.0, tiles(64, 64) / 256) * (1.6 + 0.85 * ceil(nk / 4));
+    const double s4 = (wide ? 3.6 : 4.4) + std::max(1.0, tiles(64, 64) / 256) * (1.7 + 0.98 * ceil(nk / 4));
     GemmKind best = GEMM_PIPE;
     double t = pipe;
     if (ws_ok && ws < t) { best = GEMM_WS; t = ws; }
