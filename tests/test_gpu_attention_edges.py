@@ -23,6 +23,9 @@ pytestmark = pytest.mark.gpu
     ("bf16", 2, 2, 1, 700, 128, 255, False),      # just below the staged kernels
     ("bf16", 2, 2, 1, 700, 128, 256, True),       # and just there
     ("bf16", 1, 64, 8, 64, 32, 0, False),         # no active query: every row is filled
+    ("f32", 2, 3, 1, 17, 4, 3, True),             # fp32: one query past a block, the narrowest head
+    ("f32", 1, 2, 2, 31, 96, 30, True),           # one key short of a tile, a head between one and two waves
+    ("f32", 1, 4, 2, 65, 256, 64, False),         # one key past two tiles, the widest head
 ])
 def test_attention_edges(dtype, B, nH, nG, L, dh, Uo, mask):
     gqa_case(dtype, B, nH, nG, L, dh, Uo, mask)
