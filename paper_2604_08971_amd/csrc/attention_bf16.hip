@@ -613,7 +613,10 @@ __global__ __launch_bounds__(NW * 64, DH == 128 || QB * DH == 128 ? 2 : 3) void 
         for (int kk = 0; kk < KF; ++kk) qf[qq][kk] = *reinterpret_cast<const h16x8 *>(qrow + kk * 16 + lhi * 8);
     }
     if (key_valid) __syncthreads();
-    if (__builtin_amdgcn_ballot_w64(qidx[0] >= 0) == 0ull) return;        // uniform over the workgroup: no row in these blocks
+    bool any = qidx[0] >= 0;              // a caller's list may hold its rows behind a block without any
+#pragma unroll
+    for (int qq = 1; qq < QB; ++qq) any |= qidx[qq] >= 0;
+    if (__builtin_amdgcn_ballot_w64(any) == 0ull) return;                 // uniform over the workgroup: no row in these blocks
 
     const h16 *Kb = K + sample_offset(row0, b, sk) + (int64_t)g * sk.h + lhi * 8;
     const h16 *Vb = VT + (int64_t)b * svt.b + (int64_t)g * svt.h + (int64_t)l32 * svt.l + lhi * 8;

@@ -2,12 +2,17 @@
 and two query blocks per wave, head dimension 128, the fill beside the selection, masks that leave whole tiles out."""
 from __future__ import annotations
 
+import numpy as np
 import pytest
+import torch
 
+from oracle import cpu_oracle as orc
+from oracle.packs import err_metric
 from paper_2604_08971_amd import binding as sf
 from paper_2604_08971_amd import workloads as W
+from gpu_utils import to_dev, to_host
 from helpers import make_wl
-from test_gpu_parity import _encoder_parity, _say, test_sparse_gqa_parity as gqa_case
+from test_gpu_parity import TOL, _encoder_parity, _say, test_sparse_gqa_parity as gqa_case
 
 pytestmark = pytest.mark.gpu
 
@@ -39,3 +44,23 @@ def test_encoder_with_dead_tiles(dtype):
                         dropout="upto:2", c=3)
     with sf.use_half("f16" if dtype == "f16" else "bf16"):
         _encoder_parity(make_wl(spec))
+
+
+def test_forced_rows_behind_a_block_without_any():
+    """A caller's list whose first 32 entries name no row (-1, or out of range, which counts as -1): the rows behind them are
+    active rows like any other.  130 x 2 heads and 64 slots: two query blocks per wave."""
+    B, nH, L, dh, U = 130, 2, 97, 32, 64
+    rng = np.random.default_rng(5)
+    Q, K, V = (W.to_bf16_values(rng.standard_normal(s).astype(np.float32)) for s in ((B, nH, L, dh), (B, 1, L, dh), (B, 1, L, dh)))
+    fs = np.full((B, nH, U), -1, np.int32)
+    fs[::2, :, :32] = L
+    fs[:, :, 32:35] = [3, 40, L - 1]
+    desc = sf.make_desc(B, L, 64, nH, 1, dh, 64, dtype=sf.SF_BF16, U_override=U)
+    O = torch.full((B, L, nH * dh), float("nan"), dtype=torch.bfloat16, device="cuda")
+    sf.sparse_gqa_forward_static(desc, *(to_dev(x, "bf16") for x in (Q, K, V)), torch.zeros((1, nH), dtype=torch.int32, device="cuda"),
+                                 O, forced_sel=to_dev(fs, "bf16"))
+    torch.cuda.synchronize()
+    O = to_host(O)
+    assert np.isfinite(O).all()
+    O_ref, _, _, _ = orc.sparse_gqa(Q, K, V, np.zeros(nH, np.int32), U, None, np.where(fs < L, fs, -1).astype(np.int32), True, None)
+    assert err_metric(O, O_ref) <= TOL["bf16"]
