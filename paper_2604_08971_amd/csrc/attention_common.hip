@@ -258,7 +258,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
     int c = 0;
     for (int i = threadIdx.x; i < L; i += NT) {
         const bool ok = !kv || kv[i];
-        // allowed queries get a key >= 1 (sortable_key(-inf) > 0), others key 0
+        // allowed queries get a key >= 1 (the smallest, of a NaN with every bit set, is 0 by the map), others key 0
         uint32_t key = 1u;
         if (sc.score) {
             float m = sc.score[m0 + i];
@@ -268,7 +268,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
                 if (ok && m == -INFINITY) m = 0.f;
                 if (sc.out) sc.out[((int64_t)b * sc.outH + h) * L + i] = m;
             }
-            key = sortable_key(m);
+            key = max(sortable_key(m), 1u);
         }
         keys[i] = ok ? key : 0u;
         c += ok;

@@ -64,3 +64,23 @@ def test_forced_rows_behind_a_block_without_any():
     assert np.isfinite(O).all()
     O_ref, _, _, _ = orc.sparse_gqa(Q, K, V, np.zeros(nH, np.int32), U, None, np.where(fs < L, fs, -1).astype(np.int32), True, None)
     assert err_metric(O, O_ref) <= TOL["bf16"]
+
+
+def test_allowed_query_whose_score_has_every_bit_set():
+    """A query of NaNs with every bit set (memory filled with 0xff; of either sign, since the score subtracts) can score the NaN
+    that maps to the smallest of all keys; it is still one of the allowed queries, and with no more of them than U the list
+    names each of them."""
+    B, nH, L, dh, U = 2, 2, 48, 16, 6
+    rng = np.random.default_rng(6)
+    Q, K, V = (rng.standard_normal((B, nH, L, dh)).astype(np.float32) for _ in range(3))
+    kv = np.zeros((B, L), np.uint8)
+    allowed = [5, 17, 30, 47]
+    kv[:, allowed] = 1
+    Q.view(np.uint32)[0, :, 17], Q.view(np.uint32)[1, :, 17] = 0xffffffff, 0x7fffffff
+    desc = sf.make_desc(B, L, 64, nH, nH, dh, 64, dtype=sf.SF_F32, U_override=U)
+    O, sel, _ = sf.sparse_gqa_forward(desc, *(torch.from_numpy(x).cuda() for x in (Q, K, V)),
+                                      torch.arange(nH, dtype=torch.int32, device="cuda").reshape(1, nH), key_valid=torch.from_numpy(kv).cuda())
+    torch.cuda.synchronize()
+    assert (to_host(sel) == np.array(allowed + [-1] * (U - len(allowed)))).all()
+    O = to_host(O).reshape(B, L, nH, dh)
+    assert np.isfinite(np.delete(O, 17, axis=1)).all()
