@@ -50,7 +50,7 @@ struct AttnPlan {
     int splits;            // key splits of the active pass (1 = write O directly)
     int keys_per_split;    // multiple of 64
     int stat_parts;        // key ranges of the K/V statistics (1 = one launch)
-    int score_parts;       // key ranges of the score stream (1 = the score itself)
+    int score_parts;       // key ranges of the score stream (1 = the score itself, n > 1: n + 1 planes)
     int Upad;              // U rounded up to 32
     int Lp;                // L rounded up to 8 (row length of the transposed V copy)
     int Sp;                // key-sample size rounded up to 64 (0: no sample)
@@ -69,7 +69,8 @@ int32_t attention_forward(int dtype, const AttnArgs &a, hipStream_t st);
 // bf16 MFMA kernels (attention_bf16.hip)
 // score [B,scoreH,L]; sel [B,selH,U].  The score is taken over the Lk keys `Kx` (strides skx) with
 // validity key_mask [B,Lk] (NULL: all) and mean-key statistics `stats`; queries use a.key_valid.
-// parts > 1: over `parts` ranges of keys, part p at score + p * B*scoreH*L (-inf where a range has no allowed key).
+// parts > 1: over `parts` ranges of keys, planes of B*scoreH*L: plane p the largest product q.k of range p (-inf where the
+// range has no allowed key), plane `parts` the product with the mean key.
 int32_t score_bf16(const AttnArgs &a, const void *Kx, sf_strides skx, int Lk, const uint8_t *key_mask,
                    const float *stats, float *score, int scoreH, int parts, hipStream_t st);
 int score_bf16_parts(const AttnArgs &a, int Lk);

@@ -102,7 +102,9 @@ struct KTile {
 // are double-buffered in LDS and the next tile is prefetched into registers
 // while the current one is multiplied, so one barrier per tile suffices.
 // `parts` > 1: an item is also one range of key tiles (launches with few items: one 512-token sample and six heads are 12
-// items that walk eight tiles one after the other, 9.5 us; as 96 items of one tile 5.2 us).
+// items that walk eight tiles one after the other, 9.5 us; as 96 items of one tile 5.2 us).  Then plane p of `score`
+// receives the largest product of range p (-inf: no allowed key there) and plane `parts` the product with the mean key:
+// subtracting before the ranges are joined would turn infinities of one range into the answer of another.
 template <int DH, int QBS>
 __global__ __launch_bounds__(NWAVE * 64) SF_SCORE_OCC void score_bf16_kernel(
     const h16 *__restrict__ Q, sf_strides sq, const h16 *__restrict__ K, sf_strides sk,
@@ -218,9 +220,13 @@ __global__ __launch_bounds__(NWAVE * 64) SF_SCORE_OCC void score_bf16_kernel(
         const int i = q0 + qq * 32 + l32;
         if (lhi == 0 && i < L) {
             const bool ok = !kv || kv[i];
-            // no allowed key scores 0 (with parts: decided by the selection, which sees them all)
-            score[part * part_stride + ((int64_t)b * scoreH + h) * L + i] =
-                !ok ? -INFINITY : nt == 0 ? (parts > 1 ? -INFINITY : 0.f) : (m - dot) * scale;
+            float *out = score + ((int64_t)b * scoreH + h) * L + i;
+            if (parts > 1) {                              // the selection sees every range: it takes mean, scale and mask
+                out[part * part_stride] = m;
+                if (part == 0) out[parts * part_stride] = dot;
+            } else {
+                *out = !ok ? -INFINITY : nt == 0 ? 0.f : (m - dot) * scale;      // no allowed key scores 0
+            }
         }
     }
 }

@@ -235,10 +235,10 @@ struct HeadFill {
 // ------------------------------------------------------------------- selection
 // One block per (b, head): the U_eff = min(U, u_active[b], #allowed) queries with the
 // highest score, ties to the lower index; emitted ascending.  score == NULL
-// means "every allowed query" (used when U >= L).  The score may come in parts over ranges of keys (part p at
-// score + p * part_stride): the score of a query is the largest of its parts (-inf: no allowed key in that range; no
-// allowed key at all scores 0); score_out then receives it.
-struct ScoreParts { const float *score; int64_t stride; int n, H; float *out; int outH; };     // H: heads per sample
+// means "every allowed query" (used when U >= L).  The score may come in n > 1 ranges of keys, as n planes of largest
+// products and one of products with the mean key (`stride` apart): the score is (largest of all - mean) * scale, 0 for a
+// sample without a key to score by (n_keys), and `out` then receives it.
+struct ScoreParts { const float *score; int64_t stride; int n, H; const int32_t *n_keys; float scale; float *out; int outH; };     // H: heads per sample
 
 template <int NT, int VEC, class T>
 __global__ __launch_bounds__(NT) void select_kernel(
@@ -255,6 +255,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
     int32_t *sl = slot ? slot + (int64_t)bh * L : nullptr;      // only the active-row projection reads it
     int32_t *se = sel + ((int64_t)b * selH + h) * U;
     const HeadFill<NT, VEC, T> hf(fill, b, h, L);
+    const bool no_key = sc.n > 1 && sc.n_keys[b] == 0;
     int c = 0;
     for (int i = threadIdx.x; i < L; i += NT) {
         const bool ok = !kv || kv[i];
@@ -265,7 +266,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
             if (sc.n > 1) {
 #pragma unroll 4
                 for (int p = 1; p < sc.n; ++p) m = fmaxf(m, sc.score[p * sc.stride + m0 + i]);
-                if (ok && m == -INFINITY) m = 0.f;
+                m = !ok ? -INFINITY : no_key ? 0.f : (m - sc.score[sc.n * sc.stride + m0 + i]) * sc.scale;
                 if (sc.out) sc.out[((int64_t)b * sc.outH + h) * L + i] = m;
             }
             key = max(sortable_key(m), 1u);
@@ -610,7 +611,7 @@ AttnPlan attn_plan(int dtype, const AttnArgs &a, void *ws)
     pl.stat_part = pl.stat_parts > 1 ? c.take<float>(BG * pl.stat_parts * (2 * a.dh + 1)) : nullptr;
     pl.stats = c.take<float>(BG * 2 * a.dh);
     pl.n_valid = c.take<int32_t>(a.B);
-    pl.score = c.take<float>(BH * a.L * pl.score_parts);
+    pl.score = c.take<float>(BH * a.L * (pl.score_parts > 1 ? pl.score_parts + 1 : 1));
     pl.sel = c.take<int32_t>(BH * (a.U > 0 ? a.U : 1));
     pl.slot = c.take<int32_t>(BH * a.L);
     if (pl.splits > 1) {
@@ -717,7 +718,7 @@ int32_t attention_forward(int dtype, const AttnArgs &a, hipStream_t st)
         else hipLaunchKernelGGL((forced_slot_kernel<4, h16>), SF_FORCED_ARGS, fill16);
 #undef SF_FORCED_ARGS
     } else {
-        ScoreParts parts{nullptr, 0, 1, a.nH, nullptr, userH};
+        ScoreParts parts{nullptr, 0, 1, a.nH, nullptr, 0.f, nullptr, userH};
         if (a.U > 0 && a.U < a.L) {
             // the caller's score buffer takes the score itself: from the score kernel, or (parts) from the selection
             const bool direct = a.score_out && pl.score_parts == 1;
@@ -754,8 +755,8 @@ int32_t attention_forward(int dtype, const AttnArgs &a, hipStream_t st)
                                    a.key_valid, key_mask, nkeys, a.nH, a.L, Lk, a.dh, score, scoreH, a.row0,
                                    Kx == a.K);
             }
-            parts = ScoreParts{score, (int64_t)a.B * scoreH * a.L, pl.score_parts, scoreH,
-                               pl.score_parts > 1 ? a.score_out : nullptr, userH};
+            parts = ScoreParts{score, (int64_t)a.B * scoreH * a.L, pl.score_parts, scoreH, nkeys,
+                               1.0f / sqrtf((float)a.dh), pl.score_parts > 1 ? a.score_out : nullptr, userH};
         }
         // long rows, and rows of some length where there are few of them (6 rows of 512 scores: 7.9 us against 9.7 with 256),
         // get 1024 threads

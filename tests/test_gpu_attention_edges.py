@@ -84,3 +84,32 @@ def test_allowed_query_whose_score_has_every_bit_set():
     assert (to_host(sel) == np.array(allowed + [-1] * (U - len(allowed)))).all()
     O = to_host(O).reshape(B, L, nH, dh)
     assert np.isfinite(np.delete(O, 17, axis=1)).all()
+
+
+def test_score_over_key_ranges_keeps_nan_and_infinities():
+    """The score of one sample comes in ranges of keys, the same sample in a batch of 64 without: NaN, both infinities and
+    finite values fall on the same queries (one range has no allowed key, one key overflows its products)."""
+    B, nH, L, dh = 64, 2, 600, 64
+    rng = np.random.default_rng(8)
+    Q, K, V = (W.to_bf16_values(rng.standard_normal((1, nH, L, dh)).astype(np.float32)) for _ in range(3))
+    K[0, :, 350, 0] = 3e38
+    Q[0, :, 100, 3] = np.nan
+    Q[0, :, 102:104] = 0
+    Q[0, :, 102, 0], Q[0, :, 103, 0] = 3e38, -3e38
+    kv = np.ones((1, L), np.uint8)
+    kv[0, 128:256] = 0
+    hg = torch.arange(nH, dtype=torch.int32, device="cuda").reshape(1, nH)
+    got = []
+    for n in (1, B):
+        desc = sf.make_desc(n, L, 64, nH, nH, dh, 64, dtype=sf.SF_BF16)
+        q, k, v = (to_dev(np.repeat(x, n, axis=0), "bf16") for x in (Q, K, V))
+        _, sel, score = sf.sparse_gqa_forward(desc, q, k, v, hg, key_valid=torch.from_numpy(np.repeat(kv, n, axis=0)).cuda(), want_score=True)
+        torch.cuda.synchronize()
+        got.append((to_host(sel)[0], to_host(score)[0]))
+    (sel, score), (sel_ref, ref) = got
+    assert np.isnan(ref[:, [100, 102]]).all() and np.isposinf(ref[:, 103]).all() and np.isfinite(ref).any()
+    assert np.array_equal(np.isnan(score), np.isnan(ref))
+    fin = np.isfinite(ref)
+    assert np.array_equal(score[~fin & ~np.isnan(ref)], ref[~fin & ~np.isnan(ref)])
+    assert np.allclose(score[fin], ref[fin], rtol=1e-4, atol=1e-4)
+    assert np.array_equal(sel, sel_ref)
