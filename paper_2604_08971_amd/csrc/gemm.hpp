@@ -28,6 +28,7 @@ struct GemmArgs {
     void *C; int64_t ldc; int c0;                        // EPI_ROWMAJOR: row stride, first column
     const int32_t *row_map;                              // bf16 row-major problems only (gemm_takes_row_map): row i
                                                          // of sample b reads A row row_map[b*L + i] (all of A within 4 GiB)
+    int64_t a_rows;                                      // row_map: number of rows of A, where its reads end
     int xcd_rows;                                        // hint: deal 256-row tiles to the 8 XCDs round-robin instead of in
                                                          // contiguous ranges (rows of unequal cost, e.g. n_lim / k_lim)
     int r_f32, c_f32;                                    // bf16 GEMM only: R / C hold fp32 (the residual stream)

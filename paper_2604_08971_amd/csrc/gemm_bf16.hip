@@ -241,7 +241,7 @@ static int32_t launch_cfg(const GemmArgs &a, hipStream_t st)
 
 bool gemm_takes_row_map(int dtype, const GemmArgs &a)
 {
-    return dtype == SF_BF16 && a.epi == EPI_ROWMAJOR && (gemm_bf16_ws_eligible(a) || gemm_bf16_tile_eligible(a));
+    return dtype == SF_BF16 && a.epi == EPI_ROWMAJOR && a.a_rows > 0 && (gemm_bf16_ws_eligible(a) || gemm_bf16_tile_eligible(a));
 }
 bool gemm_takes_vt_split(int dtype, const GemmArgs &a)
 {

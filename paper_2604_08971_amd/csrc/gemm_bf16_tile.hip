@@ -24,6 +24,7 @@
 #include <atomic>
 
 #include "gemm.hpp"
+#include "gemm_tile_addr.hpp"
 
 namespace sf {
 
@@ -84,16 +85,7 @@ __device__ __forceinline__ bool find_tile(const GemmArgs &a, int bm, int bn, int
     return t.nt0 < t.N;
 }
 
-// The operands of a tile as buffers: the base is the tile's first row, the scalar offset of a load walks K and a lane's
-// byte offset never changes.  The record count ends the buffer with the operand, so the K tail (K % 64 == 32: the
-// last K tile is half a tile) may request bytes behind a row - those of the next row, never used - but not behind
-// the operand.  Rows beyond the edge are clamped: they only feed outputs that are never stored.
-__device__ __forceinline__ uint32_t records(int64_t rows, int64_t ld, int K)
-{
-    const int64_t n = ((rows - 1) * ld + K) * 2;
-    return n < (int64_t)0xffffffff ? (uint32_t)n : 0xffffffffu;
-}
-
+// The operands of a tile (gemm_tile_addr.hpp)
 struct Source { const char *x, *w; uint32_t nx, nw; };
 
 __device__ __forceinline__ Source sources(const GemmArgs &a, const Tile &t)
@@ -101,18 +93,10 @@ __device__ __forceinline__ Source sources(const GemmArgs &a, const Tile &t)
     Source s;
     const int64_t row = (int64_t)t.b * a.L + t.m0;
     s.x = static_cast<const char *>(a.A) + (a.row_map ? (int64_t)0 : row * a.lda * 2);
-    s.nx = a.row_map ? 0xffffffffu : records((int64_t)a.B * a.L - row, a.lda, a.K);
+    s.nx = records(a.row_map ? a.a_rows : (int64_t)a.B * a.L - row, a.lda, a.K);
     s.w = static_cast<const char *>(a.W) + ((int64_t)t.p * a.w_pstride + (int64_t)(a.n0 + t.nt0) * a.ldw) * 2;
     s.nw = records(a.N - t.nt0, a.ldw, a.K);
     return s;
-}
-
-// Byte offset, from the tile's first row, of the 16 bytes lane `lane` brings in for super-rows sr4*4 .. sr4*4+3
-__device__ __forceinline__ uint32_t lane_off(int sr4, int lane, int rows, int64_t ld, const int32_t *rmap)
-{
-    const int sr = sr4 * 4 + (lane >> 4), t = (lane & 15) ^ (sr & 7);
-    const int r = min(sr * 2 + (t >> 3), rows - 1);
-    return (uint32_t)(rmap ? rmap[r] : r) * (uint32_t)ld * 2u + (uint32_t)(t & 7) * 16u;
 }
 
 template <int N> __device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }

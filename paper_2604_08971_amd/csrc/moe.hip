@@ -513,6 +513,7 @@ extern "C" int32_t sf_moe_ffn_forward(const sf_desc *desc, const sf_moe_compact 
     g.act = D.act == SF_GELU_ERF ? ACT_GELU : ACT_RELU;
     g.C = w.hg; g.ldc = w.Fp;
     g.row_map = w.src_row;
+    g.a_rows = rows;
     if (!(rows * D.d * 2 < ((int64_t)1 << 32) && gemm_takes_row_map(D.dtype, g))) {
         const size_t row_bytes = (size_t)D.d * es;
         dim3 grid((unsigned)((pairs + 3) / 4));

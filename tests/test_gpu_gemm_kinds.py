@@ -7,7 +7,7 @@ import pytest
 from paper_2604_08971_amd import binding as sf
 from paper_2604_08971_amd import workloads as W
 from helpers import make_wl
-from test_gpu_parity import _encoder_parity, _ffn_case, _say
+from test_gpu_parity import _encoder_parity, _ffn_case, _moe_case, _say
 
 pytestmark = pytest.mark.gpu
 
@@ -32,3 +32,15 @@ def test_encoder_with_an_odd_number_of_heads(dtype, B, seg, drop):
     spec = W.small_spec(dtype=dtype, B=B, seg=seg, d=128, Hq=4, Hk=2, dh=32, F=256, head_keep=0.75, nl=2, dropout=drop)
     with sf.use_half("f16" if dtype == "f16" else "bf16"):
         _encoder_parity(make_wl(spec))
+
+
+# MoE block: token rows read through a map, expert widths that end a tile early (n_lim, k_lim), K tails of half a K tile
+# (d % 64 == 32), with and without the LayerNorm that would otherwise hand over a padded copy of X
+@pytest.mark.parametrize("dtype,B,seg,d,F,E,k", [("bf16", 3, (70, 50, 9), 96, 200, 4, 2), ("f16", 2, (33, 95), 96, 136, 5, 1),
+                                                 ("bf16", 9, (700, 333), 160, 640, 8, 2), ("f16", 9, (700, 333), 160, 640, 4, 3)])
+def test_moe_on_small_tiles(dtype, B, seg, d, F, E, k):
+    _say(f"moe on small tiles {dtype} B={B} d={d} F={F} E={E}")
+    wl = make_wl(W.small_spec(dtype=dtype, B=B, seg=seg, d=d, dh=32, F=F, dropout="upto:1"))
+    with sf.use_half("f16" if dtype == "f16" else "bf16"):
+        _moe_case(wl, E, k, pre_ln=False)
+        _moe_case(wl, E, k, forced=True)
