@@ -414,9 +414,10 @@ int32_t sf_sparse_gqa_forward(const sf_desc *desc, int32_t nH, int32_t nG,
  * scores, active lists, key-split partials) is a buffer of
  * SF_STATIC_SCRATCH_BYTES built into the library's device image, one copy per
  * GPU, held until the process ends.  The call allocates and frees nothing.
- * A problem whose sf_sparse_gqa_workspace_bytes() exceeds the buffer is refused
- * with SF_ERR_WORKSPACE before anything is enqueued (the message names both
- * sizes).  All calls on one GPU share the buffer, so two calls that overlap in
+ * Where sf_sparse_gqa_workspace_bytes() exceeds the buffer, the sparsity score is
+ * streamed in one piece (same results, less scratch); a problem that does not fit
+ * even so is refused with SF_ERR_WORKSPACE before anything is enqueued (the
+ * message names both sizes).  All calls on one GPU share the buffer, so two calls that overlap in
  * time on one GPU (different streams or threads) race: serialise them, or use
  * sf_sparse_gqa_forward with a workspace per stream.  Nothing in the buffer
  * needs clearing between calls.  sf_sparse_gqa_static_capacity() returns

@@ -149,6 +149,7 @@ static AttnArgs enc_attn_args(const Dims &D, int kh)
     AttnArgs a{};
     a.B = D.B; a.nH = kh; a.nG = D.Hk; a.L = D.L; a.dh = D.dh; a.U = D.U; a.n_sample = D.n_sample;
     a.v_transposed = D.dtype == SF_BF16;
+    a.need_slot = 1;
     return a;
 }
 

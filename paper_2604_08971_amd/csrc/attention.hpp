@@ -31,7 +31,8 @@ struct AttnArgs {
     // [B, ceil(L/32)] or NULL: bit i of sample b is set when some head selected row i (cleared by the statistics
     // pass, set by the selection; what the active-row output projection starts from)
     uint32_t *act_bits;
-    void *ws; size_t ws_bytes;
+    int need_slot;                           // the workspace holds the row -> slot map that goes with act_bits
+    void *ws; size_t ws_bytes;               // ws_bytes = 0 when planning: as much as the fastest plan takes
 };
 
 // Element offset of sample b in a token-major tensor with strides s, and its first row in O

@@ -580,7 +580,7 @@ __global__ __launch_bounds__(64) void attend_f32_kernel(
 }
 
 // ------------------------------------------------------------------- planning
-AttnPlan attn_plan(int dtype, const AttnArgs &a, void *ws)
+static AttnPlan attn_plan_parts(int dtype, const AttnArgs &a, void *ws, int score_parts)
 {
     AttnPlan pl{};
     const bool sparse = a.U < a.L;
@@ -603,7 +603,7 @@ AttnPlan attn_plan(int dtype, const AttnArgs &a, void *ws)
             pl.splits = ceil_div(a.L, pl.keys_per_split);
         }
     }
-    pl.score_parts = dtype == SF_BF16 && sparse && a.U > 0 ? score_bf16_parts(a, pl.Sp > 0 ? pl.Sp : a.L) : 1;
+    pl.score_parts = score_parts;
     Carver c(ws);
     const size_t BH = (size_t)a.B * a.nH, BG = (size_t)a.B * a.nG;
     pl.vt = (dtype == SF_BF16 && !a.v_transposed) ? c.take<uint16_t>(BG * a.dh * pl.Lp) : nullptr;
@@ -613,7 +613,7 @@ AttnPlan attn_plan(int dtype, const AttnArgs &a, void *ws)
     pl.n_valid = c.take<int32_t>(a.B);
     pl.score = c.take<float>(BH * a.L * (pl.score_parts > 1 ? pl.score_parts + 1 : 1));
     pl.sel = c.take<int32_t>(BH * (a.U > 0 ? a.U : 1));
-    pl.slot = c.take<int32_t>(BH * a.L);
+    pl.slot = a.need_slot ? c.take<int32_t>(BH * a.L) : nullptr;
     if (pl.splits > 1) {
         pl.part_o = c.take<float>(BH * pl.Upad * pl.splits * a.dh);
         pl.part_ml = c.take<float>(BH * pl.Upad * pl.splits * 2);
@@ -625,6 +625,17 @@ AttnPlan attn_plan(int dtype, const AttnArgs &a, void *ws)
         pl.n_keys = c.take<int32_t>(a.B);
     }
     pl.bytes = c.off;
+    return pl;
+}
+
+// The score stream is split into key ranges only where the workspace has room for their planes (the score is the same
+// either way): a caller's or the built-in buffer that holds everything else is large enough.
+AttnPlan attn_plan(int dtype, const AttnArgs &a, void *ws)
+{
+    const bool sparse = a.U > 0 && a.U < a.L;
+    const int parts = dtype == SF_BF16 && sparse ? score_bf16_parts(a, a.n_sample > 0 ? (int)align_up(a.n_sample, 64) : a.L) : 1;
+    AttnPlan pl = attn_plan_parts(dtype, a, ws, parts);
+    if (parts > 1 && a.ws_bytes > 0 && pl.bytes > a.ws_bytes) pl = attn_plan_parts(dtype, a, ws, 1);
     return pl;
 }
 
@@ -700,7 +711,7 @@ int32_t attention_forward(int dtype, const AttnArgs &a, hipStream_t st)
     int32_t *sel = a.sel_out ? a.sel_out : pl.sel;
     const int selH = a.sel_out ? userH : a.nH;
     // the row -> slot map is read by the projection of the active rows only
-    int32_t *slot = a.act_bits ? pl.slot : nullptr;
+    int32_t *slot = a.act_bits ? pl.slot : nullptr;      // act_bits implies need_slot
     auto fill_args = [&](auto *O) {
         Fill<std::remove_pointer_t<decltype(O)>> f{};
         f.O = a.skip_fill ? nullptr : O; f.ldo = a.ldo; f.stats = pl.stats; f.head_group = a.head_group; f.hg_stride = a.hg_stride;
@@ -879,6 +890,7 @@ extern "C" int32_t sf_sparse_gqa_forward_static(const sf_desc *desc, int32_t nH,
     Dims D; AttnArgs a;
     if (int32_t rc = make_attn_args(desc, nH, nG, D, a)) return rc;
     a.v_transposed = v_transposed != 0;
+    a.ws_bytes = SF_STATIC_SCRATCH_BYTES;
     const size_t need = attn_plan(D.dtype, a, nullptr).bytes;
     if (need > SF_STATIC_SCRATCH_BYTES)
         return fail(SF_ERR_WORKSPACE,

@@ -224,3 +224,48 @@ def test_header_is_plain_c(tmp_path):
     src.write_text('#include "sentryfuse.h"\nint main(void) { sf_desc d; (void)d; return (int)sizeof(sf_moe_compact) == 0; }\n')
     subprocess.check_call(["gcc", "-std=c99", "-Wall", "-Wextra", "-pedantic", "-Werror", "-I", os.path.join(ROOT, "include"),
                            "-fsyntax-only", str(src)])
+
+
+def _scratch_without_key_ranges(B, nH, nG, L, dh, U, v_transposed, n_sample):
+    """Upper bound of the scratch a 16-bit problem cannot do without, piece by piece in units of 256 bytes: transposed V,
+    statistics over chunks of 128 keys, mean key and value, counts, score, active lists, one word per row and head, and for a
+    sparse problem the partial rows of the key splits (towards 256 (sample, group, split) items, 256 keys or more each)."""
+    up = lambda n: (n + 255) // 256 * 256
+    BH, BG, Lp, Upad = B * nH, B * nG, (L + 7) // 8 * 8, (max(U, 1) + 31) // 32 * 32
+    n = 0 if v_transposed else up(BG * dh * Lp * 2)
+    n += up(BG * ((L + 127) // 128) * 2 * dh * 4) + up(BG * 2 * dh * 4) + up(B * 4) + 2 * up(BH * L * 4) + up(BH * max(U, 1) * 4)
+    if 0 < U < L:
+        want = min(1 if BG >= 256 else (256 + BG - 1) // BG, max(L // 256, 1), 64)
+        if want > 1:
+            per = ((L + want - 1) // want + 63) // 64 * 64
+            splits = (L + per - 1) // per
+            n += up(BH * Upad * splits * dh * 4) + up(BH * Upad * splits * 2 * 4)
+    if n_sample:
+        Sp = (n_sample + 63) // 64 * 64
+        n += up(BG * Sp * dh * 2) + up(B * Sp) + up(BG * 2 * dh * 4) + up(B * 4)
+    return n
+
+
+def test_static_scratch_takes_what_fits_without_key_ranges():
+    """The size check of the built-in scratch buffer runs before the call looks at its arguments: a problem whose pieces fit
+    gets past it (and is then refused for its NULL arguments, or for want of a device)."""
+    import random
+    L_, z, cap = sf.lib(), sf.SfStrides(0, 0, 0), sf.sparse_gqa_static_capacity()
+    rng = random.Random(3)
+    near = 0
+    cases = [(5, 8, 4, 726, 64, 672, 0, 0), (3, 8, 4, 1960, 32, 695, 1, 0), (1, 2, 2, 8158, 128, 448, 0, 0)]
+    while len(cases) < 20000:
+        nG = rng.choice([1, 2, 4, 8])
+        L = int(2 ** rng.uniform(5, 14))
+        cases.append((int(2 ** rng.uniform(0, 6)), nG * rng.choice([1, 2, 3, 4]), nG, L, rng.choice([32, 64, 128]),
+                      rng.choice([rng.randint(1, min(L, 900)), L, 5]), rng.randint(0, 1), rng.choice([0, 0, 64, 150])))
+    for B, nH, nG, L, dh, U, vt, ns in cases:
+        n = _scratch_without_key_ranges(B, nH, nG, L, dh, U, vt, ns)
+        if n > cap:
+            continue
+        near += n > cap * 9 // 10
+        d = sf.make_desc(B, L, 64, nH, nG, dh, 64, dtype=sf.SF_BF16, U_override=U, n_sample=ns)
+        rc = L_.sf_sparse_gqa_forward_static(C.byref(d), nH, nG, None, z, None, z, None, z, vt, None, None, None, None, None, None,
+                                             nH * dh, None, None, None)
+        assert rc in (-1, -5), ((B, nH, nG, L, dh, U, vt, ns), n, rc, L_.sf_last_error())
+    assert near > 20

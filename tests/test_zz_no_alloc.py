@@ -60,6 +60,20 @@ def test_static_scratch_matches_workspace_entry_point_on_two_calls_in_a_row():
     _both(2, 6, 2, 1024, 64, seed=5, masked=True)
 
 
+def test_static_scratch_without_room_for_the_planes_of_a_split_score():
+    # the workspace query asks for more than the buffer holds, for the planes of the key ranges; the call streams the score
+    # in one piece instead, with the same results
+    B, nH, nG, L, dh, U = 5, 8, 4, 726, 64, 672
+    Q, K, V, hg, kv = _inputs(B, nH, nG, L, dh, 6, True)
+    desc = sf.make_desc(B, L, 64, nH, nG, dh, 64, dtype=sf.SF_BF16, U_override=U)
+    assert sf.sparse_gqa_workspace_bytes(desc, nH, nG) > sf.sparse_gqa_static_capacity()
+    O_ref, sel_ref, score_ref = sf.sparse_gqa_forward(desc, Q, K, V, hg, key_valid=kv, want_score=True)
+    O, sel, score = torch.full_like(O_ref, float("nan")), torch.full_like(sel_ref, -7), torch.full_like(score_ref, float("nan"))
+    sf.sparse_gqa_forward_static(desc, Q, K, V, hg, O, key_valid=kv, sel=sel, score=score)
+    torch.cuda.synchronize()
+    assert torch.equal(O, O_ref) and torch.equal(sel, sel_ref) and torch.equal(score, score_ref)
+
+
 def test_static_scratch_refuses_problems_beyond_its_size():
     B, nH, nG, L, dh = 16, 8, 4, 4096, 64
     desc = sf.make_desc(B, L, 64, nH, nG, dh, 64, dtype=sf.SF_BF16)
