@@ -407,6 +407,14 @@ int32_t sf_sparse_gqa_forward(const sf_desc *desc, int32_t nH, int32_t nG,
                               void *O, int64_t ldo, int32_t *sel_out, float *score_out,
                               void *workspace, size_t workspace_bytes, void *stream);
 
+/* How sf_sparse_gqa_forward runs a 16-bit problem with a workspace of
+ * sf_sparse_gqa_workspace_bytes() (a reporting aid; host only, nothing is launched).
+ * plan_host[0]: active rows (step 3) 1 = key tiles staged once for all heads of a
+ * group, 0 = keys dealt to the waves of a workgroup per head; [1]: pieces the keys
+ * are split into for it (joined by a merge); [2], [3]: key ranges of the score
+ * stream and of the K/V statistics. */
+int32_t sf_sparse_gqa_plan(const sf_desc *desc, int32_t nH, int32_t nG, int32_t *plan_host);
+
 /* sf_sparse_gqa_forward for callers that cannot allocate or hold a workspace:
  * code running under HIP graph capture, tight serving loops, harnesses that
  * forbid device allocation.  Same arguments, same kernels and same results as

@@ -37,7 +37,7 @@ EXPORTS = ["sf_last_error", "sf_num_active", "sf_ffn_padded", "sf_gate_scores_to
            "sf_encoder_forward_fp8", "sf_proj_fp8_padded", "sf_presence_to_key_valid",
            "sf_sparse_gqa_static_capacity", "sf_sparse_gqa_forward_static", "sf_ceiling_mfma_launch",
            "sf_ceiling_copy_launch", "sf_token_pack_rows_max", "sf_token_pack", "sf_token_unpack",
-           "sf_encoder_packed_workspace_bytes", "sf_encoder_forward_packed"]
+           "sf_encoder_packed_workspace_bytes", "sf_encoder_forward_packed", "sf_sparse_gqa_plan"]
 SF_GATE_RELU, SF_GATE_TANH = 0, 1
 SF_KERNEL_GEMM, SF_KERNEL_SCORE, SF_KERNEL_ATTEND = 0, 1, 2
 
@@ -144,8 +144,9 @@ def lib():
                   "sf_encoder_forward_ragged", "sf_encoder_forward_fp8ffn", "sf_compact_heads_channels_f16",
                   "sf_active_projection_rows", "sf_compact_proj_fp8", "sf_encoder_forward_fp8", "sf_proj_fp8_padded",
                   "sf_presence_to_key_valid", "sf_sparse_gqa_forward_static", "sf_token_pack_rows_max",
-                  "sf_token_pack", "sf_token_unpack", "sf_encoder_forward_packed"):
+                  "sf_token_pack", "sf_token_unpack", "sf_encoder_forward_packed", "sf_sparse_gqa_plan"):
             getattr(L, n).restype = C.c_int32
+        L.sf_sparse_gqa_plan.argtypes = [C.POINTER(SfDesc), C.c_int32, C.c_int32, C.POINTER(C.c_int32)]
         L.sf_token_pack_rows_max.argtypes = [C.POINTER(SfDesc)]
         L.sf_token_pack.argtypes = [C.POINTER(SfDesc), C.c_void_p, C.c_void_p, C.c_void_p, C.POINTER(SfTokenPackPlan),
                                     C.c_void_p, C.c_void_p]
@@ -495,6 +496,13 @@ def _strides4(t: torch.Tensor) -> SfStrides:
 
 def sparse_gqa_workspace_bytes(desc: SfDesc, nH: int, nG: int) -> int:
     return int(lib().sf_sparse_gqa_workspace_bytes(C.byref(desc), nH, nG))
+
+
+def sparse_gqa_plan(desc: SfDesc, nH: int, nG: int) -> Dict[str, int]:
+    """Which kernels sparse_gqa_forward takes for a 16-bit problem (see sf_sparse_gqa_plan)."""
+    p = (C.c_int32 * 4)()
+    _check(lib().sf_sparse_gqa_plan(C.byref(desc), int(nH), int(nG), p), "sf_sparse_gqa_plan")
+    return dict(zip(("staged", "splits", "score_parts", "stat_parts"), p))
 
 
 def sparse_gqa_forward(desc: SfDesc, Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor,

@@ -48,6 +48,7 @@ __device__ __forceinline__ int64_t sample_row(const int32_t *row0, int b, int L)
 // Pieces of the workspace (all sizes derive from the same few integers, so the
 // size query and the forward agree by construction).
 struct AttnPlan {
+    bool staged;           // active pass: tiles staged in LDS (else the keys are dealt to the waves of a workgroup per head)
     int splits;            // key splits of the active pass (1 = write O directly)
     int keys_per_split;    // multiple of 64
     int stat_parts;        // key ranges of the K/V statistics (1 = one launch)
@@ -63,7 +64,7 @@ struct AttnPlan {
 };
 AttnPlan attn_plan(int dtype, const AttnArgs &a, void *ws);
 
-constexpr int SLICE_U = 256;        // fewer active queries per head: the keys are dealt to the waves of a workgroup per head
+constexpr int STAGED_U = 256;       // from so many active queries per head the active pass always stages its tiles (two query blocks per wave up to dh 64)
 
 int32_t attention_forward(int dtype, const AttnArgs &a, hipStream_t st);
 
@@ -75,6 +76,7 @@ int32_t attention_forward(int dtype, const AttnArgs &a, hipStream_t st);
 int32_t score_bf16(const AttnArgs &a, const void *Kx, sf_strides skx, int Lk, const uint8_t *key_mask,
                    const float *stats, float *score, int scoreH, int parts, hipStream_t st);
 int score_bf16_parts(const AttnArgs &a, int Lk);
+bool attend_bf16_staged(const AttnArgs &a, int splits);      // splits: into how many the staged kernel would split the keys
 int32_t attend_bf16(const AttnArgs &a, const AttnPlan &pl, const void *vt, sf_strides svt,
                     const int32_t *sel, int selH, hipStream_t st);
 

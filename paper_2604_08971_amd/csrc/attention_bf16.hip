@@ -255,9 +255,10 @@ __device__ __forceinline__ float both_halves_sum(float v)
 // XCD and share its L2, and the items are spread evenly over the XCDs.
 constexpr int AWAVE = 8;
 
-// Serves head dimension 128 with U >= 256; the other shapes have kernels of their own below.
-template <int DH, int QB>
-__global__ __launch_bounds__(AWAVE * 64) void attend_bf16_kernel(
+// NW = waves per workgroup.  Four instead of eight where a (sample, group) has at most four pairs: the same registers
+// per wave then leave room for three workgroups per compute unit, and no wave is without a pair.
+template <int DH, int QB, int NW>
+__global__ __launch_bounds__(NW * 64) void attend_bf16_kernel(
     const h16 *__restrict__ Q, sf_strides sq, const h16 *__restrict__ K, sf_strides sk,
     const h16 *__restrict__ VT, sf_strides svt, const int32_t *__restrict__ head_group, int hg_stride,
     const int32_t *__restrict__ pattern_id, const uint8_t *__restrict__ key_valid,
@@ -265,7 +266,7 @@ __global__ __launch_bounds__(AWAVE * 64) void attend_bf16_kernel(
     int Upad, int splits, int keys_per_split, h16 *__restrict__ O, int64_t ldo,
     float *__restrict__ part_o, float *__restrict__ part_ml, const int32_t *__restrict__ row0)
 {
-    constexpr int NW = AWAVE, NT = NW * 64;
+    constexpr int NT = NW * 64;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int KT = BKEY * (DH + PAD), VT_ = DH * (BKEY + PAD);          // elements of one K / V^T tile
     h16 *Ks = reinterpret_cast<h16 *>(smem);                         // [2][BKEY][DH+PAD]
@@ -577,7 +578,8 @@ __global__ __launch_bounds__(AWAVE * 64) void attend_bf16_kernel(
 // for all heads of a group walked them one after the other in one workgroup per (sample, group).  us, staged (with the
 // merge launch where the keys were split) / sliced: 256 samples of 480 keys, 4 heads 38 / 29; 64 of 384 keys, 6 heads
 // 11.6 / 8.0; 37 of 1021 keys, 8 heads 20 + 7 / 18; 16 of 4096 keys, 8 heads 31 + 6 / 37; 1 of 512 keys, 6 heads 10 + 4 / 8.5;
-// 128 of 512 keys, 6 heads in two groups 19 / 23 (the one case where sharing the tiles over six pairs pays).
+// but 128 of 512 keys, 6 heads in two groups 19 / 23, 4 of 16384 keys, 2 heads in a group 16 + 5 / 118: attend_bf16_staged()
+// chooses.
 //
 // The keys of a tile are assigned to the rows of S^T so that a lane's 16 scores are two runs of 8 consecutive keys: row
 // 8 a + 4 h + r (a < 4, h < 2, r < 4) holds key 16 (a / 2) + 8 h + 4 (a % 2) + r.  P then meets V^T fragments that are
@@ -1178,6 +1180,62 @@ int32_t score_bf16(const AttnArgs &a, const void *Kx, sf_strides skx, int Lk, co
     return fail(SF_ERR_SHAPE, "sparse_gqa(bf16): dh must be 32, 64 or 128");
 }
 
+// Waves of the staged kernel: four instead of eight where the launch has a (sample, group) problem per compute unit or
+// more (no key splits) and at most four pairs per problem (256 samples of 480 keys, 4 heads of a group each: 66 -> 49 us);
+// with split keys the launch is short of work per compute unit and eight waves with key groups are faster (45 -> 40 us for 16
+// samples of 4096 keys, two heads per group); dh 128 needs 232 registers with four waves, i.e. one wave per SIMD, and so few
+// pairs of dh 32 are served by the sliced kernel.
+static int staged_waves(int dh, int pairs, int splits) { return dh == 64 && pairs <= 4 && splits == 1 ? 4 : AWAVE; }
+
+// The sliced kernel: two query blocks per wave halve the reads of K and V (256 samples of 480 keys, 4 heads: 35 -> 29 us) where
+// the heads alone fill the chip; four waves instead of eight where the items do.
+struct SliceShape { int qb, nw; int64_t items; };
+static SliceShape slice_shape(const AttnArgs &a)
+{
+    const int64_t heads = (int64_t)a.B * a.nH, nqb = ceil_div(a.U, 32);
+    const int qb = a.dh < 128 && nqb > 1 && heads >= 256 ? 2 : 1;
+    return SliceShape{qb, qb == 2 || heads * nqb >= 512 ? 4 : 8, heads * ((nqb + qb - 1) / qb)};
+}
+
+// Which kernel serves fewer than STAGED_U active rows.  Sliced, every item (head, query blocks) reads K and V for itself and
+// one workgroup walks all its keys; staged, the pairs of a group share them and the keys of a sample are split over the
+// compute units, at the price of a merge.  So sliced it is for short sequences, and where a group has one head or two;
+// long ones (16384 keys, 4 heads: 118 us sliced, 17 + 5 staged) and groups of many pairs (512 samples of 512 keys,
+// 16 heads in one group, dh 128: 538 / 206) stay with the staged tiles.
+// Where nothing is split, few pairs are sliced, and with a (sample, group) problem per compute unit more of them are not;
+// the rest is an estimate of both times in us (a chain of key tiles, longer where the workgroups need more than one round;
+// or the traffic, each item's own where it is sliced).  Its constants are a fit to 2400 calls drawn at random (1 to 512
+// samples of 48 to 16384 keys, 1 to 8 groups of 1 to 16 heads, 1 to 255 active rows, a third of them masked): over those the
+// choice costs 0.4 % of a call against the better kernel, 20 % at worst (all sliced: 6 %, a factor of 1.9; all staged: 11 %,
+// 2.1).
+bool attend_bf16_staged(const AttnArgs &a, int splits)
+{
+    if (a.U >= STAGED_U) return true;
+    struct Fit {
+        double c, step8, step4, step2, room, room2;          // sliced: call, step of 32 keys (8 waves, 4, two query blocks), workgroups per compute unit
+        double c_st, tile8, tile4, room8, room4, merge;      // staged: call, tile of 64 keys (8 waves, 4), workgroups per compute unit, merge launch
+        double mb, mb_item;                                  // a megabyte of K and V from memory, and once more per item
+    };
+    static constexpr Fit f32 = {4.1, 0.76, 0.56, 0.29, 1.55, 1.25, 4.5, 0.27, 0.27, 0.41, 0.41, 6.1, 0.16, 0.024};
+    static constexpr Fit f64 = {5.4, 1.40, 1.10, 0.85, 0.92, 0.67, 6.5, 0.96, 1.35, 0.53, 1.25, 3.8, 0.17, 0.071};
+    static constexpr Fit f128 = {3.5, 2.98, 2.60, 2.60, 0.90, 0.90, 5.2, 1.45, 1.45, 0.59, 0.59, 5.9, 0.18, 0.080};
+    const Fit &f = a.dh == 32 ? f32 : a.dh == 64 ? f64 : f128;
+    const int64_t bg = (int64_t)a.B * a.nG;
+    const int nqb = ceil_div(a.U, 32), per_group = ceil_div(a.nH, a.nG), pairs = per_group * nqb;
+    if (splits == 1 && pairs <= (a.dh == 32 ? 6 : a.dh == 64 ? 2 : 1)) return false;
+    if (bg >= 256) return true;
+    const double mb = 4e-6 * bg * a.L * a.dh;
+    const SliceShape s = slice_shape(a);
+    const double step = s.qb == 2 ? f.step2 : s.nw == 4 ? f.step4 : f.step8, steps = ceil_div(ceil_div(a.L, 32), s.nw);
+    const double sliced = f.c + std::max(step * steps * std::max(1.0, s.items * s.nw / (2048.0 * (s.qb == 2 ? f.room2 : f.room))),
+                                         mb * (f.mb + f.mb_item * per_group * ((nqb + s.qb - 1) / s.qb)));
+    const int nw = staged_waves(a.dh, pairs, splits);
+    const double tiles = ceil_div(ceil_div(a.L, BKEY), splits), wgs = (double)ceil_div(pairs, nw) * bg * splits;
+    const double staged = f.c_st + std::max(tiles * (nw == 4 ? f.tile4 : f.tile8) * std::max(1.0, wgs / (256.0 * (nw == 4 ? f.room4 : f.room8))), mb * f.mb) +
+                          (splits > 1 ? f.merge : 0.0);
+    return staged <= sliced;
+}
+
 template <int DH, int QB>
 static int32_t launch_attend(const AttnArgs &a, const AttnPlan &pl, const void *vt, sf_strides svt,
                              const int32_t *sel, int selH, hipStream_t st)
@@ -1187,7 +1245,8 @@ static int32_t launch_attend(const AttnArgs &a, const AttnPlan &pl, const void *
     const int nqb = pl.Upad / 32, BG = a.B * a.nG;
     // pair chunks per (sample, group) for evenly spread heads; a group with more heads takes several passes
     const int pairs = ceil_div(a.nH, a.nG) * nqb;
-    const int chunks = ceil_div(pairs, AWAVE * QB);
+    const int nw = QB == 1 ? staged_waves(DH, pairs, pl.splits) : AWAVE;
+    const int chunks = ceil_div(pairs, nw * QB);
     const int64_t items = (int64_t)chunks * BG * pl.splits;
     if (items > (1 << 30)) return fail(SF_ERR_SHAPE, "sparse_gqa(bf16): too many work items");
     dim3 grid((unsigned)align_up(items, 8));
@@ -1198,10 +1257,12 @@ static int32_t launch_attend(const AttnArgs &a, const AttnPlan &pl, const void *
                            a.pattern_id, a.key_valid, sel, selH, a.nH, a.nG, BG, chunks, a.L, pl.Lp, a.U, pl.Upad,
                            pl.splits, pl.keys_per_split, (h16 *)a.O, a.ldo, pl.part_o, pl.part_ml, a.row0);
     } else {
-        hipLaunchKernelGGL((attend_bf16_kernel<DH, QB>), grid, dim3(AWAVE * 64), lds, st, (const h16 *)a.Q, a.sq, (const h16 *)a.K,
-                           a.sk, (const h16 *)vt, svt, a.head_group, a.hg_stride, a.pattern_id, a.key_valid, sel, selH, a.nH,
-                           a.nG, BG, chunks, a.L, pl.Lp, a.U, pl.Upad, pl.splits, pl.keys_per_split, (h16 *)a.O, a.ldo,
-                           pl.part_o, pl.part_ml, a.row0);
+#define SF_ATTEND_ARGS grid, dim3(nw * 64), lds, st, (const h16 *)a.Q, a.sq, (const h16 *)a.K, a.sk, (const h16 *)vt, \
+                       svt, a.head_group, a.hg_stride, a.pattern_id, a.key_valid, sel, selH, a.nH, a.nG, BG, chunks, a.L, \
+                       pl.Lp, a.U, pl.Upad, pl.splits, pl.keys_per_split, (h16 *)a.O, a.ldo, pl.part_o, pl.part_ml, a.row0
+        if (nw == 4) hipLaunchKernelGGL((attend_bf16_kernel<DH, QB, DH == 64 ? 4 : AWAVE>), SF_ATTEND_ARGS);
+        else hipLaunchKernelGGL((attend_bf16_kernel<DH, QB, AWAVE>), SF_ATTEND_ARGS);
+#undef SF_ATTEND_ARGS
     }
     return SF_OK;
 }
@@ -1233,22 +1294,25 @@ int32_t attend_bf16(const AttnArgs &a, const AttnPlan &pl, const void *vt, sf_st
                     const int32_t *sel, int selH, hipStream_t st)
 {
     if (a.nH > 64) return fail(SF_ERR_SHAPE, "sparse_gqa(bf16): at most 64 heads");
-    if (a.U >= SLICE_U) {                        // dense-like: two query blocks per wave
+    if (pl.staged && a.U < STAGED_U) {
+        switch (a.dh) {
+        case 32: return launch_attend<32, 1>(a, pl, vt, svt, sel, selH, st);
+        case 64: return launch_attend<64, 1>(a, pl, vt, svt, sel, selH, st);
+        case 128: return launch_attend<128, 1>(a, pl, vt, svt, sel, selH, st);
+        }
+    } else if (pl.staged) {                      // dense-like: two query blocks per wave
         switch (a.dh) {
         case 32: return launch_attend<32, 2>(a, pl, vt, svt, sel, selH, st);
         case 64: return launch_attend<64, 2>(a, pl, vt, svt, sel, selH, st);
         case 128: return launch_attend<128, 1>(a, pl, vt, svt, sel, selH, st);
         }
     } else {
-        // two query blocks per wave halve the reads of K and V (256 samples of 480 keys, 4 heads: 35 -> 29 us) where the
-        // heads alone fill the chip; four waves instead of eight where the items do
-        const int64_t heads = (int64_t)a.B * a.nH, nqb = pl.Upad / 32;
-        const bool two = nqb > 1 && heads >= 256, four = heads * nqb >= 512;
+        const SliceShape s = slice_shape(a);
 #define SF_SLICE(DH, QB, NW) launch_attend_slice<DH, QB, NW>(a, pl, vt, svt, sel, selH, st)
         switch (a.dh) {
-        case 32: return two ? SF_SLICE(32, 2, 4) : four ? SF_SLICE(32, 1, 4) : SF_SLICE(32, 1, 8);
-        case 64: return two ? SF_SLICE(64, 2, 4) : four ? SF_SLICE(64, 1, 4) : SF_SLICE(64, 1, 8);
-        case 128: return four ? SF_SLICE(128, 1, 4) : SF_SLICE(128, 1, 8);
+        case 32: return s.qb == 2 ? SF_SLICE(32, 2, 4) : s.nw == 4 ? SF_SLICE(32, 1, 4) : SF_SLICE(32, 1, 8);
+        case 64: return s.qb == 2 ? SF_SLICE(64, 2, 4) : s.nw == 4 ? SF_SLICE(64, 1, 4) : SF_SLICE(64, 1, 8);
+        case 128: return s.nw == 4 ? SF_SLICE(128, 1, 4) : SF_SLICE(128, 1, 8);
         }
 #undef SF_SLICE
     }

@@ -589,19 +589,19 @@ static AttnPlan attn_plan_parts(int dtype, const AttnArgs &a, void *ws, int scor
     pl.Sp = a.n_sample > 0 ? (int)align_up(a.n_sample, 64) : 0;
     pl.splits = 1;
     pl.keys_per_split = (int)align_up(a.L, 64);
-    if (dtype == SF_BF16 && sparse && a.U >= SLICE_U) {
+    if (dtype == SF_BF16 && a.U > 0) {
         // the staged active pass has only B*nG independent (sample, group) problems: with fewer than one per compute unit
         // the keys are split until one workgroup per compute unit exists (256; the kernel keeps one workgroup per compute
-        // unit resident), and only into pieces of at least four key tiles
+        // unit resident, so 384 or 512 workgroups run in two rounds: 16 samples of 4096 keys, 36 us for 256 against
+        // 47 / 41 / 51 us for 384 / 512 / 1024), and only into pieces of at least four key tiles
         const int64_t bg = (int64_t)a.B * a.nG;
-        int want = bg >= 256 ? 1 : (int)((256 + bg - 1) / bg);
+        int want = bg >= 256 || !sparse ? 1 : (int)((256 + bg - 1) / bg);
         const int max_splits = a.L / 256 > 0 ? a.L / 256 : 1;
         if (want > max_splits) want = max_splits;
         if (want > 64) want = 64;                     // the merge holds one split per lane
-        if (want > 1) {
-            pl.keys_per_split = (int)align_up(ceil_div(a.L, want), 64);
-            pl.splits = ceil_div(a.L, pl.keys_per_split);
-        }
+        const int keys = (int)align_up(ceil_div(a.L, want), 64), splits = ceil_div(a.L, keys);
+        pl.staged = attend_bf16_staged(a, splits);
+        if (pl.staged) { pl.splits = splits; pl.keys_per_split = keys; }
     }
     pl.score_parts = score_parts;
     Carver c(ws);
@@ -827,6 +827,17 @@ extern "C" size_t sf_sparse_gqa_workspace_bytes(const sf_desc *desc, int32_t nH,
     if (make_attn_args(desc, nH, nG, D, a)) return 0;
     a.v_transposed = 0;       // the larger of the two cases
     return attn_plan(D.dtype, a, nullptr).bytes;
+}
+
+extern "C" int32_t sf_sparse_gqa_plan(const sf_desc *desc, int32_t nH, int32_t nG, int32_t *plan_host)
+{
+    Dims D; AttnArgs a;
+    if (int32_t rc = make_attn_args(desc, nH, nG, D, a)) return rc;
+    if (!plan_host) return fail(SF_ERR_INVALID_ARG, "sparse_gqa_plan: NULL argument");
+    if (D.dtype != SF_BF16) return fail(SF_ERR_UNSUPPORTED, "sparse_gqa_plan: 16-bit models only");
+    const AttnPlan pl = attn_plan(D.dtype, a, nullptr);
+    plan_host[0] = pl.staged; plan_host[1] = pl.splits; plan_host[2] = pl.score_parts; plan_host[3] = pl.stat_parts;
+    return SF_OK;
 }
 
 extern "C" int32_t sf_sparse_gqa_forward(const sf_desc *desc, int32_t nH, int32_t nG, const void *Q,

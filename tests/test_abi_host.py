@@ -269,3 +269,21 @@ def test_static_scratch_takes_what_fits_without_key_ranges():
                                              nH * dh, None, None, None)
         assert rc in (-1, -5), ((B, nH, nG, L, dh, U, vt, ns), n, rc, L_.sf_last_error())
     assert near > 20
+
+
+def test_active_pass_kernel_follows_length_and_pairs():
+    """Short sequences and groups of one or two heads deal their keys to the waves; long sequences with little else to do,
+    groups of many pairs and U >= 256 stage their tiles, split where there is less than a (sample, group) per compute unit."""
+    def plan(B, nH, nG, L, dh, U=-1):
+        return sf.sparse_gqa_plan(sf.make_desc(B, L, 64, nH, nG, dh, 64, dtype=sf.SF_BF16, U_override=U), nH, nG)
+    for dh in (32, 64, 128):
+        assert not plan(1, 6, 2, 512, dh)["staged"] and not plan(512, 1, 1, 100, dh, 20)["staged"]
+        assert plan(4, 4, 1, 16384, dh)["staged"] and plan(4, 4, 1, 16384, dh)["splits"] == 64
+        assert plan(512, 16, 1, 512, dh)["staged"] and plan(512, 16, 1, 512, dh)["splits"] == 1
+        assert plan(1, 2, 1, 300, dh, 256)["staged"] and plan(1, 2, 1, 300, dh, 300)["splits"] == 1
+        assert plan(2, 4, 2, 700, dh, 0) == dict(staged=0, splits=1, score_parts=1, stat_parts=1)
+    L = sf.lib()
+    d = sf.make_desc(1, 64, 64, 4, 2, 16, 64, dtype=sf.SF_F32)
+    assert L.sf_sparse_gqa_plan(C.byref(d), 4, 2, (C.c_int32 * 4)()) == -3
+    d = sf.make_desc(1, 64, 64, 4, 2, 32, 64, dtype=sf.SF_BF16)
+    assert L.sf_sparse_gqa_plan(C.byref(d), 4, 2, None) == -1 and L.sf_sparse_gqa_plan(C.byref(d), 0, 2, (C.c_int32 * 4)()) == -1

@@ -36,6 +36,27 @@ def test_attention_edges(dtype, B, nH, nG, L, dh, Uo, mask):
     gqa_case(dtype, B, nH, nG, L, dh, Uo, mask)
 
 
+# Which of the two kernels takes fewer than 256 active rows is an estimate of their times: the plan is asserted, so that every
+# form stays covered.  Staged tiles: key splits with key groups inside a workgroup, four waves, a group with more pairs than
+# waves, each head dimension; sliced keys: four waves with one query block each.
+@pytest.mark.parametrize("B,nH,nG,L,dh,Uo,mask,staged,splits", [
+    (1, 2, 1, 4097, 64, -1, True, 1, 13),         # last tile of one key
+    (3, 3, 1, 9000, 32, -1, False, 1, 29),
+    (2, 2, 1, 2049, 128, -1, True, 1, 7),
+    (130, 4, 2, 97, 64, 33, True, 1, 1),          # four waves
+    (130, 10, 2, 97, 64, 64, False, 1, 1),        # ten pairs
+    (130, 8, 2, 97, 32, 33, True, 1, 1),
+    (130, 2, 2, 97, 128, 33, False, 1, 1),
+    (130, 4, 4, 97, 64, 31, True, 0, 1),
+    (130, 4, 4, 65, 128, 32, True, 0, 1),
+    (130, 6, 2, 65, 32, 32, False, 0, 1),
+])
+def test_active_pass_kernels(B, nH, nG, L, dh, Uo, mask, staged, splits):
+    plan = sf.sparse_gqa_plan(sf.make_desc(B, L, 64, 8, 2, dh, 64, dtype=sf.SF_BF16, U_override=Uo), nH, nG)
+    assert (plan["staged"], plan["splits"]) == (staged, splits), plan
+    gqa_case("bf16", B, nH, nG, L, dh, Uo, mask)
+
+
 # one sample whose only modality is a few tokens at the end: most key tiles are dead
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 def test_encoder_with_dead_tiles(dtype):
