@@ -193,7 +193,7 @@ static int stats_parts(int64_t problems, int L)
 // ------------------------------------------------------------------- lazy rows
 // Every row that is not active in a head takes the head's group's context vector there: done by the block that has just
 // chosen the head's active rows (it needs no row -> slot map from memory), before the active pass writes those rows.
-// O == NULL: the caller projects the lazy rows itself.  us, selection + fill in two launches / in one: 1024 rows of 480
+// O == NULL: somebody else does (fill_rows_kernel, or a caller that projects the lazy rows itself).  us, selection + fill in two launches / in one: 1024 rows of 480
 // scores 10.3 + 22.7 / 18.7 (63 MB written), 768 rows of 512 8.8 + 18.0 / 15.6, 384 rows of 384 7.4 + 7.0 / 9.0.
 template <class T>
 struct Fill {
@@ -223,14 +223,25 @@ struct HeadFill {
         for (int t = 0; t < VEC; ++t) v[t] = from_f32<T>(ctx[t]);
         o = f.O + sample_row(f.row0, b, L) * f.ldo + (int64_t)h * f.dh + c * VEC;
     }
+    __device__ __forceinline__ void put(const Fill<T> &f, int r) const { *reinterpret_cast<vec *>(o + (int64_t)r * f.ldo) = v; }
     __device__ __forceinline__ void write(const Fill<T> &f, int L, const uint32_t *kept) const
     {
         if (!o) return;
 #pragma unroll 4
         for (int r = threadIdx.x / (f.dh / VEC); r < rows; r += step)
-            if (r >= L || !kept[r]) *reinterpret_cast<vec *>(o + (int64_t)r * f.ldo) = v;
+            if (r >= L || !kept[r]) put(f, r);
     }
 };
+
+// Every row of a head, by many blocks: the active pass, which comes later, writes the active ones over it.
+template <int VEC, class T>
+__global__ __launch_bounds__(256) void fill_rows_kernel(int nH, int L, Fill<T> fill)
+{
+    const HeadFill<256, VEC, T> hf(fill, blockIdx.y / nH, blockIdx.y % nH, L);
+    if (!hf.o) return;
+#pragma unroll 4
+    for (int r = blockIdx.x * hf.step + threadIdx.x / (fill.dh / VEC); r < hf.rows; r += gridDim.x * hf.step) hf.put(fill, r);
+}
 
 // ------------------------------------------------------------------- selection
 // One block per (b, head): the U_eff = min(U, u_active[b], #allowed) queries with the
@@ -264,9 +275,10 @@ __global__ __launch_bounds__(NT) void select_kernel(
         if (sc.score) {
             float m = sc.score[m0 + i];
             if (sc.n > 1) {
+                const float mean = sc.score[sc.n * sc.stride + m0 + i];
 #pragma unroll 4
                 for (int p = 1; p < sc.n; ++p) m = fmaxf(m, sc.score[p * sc.stride + m0 + i]);
-                m = !ok ? -INFINITY : no_key ? 0.f : (m - sc.score[sc.n * sc.stride + m0 + i]) * sc.scale;
+                m = !ok ? -INFINITY : no_key ? 0.f : (m - mean) * sc.scale;
                 if (sc.out) sc.out[((int64_t)b * sc.outH + h) * L + i] = m;
             }
             key = max(sortable_key(m), 1u);
@@ -712,17 +724,31 @@ int32_t attention_forward(int dtype, const AttnArgs &a, hipStream_t st)
     const int selH = a.sel_out ? userH : a.nH;
     // the row -> slot map is read by the projection of the active rows only
     int32_t *slot = a.act_bits ? pl.slot : nullptr;      // act_bits implies need_slot
-    auto fill_args = [&](auto *O) {
+    // Few heads with long rows: a block per head would write for longer than a launch costs.  us, fill beside the selection /
+    // spread over the chip, 8 heads, dh 64: 2048 rows (256 KB a head) 44.1 / 43.5, 4096 62.9 / 59.8, 16384 373 / 356; 64 heads
+    // even.  The blocks of a caller's list have 256 threads instead of 1024: 1024 rows 25.9 / 23.6, 16384 119 / 57; 128 heads
+    // of 2048 rows 39.7 / 35.9, 256 even.  With most rows active there is little to fill.
+    const bool forced = a.forced_sel && a.U > 0;
+    const int64_t head_bytes = (int64_t)a.L * a.dh * elem_size(dtype);
+    const bool spread = !a.skip_fill && a.U * 2 <= a.L && BH < (forced ? 256 : 64) && head_bytes >= (forced ? 128 : 256) * 1024;
+    auto fill_args = [&](auto *O, bool beside) {
         Fill<std::remove_pointer_t<decltype(O)>> f{};
-        f.O = a.skip_fill ? nullptr : O; f.ldo = a.ldo; f.stats = pl.stats; f.head_group = a.head_group; f.hg_stride = a.hg_stride;
+        f.O = a.skip_fill || beside == spread ? nullptr : O; f.ldo = a.ldo; f.stats = pl.stats; f.head_group = a.head_group; f.hg_stride = a.hg_stride;
         f.pattern_id = a.pattern_id; f.nG = a.nG; f.dh = a.dh; f.row0 = a.row0; f.ext = a.ext;
         return f;
     };
-    const Fill<h16> fill16 = fill_args((h16 *)a.O);
-    const Fill<float> fill32 = fill_args((float *)a.O);
+    const Fill<h16> fill16 = fill_args((h16 *)a.O, true);
+    const Fill<float> fill32 = fill_args((float *)a.O, true);
     const bool v8 = a.ldo % 8 == 0 && ((uintptr_t)a.O % 16 == 0);              // 16-byte rows of O
+    if (spread) {                                  // every row; the active pass writes its rows over it
+        const int vec = dtype == SF_BF16 && v8 ? 8 : 4;
+        const dim3 grid(ceil_div(a.L, 8 * (256 / (a.dh / vec))), BH);            // eight rows per thread
+        if (dtype != SF_BF16) hipLaunchKernelGGL((fill_rows_kernel<4, float>), grid, dim3(256), 0, st, a.nH, a.L, fill_args((float *)a.O, false));
+        else if (v8) hipLaunchKernelGGL((fill_rows_kernel<8, h16>), grid, dim3(256), 0, st, a.nH, a.L, fill_args((h16 *)a.O, false));
+        else hipLaunchKernelGGL((fill_rows_kernel<4, h16>), grid, dim3(256), 0, st, a.nH, a.L, fill_args((h16 *)a.O, false));
+    }
     const size_t key_bytes = (size_t)a.L * sizeof(uint32_t);
-    if (a.forced_sel && a.U > 0) {
+    if (forced) {
 #define SF_FORCED_ARGS dim3(BH), dim3(256), key_bytes, st, a.forced_sel, userH, a.nH, a.L, a.U, sel, selH, slot, a.act_bits
         if (dtype != SF_BF16) hipLaunchKernelGGL((forced_slot_kernel<4, float>), SF_FORCED_ARGS, fill32);
         else if (v8) hipLaunchKernelGGL((forced_slot_kernel<8, h16>), SF_FORCED_ARGS, fill16);

@@ -12,7 +12,8 @@ from paper_2604_08971_amd import binding as sf
 from paper_2604_08971_amd import workloads as W
 from gpu_utils import to_dev, to_host
 from helpers import make_wl
-from test_gpu_parity import TOL, _encoder_parity, _say, test_sparse_gqa_parity as gqa_case
+from test_gpu_tokens_packed import _packed_case
+from test_gpu_parity import TOL, _encoder_parity, _gqa_case, _say, test_sparse_gqa_parity as gqa_case
 
 pytestmark = pytest.mark.gpu
 
@@ -55,6 +56,22 @@ def test_active_pass_kernels(B, nH, nG, L, dh, Uo, mask, staged, splits):
     plan = sf.sparse_gqa_plan(sf.make_desc(B, L, 64, 8, 2, dh, 64, dtype=sf.SF_BF16, U_override=Uo), nH, nG)
     assert (plan["staged"], plan["splits"]) == (staged, splits), plan
     gqa_case("bf16", B, nH, nG, L, dh, Uo, mask)
+
+
+# Rows of few heads that are filled by many blocks (256 KB a head, half of it with a caller's list; the last block's rows end
+# with the sequence): every row that is not active is its group's context vector
+@pytest.mark.parametrize("dtype,B,nH,nG,L,dh,forced", [
+    ("bf16", 1, 3, 1, 2049, 64, False), ("bf16", 2, 2, 2, 4097, 32, False), ("bf16", 1, 2, 1, 1031, 128, True),
+    ("f32", 1, 2, 1, 1025, 64, False), ("f32", 2, 1, 1, 601, 96, True),
+])
+def test_rows_of_few_heads(dtype, B, nH, nG, L, dh, forced):
+    _say(f"few heads {dtype} B={B} nH={nH} L={L} dh={dh} forced={forced}")
+    _gqa_case(dtype, B, nH, nG, L, dh, -1, True, seed=L, forced=forced)
+
+
+def test_packed_rows_of_few_heads():
+    _say("few heads, packed")
+    _packed_case(make_wl(W.small_spec(dtype="bf16", d=64, Hq=2, Hk=1, dh=32, F=128, nl=1, seg=(2900, 1300), B=2, head_keep=1.0, dropout="upto:1")))
 
 
 # one sample whose only modality is a few tokens at the end: most key tiles are dead
