@@ -70,7 +70,8 @@ __global__ __launch_bounds__(STATS_NT) void kv_stats_f32_kernel(
 
 // 16 bits: 16-byte loads, K rows dh-contiguous, V from its key-contiguous transposed layout [dh][Lp].  A pass covers
 // NT * 8 / DH keys with one load of K and one of V per thread; UN passes are in flight while the previous UN are summed.
-// NT = 256 where the problems fill the chip several times over, 1024 where a problem has a compute unit to itself.
+// NT = 256 where the problems fill the chip several times over or a block has one range of a problem, 1024 where a whole
+// problem has a compute unit to itself.
 template <int DH, int NT>
 __global__ __launch_bounds__(NT) void kv_stats_bf16_kernel(
     const h16 *__restrict__ K, sf_strides sk, const h16 *__restrict__ VT, sf_strides svt,
@@ -161,32 +162,39 @@ __global__ __launch_bounds__(NT) void kv_stats_bf16_kernel(
     }
 }
 
+// Latency is all there is: the counts are one load per thread, and 256 / (2 dh) threads share a column's ranges (one after the
+// other, counts first, 128 ranges of dh 32 took 10 us longer).
 __global__ __launch_bounds__(256) void kv_stats_sum_kernel(const float *__restrict__ part, int parts, int nG, int L, int dh,
                                                            StatsOut out)
 {
-    const int bg = blockIdx.x, b = bg / nG;
-    const float *p = part + (int64_t)bg * parts * (2 * dh + 1);
-    float n = 0.f;
+    __shared__ float red[256];
+    __shared__ int red_n[4];
+    const int bg = blockIdx.x, b = bg / nG, cols = 2 * dh, share = 256 / cols;       // dh 32, 64 or 128
+    const int t = threadIdx.x % cols, first = threadIdx.x / cols;
+    const float *p = part + (int64_t)bg * parts * (cols + 1);
+    int n = 0;
+    for (int c = threadIdx.x; c < parts; c += 256) n += (int)p[(int64_t)c * (cols + 1) + cols];
+    float s = 0.f;
 #pragma unroll 8
-    for (int c = 0; c < parts; ++c) n += p[(int64_t)c * (2 * dh + 1) + 2 * dh];       // whole numbers below 2^24
-    const float inv = n > 0.f ? 1.0f / n : 0.f;
-    for (int t = threadIdx.x; t < 2 * dh; t += 256) {
-        float s = 0.f;
-#pragma unroll 8
-        for (int c = 0; c < parts; ++c) s += p[(int64_t)c * (2 * dh + 1) + t];
-        out.stats[(int64_t)bg * 2 * dh + t] = s * inv;
+    for (int c = first; c < parts; c += share) s += p[(int64_t)c * (cols + 1) + t];
+    red[threadIdx.x] = s;
+    n = block_sum<256>(n, red_n);                                                    // also orders the LDS writes
+    if (first == 0) {
+        for (int k = 1; k < share; ++k) s += red[k * cols + t];
+        out.stats[(int64_t)bg * cols + t] = s * (n > 0 ? 1.0f / (float)n : 0.f);
     }
     if (bg % nG == 0) {
-        if (threadIdx.x == 0) out.n_valid[b] = (int32_t)n;
+        if (threadIdx.x == 0) out.n_valid[b] = n;
         clear_act_bits(out.act_bits, b, L, 256);
     }
 }
 
-// Ranges of keys per problem: one where there are twice as many problems as compute units, or at most 1024 keys; else
-// towards 1024 blocks of at least 128 keys.
-static int stats_parts(int64_t problems, int L)
+// Ranges of keys per problem: one where there are twice as many problems as compute units, or at most 1024 keys of 64 KB
+// (8 problems of 1024 keys, dh 128: 35.6 us for the whole call with one range, 29.9 with eight; 2048 keys, dh 32: 24.5 / 22.3);
+// else towards 1024 blocks of at least 128 keys.
+static int stats_parts(int64_t problems, int L, int dh)
 {
-    if (problems >= 512 || L <= 1024) return 1;
+    if (problems >= 512 || (L <= 1024 && L * dh <= 65536)) return 1;
     return (int)std::min<int64_t>(ceil_div(L, 128), (1024 + problems - 1) / problems);
 }
 
@@ -619,7 +627,7 @@ static AttnPlan attn_plan_parts(int dtype, const AttnArgs &a, void *ws, int scor
     Carver c(ws);
     const size_t BH = (size_t)a.B * a.nH, BG = (size_t)a.B * a.nG;
     pl.vt = (dtype == SF_BF16 && !a.v_transposed) ? c.take<uint16_t>(BG * a.dh * pl.Lp) : nullptr;
-    pl.stat_parts = dtype == SF_BF16 ? stats_parts(BG, a.L) : 1;
+    pl.stat_parts = dtype == SF_BF16 ? stats_parts(BG, a.L, a.dh) : 1;
     pl.stat_part = pl.stat_parts > 1 ? c.take<float>(BG * pl.stat_parts * (2 * a.dh + 1)) : nullptr;
     pl.stats = c.take<float>(BG * 2 * a.dh);
     pl.n_valid = c.take<int32_t>(a.B);
@@ -695,7 +703,7 @@ int32_t attention_forward(int dtype, const AttnArgs &a, hipStream_t st)
         const StatsOut so{pl.stats, pl.n_valid, a.act_bits};
         if (dtype == SF_BF16) {
             const int parts = pl.stat_parts;
-            const bool many = (int64_t)BG * parts >= 512;
+            const bool many = parts > 1 || BG >= 512;
 #define SF_STATS_ARGS 0, st, (const h16 *)a.K, a.sk, (const h16 *)Vuse, svu, a.key_valid, a.nG, a.L, parts, pl.stat_part, so, a.row0
 #define SF_STATS_LAUNCH(DH)                                                                                         \
     do {                                                                                                            \
