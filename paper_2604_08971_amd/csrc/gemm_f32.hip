@@ -58,14 +58,15 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a)
         }
         __syncthreads();
         if (k0 + FK < a.K) fetch(k0 + FK);
-#pragma unroll 16
-        for (int k = 0; k < FK; ++k) {
+        for (int kq = 0; kq < min(FK, a.K - k0); kq += 16)       // K of 16 or 40 has no use for the rest of the step
 #pragma unroll
-            for (int u = 0; u < 2; ++u)
+            for (int k = kq; k < kq + 16; ++k) {
 #pragma unroll
-                for (int v = 0; v < 2; ++v)
-                    acc[u][v] = fmaf(Xs[ty * 2 + u][k], Ws[tx * 2 + v][k], acc[u][v]);
-        }
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int v = 0; v < 2; ++v)
+                        acc[u][v] = fmaf(Xs[ty * 2 + u][k], Ws[tx * 2 + v][k], acc[u][v]);
+            }
         __syncthreads();
     }
     const float *bias = a.bias ? static_cast<const float *>(a.bias) + (int64_t)p * a.bias_pstride + a.n0 : nullptr;
