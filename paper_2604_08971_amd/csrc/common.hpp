@@ -6,6 +6,7 @@
 #include <stdio.h>
 #include <stdarg.h>
 
+#include "gelu.hpp"
 #include "sentryfuse.h"
 
 namespace sf {
@@ -93,28 +94,9 @@ __device__ __forceinline__ uint32_t pack2_h16(float a, float b)
 #endif
 }
 
-// erf-GELU z * Phi(z) for outputs that are rounded to 16 bits or fewer.  With a = |z|,
-//     Phi(-a) = 2^(-a^2 log2(e) / 2) * P(t),  t = 1 / (1 + 0.295 a),
-// P the degree-8 polynomial that approximates erfcx(a / sqrt(2)) / 2 on 0 <= a <= 14 with the smallest relative error
-// (3.7e-8; iteratively reweighted least squares in t).  In fp32 the result is within 7e-7 of the true value (relative)
-// for z > -3 and within 8e-6 for every z down to -13; 0.5 z (1 + erf(z / sqrt(2))) loses its last digits to the
-// cancellation there (5e-4 at -4, all of them below -5.5).  About 20 instructions without a branch where erff is two
-// divergent branches of about 20 each: 37 777 x 960 outputs with K 384 take 80 us with erff, 42 us without.
 __device__ __forceinline__ float gelu_erf(float z)
 {
-    const float a = fabsf(z);
-    const float t = __builtin_amdgcn_rcpf(fmaf(0.295f, a, 1.0f));
-    float p = 0.039421223f;
-    p = fmaf(p, t, -0.18340647f);
-    p = fmaf(p, t, 0.27101713f);
-    p = fmaf(p, t, -0.117071636f);
-    p = fmaf(p, t, 0.16628928f);
-    p = fmaf(p, t, 0.08474469f);
-    p = fmaf(p, t, 0.121699415f);
-    p = fmaf(p, t, 0.11728934f);
-    p = fmaf(p, t, 1.7007076e-05f);
-    const float q = p * __builtin_amdgcn_exp2f(z * z * -0.72134752f);      // Phi(-a)
-    return z * (z < 0.f ? q : 1.0f - q);
+    return gelu_erf(z, [](float x) { return __builtin_amdgcn_rcpf(x); }, [](float x) { return __builtin_amdgcn_exp2f(x); });
 }
 
 // Order-preserving map of fp32 to uint32 (larger float <=> larger key).

@@ -70,7 +70,10 @@ __device__ __forceinline__ float activate(float z)
 {
     // integer max on the bit pattern: one instruction, -0 and negatives give +0, no canonicalisation pass
     if (ACT == ACT_RELU) return __int_as_float(max(__float_as_int(z), 0));
-    if (ACT == ACT_GELU) return gelu_erf(z);
+    if (ACT == ACT_GELU) {
+        asm volatile("" : "+v"(z));      // keeps the two epilogues' copies apart: hoisted above their branch they spill the accumulators
+        return gelu_erf(z);
+    }
     return z;
 }
 
