@@ -552,6 +552,7 @@ bool gemm_bf16_tile_eligible(const GemmArgs &a)
         if (a.R || a.c_f32 || ((a.vt_b | a.vt_n) & 7)) return false;
     }
     if (a.epi == EPI_ROWMAJOR && (a.ldc % 8 || a.c0 % 8 || (a.R && (a.ldr % 8 || a.r0 % 8)))) return false;
+    if (((uintptr_t)a.A | (uintptr_t)a.W) & 15) return false;              // loads straight into LDS: whole aligned chunks
     // 32-bit byte offsets: within a tile, or (row_map) anywhere in A, which the caller keeps below 4 GiB
     return a.lda < ((int64_t)1 << 23) && a.ldw < ((int64_t)1 << 23);
 }

@@ -644,6 +644,7 @@ bool gemm_bf16_ws_eligible(const GemmArgs &a)
         a.ldc % 8 || a.c0 % 8 || (a.R && (a.ldr % 8 || a.r0 % 8)))
         return false;
     if (a.L < 192 || a.N < 192) return false;
+    if (((uintptr_t)a.A | (uintptr_t)a.W) & 15) return false;              // loads straight into LDS: whole aligned chunks
     if ((int64_t)a.L * a.lda * 2 >= ((int64_t)1 << 32) || (int64_t)a.N * a.ldw * 2 >= ((int64_t)1 << 32)) return false;
     return true;
 }

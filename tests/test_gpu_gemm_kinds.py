@@ -3,10 +3,12 @@ edges of their tiles and at a K tail of half a K tile, through the pruned FFN an
 from __future__ import annotations
 
 import pytest
+import torch
 
 from paper_2604_08971_amd import binding as sf
 from paper_2604_08971_amd import workloads as W
-from helpers import make_wl
+from gpu_utils import DeviceModel, to_host
+from helpers import err_metric, make_wl
 from test_gpu_parity import _encoder_parity, _ffn_case, _moe_case, _say
 
 pytestmark = pytest.mark.gpu
@@ -44,3 +46,20 @@ def test_moe_on_small_tiles(dtype, B, seg, d, F, E, k):
     with sf.use_half("f16" if dtype == "f16" else "bf16"):
         _moe_case(wl, E, k, pre_ln=False)
         _moe_case(wl, E, k, forced=True)
+
+
+# a caller's X that starts on an odd element, which the loads straight into LDS do not take: few rows and many
+@pytest.mark.parametrize("B,L,d,F", [(1, 33, 96, 200), (2, 300, 256, 512)])
+def test_ffn_on_a_misaligned_input(B, L, d, F):
+    _say(f"misaligned X B={B} L={L} d={d} F={F}")
+    wl = make_wl(W.small_spec(dtype="bf16", B=B, seg=(L - 1,), extra=1, d=d, Hq=2, Hk=1, dh=32, F=F, nl=1, dropout="none", final_ln=False))
+    dm = DeviceModel(wl).build_plan()
+    X = dm.x.view(B * L, d)
+    odd = torch.empty(X.numel() + 8, dtype=X.dtype, device="cuda")[1:X.numel() + 1].view(B * L, d)
+    odd.copy_(X)
+    assert odd.data_ptr() % 16 == 2
+    for res in (True, False):
+        ref, got = (sf.pruned_ffn_forward(dm.desc, dm.layers[0], x, dm.pattern_id, False, res) for x in (X, odd))
+        torch.cuda.synchronize()
+        # the same rounding points, sums in another order: one unit of the hidden activations and of the output
+        assert err_metric(to_host(got), to_host(ref)) <= 2.0 ** -6
