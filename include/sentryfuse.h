@@ -453,6 +453,13 @@ int32_t sf_pruned_ffn_forward(const sf_desc *desc, const sf_compact_layer *layer
                               int32_t add_residual, void *Y, void *workspace,
                               size_t workspace_bytes, void *stream);
 
+/* Which GEMM kernel a 16-bit model runs for desc->B samples of desc->L rows, N
+ * outputs and K inputs (a reporting aid; host only, nothing is launched): 0 =
+ * 256 x 256 tiles, 1 = 128 x 128 tiles, 2 / 3 = four / eight K slices, 4 = the
+ * kernel for sizes the others refuse.  act 0 none, 1 ReLU, 2 GELU; residual: fp32
+ * output added to an fp32 residual; desc->P > 1: each sample has its own weights. */
+int32_t sf_gemm_kernel(const sf_desc *desc, int32_t N, int32_t K, int32_t act, int32_t residual);
+
 /* ------------------------------------------------------------------------
  * encoder_forward -- the pruned encoder: for l = 0..n_layers-1
  *     x <- x + OutProj( SentryAttend( QKV( LN1(x) ) ) )

@@ -37,7 +37,8 @@ EXPORTS = ["sf_last_error", "sf_num_active", "sf_ffn_padded", "sf_gate_scores_to
            "sf_encoder_forward_fp8", "sf_proj_fp8_padded", "sf_presence_to_key_valid",
            "sf_sparse_gqa_static_capacity", "sf_sparse_gqa_forward_static", "sf_ceiling_mfma_launch",
            "sf_ceiling_copy_launch", "sf_token_pack_rows_max", "sf_token_pack", "sf_token_unpack",
-           "sf_encoder_packed_workspace_bytes", "sf_encoder_forward_packed", "sf_sparse_gqa_plan"]
+           "sf_encoder_packed_workspace_bytes", "sf_encoder_forward_packed", "sf_sparse_gqa_plan",
+           "sf_gemm_kernel"]
 SF_GATE_RELU, SF_GATE_TANH = 0, 1
 SF_KERNEL_GEMM, SF_KERNEL_SCORE, SF_KERNEL_ATTEND = 0, 1, 2
 
@@ -144,8 +145,10 @@ def lib():
                   "sf_encoder_forward_ragged", "sf_encoder_forward_fp8ffn", "sf_compact_heads_channels_f16",
                   "sf_active_projection_rows", "sf_compact_proj_fp8", "sf_encoder_forward_fp8", "sf_proj_fp8_padded",
                   "sf_presence_to_key_valid", "sf_sparse_gqa_forward_static", "sf_token_pack_rows_max",
-                  "sf_token_pack", "sf_token_unpack", "sf_encoder_forward_packed", "sf_sparse_gqa_plan"):
+                  "sf_token_pack", "sf_token_unpack", "sf_encoder_forward_packed", "sf_sparse_gqa_plan",
+                  "sf_gemm_kernel"):
             getattr(L, n).restype = C.c_int32
+        L.sf_gemm_kernel.argtypes = [C.POINTER(SfDesc)] + [C.c_int32] * 4
         L.sf_sparse_gqa_plan.argtypes = [C.POINTER(SfDesc), C.c_int32, C.c_int32, C.POINTER(C.c_int32)]
         L.sf_token_pack_rows_max.argtypes = [C.POINTER(SfDesc)]
         L.sf_token_pack.argtypes = [C.POINTER(SfDesc), C.c_void_p, C.c_void_p, C.c_void_p, C.POINTER(SfTokenPackPlan),
@@ -563,6 +566,17 @@ def _check_sample(desc: SfDesc, sample_idx: Optional[torch.Tensor], B: int):
 
 
 # --------------------------------------------------------------------------- a9
+GEMM_KERNELS = ("256x256", "128x128", "slices4", "slices8", "generic")
+
+
+def gemm_kernel(desc: SfDesc, N: int, K: int, act: int = 0, residual: bool = False) -> str:
+    """Which of GEMM_KERNELS runs desc.B samples of desc.L rows, N outputs and K inputs (see sf_gemm_kernel)."""
+    r = lib().sf_gemm_kernel(C.byref(desc), int(N), int(K), int(act), int(residual))
+    if r < 0:
+        _check(r, "sf_gemm_kernel")
+    return GEMM_KERNELS[r]
+
+
 def pruned_ffn_forward(desc: SfDesc, layer: CompactLayer, X: torch.Tensor,
                        pattern_id: Optional[torch.Tensor] = None, pre_ln: bool = True,
                        add_residual: bool = True, ws: Optional[torch.Tensor] = None) -> torch.Tensor:

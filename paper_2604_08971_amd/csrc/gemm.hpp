@@ -73,8 +73,9 @@ void quantize_rows_fp8(const void *x, int64_t ld, int64_t rows, int K, int Kp, f
 void transpose_v(const void *src, int64_t ld, int col0, int ncols, int B, int L, int Lp, void *vt, hipStream_t st,
                  const int32_t *row0 = nullptr);
 
-// The bf16 GEMM kernels: 256 x 256 tiles (gemm_bf16_ws.hip), 128 x 128 tiles and K slices (gemm_bf16_tile.hip)
-enum GemmKind { GEMM_WS, GEMM_PIPE, GEMM_SLICE4, GEMM_SLICE8 };
+// The bf16 GEMM kernels: 256 x 256 tiles (gemm_bf16_ws.hip), 128 x 128 tiles and K slices (gemm_bf16_tile.hip), and the one
+// for sizes and alignments that those refuse (gemm_bf16.hip).  Numbered in sentryfuse.h (sf_gemm_kernel).
+enum GemmKind { GEMM_WS, GEMM_PIPE, GEMM_SLICE4, GEMM_SLICE8, GEMM_GENERIC };
 bool gemm_bf16_ws_eligible(const GemmArgs &a);
 int32_t gemm_bf16_ws(const GemmArgs &a, hipStream_t st);
 bool gemm_bf16_tile_eligible(const GemmArgs &a);

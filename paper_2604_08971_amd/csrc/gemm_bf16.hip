@@ -250,22 +250,28 @@ bool gemm_takes_vt_split(int dtype, const GemmArgs &a)
            !a.c_f32 && !a.n_lim;
 }
 
+// The kernel of a problem, which may become one long sample
+static GemmKind choose(GemmArgs &a)
+{
+    // one weight set and row-major output: the samples are one long one, and no tile is cut at a sample's end
+    if (!a.pattern_id && a.epi == EPI_ROWMAJOR && !a.VT && !a.row_map && (int64_t)a.B * a.L * a.lda * 2 < ((int64_t)1 << 32)) {
+        a.L *= a.B;
+        a.B = 1;
+    }
+    const bool ws_ok = gemm_bf16_ws_eligible(a);
+    if (gemm_bf16_tile_eligible(a)) return gemm_bf16_choose(a, ws_ok);
+    return ws_ok ? GEMM_WS : GEMM_GENERIC;
+}
+
 int32_t gemm_bf16(const GemmArgs &a0, hipStream_t st)
 {
     GemmArgs a = a0;
     if (a.B <= 0 || a.N <= 0) return SF_OK;
     if (a.VT && !gemm_takes_vt_split(SF_BF16, a)) return fail(SF_ERR_UNSUPPORTED, "gemm(bf16): transposed column range on a problem the tiled kernels do not take");
     if (a.row_map && !gemm_takes_row_map(SF_BF16, a)) return fail(SF_ERR_UNSUPPORTED, "gemm(bf16): row_map on a problem the tiled kernels do not take");
-    // one weight set and row-major output: the samples are one long one, and no tile is cut at a sample's end
-    if (!a.pattern_id && a.epi == EPI_ROWMAJOR && !a.VT && !a.row_map && (int64_t)a.B * a.L * a.lda * 2 < ((int64_t)1 << 32)) {
-        a.L *= a.B;
-        a.B = 1;
-    }
-    const bool ws_ok = gemm_bf16_ws_eligible(a), tile_ok = gemm_bf16_tile_eligible(a);
-    if (ws_ok || tile_ok) {
-        const GemmKind kind = tile_ok ? gemm_bf16_choose(a, ws_ok) : GEMM_WS;
-        return kind == GEMM_WS ? gemm_bf16_ws(a, st) : gemm_bf16_tile(kind, a, st);
-    }
+    const GemmKind kind = choose(a);
+    if (kind == GEMM_WS) return gemm_bf16_ws(a, st);
+    if (kind != GEMM_GENERIC) return gemm_bf16_tile(kind, a, st);
     if (a.K % 8 || a.lda % 8 || a.ldw % 8 || a.N % 4 || a.n0 % 4 || (a.R && (a.ldr % 4 || a.r0 % 4)) ||
         (a.epi == EPI_ROWMAJOR && (a.ldc % 4 || a.c0 % 4)))
         return fail(SF_ERR_SHAPE, "gemm(bf16): K, leading dimensions and column origins must be multiples of 8/4");
@@ -275,3 +281,18 @@ int32_t gemm_bf16(const GemmArgs &a0, hipStream_t st)
 }
 
 }  // namespace sf
+
+using namespace sf;
+
+extern "C" int32_t sf_gemm_kernel(const sf_desc *desc, int32_t N, int32_t K, int32_t act, int32_t residual)
+{
+    Dims D;
+    if (int32_t rc = read_desc(desc, D)) return rc;
+    if (N < 1 || K < 1) return fail(SF_ERR_INVALID_ARG, "gemm_kernel: N and K must be positive");
+    if (D.dtype != SF_BF16) return fail(SF_ERR_UNSUPPORTED, "gemm_kernel: 16-bit models only");
+    GemmArgs a{};
+    a.B = D.B; a.L = D.L; a.N = N; a.K = K; a.lda = a.ldw = K; a.ldc = a.ldr = N; a.act = act;
+    a.R = residual ? &a : nullptr; a.r_f32 = a.c_f32 = residual != 0;               // only looked at, never followed
+    a.pattern_id = D.P > 1 ? &D.P : nullptr;
+    return choose(a);
+}

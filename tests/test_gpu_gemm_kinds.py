@@ -25,6 +25,22 @@ def test_ffn_on_small_tiles(act, B, L, d, F, keep):
     _ffn_case("bf16", act, B, L, d, F, keep)
 
 
+# Which kernel takes a problem is an estimate: the choice is asserted, so that the remainders of each kernel stay covered
+# (up-projection, down-projection; K tails in the up-projections)
+@pytest.mark.parametrize("act,B,L,d,F,keep,up,down", [
+    (0, 4, 129, 352, 1000, 1.0, "slices4", "slices8"), (1, 2, 513, 480, 640, 1.0, "slices4", "slices4"),
+    (1, 1, 33, 96, 200, 0.5, "slices8", "slices8"), (0, 30, 129, 352, 1000, 0.64, "128x128", "128x128"),
+    (0, 1, 193, 72, 72, 1.0, "generic", "slices8"), (0, 16, 2100, 512, 2048, 0.6, "256x256", "128x128"),
+])
+def test_ffn_on_each_kernel(act, B, L, d, F, keep, up, down):
+    _say(f"gemm kernels act={act} B={B} L={L} d={d} F={F}: {up}, {down}")
+    desc = sf.make_desc(B, L, d, 8, 2, 8, F, P=3, dtype=sf.SF_BF16)
+    Fp = sf.ffn_padded(desc, max(1, int(keep * F + 0.5)))
+    assert (sf.gemm_kernel(desc, Fp, d, act + 1), sf.gemm_kernel(desc, d, Fp)) == (up, down)
+    if B * L < 8000:                             # the largest case is covered at its size elsewhere
+        _ffn_case("bf16", act, B, L, d, F, keep)
+
+
 # K = kept heads x 32: an odd number of heads leaves a K tail in the output projection; ragged lengths in the transposed
 # column range of the Q/K/V projection, with slices (B = 2) and 128 x 128 tiles (B = 40)
 @pytest.mark.parametrize("dtype,B,seg,drop", [("bf16", 2, (70, 50, 91), "bernoulli:0.3"), ("bf16", 40, (170, 91), "none"),
@@ -38,12 +54,16 @@ def test_encoder_with_an_odd_number_of_heads(dtype, B, seg, drop):
 
 # MoE block: token rows read through a map, expert widths that end a tile early (n_lim, k_lim), K tails of half a K tile
 # (d % 64 == 32), with and without the LayerNorm that would otherwise hand over a padded copy of X
-@pytest.mark.parametrize("dtype,B,seg,d,F,E,k", [("bf16", 3, (70, 50, 9), 96, 200, 4, 2), ("f16", 2, (33, 95), 96, 136, 5, 1),
-                                                 ("bf16", 9, (700, 333), 160, 640, 8, 2), ("f16", 9, (700, 333), 160, 640, 4, 3)])
-def test_moe_on_small_tiles(dtype, B, seg, d, F, E, k):
+@pytest.mark.parametrize("dtype,B,seg,d,F,E,k,up", [("bf16", 3, (70, 50, 9), 96, 200, 4, 2, "128x128"), ("f16", 2, (33, 95), 96, 136, 5, 1, "slices8"),
+                                                    ("bf16", 9, (700, 333), 160, 640, 8, 2, "128x128"), ("f16", 9, (700, 333), 160, 640, 4, 3, "128x128")])
+def test_moe_on_small_tiles(dtype, B, seg, d, F, E, k, up):
     _say(f"moe on small tiles {dtype} B={B} d={d} F={F} E={E}")
     wl = make_wl(W.small_spec(dtype=dtype, B=B, seg=seg, d=d, dh=32, F=F, dropout="upto:1"))
+    # 256-row blocks of one (pattern, expert) each
+    blocks = (wl.x.shape[0] * wl.spec.L * k + 255) // 256 + wl.P * E
+    desc = sf.make_desc(blocks, 256, d, 8, 2, 8, F, P=2, dtype=sf.SF_F16 if dtype == "f16" else sf.SF_BF16)
     with sf.use_half("f16" if dtype == "f16" else "bf16"):
+        assert sf.gemm_kernel(desc, sf.ffn_padded(desc, int(W.make_moe_block(wl, E, k).k_ffn.max())), d, 1) == up
         _moe_case(wl, E, k, pre_ln=False)
         _moe_case(wl, E, k, forced=True)
 
