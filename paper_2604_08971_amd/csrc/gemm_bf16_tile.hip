@@ -72,7 +72,7 @@ __device__ __forceinline__ bool find_tile(const GemmArgs &a, int bm, int bn, int
     t.m0 = (tm_i % tiles_m) * bm;
     t.p = a.pattern_id ? a.pattern_id[t.b] : 0;
     if (t.p < 0) return false;                                     // sample not in use
-    t.vt = a.epi == EPI_VT;
+    t.vt = false;
     t.nt0 = tn_i * bn;
     t.N = a.n_lim ? min(a.N, a.n_lim[t.p]) : a.N;
     if (a.VT) {
@@ -265,13 +265,12 @@ void gemm_pipe_kernel(GemmArgs a, int tiles_m, int tiles_n, int total_tiles, int
                         __builtin_bit_cast(uint2, m);
                 }
         if (vt) {
-            h16 *V = static_cast<h16 *>(a.VT ? a.VT : a.C) + (int64_t)tl.b * a.vt_b;
-            const int vf = a.VT ? a.vt_from : 0;
+            h16 *V = static_cast<h16 *>(a.VT) + (int64_t)tl.b * a.vt_b;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const h16x8 o = *reinterpret_cast<const h16x8 *>(stg + lay(j * 8 + er, ec) * 2);
                 const int n = ncol0 + j * 8 + er, i = mrow0 + ec * 8;
-                h16 *dst = V + (int64_t)(n - vf) * a.vt_n + i;
+                h16 *dst = V + (int64_t)(n - a.vt_from) * a.vt_n + i;
                 if (n < N && i + 7 < a.L) {
                     *reinterpret_cast<h16x8 *>(dst) = o;
                 } else if (n < N) {
@@ -470,12 +469,11 @@ void gemm_slice_kernel(GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
             }
         }
     } else {
-        h16 *V = static_cast<h16 *>(a.VT ? a.VT : a.C) + (int64_t)tl.b * a.vt_b;
-        const int vf = a.VT ? a.vt_from : 0;
+        h16 *V = static_cast<h16 *>(a.VT) + (int64_t)tl.b * a.vt_b;
         for (int c = threadIdx.x; c < BN * (BM / 4); c += NT) {  // one feature of 4 tokens per thread
             const int f = c / (BM / 4), r0 = (c % (BM / 4)) * 4, n = tl.nt0 + f, i = tl.m0 + r0;
             if (n >= N) continue;
-            h16 *dst = V + (int64_t)(n - vf) * a.vt_n + i;
+            h16 *dst = V + (int64_t)(n - a.vt_from) * a.vt_n + i;
             const float bv = bias ? (float)bias[n] : 0.f;
             h16x4 o;
 #pragma unroll
@@ -547,11 +545,10 @@ int32_t launch_kind(GemmKind kind, const GemmArgs &a, hipStream_t st)
 // 16-byte rows and columns, K a multiple of 32 (the K tail is half a tile), offsets within a tile below 4 GiB
 bool gemm_bf16_tile_eligible(const GemmArgs &a)
 {
-    if (a.K % 32 || a.K < TBK || a.N % 8 || a.n0 % 8 || a.lda % 8 || a.ldw % 8) return false;
-    if (a.epi == EPI_VT || a.VT) {
-        if (a.R || a.c_f32 || ((a.vt_b | a.vt_n) & 7)) return false;
-    }
-    if (a.epi == EPI_ROWMAJOR && (a.ldc % 8 || a.c0 % 8 || (a.R && (a.ldr % 8 || a.r0 % 8)))) return false;
+    if (a.epi != EPI_ROWMAJOR || a.K % 32 || a.K < TBK || a.N % 8 || a.n0 % 8 || a.lda % 8 || a.ldw % 8 || a.ldc % 8 || a.c0 % 8 ||
+        (a.R && (a.ldr % 8 || a.r0 % 8)))
+        return false;
+    if (a.VT && (a.R || a.c_f32 || ((a.vt_b | a.vt_n) & 7))) return false;
     if (((uintptr_t)a.A | (uintptr_t)a.W) & 15) return false;              // loads straight into LDS: whole aligned chunks
     // 32-bit byte offsets: within a tile, or (row_map) anywhere in A, which the caller keeps below 4 GiB
     return a.lda < ((int64_t)1 << 23) && a.ldw < ((int64_t)1 << 23);
@@ -566,8 +563,8 @@ int32_t gemm_bf16_tile(GemmKind kind, const GemmArgs &a, hipStream_t st)
     }
 }
 
-// Which kernel takes a problem: an estimate of each one's time in microseconds.  The constants are a fit to 456
-// launches of layers drawn at random (10 to 130 000 rows, d 128 to 1024, K 128 to 4096, kept heads and channels at
+// Which kernel takes a problem: an estimate of each one's time in microseconds, on a whole card of 256 compute units.
+// The constants are a fit to 456 launches of layers drawn at random (10 to 130 000 rows, d 128 to 1024, K 128 to 4096, kept heads and channels at
 // random), with weights that no cache holds: fixed cost, cost of a K tile and cost of an epilogue per workgroup and
 // round.
 //   256 x 256: whole rounds of one workgroup per compute unit, 1.06 us per K tile (1.12 with a residual or fp32 output)
