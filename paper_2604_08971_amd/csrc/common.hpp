@@ -80,18 +80,15 @@ template <class T> __device__ __forceinline__ T from_f32(float x);
 template <> __device__ __forceinline__ float from_f32<float>(float x) { return x; }
 template <> __device__ __forceinline__ h16 from_f32<h16>(float x) { return (h16)x; }   // RNE
 
-// Two fp32 values -> two 16-bit values in one register (a in the low half), round to nearest even
+// Two fp32 values -> two 16-bit values in one register (a in the low half), round to nearest even.  As a vector conversion:
+// one v_cvt_pk_bf16_f32, where element by element the compiler merges two results with a byte permute.  Not as inline
+// assembly, in which the compiler does not see the write: it then left one instruction between the conversion and a matrix
+// instruction that reads the register, where the hardware wants two, and the products were NaN.
 __device__ __forceinline__ uint32_t pack2_h16(float a, float b)
 {
-#ifdef SF_HALF_F16
-    const h16x2 v = {(h16)a, (h16)b};
-    return __builtin_bit_cast(uint32_t, v);
-#else
-    // written out: the compiler converts the elements one by one and merges them with a byte permute
-    uint32_t r;
-    asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-#endif
+    typedef __attribute__((ext_vector_type(2))) float f32x2;
+    const f32x2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, h16x2));
 }
 
 __device__ __forceinline__ float gelu_erf(float z)
