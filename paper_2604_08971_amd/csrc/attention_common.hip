@@ -304,14 +304,17 @@ __global__ __launch_bounds__(NT) void select_kernel(
             if (sl) sl[i] = -1;
         }
     } else {
-        block_topk<NT>(keys, L, k, scratch, k == n_ok, [&](int i, bool kept, int pos) {
+        auto emit = [&](int i, bool kept, int pos) {
             keys[i] = kept ? 1u : 0u;
             if (sl) sl[i] = kept ? pos : -1;
             if (kept) {
                 se[pos] = i;
                 if (act_bits) atomicOr(&act_bits[(int64_t)b * ((L + 31) / 32) + (i >> 5)], 1u << (i & 31));
             }
-        });
+        };
+        if (L <= NT) block_topk<NT, 1>(keys, L, k, scratch, k == n_ok, emit);
+        else if (L <= NT * 4) block_topk<NT, 4>(keys, L, k, scratch, k == n_ok, emit);
+        else block_topk<NT>(keys, L, k, scratch, k == n_ok, emit);
     }
     for (int r = k + threadIdx.x; r < U; r += NT) se[r] = -1;
     __syncthreads();

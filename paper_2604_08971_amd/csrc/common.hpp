@@ -96,6 +96,14 @@ __device__ __forceinline__ float gelu_erf(float z)
     return gelu_erf(z, [](float x) { return __builtin_amdgcn_rcpf(x); }, [](float x) { return __builtin_amdgcn_exp2f(x); });
 }
 
+// A barrier that orders LDS only: __syncthreads() also waits for every load from memory in flight.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Order-preserving map of fp32 to uint32 (larger float <=> larger key).
 __device__ __forceinline__ uint32_t sortable_key(float f)
 {

@@ -23,10 +23,13 @@ __device__ void keep_topk_block(const float *__restrict__ g, int n, int lp, int 
     int32_t *ix = idx + (size_t)lp * n;
 
     for (int i = threadIdx.x; i < n; i += NT) keys[i] = sortable_key(gs[i]);
-    block_topk<NT>(keys, n, k, scratch, false, [&](int i, bool kept, int pos) {
+    auto emit = [&](int i, bool kept, int pos) {
         m[i] = kept ? 1 : 0;
         if (kept) ix[pos] = i;
-    });
+    };
+    if (n <= NT) block_topk<NT, 1>(keys, n, k, scratch, false, emit);
+    else if (n <= NT * 4) block_topk<NT, 4>(keys, n, k, scratch, false, emit);
+    else block_topk<NT>(keys, n, k, scratch, false, emit);
     for (int i = k + threadIdx.x; i < n; i += NT) ix[i] = -1;
 
     if (GROUPS) {
