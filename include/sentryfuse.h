@@ -412,7 +412,9 @@ int32_t sf_sparse_gqa_forward(const sf_desc *desc, int32_t nH, int32_t nG,
  * plan_host[0]: active rows (step 3) 1 = key tiles staged once for all heads of a
  * group, 0 = keys dealt to the waves of a workgroup per head; [1]: pieces the keys
  * are split into for it (joined by a merge); [2], [3]: key ranges of the score
- * stream and of the K/V statistics. */
+ * stream and of the K/V statistics, 0 where the whole call is one launch (short
+ * sequences; rows of O that start on 16 bytes).  A caller's list (forced_sel)
+ * always takes the launches of [0] and [1]. */
 int32_t sf_sparse_gqa_plan(const sf_desc *desc, int32_t nH, int32_t nG, int32_t *plan_host);
 
 /* sf_sparse_gqa_forward for callers that cannot allocate or hold a workspace:

@@ -80,6 +80,12 @@ bool attend_bf16_staged(const AttnArgs &a, int splits);      // splits: into how
 int32_t attend_bf16(const AttnArgs &a, const AttnPlan &pl, const void *vt, sf_strides svt,
                     const int32_t *sel, int selH, hipStream_t st);
 
+// The whole operator in one launch (attention_short.hip): attend_short() says by shape where that is the faster way; the call
+// must have no list of its own (forced_sel), nobody who projects the lazy rows (skip_fill, act_bits), and rows
+// of O that start on 16 bytes.
+bool attend_short(const AttnArgs &a);
+int32_t attend_short_bf16(const AttnArgs &a, const void *vt, sf_strides svt, int Lp, hipStream_t st);
+
 // Output projection when most rows are lazy (lazy_proj.hip).  lazy_cap: rows per sample of the compact buffers, 0
 // when the shortcut does not apply.  slot [B,nH,L] and stats are the pieces of the attention plan.
 int lazy_cap(int L, int nH, int U, int dh, int d);

@@ -701,6 +701,12 @@ int32_t attention_forward(int dtype, const AttnArgs &a, hipStream_t st)
     }
     const int64_t v_sj = vT ? 1 : svu.l, v_se = vT ? svu.l : 1;
 
+    if (dtype == SF_BF16 && attend_short(a) && !a.forced_sel && !a.skip_fill && !a.act_bits && a.ldo % 8 == 0 &&
+        (uintptr_t)a.O % 16 == 0) {
+        if (int32_t rc = attend_short_bf16(a, Vuse, svu, pl.Lp, st)) return rc;
+        return check_launch("sparse_gqa_forward");
+    }
+
     // 1. statistics: mean key (for the score's mean term) and context vector
     {
         const StatsOut so{pl.stats, pl.n_valid, a.act_bits};
@@ -873,7 +879,9 @@ extern "C" int32_t sf_sparse_gqa_plan(const sf_desc *desc, int32_t nH, int32_t n
     if (!plan_host) return fail(SF_ERR_INVALID_ARG, "sparse_gqa_plan: NULL argument");
     if (D.dtype != SF_BF16) return fail(SF_ERR_UNSUPPORTED, "sparse_gqa_plan: 16-bit models only");
     const AttnPlan pl = attn_plan(D.dtype, a, nullptr);
-    plan_host[0] = pl.staged; plan_host[1] = pl.splits; plan_host[2] = pl.score_parts; plan_host[3] = pl.stat_parts;
+    const bool whole = attend_short(a);
+    plan_host[0] = pl.staged; plan_host[1] = pl.splits;
+    plan_host[2] = whole ? 0 : pl.score_parts; plan_host[3] = whole ? 0 : pl.stat_parts;
     return SF_OK;
 }
 

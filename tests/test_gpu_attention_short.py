@@ -1,0 +1,43 @@
+"""The launch that serves a whole short sequence, at the edges of its tiles and of its choice (waves, blocks of queries, length)."""
+from __future__ import annotations
+
+import pytest
+
+from paper_2604_08971_amd import binding as sf
+from test_gpu_parity import _gqa_case, _say
+
+pytestmark = pytest.mark.gpu
+
+
+def _one_launch(B, nH, nG, L, dh, Uo, dtype="bf16"):
+    plan = sf.sparse_gqa_plan(sf.make_desc(B, L, 64, 8, 2, dh, 64, dtype=sf.SF_BF16 if dtype == "bf16" else sf.SF_F16, U_override=Uo), nH, nG)
+    return plan["score_parts"] == 0 and plan["stat_parts"] == 0
+
+
+# four, eight and sixteen waves with one and two blocks of queries each, one to four queries per thread in the selection; last
+# tiles of one key and of 31; active rows that fill a block of 32 with and without the context vector
+@pytest.mark.parametrize("dtype,B,nH,nG,L,dh,Uo,mask", [
+    ("bf16", 3, 2, 1, 33, 64, -1, True), ("bf16", 2, 3, 3, 64, 32, 31, False), ("bf16", 2, 3, 3, 65, 32, 32, True),
+    ("bf16", 1, 2, 2, 127, 64, 33, False), ("bf16", 2, 2, 1, 129, 64, 63, True), ("bf16", 130, 2, 2, 97, 64, 33, True),
+    ("bf16", 130, 4, 2, 257, 32, 64, True), ("bf16", 130, 2, 2, 512, 32, 1, False), ("bf16", 2, 5, 1, 257, 64, -1, True),
+    ("bf16", 2, 4, 2, 511, 64, 96, True), ("bf16", 1, 6, 2, 513, 64, -1, True), ("bf16", 2, 2, 2, 545, 32, -1, False),
+    ("bf16", 130, 2, 1, 1023, 32, 200, True), ("bf16", 1, 3, 1, 1024, 64, 300, False), ("bf16", 33, 2, 1, 1025, 32, -1, True),
+    ("bf16", 2, 32, 4, 1900, 32, -1, False), ("f16", 3, 4, 2, 300, 64, -1, True), ("f16", 2, 4, 4, 700, 32, -1, True),
+])
+def test_short_attention(dtype, B, nH, nG, L, dh, Uo, mask):
+    _say(f"short attention {dtype} B={B} nH={nH} L={L} dh={dh} U={Uo} mask={mask}")
+    with sf.use_half("f16" if dtype == "f16" else "bf16"):
+        assert _one_launch(B, nH, nG, L, dh, Uo, dtype)
+        for kw in (dict(), dict(strided=True, per_sample_map=True), dict(v_transposed=True), dict(n_sample=24), dict(n_sample=min(100, L))):
+            _gqa_case(dtype, B, nH, nG, L, dh, Uo, mask, seed=L + dh, **kw)
+
+
+def test_what_stays_with_the_separate_launches():
+    """A caller's list, head dimension 128, every query active, long sequences of few heads."""
+    assert not _one_launch(2, 4, 2, 300, 128, -1) and not _one_launch(2, 4, 2, 48, 64, 48)
+    assert not _one_launch(2, 4, 2, 1025, 32, -1) and not _one_launch(64, 4, 2, 1200, 64, -1)
+    for B, nH, nG, L, dh, U in ((130, 4, 2, 97, 64, 33), (130, 10, 2, 97, 64, 64), (130, 8, 2, 97, 32, 33), (130, 4, 4, 97, 64, 31),
+                                (130, 6, 2, 65, 32, 32), (1, 6, 2, 512, 64, 35)):
+        assert _one_launch(B, nH, nG, L, dh, U)
+        _gqa_case("bf16", B, nH, nG, L, dh, U, True, seed=L, forced=True)
+    _gqa_case("bf16", 3, 4, 2, 301, 128, -1, True, seed=9, n_sample=70)
