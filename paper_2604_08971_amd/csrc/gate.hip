@@ -3,8 +3,10 @@
 // locations; Sec. 4.2 names the FLOPs / energy budget).  Both are plan-construction steps: tiny next to the
 // encoder forward, so the kernels aim at being exact and launch-cheap, not at a roofline.
 #include <atomic>
+#include <type_traits>
 
 #include "common.hpp"
+#include "topk.hpp"
 
 namespace sf {
 
@@ -81,88 +83,119 @@ struct BudgetCosts { int64_t head[MAX_LAYERS_BUDGET], group[MAX_LAYERS_BUDGET], 
 // The cost of a threshold K is a weighted count: c_fixed, plus one head, one K/V group and one channel per layer (which
 // always stay), plus the cost of every other unit whose key is >= K - heads and channels with their own keys, a K/V
 // group with the largest key of its heads, one best unit of each kind and layer left out.  So the threshold is found
-// as a weighted radix select: v, the largest key at which the cost exceeds the budget, eight bits per pass over a
-// histogram of costs (integers: the order of the atomics does not matter); the keep set is { key > v }.
+// as a weighted selection: v, the largest key at which the cost exceeds the budget; the keep set is { key > v }.  One
+// histogram of costs over 1024 equal steps of the score's range finds the step that holds v, and its few units are summed
+// up pair by pair; where it has more than 64 of them, or the scores are no finite range, a radix select (eight bits per
+// pass over a histogram of costs) finds v.  Costs are integers: the order of the atomics does not matter.
 //
-// One block and latency-bound: the scores are read once (into LDS where they fit) and passed over four times, where a
-// bisection over the key's bits takes 32 passes.  Six layers of 8 heads and 2048 channels: 260 -> 16 us.
-constexpr int BUDGET_NT = 1024;
-constexpr int BUDGET_LDS_KEYS = 32768;                                // channels cached in LDS (128 KB)
+// One block and latency-bound: the scores are read once, eight loads of a thread in flight, and kept in LDS where they
+// fit; layers are shared by all waves.  Six layers of 8 heads and 2048 channels: 39 -> 18.6 us in a kernel trace (the radix
+// passes, loads one after the other, a wave per layer).
+constexpr int BUDGET_NT = 1024, BUDGET_BINS = 1024, BUDGET_LIST = 64;
+constexpr int BUDGET_LDS_KEYS = 38000;                                // keys in LDS (152 KB)
 
 __global__ __launch_bounds__(BUDGET_NT) void budget_search_kernel(
     const float *__restrict__ gh, const float *__restrict__ gf, int64_t lstride_h, int64_t lstride_f, int nl, int Hq,
-    int Hk, int F, int cached, BudgetCosts costs, int64_t c_fixed, int64_t budget, float *__restrict__ tau_out,
+    int Hk, int F, uint32_t f_magic, int cached, int cached_h, BudgetCosts costs, int64_t c_fixed, int64_t budget, float *__restrict__ tau_out,
     int32_t *__restrict__ k_head_out, int32_t *__restrict__ k_ffn_out, int64_t *__restrict__ cost_out,
     int32_t *__restrict__ feasible_out)
 {
-    extern __shared__ uint32_t fkeys[];                               // [nl][F] when cached
-    __shared__ unsigned long long hist[256];
-    __shared__ uint32_t gkey[MAX_LAYERS_BUDGET * 64];                 // [nl][Hk] largest key of a group's heads
-    __shared__ int best_h[MAX_LAYERS_BUDGET], best_g[MAX_LAYERS_BUDGET], best_f[MAX_LAYERS_BUDGET];
-    __shared__ uint32_t s_max, s_min, s_digit;
+    extern __shared__ uint32_t gkey[];                                // [nl][Hk] largest key of a group's heads, [nl][Hq] when cached_h, [nl][F] when cached
+    __shared__ unsigned long long hist[BUDGET_BINS];
+    __shared__ unsigned long long best64[MAX_LAYERS_BUDGET];          // key and complement of the index: first of the largest channels
+    __shared__ int best_h[MAX_LAYERS_BUDGET], best_g[MAX_LAYERS_BUDGET], best_f[MAX_LAYERS_BUDGET], n_f[MAX_LAYERS_BUDGET];
+    __shared__ long long list_cost[BUDGET_LIST];
+    __shared__ uint32_t list_key[BUDGET_LIST];
+    __shared__ uint32_t s_max, s_low, s_min, s_digit;
     __shared__ long long s_rest, s_cost;
-    __shared__ int s_found;
+    __shared__ int s_found, s_list;
+    uint32_t *hkeys = gkey + nl * Hk, *fkeys = hkeys + (cached_h ? nl * Hq : 0);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr int NWAVES = BUDGET_NT / 64;
+    // the channels of a layer are shared by `parts` waves: share w of nl * parts
+    const int parts = nl < NWAVES ? NWAVES / nl : 1;
 
-    auto key_h = [&](int l, int i) { return score_key(gh[l * lstride_h + i]); };
+    auto key_h = [&](int l, int i) { return cached_h ? hkeys[l * Hq + i] : score_key(gh[l * lstride_h + i]); };
     auto key_f = [&](int l, int i) { return cached ? fkeys[l * F + i] : score_key(gf[l * lstride_f + i]); };
 
-    if (tid == 0) { s_max = 0u; s_min = 0xffffffffu; s_cost = 0; }
-    if (cached)
-        for (int l = 0; l < nl; ++l)
-            for (int i = tid; i < F; i += BUDGET_NT) fkeys[l * F + i] = score_key(gf[l * lstride_f + i]);
-    __syncthreads();
-
-    // a wave per layer: the best head, group and channel (first of the largest) and the groups' keys
-    auto first_of_max = [&](uint32_t mk, int mi, int &idx) {          // over the wave
-        uint32_t m = mk;
+    if (tid == 0) { s_max = 0u; s_low = s_min = 0xffffffffu; s_cost = 0; s_list = 0; }
+    for (int j = tid; j < BUDGET_BINS; j += BUDGET_NT) hist[j] = 0ull;
+    for (int l = tid; l < nl; l += BUDGET_NT) { best64[l] = 0ull; n_f[l] = 0; }
+    if (cached_h)
+        for (int t = tid; t < nl * Hq; t += BUDGET_NT) hkeys[t] = score_key(gh[t / Hq * lstride_h + t % Hq]);
+    if (cached) {
+        constexpr int UN = 8;
+        for (int t0 = 0; t0 < nl * F; t0 += UN * BUDGET_NT) {
+            float v[UN];
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
-        int at = mk == m ? mi : 0x7fffffff;
+            for (int u = 0; u < UN; ++u) {
+                const int t = t0 + u * BUDGET_NT + tid, l = F > 1 ? (int)__umulhi((uint32_t)t, f_magic) : t;      // t / F
+                v[u] = t < nl * F ? gf[l * lstride_f + (t - l * F)] : 0.f;
+            }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) at = min(at, __shfl_xor(at, o));
-        idx = at;
-        return m;
-    };
-    const int per_group = Hq / Hk;
-    for (int l = wave; l < nl; l += NWAVES) {
-        uint32_t mk = 0u;
-        int mi = 0x7fffffff, idx;
-        for (int i = lane; i < F; i += 64) {
-            const uint32_t k = key_f(l, i);
-            if (k > mk || mi == 0x7fffffff) { mk = k; mi = i; }
-        }
-        const uint32_t mf = first_of_max(mk, mi, idx);
-        if (lane == 0) best_f[l] = idx;
-        mk = 0u;
-        mi = 0x7fffffff;
-        for (int i = lane; i < Hq; i += 64) {
-            const uint32_t k = key_h(l, i);
-            if (k > mk || mi == 0x7fffffff) { mk = k; mi = i; }
-        }
-        const uint32_t mh = first_of_max(mk, mi, idx);
-        if (lane == 0) {
-            best_h[l] = idx;
-            best_g[l] = idx / per_group;                              // the best head's group
-            atomicMax(&s_max, max(mf, mh));
-        }
-        if (lane < Hk) {
-            uint32_t g = 0u;
-            for (int j = 0; j < per_group; ++j) g = max(g, key_h(l, lane * per_group + j));
-            gkey[l * 64 + lane] = g;
+            for (int u = 0; u < UN; ++u) {
+                const int t = t0 + u * BUDGET_NT + tid;
+                if (t < nl * F) fkeys[t] = score_key(v[u]);
+            }
         }
     }
     __syncthreads();
 
-    // every unit but the ones that always stay: visit(key, cost, everyone in the wave has the same cost)
+    // the best head, group and channel of a layer (first of the largest), the groups' keys, the range of all keys
+    for (int w = wave; w < nl * parts; w += NWAVES) {
+        const int l = w / parts;
+        uint32_t mk = 0u, lo = 0xffffffffu;
+        int mi = -1;
+#pragma unroll 4
+        for (int i = w % parts * 64 + lane; i < F; i += parts * 64) {
+            const uint32_t k = key_f(l, i);
+            lo = min(lo, k);
+            if (k > mk || mi < 0) { mk = k; mi = i; }
+        }
+        const uint32_t m = wave_max_u32(mk), at = wave_max_u32(mi >= 0 && mk == m ? ~(uint32_t)mi : 0u);
+        lo = ~wave_max_u32(~lo);
+        if (lane == 0 && at) {                                        // at 0: no channel in this share
+            atomicMax(&best64[l], (unsigned long long)m << 32 | at);
+            atomicMax(&s_max, m);
+            atomicMin(&s_low, lo);
+        }
+    }
+    const int per_group = Hq / Hk;
+    for (int l = wave; l < nl; l += NWAVES) {
+        uint32_t mk = 0u, lo = 0xffffffffu;
+        int mi = -1;
+        for (int i = lane; i < Hq; i += 64) {
+            const uint32_t k = key_h(l, i);
+            lo = min(lo, k);
+            if (k > mk || mi < 0) { mk = k; mi = i; }
+        }
+        const uint32_t m = wave_max_u32(mk), at = wave_max_u32(mi >= 0 && mk == m ? ~(uint32_t)mi : 0u);
+        lo = ~wave_max_u32(~lo);
+        if (lane == 0) {
+            best_h[l] = (int)~at;
+            best_g[l] = (int)~at / per_group;                         // the best head's group
+            atomicMax(&s_max, m);
+            atomicMin(&s_low, lo);
+        }
+        if (lane < Hk) {
+            uint32_t g = 0u;
+            for (int j = 0; j < per_group; ++j) g = max(g, key_h(l, lane * per_group + j));
+            gkey[l * Hk + lane] = g;
+        }
+    }
+    __syncthreads();
+    for (int l = tid; l < nl; l += BUDGET_NT) best_f[l] = (int)~(uint32_t)best64[l];
+    __syncthreads();
+
+    // every unit but the ones that always stay: visit(key, in, cost)
     auto units = [&](auto visit) {
         for (int l = 0; l < nl; ++l) {
             const int bf = best_f[l];
+            const int64_t cost = costs.ffn[l];
             for (int i0 = 0; i0 < F; i0 += BUDGET_NT) {
                 const int i = i0 + tid;
                 const bool in = i < F && i != bf;
-                visit(in ? key_f(l, i) : 0u, in, costs.ffn[l]);
+                visit(in ? key_f(l, i) : 0u, in, cost);
             }
         }
         for (int t0 = 0; t0 < nl * Hq; t0 += BUDGET_NT) {
@@ -173,59 +206,82 @@ __global__ __launch_bounds__(BUDGET_NT) void budget_search_kernel(
         for (int t0 = 0; t0 < nl * Hk; t0 += BUDGET_NT) {
             const int t = t0 + tid, l = t / Hk, i = t % Hk;
             const bool in = t < nl * Hk && i != best_g[l];
-            visit(in ? gkey[l * 64 + i] : 0u, in, in ? costs.group[l] : 0);
+            visit(in ? gkey[t] : 0u, in, in ? costs.group[l] : 0);
         }
     };
     long long base = c_fixed;
     for (int l = 0; l < nl; ++l) base += costs.head[l] + costs.group[l] + costs.ffn[l];
 
-    uint32_t v = 0u, mask = 0u;
+    // a wave's lane owns PER consecutive bins of a histogram: the bin in which the cost from the top passes `rest`
+    auto scan = [&](auto per, long long rest) {
+        constexpr int PER = decltype(per)::value;
+        long long h[PER], local = 0;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) { h[j] = (long long)hist[PER * lane + j]; local += h[j]; }
+        long long incl = local;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const long long t = __shfl_down(incl, o);
+            if (lane + o < 64) incl += t;
+        }
+        long long run = incl - local;                                 // cost of the strictly higher bins
+#pragma unroll
+        for (int j = PER - 1; j >= 0; --j) {
+            if (run <= rest && run + h[j] > rest) { s_digit = (uint32_t)(PER * lane + j); s_cost = rest - run; s_found = 1; }
+            run += h[j];
+        }
+    };
+    uint32_t v = 0u;
     bool exceeds = budget >= base;                                    // is there a key at which the budget is exceeded?
-    if (tid == 0) s_rest = budget - base;
-    if (exceeds)
+    bool open = exceeds;                                              // v still to be found
+    const float vlo = key_score(s_low), span = key_score(s_max) - vlo;      // NaN, or infinite: not a range
+    if (open && span > 0.f && span < 3.0e38f) {
+        const float step = ((float)BUDGET_BINS - 0.5f) / span;
+        // a key's score minus the smallest, times the step: both roundings keep the order
+        auto bin_of = [&](uint32_t key) { return min((int)((key_score(key) - vlo) * step), BUDGET_BINS - 1); };
+        if (tid == 0) s_found = 0;
+        units([&](uint32_t key, bool in, int64_t cost) {
+            if (in) atomicAdd(&hist[bin_of(key)], (unsigned long long)cost);
+        });
+        __syncthreads();
+        if (tid < 64) scan(std::integral_constant<int, BUDGET_BINS / 64>(), budget - base);
+        __syncthreads();
+        if (!s_found) {                                               // everything fits
+            exceeds = open = false;
+        } else {
+            const int bin = (int)s_digit;
+            const long long rest = s_cost;
+            units([&](uint32_t key, bool in, int64_t cost) {
+                if (in && bin_of(key) == bin) {
+                    const int at = atomicAdd(&s_list, 1);
+                    if (at < BUDGET_LIST) { list_key[at] = key; list_cost[at] = cost; }
+                }
+            });
+            __syncthreads();
+            const int n = s_list;
+            if (n <= BUDGET_LIST) {
+                const uint32_t mine = lane < n ? list_key[lane] : 0u;
+                long long sum = 0;                                    // cost of the step's units with this key or a larger one
+                for (int j = 0; j < n; ++j) sum += list_key[j] >= mine ? list_cost[j] : 0;
+                v = wave_max_u32(lane < n && sum > rest ? mine : 0u);
+                open = false;
+            }
+        }
+        __syncthreads();
+    }
+    if (open) {
+        uint32_t mask = 0u;
+        if (tid == 0) s_rest = budget - base;
         for (int pass = 0; pass < 4; ++pass) {                        // uniform over the block
             const int shift = 24 - 8 * pass;
             for (int j = tid; j < 256; j += BUDGET_NT) hist[j] = 0ull;
             if (tid == 0) s_found = 0;
             __syncthreads();
             units([&](uint32_t key, bool in, int64_t cost) {
-                const bool use = in && (key & mask) == v;
-                const uint32_t bin = (key >> shift) & 255u;
-                if (pass == 0) {
-                    // scores of one layer share a few exponents: one atomic per wave, bin and cost
-                    unsigned long long left = __ballot(use);
-                    while (left) {
-                        const int src = __ffsll((long long)left) - 1;
-                        const uint32_t b = (uint32_t)__shfl((int)bin, src);
-                        const long long c = __shfl((long long)cost, src);
-                        const unsigned long long same = __ballot(use && bin == b && cost == c) & left;
-                        if (lane == src) atomicAdd(&hist[b], (unsigned long long)c * (unsigned long long)__popcll(same));
-                        left &= ~same;
-                    }
-                } else if (use) {
-                    atomicAdd(&hist[bin], (unsigned long long)cost);
-                }
+                if (in && (key & mask) == v) atomicAdd(&hist[(key >> shift) & 255u], (unsigned long long)cost);
             });
             __syncthreads();
-            if (tid < 64) {
-                // lane owns bins 4*lane .. 4*lane+3: the bin in which the cost from the top passes the rest of the budget
-                long long h[4], local = 0;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) { h[j] = (long long)hist[4 * lane + j]; local += h[j]; }
-                long long incl = local;
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const long long t = __shfl_down(incl, o);
-                    if (lane + o < 64) incl += t;
-                }
-                const long long rest = s_rest;
-                long long run = incl - local;                         // cost of the strictly higher bins
-#pragma unroll
-                for (int j = 3; j >= 0; --j) {
-                    if (run <= rest && run + h[j] > rest) { s_digit = (uint32_t)(4 * lane + j); s_cost = rest - run; s_found = 1; }
-                    run += h[j];
-                }
-            }
+            if (tid < 64) scan(std::integral_constant<int, 4>(), s_rest);
             __syncthreads();
             if (!s_found) { exceeds = false; break; }                 // pass 0 only: everything fits
             v |= s_digit << shift;
@@ -233,36 +289,46 @@ __global__ __launch_bounds__(BUDGET_NT) void budget_search_kernel(
             if (tid == 0) s_rest = s_cost;
             __syncthreads();
         }
+    }
     // v: the largest key at which the budget is exceeded.  The strictest threshold is the largest score itself.
     const bool feasible = budget >= base && !(exceeds && v >= s_max);
     const uint32_t lo = exceeds ? v + 1u : 0u;                        // keep { key >= lo }; unused when infeasible
     __syncthreads();
     if (tid == 0) s_cost = 0;
-    __syncthreads();
-    for (int l = wave; l < nl; l += NWAVES) {
-        int kf = 0, kh = 0, kg = 0;
-        uint32_t mk = 0xffffffffu;
-        if (feasible) {
-            for (int i = lane; i < F; i += 64) {
+    if (feasible)
+        for (int w = wave; w < nl * parts; w += NWAVES) {
+            const int l = w / parts;
+            int kf = 0;
+            uint32_t mk = 0xffffffffu;
+#pragma unroll 4
+            for (int i = w % parts * 64 + lane; i < F; i += parts * 64) {
                 const uint32_t k = key_f(l, i);
                 if (k >= lo) { ++kf; mk = min(mk, k); }
             }
+            kf = wave_incl_scan(kf);
+            mk = ~wave_max_u32(~mk);
+            if (lane == 63) {
+                atomicAdd(&n_f[l], kf);
+                atomicMin(&s_min, mk);
+            }
+        }
+    __syncthreads();
+    for (int l = wave; l < nl; l += NWAVES) {
+        int kh = 0, kg = 0;
+        uint32_t mk = 0xffffffffu;
+        if (feasible) {
             for (int i = lane; i < Hq; i += 64) {
                 const uint32_t k = key_h(l, i);
                 if (k >= lo) { ++kh; mk = min(mk, k); }
             }
-            if (lane < Hk) kg = gkey[l * 64 + lane] >= lo;
+            if (lane < Hk) kg = gkey[l * Hk + lane] >= lo;
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            kf += __shfl_xor(kf, o);
-            kh += __shfl_xor(kh, o);
-            kg += __shfl_xor(kg, o);
-            mk = min(mk, (uint32_t)__shfl_xor((int)mk, o));
-        }
-        if (lane == 0) {
+        kh = wave_incl_scan(kh);
+        kg = wave_incl_scan(kg);
+        mk = ~wave_max_u32(~mk);
+        if (lane == 63) {
             if (kh == 0) { kh = 1; kg = 1; }                          // the best head stays, with its group
-            if (kf == 0) kf = 1;                                      // the best channel stays
+            const int kf = max(n_f[l], 1);                            // the best channel stays
             k_head_out[l] = kh;
             k_ffn_out[l] = kf;
             atomicAdd(reinterpret_cast<unsigned long long *>(&s_cost),
@@ -325,8 +391,13 @@ extern "C" int32_t sf_budget_search(const sf_desc *desc, const float *g_head, co
             return fail(SF_ERR_INVALID_ARG, "budget_search: negative cost in layer %d", l);
         bc.head[l] = c_head_host[l]; bc.group[l] = c_group_host[l]; bc.ffn[l] = c_ffn_host[l];
     }
-    const bool cached = (int64_t)D.nl * D.F <= BUDGET_LDS_KEYS;
-    const size_t lds = cached ? (size_t)D.nl * D.F * sizeof(uint32_t) : 0;
+    int64_t keys = (int64_t)D.nl * D.Hk;                              // the groups' always, then the heads', the channels' where they fit
+    const bool cached_h = keys + (int64_t)D.nl * D.Hq <= BUDGET_LDS_KEYS;
+    if (cached_h) keys += (int64_t)D.nl * D.Hq;
+    const bool cached = keys + (int64_t)D.nl * D.F <= BUDGET_LDS_KEYS;
+    if (cached) keys += (int64_t)D.nl * D.F;
+    const size_t lds = (size_t)keys * sizeof(uint32_t);
+    const uint32_t f_magic = (uint32_t)((((uint64_t)1 << 32) + D.F - 1) / D.F);      // t / F = umulhi(t, f_magic) for t F < 2^32
     static std::atomic<bool> attr_set{false};     // setting the attribute twice is harmless
     if (!attr_set) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(budget_search_kernel),
@@ -336,6 +407,6 @@ extern "C" int32_t sf_budget_search(const sf_desc *desc, const float *g_head, co
     }
     hipLaunchKernelGGL(budget_search_kernel, dim3(1), dim3(BUDGET_NT), lds, static_cast<hipStream_t>(stream),
                        g_head + (int64_t)pattern * D.Hq, g_ffn + (int64_t)pattern * D.F, (int64_t)D.P * D.Hq,
-                       (int64_t)D.P * D.F, D.nl, D.Hq, D.Hk, D.F, cached ? 1 : 0, bc, c_fixed, budget, tau, k_head, k_ffn, cost, feasible);
+                       (int64_t)D.P * D.F, D.nl, D.Hq, D.Hk, D.F, f_magic, cached, cached_h, bc, c_fixed, budget, tau, k_head, k_ffn, cost, feasible);
     return check_launch("budget_search");
 }
