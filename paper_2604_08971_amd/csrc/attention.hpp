@@ -85,6 +85,8 @@ int32_t attend_bf16(const AttnArgs &a, const AttnPlan &pl, const void *vt, sf_st
 // of O that start on 16 bytes.
 bool attend_short(const AttnArgs &a);
 int32_t attend_short_bf16(const AttnArgs &a, const void *vt, sf_strides svt, int Lp, hipStream_t st);
+bool attend_short_f32(const AttnArgs &a);                    // fp32: no key sample either
+int32_t attend_short_f32_run(const AttnArgs &a, hipStream_t st);
 
 // Output projection when most rows are lazy (lazy_proj.hip).  lazy_cap: rows per sample of the compact buffers, 0
 // when the shortcut does not apply.  slot [B,nH,L] and stats are the pieces of the attention plan.

@@ -707,6 +707,12 @@ int32_t attention_forward(int dtype, const AttnArgs &a, hipStream_t st)
         return check_launch("sparse_gqa_forward");
     }
 
+    if (dtype == SF_F32 && attend_short_f32(a) && !a.forced_sel && !(a.sample_idx && pl.Sp > 0) && !a.skip_fill && !a.act_bits &&
+        (uintptr_t)a.O % 16 == 0) {
+        if (int32_t rc = attend_short_f32_run(a, st)) return rc;
+        return check_launch("sparse_gqa_forward");
+    }
+
     // 1. statistics: mean key (for the score's mean term) and context vector
     {
         const StatsOut so{pl.stats, pl.n_valid, a.act_bits};

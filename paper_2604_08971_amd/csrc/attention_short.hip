@@ -553,4 +553,261 @@ int32_t attend_short_bf16(const AttnArgs &a, const void *vt, sf_strides svt, int
     return a.dh == 32 ? launch_dim<32, false>(s, nw, st) : launch_dim<64, false>(s, nw, st);
 }
 
+// ------------------------------------------------------------------------------------------------ fp32
+// The same in fp32, for the small models that the fp32 path is there for: a workgroup per (sample, head) holds its queries, keys
+// and values in LDS; sixteen threads share a query (or an active row), as in score_f32_kernel, whose sums it keeps.  What
+// bounds it is the chain of phases, and in each the latency of LDS: four keys are on their way per thread.  us, launches of their
+// own / this one: 2 x 2 heads of 48 keys, dh 16 18.6 / 11.7; 128 heads of 90, dh 32 66 / 25; 128 of 256, dh 16 74 / 46.
+namespace {
+
+struct ShortF32Args {
+    const float *Q; sf_strides sq;
+    const float *K; sf_strides sk;
+    const float *V; int64_t v_b, v_h, v_sj, v_se; int v_rows;             // v_rows: V is token-major, row0 applies to it
+    const int32_t *head_group; int hg_stride; const int32_t *pattern_id;
+    const uint8_t *key_valid; const int32_t *u_active;
+    const int32_t *row0, *ext;
+    int nH, L, U;
+    int32_t *sel; float *score; int userH;               // the caller's, or NULL
+    float *O; int64_t ldo;
+};
+
+constexpr int F32_WORDS = 10;                             // 32 queries each
+
+// floats of LDS: Q, K, V rows, selection keys, a row of probabilities per group of sixteen threads, rows, context vector
+size_t short_f32_lds(int L, int dh, int U, int nt)
+{
+    return sizeof(float) * ((size_t)3 * L * (dh + 4) + L + (size_t)(nt / 16) * (L | 1) + U + dh);
+}
+
+template <int DH, int NT>
+__global__ __launch_bounds__(NT) void attend_short_f32_kernel(ShortF32Args a)
+{
+    constexpr int LD = DH + 4, NG = NT / 16, C4 = DH / 4;
+    extern __shared__ __attribute__((aligned(16))) float fsm[];
+    __shared__ __attribute__((aligned(16))) int scratch[TOPK_SCRATCH];
+    __shared__ uint32_t words[F32_WORDS];
+    const int L = a.L, ldp = L | 1, tid = threadIdx.x, lane = tid & 63;
+    float *Qs = fsm, *Ks = Qs + L * LD, *Vs = Ks + L * LD;
+    uint32_t *keys = reinterpret_cast<uint32_t *>(Vs + L * LD);
+    float *prob = reinterpret_cast<float *>(keys + L);
+    int32_t *rows = reinterpret_cast<int32_t *>(prob + NG * ldp);
+    float *ctx = reinterpret_cast<float *>(rows + a.U);
+    const int b = blockIdx.x / a.nH, h = blockIdx.x % a.nH;
+    const int g = a.head_group[(int64_t)(a.pattern_id ? a.pattern_id[b] : 0) * a.hg_stride + h];
+    const float *Qb = a.Q + sample_offset(a.row0, b, a.sq) + (int64_t)h * a.sq.h;
+    const float *Kb = a.K + sample_offset(a.row0, b, a.sk) + (int64_t)g * a.sk.h;
+    const float *Vb = a.V + (a.v_rows && a.row0 ? (int64_t)a.row0[b] * a.v_sj : (int64_t)b * a.v_b) + (int64_t)g * a.v_h;
+    const uint8_t *kv = a.key_valid ? a.key_valid + (int64_t)b * L : nullptr;
+    {
+        constexpr int STEP = NT / DH;
+        const int e = tid % DH;
+#pragma unroll 4
+        for (int r = tid / DH; r < L; r += STEP) {
+            Qs[r * LD + e] = Qb[(int64_t)r * a.sq.l + e];
+            Ks[r * LD + e] = Kb[(int64_t)r * a.sk.l + e];
+            Vs[r * LD + e] = Vb[(int64_t)r * a.v_sj + (int64_t)e * a.v_se];
+        }
+    }
+    for (int j0 = 0; j0 < F32_WORDS * 32; j0 += NT) {                     // the same trip count for every wave
+        const int j = j0 + tid;
+        const unsigned long long bal = __ballot(j < L && (!kv || kv[j]));
+        if ((lane & 31) == 0 && j < F32_WORDS * 32) words[j >> 5] = (uint32_t)(bal >> (lane & 32));
+    }
+    lds_barrier();
+    const uint32_t word = lane < F32_WORDS ? words[lane] : 0u;
+    const int n = __builtin_amdgcn_readlane(wave_incl_scan(__popc(word)), 63);      // allowed keys
+    auto allowed = [&](int j) { return (words[j >> 5] >> (j & 31)) & 1u; };
+
+    const int gi = tid >> 4, kl = tid & 15;
+    const float scale = 1.0f / sqrtf((float)DH);
+    float q[DH];
+    auto load_q = [&](int i) {
+#pragma unroll
+        for (int c = 0; c < C4; ++c) {
+            const f32x4 v = *reinterpret_cast<const f32x4 *>(Qs + i * LD + c * 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) q[c * 4 + e] = v[e];
+        }
+    };
+    // four keys at a time, j, j + 16, ...: four chains of products instead of one.  -inf: no such key, or masked
+    auto dots = [&](int j, bool any, float (&s)[4]) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s[u] = 0.f;
+        if (any)
+#pragma unroll
+            for (int c = 0; c < C4; ++c)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const f32x4 v = *reinterpret_cast<const f32x4 *>(Ks + min(j + u * 16, L - 1) * LD + c * 4);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) s[u] = fmaf(q[c * 4 + e], v[e], s[u]);
+                }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s[u] = j + u * 16 < L && allowed(j + u * 16) ? s[u] * scale : -INFINITY;
+    };
+    // ---- sparsity score
+    for (int i0 = 0; i0 < L; i0 += NG) {
+        const int i = i0 + gi;
+        load_q(min(i, L - 1));
+        float mx = -INFINITY, sum = 0.f;
+        for (int j = kl; j < L; j += 64) {
+            float s[4];
+            dots(j, true, s);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int jj = j + u * 16;
+                mx = fmaxf(mx, s[u]);
+                sum += jj < L && allowed(jj) ? s[u] : 0.f;
+            }
+        }
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) {
+            mx = fmaxf(mx, __shfl_xor(mx, o));
+            sum += __shfl_xor(sum, o);
+        }
+        if (kl == 0 && i < L) {
+            const bool ok = allowed(i);
+            const float m = !ok ? -INFINITY : mx - sum / (float)n;        // an allowed query: n > 0
+            if (a.score) a.score[((int64_t)b * a.userH + h) * L + i] = m;
+            keys[i] = ok ? max(sortable_key(m), 1u) : 0u;
+        }
+    }
+    // ---- the k allowed queries of the highest score, ascending
+    const int k = min(a.u_active ? min(max(a.u_active[b], 0), a.U) : a.U, n);
+    lds_barrier();
+    if (k == 0) {
+        for (int i = tid; i < L; i += NT) keys[i] = 0u;
+    } else {
+        block_topk<NT, (F32_WORDS * 32 + NT - 1) / NT>(keys, L, k, scratch, k == n, [&](int i, bool kept, int pos) {
+            keys[i] = kept ? 1u : 0u;
+            if (kept) rows[pos] = i;
+        });
+    }
+    lds_barrier();
+    if (a.sel)
+        for (int s = tid; s < a.U; s += NT) a.sel[((int64_t)b * a.userH + h) * a.U + s] = s < k ? rows[s] : -1;
+
+    // ---- active rows, and the one of equal scores: the context vector
+    float *Ob = a.O + sample_row(a.row0, b, L) * a.ldo + (int64_t)h * DH;
+    float *p = prob + gi * ldp;
+    for (int r0 = 0; r0 <= k; r0 += NG) {
+        const int r = r0 + gi;
+        const bool row = r < k;
+        const int i = row ? rows[r] : 0;
+        load_q(i);
+        float mx = -INFINITY;
+        for (int j = kl; j < L; j += 64) {
+            float s[4];
+            dots(j, row, s);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (j + u * 16 < L) p[j + u * 16] = s[u];
+                mx = fmaxf(mx, s[u]);
+            }
+        }
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+        float den = 0.f;
+        for (int j = kl; j < L; j += 16) {
+            const float s = p[j], pj = s == -INFINITY ? 0.f : expf(s - mx);
+            p[j] = pj;
+            den += pj;
+        }
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) den += __shfl_xor(den, o);
+        // the sixteen threads are in one wave: its LDS accesses are in order
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+        const float inv = den > 0.f ? 1.0f / den : 0.f;
+        constexpr int SHARE = DH < 16 ? 16 / DH : 1, PER = DH < 16 ? 1 : DH / 16;      // threads of a dimension, dimensions of a thread
+        float acc[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) acc[u] = 0.f;
+#pragma unroll 8
+        for (int j = kl / (16 / SHARE); j < L; j += SHARE) {
+            const float pj = p[j];
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const float v = Vs[j * LD + kl % (16 / SHARE) + u * 16];
+                acc[u] = pj != 0.f ? fmaf(pj, v, acc[u]) : acc[u];        // masked rows may hold anything
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+#pragma unroll
+            for (int o = 16 / SHARE; o < 16; o <<= 1) acc[u] += __shfl_xor(acc[u], o);
+            const int e = kl % (16 / SHARE) + u * 16;
+            if (kl < 16 / SHARE && r <= k) {
+                if (row) Ob[(int64_t)i * a.ldo + e] = acc[u] * inv;
+                else ctx[e] = acc[u] * inv;
+            }
+        }
+    }
+    lds_barrier();
+    // ---- lazy rows
+    const int end = a.ext ? a.ext[b] : L, c = tid % C4;
+    const f32x4 v = {ctx[c * 4], ctx[c * 4 + 1], ctx[c * 4 + 2], ctx[c * 4 + 3]};
+    for (int i = tid / C4; i < end; i += NT / C4)
+        if (i >= L || !keys[i]) *reinterpret_cast<f32x4 *>(Ob + (int64_t)i * a.ldo + c * 4) = v;
+}
+
+template <int DH, int NT>
+int32_t launch_short_f32(const ShortF32Args &s, int B, hipStream_t st)
+{
+    auto kern = attend_short_f32_kernel<DH, NT>;
+    static std::atomic<bool> attr_set{false};     // setting the attribute twice is harmless
+    if (!attr_set) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, SHORT_LDS) != hipSuccess)
+            return fail(SF_ERR_HIP, "sparse_gqa: cannot reserve LDS for the short attention");
+        attr_set = true;
+    }
+    const size_t lds = short_f32_lds(s.L, DH, s.U, NT);
+    hipLaunchKernelGGL(kern, dim3(B * s.nH), dim3(NT), lds, st, s);
+    return SF_OK;
+}
+
+// Eight waves where sixteen have no queries for them or no registers (dh 32), or there are more heads than compute units
+// (64 x 8 heads of 64 keys, dh 16: 17 us, 27 with sixteen; 2 heads 13.6 with sixteen, 18 with eight)
+int short_f32_threads(const AttnArgs &a)
+{
+    return a.L <= 32 || a.dh == 32 || (int64_t)a.B * a.nH > 256 ? 512 : short_f32_lds(a.L, a.dh, a.U, 1024) <= SHORT_LDS ? 1024 : 512;
+}
+
+template <int DH>
+int32_t launch_f32_threads(const ShortF32Args &s, int B, int nt, hipStream_t st)
+{
+    if constexpr (DH < 32) {
+        if (nt == 1024) return launch_short_f32<DH, 1024>(s, B, st);
+    }
+    return launch_short_f32<DH, 512>(s, B, st);
+}
+
+}  // namespace
+
+// Up to 128 queries whatever the number of heads; longer ones where there are heads enough, since the separate launches spread a
+// head over the chip (us, separate / this: 2 heads of 160 keys, dh 16 27 / 28, 64 heads 35 / 29, 64 heads of 300 58 / 56, of 400
+// 78 / 92).
+bool attend_short_f32(const AttnArgs &a)
+{
+    if ((a.dh != 8 && a.dh != 16 && a.dh != 32) || a.U < 1 || a.U >= a.L || a.L > ((int64_t)a.B * a.nH < 48 ? 128 : 300)) return false;
+    return short_f32_lds(a.L, a.dh, a.U, short_f32_threads(a)) <= SHORT_LDS;
+}
+
+int32_t attend_short_f32_run(const AttnArgs &a, hipStream_t st)
+{
+    ShortF32Args s{};
+    s.Q = (const float *)a.Q; s.sq = a.sq; s.K = (const float *)a.K; s.sk = a.sk;
+    s.V = (const float *)a.V; s.v_b = a.sv.b; s.v_h = a.sv.h;
+    s.v_sj = a.v_transposed ? 1 : a.sv.l; s.v_se = a.v_transposed ? a.sv.l : 1; s.v_rows = !a.v_transposed;
+    s.head_group = a.head_group; s.hg_stride = a.hg_stride; s.pattern_id = a.pattern_id;
+    s.key_valid = a.key_valid; s.u_active = a.u_active; s.row0 = a.row0; s.ext = a.ext;
+    s.nH = a.nH; s.L = a.L; s.U = a.U;
+    s.sel = a.sel_out; s.score = a.score_out; s.userH = a.selH > 0 ? a.selH : a.nH;
+    s.O = (float *)a.O; s.ldo = a.ldo;
+    const int nt = short_f32_threads(a);
+    return a.dh == 8 ? launch_f32_threads<8>(s, a.B, nt, st) : a.dh == 16 ? launch_f32_threads<16>(s, a.B, nt, st) : launch_f32_threads<32>(s, a.B, nt, st);
+}
+
 }  // namespace sf

@@ -41,3 +41,14 @@ def test_what_stays_with_the_separate_launches():
         assert _one_launch(B, nH, nG, L, dh, U)
         _gqa_case("bf16", B, nH, nG, L, dh, U, True, seed=L, forced=True)
     _gqa_case("bf16", 3, 4, 2, 301, 128, -1, True, seed=9, n_sample=70)
+
+
+# fp32: 512 and 1024 threads, half a thread to two dimensions per thread, the lengths at which the choice changes
+@pytest.mark.parametrize("B,nH,nG,L,dh,Uo,mask", [
+    (2, 2, 2, 48, 16, -1, True), (3, 4, 2, 64, 8, 15, False), (2, 3, 1, 17, 32, 16, True), (1, 2, 1, 65, 32, -1, True), (5, 4, 4, 128, 8, 63, True),
+    (24, 2, 2, 129, 16, -1, False), (12, 4, 2, 256, 32, 64, True), (24, 2, 1, 300, 8, -1, True), (130, 2, 1, 33, 16, 20, False), (1, 1, 1, 129, 8, 100, False),
+])
+def test_short_attention_f32(B, nH, nG, L, dh, Uo, mask):
+    _say(f"short attention f32 B={B} nH={nH} L={L} dh={dh} U={Uo} mask={mask}")
+    for kw in (dict(), dict(strided=True, per_sample_map=True), dict(v_transposed=True), dict(forced=True), dict(n_sample=min(24, L))):
+        _gqa_case("f32", B, nH, nG, L, dh, Uo, mask, seed=L + dh, **kw)
