@@ -103,6 +103,17 @@ static FfnWs ffn_ws(const Dims &D, int Fp, bool pre_ln, void *ws)
     return w;
 }
 
+// The operand of g is LayerNorm(x), rows of g.K elements: the product takes it along where it can (g.A = x then), else it
+// is formed in xn.
+static void normalised(int dtype, GemmArgs &g, bool x_f32, const void *x, const void *gamma, const void *beta, float eps, void *xn,
+                       hipStream_t st)
+{
+    GemmArgs t = g;
+    t.A = x; t.ln_g = gamma; t.ln_b = beta; t.ln_eps = eps; t.ln_x32 = x_f32;
+    if (gamma && beta && gemm_takes_ln(dtype, t)) g = t;
+    else layernorm(dtype, x_f32, x, gamma, beta, eps, (int64_t)g.B * g.L, g.K, xn, st);
+}
+
 // x_f32 / y_f32: X / Y hold fp32 although the model dtype is bf16 (the
 // encoder's residual stream).  With x_f32, pre_ln is required (the GEMM reads bf16).
 static int32_t ffn_forward(const Dims &D, const sf_compact_layer &ly, const void *X, bool x_f32,
@@ -110,18 +121,13 @@ static int32_t ffn_forward(const Dims &D, const sf_compact_layer &ly, const void
                            void *xn, void *hid, hipStream_t st, bool xn_ready = false)
 {
     const int Fp = (int)align_up(ly.k_ffn, D.ffn_pad);
-    const void *in = X;
-    if (xn_ready) {
-        in = xn;                              // LN2(X) is already there (written together with X)
-    } else if (pre_ln) {
-        layernorm(D.dtype, x_f32, X, ly.ln2_g, ly.ln2_b, D.eps, (int64_t)D.B * D.L, D.d, xn, st);
-        in = xn;
-    }
     GemmArgs g{};
-    g.A = in; g.lda = D.d; g.W = ly.W1; g.ldw = D.d; g.w_pstride = (int64_t)Fp * D.d;
+    g.A = xn_ready || pre_ln ? xn : X; g.lda = D.d; g.W = ly.W1; g.ldw = D.d; g.w_pstride = (int64_t)Fp * D.d;
     g.bias = ly.b1; g.bias_pstride = Fp; g.pattern_id = pattern_id;
     g.B = D.B; g.L = D.L; g.N = Fp; g.K = D.d; g.epi = EPI_ROWMAJOR; g.act = gemm_act(D.act);
     g.C = hid; g.ldc = Fp;
+    // xn_ready: LN2(X) is already there (written together with X)
+    if (pre_ln && !xn_ready) normalised(D.dtype, g, x_f32, X, ly.ln2_g, ly.ln2_b, D.eps, xn, st);
     if (int32_t rc = gemm(D.dtype, g, st)) return rc;
 
     GemmArgs h{};
@@ -417,12 +423,12 @@ static int32_t encoder_forward_impl(const sf_desc *desc, const sf_compact_layer 
             if (int32_t rc = gemm_fp8(q8, st)) return rc;
             transpose_v(w.qkv, Nqkv, Nqk, Hk * dh, D.B, D.L, w.Lp, w.vt, st);
         } else {
-            layernorm(D.dtype, in_f32, in, ly.ln1_g, ly.ln1_b, D.eps, rows, D.d, w.xn, st);
             GemmArgs g{};
             g.A = w.xn; g.lda = D.d; g.W = ly.Wqkv; g.ldw = D.d; g.w_pstride = (int64_t)Nqkv * D.d;
             g.bias = ly.bqkv; g.bias_pstride = Nqkv; g.pattern_id = gpat;
             g.B = Dg.B; g.L = Dg.L; g.K = D.d; g.act = ACT_NONE; g.epi = EPI_ROWMAJOR;
             g.C = w.qkv; g.ldc = ldq; g.n0 = 0; g.N = bf && !pk ? Nqk : Nqkv;
+            if (!bf || pk) normalised(D.dtype, g, in_f32, in, ly.ln1_g, ly.ln1_b, D.eps, w.xn, st);
             if (bf && pk) {
                 // Q, K, V token-major in one launch; V^T per sample (what the attention kernels read) by a pass of
                 // its own, since a 256-row block of packed rows may straddle samples
@@ -434,8 +440,10 @@ static int32_t encoder_forward_impl(const sf_desc *desc, const sf_compact_layer 
                 GemmArgs q3 = g;
                 q3.N = Nqkv; q3.VT = w.vt; q3.vt_from = Nqk; q3.vt_b = (int64_t)Hk * dh * w.Lp; q3.vt_n = w.Lp;
                 if (gemm_takes_vt_split(D.dtype, q3)) {
+                    normalised(D.dtype, q3, in_f32, in, ly.ln1_g, ly.ln1_b, D.eps, w.xn, st);
                     if (int32_t rc = gemm(D.dtype, q3, st)) return rc;
                 } else {
+                    layernorm(D.dtype, in_f32, in, ly.ln1_g, ly.ln1_b, D.eps, rows, D.d, w.xn, st);
                     if (int32_t rc = gemm(D.dtype, g, st)) return rc;
                     g.n0 = Nqk; g.N = Hk * dh; g.epi = EPI_VT; g.C = w.vt;
                     g.vt_b = q3.vt_b; g.vt_n = q3.vt_n;

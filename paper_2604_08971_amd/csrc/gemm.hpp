@@ -37,6 +37,8 @@ struct GemmArgs {
                                                          // elements = bytes), K % 128 == 0
     float out_scale;                                     // f8: factor of the sum of code products (the two tensor scales)
     int c_f8; float c_scale;                             // f8: C receives E4M3 codes of act(value) * c_scale (ldc in bytes)
+    const void *ln_g, *ln_b; float ln_eps; int ln_x32;   // bf16 GEMM only, ln_g != NULL (gemm_takes_ln): A holds rows x (fp32 when
+                                                         // ln_x32) and the operand is LayerNorm(x) rounded to 16 bits
     void *VT; int vt_from;                               // bf16 row-major problems only (gemm_takes_vt_split):
                                                          // features n >= vt_from go to VT[b, n - vt_from, i] (strides
                                                          // vt_b, vt_n, both % 8 == 0; vt_from % 8 == 0) instead of C
@@ -87,6 +89,10 @@ bool gemm_takes_row_map(int dtype, const GemmArgs &a);
 
 // True when gemm() honours a.VT / a.vt_from for this problem (else it fails with SF_ERR_UNSUPPORTED).
 bool gemm_takes_vt_split(int dtype, const GemmArgs &a);
+
+// True when gemm() takes the LayerNorm of its operand along (a.ln_g) and that is the faster way, else the caller runs layernorm().
+bool gemm_takes_ln(int dtype, const GemmArgs &a);
+bool gemm_bf16_tile_takes_ln(const GemmArgs &a);
 
 // LayerNorm over rows of d elements (biased variance).  gamma/beta are in the
 // model dtype; x is fp32 when x_f32 (or dtype is SF_F32), y is in the model dtype.

@@ -250,17 +250,30 @@ bool gemm_takes_vt_split(int dtype, const GemmArgs &a)
            !a.c_f32 && !a.n_lim;
 }
 
-// The kernel of a problem, which may become one long sample
-static GemmKind choose(GemmArgs &a)
+// One weight set and row-major output: the samples are one long one, and no tile is cut at a sample's end
+static void join_samples(GemmArgs &a)
 {
-    // one weight set and row-major output: the samples are one long one, and no tile is cut at a sample's end
     if (!a.pattern_id && a.epi == EPI_ROWMAJOR && !a.VT && !a.row_map && (int64_t)a.B * a.L * a.lda * 2 < ((int64_t)1 << 32)) {
         a.L *= a.B;
         a.B = 1;
     }
+}
+
+// The kernel of a problem, which may become one long sample
+static GemmKind choose(GemmArgs &a)
+{
+    join_samples(a);
     const bool ws_ok = gemm_bf16_ws_eligible(a);
     if (gemm_bf16_tile_eligible(a)) return gemm_bf16_choose(a, ws_ok);
     return ws_ok ? GEMM_WS : GEMM_GENERIC;
+}
+
+bool gemm_takes_ln(int dtype, const GemmArgs &a0)
+{
+    GemmArgs a = a0;
+    if (dtype != SF_BF16 || a.epi != EPI_ROWMAJOR || (a.VT && !gemm_takes_vt_split(dtype, a))) return false;
+    join_samples(a);
+    return gemm_bf16_tile_eligible(a) && gemm_bf16_tile_takes_ln(a);
 }
 
 int32_t gemm_bf16(const GemmArgs &a0, hipStream_t st)
@@ -269,6 +282,11 @@ int32_t gemm_bf16(const GemmArgs &a0, hipStream_t st)
     if (a.B <= 0 || a.N <= 0) return SF_OK;
     if (a.VT && !gemm_takes_vt_split(SF_BF16, a)) return fail(SF_ERR_UNSUPPORTED, "gemm(bf16): transposed column range on a problem the tiled kernels do not take");
     if (a.row_map && !gemm_takes_row_map(SF_BF16, a)) return fail(SF_ERR_UNSUPPORTED, "gemm(bf16): row_map on a problem the tiled kernels do not take");
+    if (a.ln_g) {
+        if (!gemm_takes_ln(SF_BF16, a)) return fail(SF_ERR_UNSUPPORTED, "gemm(bf16): LayerNorm on a problem that does not take it along");
+        join_samples(a);
+        return gemm_bf16_tile(GEMM_SLICE8, a, st);
+    }
     const GemmKind kind = choose(a);
     if (kind == GEMM_WS) return gemm_bf16_ws(a, st);
     if (kind != GEMM_GENERIC) return gemm_bf16_tile(kind, a, st);

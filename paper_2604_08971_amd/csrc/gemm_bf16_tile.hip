@@ -35,6 +35,7 @@ constexpr int N_XCD = 8;
 
 typedef __attribute__((address_space(3))) void lds_void;
 typedef short i16x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // Element offset of (row, 16-byte chunk) in a [rows][64] tile: 256-byte super-rows of two rows, slot XOR super-row, so
 // that any 16 consecutive rows of one chunk fall into different LDS slots (16 lanes of a ds_read_b128 per cycle).
@@ -347,8 +348,20 @@ void gemm_pipe_kernel(GemmArgs a, int tiles_m, int tiles_n, int total_tiles, int
 }
 
 // ----------------------------------------------------------------------------------------------------- K slices
+// Sum over the eight lanes 8 i .. 8 i + 7, in each of them
+__device__ __forceinline__ float sum8(float x)
+{
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xb1, 0xf, 0xf, false));      // quad_perm: lane ^ 1
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x4e, 0xf, 0xf, false));      // quad_perm: lane ^ 2
+    return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x141, 0xf, 0xf, false));      // row_half_mirror: lane 7 - i
+}
+
 // (TM * 32) x (TN * 32) tile; wave w takes the K tiles w, w + NWK, ... through its own LDS region.
-template <int TM, int TN, int NWK, int ACT>
+// LN: the rows of A come unnormalised, in fp32 (1) or 16 bits (2), and at most two K tiles of 64 per wave.  A wave then holds
+// its K tiles of the rows in registers, the waves exchange mean and squared deviations of their 64 columns (joined as in a
+// parallel variance: no less exact than two passes over the row), and the normalised rows go to LDS.  Every column of tiles
+// does that again for its rows, which costs 0.7 us where the launch of a LayerNorm is 3 to 4.
+template <int TM, int TN, int NWK, int ACT, int LN>
 __global__ __launch_bounds__(64 * NWK)
 void gemm_slice_kernel(GemmArgs a, int tiles_m, int tiles_n, int total_tiles, int per_xcd)
 {
@@ -383,14 +396,37 @@ void gemm_slice_kernel(GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
         for (int j = 0; j < TM; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    for (int kt = wave; kt < nkt; kt += NWK) {
-#pragma unroll
-        for (int j = 0; j < LX; ++j)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_void *)(mine + j * 1024), 16, xoff[j], kt * (TBK * 2), 0, 0);
+    // What the epilogue adds: bias and residual of the thread's outputs.  With one output chunk per thread (the 32 x 64 tile) it is
+    // on its way with the first K tiles, since read at the end it is a memory round trip of its own; four chunks would cost
+    // the 64 x 64 tile more in registers than that.
+    constexpr int NT = 64 * NWK, CPR = BN / 4, NC = BM * CPR / NT;
+    static_assert(NC * NT == BM * CPR, "whole chunks per thread");
+    const h16 *bias = a.bias ? static_cast<const h16 *>(a.bias) + (int64_t)tl.p * a.bias_pstride + a.n0 : nullptr;
+    struct Added { h16x4 bias; u32x4 res; };                    // res: fp32, or 16 bits in the first two words
+    auto fetch_added = [&](int c) {
+        const int i = tl.m0 + c / CPR, n = tl.nt0 + c % CPR * 4;
+        Added x{};
+        if (tl.vt || i >= a.L || n >= N) return x;
+        if (bias) x.bias = *reinterpret_cast<const h16x4 *>(bias + n);
+        if (!a.R) return x;
+        const int64_t ro = ((int64_t)tl.b * a.L + i) * a.ldr + a.r0 + n;
+        if (a.r_f32) {
+            x.res = *reinterpret_cast<const u32x4 *>(static_cast<const float *>(a.R) + ro);
+        } else {
+            const uint2 t = *reinterpret_cast<const uint2 *>(static_cast<const h16 *>(a.R) + ro);
+            x.res[0] = t.x;
+            x.res[1] = t.y;
+        }
+        return x;
+    };
+    Added early{};
+    if (NC == 1) early = fetch_added(threadIdx.x);
+    auto load_w = [&](int kt) {
 #pragma unroll
         for (int j = 0; j < LW; ++j)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, (lds_void *)(mine + BM * 128 + j * 1024), 16, woff[j], kt * (TBK * 2), 0, 0);
-        wait_vmcnt<0>();
+    };
+    auto multiply = [&](int kt) {
         const int steps = min(4, (K - kt * TBK) / 16);
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
@@ -407,10 +443,90 @@ void gemm_slice_kernel(GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
                 for (int j = 0; j < TM; ++j) acc[i][j] = SF_MFMA16(wf[i], xf[j], acc[i][j], 0, 0, 0);
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // this wave's fragments are in registers: reuse the region
+    };
+    if constexpr (LN == 0) {
+        for (int kt = wave; kt < nkt; kt += NWK) {
+#pragma unroll
+            for (int j = 0; j < LX; ++j)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_void *)(mine + j * 1024), 16, xoff[j], kt * (TBK * 2), 0, 0);
+            load_w(kt);
+            wait_vmcnt<0>();
+            multiply(kt);
+        }
+    } else {
+        // rows of a lane: chunk lane % 8 (8 columns) of rows lane / 8 + 8 i
+        constexpr int KPW = 2, RPL = BM / 8;
+        const int ch = lane & 7, r8 = lane >> 3;
+        const int64_t row0 = (int64_t)tl.b * a.L + tl.m0;
+        float2 *stat = reinterpret_cast<float2 *>(smem + (BUF > BM * BN * 4 ? BUF : BM * BN * 4) * NWK);      // [K tile][row] mean and squared deviations of 64 columns
+        float xv[KPW][RPL][8];
+        h16x8 gv[KPW], bv[KPW];
+        if (wave < nkt) load_w(wave);
+#pragma unroll
+        for (int p = 0; p < KPW; ++p) {
+            const int kt = wave + p * NWK, col = kt * TBK + ch * 8;
+            if (kt >= nkt) break;                                         // uniform
+            gv[p] = *reinterpret_cast<const h16x8 *>(static_cast<const h16 *>(a.ln_g) + col);
+            bv[p] = *reinterpret_cast<const h16x8 *>(static_cast<const h16 *>(a.ln_b) + col);
+#pragma unroll
+            for (int i = 0; i < RPL; ++i) {
+                const int64_t at = (row0 + min(r8 + i * 8, a.L - tl.m0 - 1)) * a.lda + col;      // rows beyond the edge: never stored
+                if (LN == 1) {
+                    const float *x = static_cast<const float *>(a.A) + at;
+                    const f32x4 v0 = *reinterpret_cast<const f32x4 *>(x), v1 = *reinterpret_cast<const f32x4 *>(x + 4);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) { xv[p][i][e] = v0[e]; xv[p][i][4 + e] = v1[e]; }
+                } else {
+                    const h16x8 v = *reinterpret_cast<const h16x8 *>(static_cast<const h16 *>(a.A) + at);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) xv[p][i][e] = (float)v[e];
+                }
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < KPW; ++p) {
+            if (wave + p * NWK >= nkt) break;
+#pragma unroll
+            for (int i = 0; i < RPL; ++i) {
+                float s = 0.f, q = 0.f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) s += xv[p][i][e];
+                const float m = sum8(s) * (1.0f / TBK);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) { const float t = xv[p][i][e] - m; q += t * t; }
+                q = sum8(q);
+                if (ch == 0) stat[(wave + p * NWK) * BM + r8 + i * 8] = make_float2(m, q);
+            }
+        }
+        lds_barrier();
+        float mean[RPL], inv[RPL];
+#pragma unroll
+        for (int i = 0; i < RPL; ++i) {                                   // lane ch joins the K tiles ch and ch + 8
+            const float2 t0 = ch < nkt ? stat[ch * BM + r8 + i * 8] : make_float2(0.f, 0.f);
+            const float2 t1 = ch + 8 < nkt ? stat[(ch + 8) * BM + r8 + i * 8] : make_float2(0.f, 0.f);
+            mean[i] = sum8(t0.x + t1.x) / (float)nkt;
+            const float d0 = ch < nkt ? t0.x - mean[i] : 0.f, d1 = ch + 8 < nkt ? t1.x - mean[i] : 0.f;
+            const float var = sum8(t0.y + t1.y + (float)TBK * (d0 * d0 + d1 * d1)) / (float)K;
+            inv[i] = 1.0f / sqrtf(var + a.ln_eps);
+        }
+#pragma unroll
+        for (int p = 0; p < KPW; ++p) {
+            const int kt = wave + p * NWK;
+            if (kt >= nkt) break;
+            if (p) load_w(kt);
+#pragma unroll
+            for (int i = 0; i < RPL; ++i) {
+                h16x8 o;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[e] = (h16)((xv[p][i][e] - mean[i]) * inv[i] * (float)gv[p][e] + (float)bv[p][e]);
+                *reinterpret_cast<h16x8 *>(mine + lay(r8 + i * 8, ch) * 2) = o;
+            }
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            multiply(kt);
+        }
     }
     barrier();
     // partial tiles: part[wave][token][feature], fp32, 16-byte chunks of a row XOR-ed by the row
-    constexpr int CPR = BN / 4;
     float *part = reinterpret_cast<float *>(smem);
     auto po = [](int row, int c) { return row * BN + ((c ^ (row & (CPR - 1))) << 2); };
 #pragma unroll
@@ -426,30 +542,16 @@ void gemm_slice_kernel(GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
             }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     barrier();
-    const h16 *bias = a.bias ? static_cast<const h16 *>(a.bias) + (int64_t)tl.p * a.bias_pstride + a.n0 : nullptr;
-    constexpr int NT = 64 * NWK;
     if (!tl.vt) {
 #pragma unroll 2
         for (int c = threadIdx.x; c < BM * CPR; c += NT) {      // 4 features of a token per thread
+            const Added x = NC == 1 ? early : fetch_added(c);
             const int r = c / CPR, cc = c % CPR, i = tl.m0 + r, n = tl.nt0 + cc * 4;
             if (i >= a.L || n >= N) continue;
             const int64_t row = (int64_t)tl.b * a.L + i;
-            f32x4 rv = {}, v = {};
-            if (a.R) {
-                const int64_t ro = row * a.ldr + a.r0 + n;
-                if (a.r_f32) {
-                    rv = *reinterpret_cast<const f32x4 *>(static_cast<const float *>(a.R) + ro);
-                } else {
-                    const h16x4 t = *reinterpret_cast<const h16x4 *>(static_cast<const h16 *>(a.R) + ro);
+            f32x4 v;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) rv[e] = (float)t[e];
-                }
-            }
-            if (bias) {
-                const h16x4 t = *reinterpret_cast<const h16x4 *>(bias + n);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = (float)t[e];
-            }
+            for (int e = 0; e < 4; ++e) v[e] = (float)x.bias[e];
 #pragma unroll
             for (int k = 0; k < NWK; ++k) {
                 const f32x4 t = *reinterpret_cast<const f32x4 *>(part + k * BM * BN + po(r, cc));
@@ -457,7 +559,12 @@ void gemm_slice_kernel(GemmArgs a, int tiles_m, int tiles_n, int total_tiles, in
                 for (int e = 0; e < 4; ++e) v[e] += t[e];
             }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = activate<ACT>(v[e]) + rv[e];
+            for (int e = 0; e < 4; ++e) v[e] = activate<ACT>(v[e]);
+            if (a.R) {
+                const h16x4 t16 = __builtin_bit_cast(h16x4, make_uint2(x.res[0], x.res[1]));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] += a.r_f32 ? __uint_as_float(x.res[e]) : (float)t16[e];
+            }
             const int64_t co = row * a.ldc + a.c0 + n;
             if (a.c_f32) {
                 *reinterpret_cast<f32x4 *>(static_cast<float *>(a.C) + co) = v;
@@ -522,17 +629,19 @@ int32_t launch_pipe(const GemmArgs &a, hipStream_t st)
     return launch(gemm_pipe_kernel<ACT>, set, a, 128, 128, 256, 2 * 256 * TBK * 2, st);
 }
 
-template <int TM, int TN, int NWK, int ACT>
+template <int TM, int TN, int NWK, int ACT, int LN = 0>
 int32_t launch_slice(const GemmArgs &a, hipStream_t st)
 {
     static std::atomic<bool> set{false};
     constexpr size_t loads = (size_t)NWK * (TM + TN) * 32 * TBK * 2, parts = (size_t)NWK * TM * TN * 1024 * 4;
-    return launch(gemm_slice_kernel<TM, TN, NWK, ACT>, set, a, TM * 32, TN * 32, 64 * NWK, loads > parts ? loads : parts, st);
+    constexpr size_t stats = LN ? (size_t)2 * NWK * TM * 32 * sizeof(float2) : 0;
+    return launch(gemm_slice_kernel<TM, TN, NWK, ACT, LN>, set, a, TM * 32, TN * 32, 64 * NWK, (loads > parts ? loads : parts) + stats, st);
 }
 
 template <int ACT>
 int32_t launch_kind(GemmKind kind, const GemmArgs &a, hipStream_t st)
 {
+    if (a.ln_g) return a.ln_x32 ? launch_slice<1, 2, 8, ACT, 1>(a, st) : launch_slice<1, 2, 8, ACT, 2>(a, st);
     switch (kind) {
     case GEMM_SLICE8: return launch_slice<1, 2, 8, ACT>(a, st);
     case GEMM_SLICE4: return launch_slice<2, 2, 4, ACT>(a, st);
@@ -552,6 +661,16 @@ bool gemm_bf16_tile_eligible(const GemmArgs &a)
     if (((uintptr_t)a.A | (uintptr_t)a.W) & 15) return false;              // loads straight into LDS: whole aligned chunks
     // 32-bit byte offsets: within a tile, or (row_map) anywhere in A, which the caller keeps below 4 GiB
     return a.lda < ((int64_t)1 << 23) && a.ldw < ((int64_t)1 << 23);
+}
+
+// The LayerNorm rides along where the K tiles of the rows fit the registers of eight waves and there is at most a tile of
+// 32 x 64 per compute unit: FFNs of 32 to 2000 rows, d 128 to 1024, then take 0.84 to 0.97 of their time with the launch (d 128
+// 11.6 -> 9.9 us, d 512 12.7 -> 11.9), 1.03 to 1.20 from the 257th tile on; tiles of 64 x 64 gain nothing (0.93 to 1.04).
+bool gemm_bf16_tile_takes_ln(const GemmArgs &a)
+{
+    if (a.K % TBK || a.K > 16 * TBK || a.row_map || a.n_lim || a.k_lim || (((uintptr_t)a.ln_g | (uintptr_t)a.ln_b) & 15)) return false;
+    const int64_t cols = a.VT ? ceil_div(a.vt_from, 64) + ceil_div(a.N - a.vt_from, 64) : ceil_div(a.N, 64);
+    return (int64_t)a.B * ceil_div(a.L, 32) * cols <= 256;
 }
 
 int32_t gemm_bf16_tile(GemmKind kind, const GemmArgs &a, hipStream_t st)

@@ -83,3 +83,29 @@ def test_ffn_on_a_misaligned_input(B, L, d, F):
         torch.cuda.synchronize()
         # the same rounding points, sums in another order: one unit of the hidden activations and of the output
         assert err_metric(to_host(got), to_host(ref)) <= 2.0 ** -6
+
+
+# The LayerNorm that rides along with few rows: one row, one past a tile, one and two K tiles per slice (d 64 .. 1024), the last
+# number of tiles that takes it and the first that does not (16 x 16 and 17 x 16 tiles); rows far from zero, whose
+# variance a sum of squares would lose.  Against the FFN of rows normalised in 64 bits: both round them to 16 bits, a last
+# place apart at most where the exact value lies between two numbers, so the outputs differ by less than one rounding of the
+# hidden activations and of the output.
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("B,L,d,F", [(1, 1, 64, 64), (1, 33, 64, 200), (3, 65, 512, 520), (1, 31, 576, 640), (2, 40, 1024, 1000),
+                                     (1, 512, 256, 1024), (1, 513, 256, 1024)])
+def test_ffn_with_layernorm_along(dtype, B, L, d, F):
+    _say(f"layernorm along {dtype} B={B} L={L} d={d} F={F}")
+    with sf.use_half(dtype):
+        wl = make_wl(W.small_spec(dtype=dtype, B=B, seg=(max(1, L - 1),), extra=int(L > 1), d=d, Hq=2, Hk=1, dh=32, F=F, nl=1, ffn_keep=1.0,
+                                  dropout="none", final_ln=False))
+        dm = DeviceModel(wl).build_plan()
+        lay = dm.layers[0]
+        g = torch.Generator(device="cuda").manual_seed(L)
+        x = torch.randn((B * L, d), generator=g, device="cuda") + torch.randn((B * L, 1), generator=g, device="cuda") * 50
+        x = x.to(dm.x.dtype)
+        gamma, beta = (lay.dense[n].double() for n in ("ln2_g", "ln2_b"))
+        xn = torch.nn.functional.layer_norm(x.double(), (d,), gamma, beta, 1e-5).to(x.dtype)
+        got = sf.pruned_ffn_forward(dm.desc, lay, x, dm.pattern_id, True, False)
+        ref = sf.pruned_ffn_forward(dm.desc, lay, xn, dm.pattern_id, False, False)
+        torch.cuda.synchronize()
+        assert err_metric(to_host(got), to_host(ref)) <= (2.0 ** -6 if dtype == "bf16" else 2.0 ** -9)
