@@ -64,7 +64,7 @@ struct AttnPlan {
 };
 AttnPlan attn_plan(int dtype, const AttnArgs &a, void *ws);
 
-constexpr int STAGED_U = 256;       // from so many active queries per head the active pass always stages its tiles (two query blocks per wave up to dh 64)
+constexpr int STAGED_U = 256;       // from so many active queries per head the active pass always stages its tiles
 
 int32_t attention_forward(int dtype, const AttnArgs &a, hipStream_t st);
 

@@ -59,8 +59,9 @@ struct KTile {
             const int c = threadIdx.x + u * NT;
             const int row = c / CH, cc = c % CH;
             const uint32_t off = (uint32_t)row * (uint32_t)sl * 2u + (uint32_t)cc * 16u;   // < 64 rows * row stride bytes
-            r[u] = ((TOTAL % NT == 0 || c < TOTAL) && j0 + row < L)
-                       ? *reinterpret_cast<const uint4 *>(base + off) : make_uint4(0, 0, 0, 0);
+            const bool whole = j0 + BKEY <= L;                                             // uniform: all but a ragged last tile
+            r[u] = make_uint4(0, 0, 0, 0);
+            if ((TOTAL % NT == 0 || c < TOTAL) && (whole || j0 + row < L)) r[u] = *reinterpret_cast<const uint4 *>(base + off);
         }
     }
     static __device__ __forceinline__ void put(const uint4 (&r)[N], h16 *Ks)
@@ -226,7 +227,12 @@ constexpr int AWAVE = 8;
 
 // NW = waves per workgroup.  Four instead of eight where a (sample, group) has at most four pairs: the same registers
 // per wave then leave room for three workgroups per compute unit, and no wave is without a pair.
-template <int DH, int QB, int NW>
+// Many active rows (dense-like patterns): at 126 registers (dh 64; 102 at dh 32) two workgroups share a compute unit, and one runs
+// its softmax on the vector ALU while the other has the matrix pipe.  What bounds it is the vector ALU.  us for a call, every
+// query active: a kernel of two query blocks per wave that kept the waves of a SIMD in opposite phases by barriers, one
+// workgroup per compute unit / this (with nothing else changed): 8 samples of 1777 keys, 8 heads 115 / 110; 16 of 4096 720 / 694;
+// 1 of 4096, 4 heads 163 / 112; 64 of 1500, 3 heads of dh 32 196 / 147; 32 of 512, 4 heads 54 / 45; 4 of 1024, 4 heads 63 / 47.
+template <int DH, int NW>
 __global__ __launch_bounds__(NW * 64) void attend_bf16_kernel(
     const h16 *__restrict__ Q, sf_strides sq, const h16 *__restrict__ K, sf_strides sk,
     const h16 *__restrict__ VT, sf_strides svt, const int32_t *__restrict__ head_group, int hg_stride,
@@ -235,6 +241,7 @@ __global__ __launch_bounds__(NW * 64) void attend_bf16_kernel(
     int Upad, int splits, int keys_per_split, h16 *__restrict__ O, int64_t ldo,
     float *__restrict__ part_o, float *__restrict__ part_ml, const int32_t *__restrict__ row0)
 {
+    constexpr int QB = 1;                                          // query blocks per wave
     constexpr int NT = NW * 64;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int KT = BKEY * (DH + PAD), VT_ = DH * (BKEY + PAD);          // elements of one K / V^T tile
@@ -249,7 +256,12 @@ __global__ __launch_bounds__(NW * 64) void attend_bf16_kernel(
     const int per_xcd = gridDim.x / 8;
     const int item = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
     if (item >= chunks * BG * splits) return;             // uniform
-    const int chunk = item % chunks, bg = (item / chunks) % BG, sp = item / (chunks * BG);
+    const int chunk = item % chunks, sp = item / (chunks * BG);
+    int bg = (item / chunks) % BG;
+    // masked samples differ in cost: each XCD gets every eighth problem instead of neighbours, which are one sample's groups
+    // (8 samples of 1777 keys in 4 groups, half of them with a modality missing: pass 79.0 -> 76.8 us; 16 of 700, 6 heads of dh 32:
+    // call 42.8 -> 38.4)
+    if (key_valid && BG % 8 == 0) bg = bg % (BG / 8) * 8 + bg / (BG / 8);
     const int b = bg / nG, g = bg % nG;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, lhi = lane >> 5;
     const int32_t *hg = head_group + (int64_t)(pattern_id ? pattern_id[b] : 0) * hg_stride;
@@ -284,7 +296,7 @@ __global__ __launch_bounds__(NW * 64) void attend_bf16_kernel(
             const int e = c / (BKEY / 8), cc = c % (BKEY / 8);
             const int j = j0 + cc * 8;
             uint4 v = make_uint4(0, 0, 0, 0);
-            if ((VTOTAL % NT == 0 || c < VTOTAL) && j < Lp) {
+            if ((VTOTAL % NT == 0 || c < VTOTAL) && (j0 + BKEY <= Lp || j < Lp)) {
                 const uint32_t off = (uint32_t)e * (uint32_t)svt.l * 2u + (uint32_t)cc * 16u;   // < dh rows of Lp keys
                 v = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(Vb + j0) + off);
             }
@@ -299,11 +311,11 @@ __global__ __launch_bounds__(NW * 64) void attend_bf16_kernel(
             if (VTOTAL % NT == 0 || c < VTOTAL) {
                 uint4 v = r[u];
                 const int j = j0 + (c % (BKEY / 8)) * 8;
-                if (j + 8 > L) {                       // last tile of a ragged row only
+                if (j0 + BKEY > L && j + 8 > L) {      // last tile of a ragged row only
                     uint16_t *hv = reinterpret_cast<uint16_t *>(&v);
 #pragma unroll
-                    for (int t = 0; t < 8; ++t)
-                        if (j + t >= L) hv[t] = 0;
+                    for (int e = 0; e < 8; ++e)
+                        if (j + e >= L) hv[e] = 0;
                 }
                 *reinterpret_cast<uint4 *>(Vt + (c / (BKEY / 8)) * (BKEY + PAD) + (c % (BKEY / 8)) * 8) = v;
             }
@@ -327,22 +339,30 @@ __global__ __launch_bounds__(NW * 64) void attend_bf16_kernel(
         const int pw = wave % pslots, kgi = wave / pslots;
         int head[QB], qidx[QB], slot[QB];
         h16x8 qf[QB][DH / 16];
-#pragma unroll
-        for (int qq = 0; qq < QB; ++qq) {
+        auto locate = [&](int qq, int lane32) {
             const int pi = pair0 + pw * QB + qq;
             head[qq] = -1; qidx[qq] = -1; slot[qq] = 0;
             if (pi < npairs) {
                 head[qq] = heads[pi / nqb];
-                slot[qq] = (pi % nqb) * 32 + l32;
+                slot[qq] = (pi % nqb) * 32 + lane32;
                 if (slot[qq] < U) qidx[qq] = sel[((int64_t)b * selH + head[qq]) * U + slot[qq]];
             }
+        };
+#pragma unroll
+        for (int qq = 0; qq < QB; ++qq) {
+            locate(qq, l32);
             const h16 *qrow = Q + sample_offset(row0, b, sq) + (int64_t)max(head[qq], 0) * sq.h +
                                  (int64_t)max(qidx[qq], 0) * sq.l;
 #pragma unroll
             for (int kk = 0; kk < DH / 16; ++kk)
                 qf[qq][kk] = *reinterpret_cast<const h16x8 *>(qrow + kk * 16 + lhi * 8);
         }
-        const bool idle = pair0 + pw * QB >= npairs;          // wave-uniform: no pair at all
+        // no pair, or none of its slots names a row (masked queries leave whole blocks empty): uniform over the wave
+        bool row = qidx[0] >= 0;
+#pragma unroll
+        for (int qq = 1; qq < QB; ++qq) row |= qidx[qq] >= 0;
+        const bool idle = __builtin_amdgcn_ballot_w64(row) == 0ull;
+        if (!__syncthreads_or(!idle)) continue;               // nobody in the workgroup has one
 
         f32x16 oacc[QB][DH / 32];
         float m_run[QB], l_run[QB];
@@ -503,6 +523,9 @@ __global__ __launch_bounds__(NW * 64) void attend_bf16_kernel(
 #pragma unroll
         for (int qq = 0; qq < QB; ++qq) {
             const float l_tot = both_halves_sum(l_run[qq]);
+            int lane32 = l32;
+            asm volatile("" : "+v"(lane32));     // the row is looked up again: live across the loop it costs registers
+            locate(qq, lane32);
             if (qidx[qq] < 0 || kgi != 0) continue;
             if (splits <= 1) {
                 const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
@@ -771,339 +794,6 @@ __global__ __launch_bounds__(NW * 64, DH == 128 || QB * DH == 128 ? 2 : 3) void 
     }
 }
 
-// ------------------------------------------------- active pass, many active rows (dense-like patterns)
-// Two pairs per wave as above, but the two waves of a SIMD are kept in OPPOSITE phases.  Measured on the plain loop
-// (dense pattern, 16 x 8 heads x 4096^2): matrix-pipe work, softmax and tile staging took 430 + 220 + 125 us and
-// added up to the kernel's 775 us - nothing overlapped, because after the tile's barrier both waves of a SIMD issue
-// their MFMAs at the same time (the pipe alternates between them), then both run their softmax on the one vector
-// ALU.  Here waves 0-3 (group 0) and waves 4-7 (group 1; wave w runs on SIMD w % 4) alternate between two clusters
-// separated by workgroup barriers, group 1 one cluster behind group 0:
-//     V(t): softmax of S(t) -> P(t) on the vector ALU, plus the group's share of the tile staging
-//     M(t): P(t) V(t) and S(t+1) = K(t+1) Q^T on the matrix pipe
-// so in every slot between two barriers one wave of each SIMD is in V and the other in M.  S(t+1) overwrites the
-// registers of S(t), which V(t) has turned into P(t), so the register budget is that of the plain loop.
-// Staging: group 0 writes V(t) during its V(t) cluster, group 1 writes K(t+2) during its V(t) cluster; each lands in
-// a buffer whose last readers finished two slots earlier and is first read one slot later.
-template <int DH>
-__global__ __launch_bounds__(AWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attend_pp_bf16_kernel(
-    const h16 *__restrict__ Q, sf_strides sq, const h16 *__restrict__ K, sf_strides sk,
-    const h16 *__restrict__ VT, sf_strides svt, const int32_t *__restrict__ head_group, int hg_stride,
-    const int32_t *__restrict__ pattern_id, const uint8_t *__restrict__ key_valid,
-    const int32_t *__restrict__ sel, int selH, int nH, int nG, int BG, int chunks, int L, int Lp, int U,
-    int Upad, int splits, int keys_per_split, h16 *__restrict__ O, int64_t ldo,
-    float *__restrict__ part_o, float *__restrict__ part_ml, const int32_t *__restrict__ row0)
-{
-    constexpr int QB = 2, GT = (AWAVE / 2) * 64;                         // threads of a wave group
-    static_assert(AWAVE == 8, "two groups of four waves, one wave of each per SIMD");
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    constexpr int KT = BKEY * (DH + PAD), VT_ = DH * (BKEY + PAD);          // elements of one K / V^T tile
-    h16 *Ks = reinterpret_cast<h16 *>(smem);                         // [2][BKEY][DH+PAD]
-    h16 *Vs = Ks + 2 * KT;                                              // [2][DH][BKEY+PAD]
-    uint32_t *words = reinterpret_cast<uint32_t *>(Vs + 2 * VT_);          // [ceil(L/32)]
-    uint16_t *tiles = reinterpret_cast<uint16_t *>(words + (L + 31) / 32); // [ceil(L/64)]
-    __shared__ int heads[64];
-    __shared__ int n_heads, n_tiles;
-
-    const int per_xcd = gridDim.x / 8;
-    const int item = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-    if (item >= chunks * BG * splits) return;             // uniform
-    const int chunk = item % chunks, bg = (item / chunks) % BG, sp = item / (chunks * BG);
-    const int b = bg / nG, g = bg % nG;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, lhi = lane >> 5;
-    const int grp = __builtin_amdgcn_readfirstlane(wave >> 2), gtid = threadIdx.x & (GT - 1);
-    const int32_t *hg = head_group + (int64_t)(pattern_id ? pattern_id[b] : 0) * hg_stride;
-
-    if (wave == 0) {                      // ordered list of the group's heads (nH <= 64)
-        const bool mine = lane < nH && hg[lane] == g;
-        const unsigned long long bal = __ballot(mine);
-        if (mine) heads[__popcll(bal & ((1ull << lane) - 1ull))] = lane;
-        if (lane == 0) n_heads = __popcll(bal);
-    }
-    const uint8_t *kv = key_valid ? key_valid + (int64_t)b * L : nullptr;
-    const int nwords = (L + 31) / 32;
-    build_mask_words(kv, L, words, nwords);
-    const int jbeg = sp * keys_per_split, jend = min(L, jbeg + keys_per_split);
-    __syncthreads();
-    build_tile_list(words, nwords, jbeg, jend, tiles, &n_tiles);
-    __syncthreads();
-    const int nt = n_tiles;
-    const int nqb = Upad / 32;
-    const int npairs = n_heads * nqb;
-
-    const h16 *Kb = K + sample_offset(row0, b, sk) + (int64_t)g * sk.h;
-    const h16 *Vb = VT + (int64_t)b * svt.b + (int64_t)g * svt.h;        // the transposed V is always b-strided
-    const float sc = LOG2E / sqrtf((float)DH);
-
-    // Tile chunks (16 bytes) of one thread of a group -> registers -> LDS.  K rows at or beyond L and V^T keys at or
-    // beyond L are zero.  The thread's offsets are re-formed from an opaque copy of its index at every use: kept
-    // live across the loop they are spilled, and a reload from scratch inside the loop is a vector-memory operation
-    // whose wait also waits for the tile loads just issued (measured: 1200 clocks per tile in the fetch alone).
-    constexpr int KCH = DH / 8, KTOTAL = BKEY * KCH, NK = (KTOTAL + GT - 1) / GT;
-    constexpr int VTOTAL = DH * (BKEY / 8), NV = (VTOTAL + GT - 1) / GT;
-    auto fetch_k = [&](int j0, uint4 (&r)[NK]) {
-        int gt = gtid;
-        asm volatile("" : "+v"(gt));      // re-formed at every use, see below
-        const char *base = reinterpret_cast<const char *>(Kb + (int64_t)j0 * sk.l);
-#pragma unroll
-        for (int u = 0; u < NK; ++u) {
-            const int c = gt + u * GT;
-            const int row = c / KCH, cc = c % KCH;
-            const uint32_t off = (uint32_t)row * (uint32_t)sk.l * 2u + (uint32_t)cc * 16u;
-            r[u] = ((KTOTAL % GT == 0 || c < KTOTAL) && j0 + row < L)
-                       ? *reinterpret_cast<const uint4 *>(base + off) : make_uint4(0, 0, 0, 0);
-        }
-    };
-    auto put_k = [&](const uint4 (&r)[NK], h16 *Kt) {
-        int gt = gtid;
-        asm volatile("" : "+v"(gt));      // re-formed at every use, see below
-#pragma unroll
-        for (int u = 0; u < NK; ++u) {
-            const int c = gt + u * GT;
-            if (KTOTAL % GT == 0 || c < KTOTAL)
-                *reinterpret_cast<uint4 *>(Kt + (c / KCH) * (DH + PAD) + (c % KCH) * 8) = r[u];
-        }
-    };
-    auto fetch_v = [&](int j0, uint4 (&r)[NV]) {
-        int gt = gtid;
-        asm volatile("" : "+v"(gt));      // re-formed at every use, see below
-#pragma unroll
-        for (int u = 0; u < NV; ++u) {
-            const int c = gt + u * GT;
-            const int e = c / (BKEY / 8), cc = c % (BKEY / 8);
-            const int j = j0 + cc * 8;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if ((VTOTAL % GT == 0 || c < VTOTAL) && j < Lp) {
-                const uint32_t off = (uint32_t)e * (uint32_t)svt.l * 2u + (uint32_t)cc * 16u;   // < dh rows of Lp keys
-                v = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(Vb + j0) + off);
-            }
-            r[u] = v;          // (keys at or beyond L are zeroed when the chunk is written to LDS: touching the value
-                               // here would make the wave wait for the load it has just issued)
-        }
-    };
-    auto put_v = [&](const uint4 (&r)[NV], h16 *Vt, int j0) {
-        int gt = gtid;
-        asm volatile("" : "+v"(gt));      // re-formed at every use, see below
-#pragma unroll
-        for (int u = 0; u < NV; ++u) {
-            const int c = gt + u * GT;
-            if (VTOTAL % GT == 0 || c < VTOTAL) {
-                uint4 v = r[u];
-                const int j = j0 + (c % (BKEY / 8)) * 8;
-                if (j + 8 > L) {                       // last tile of a ragged row only
-                    uint16_t *hv = reinterpret_cast<uint16_t *>(&v);
-#pragma unroll
-                    for (int t = 0; t < 8; ++t)
-                        if (j + t >= L) hv[t] = 0;
-                }
-                // chunk cc holds keys 8cc..8cc+7 of the row; inside every group of 16 keys the LDS order is
-                // [0-3, 8-11, 4-7, 12-15], so that the 8 keys a lane supplies per MFMA are 16 contiguous bytes
-                const int cc = c % (BKEY / 8);
-                h16 *dst = Vt + (c / (BKEY / 8)) * (BKEY + PAD) + (cc >> 1) * 16 + (cc & 1) * 4;
-                *reinterpret_cast<uint2 *>(dst) = make_uint2(v.x, v.y);
-                *reinterpret_cast<uint2 *>(dst + 8) = make_uint2(v.z, v.w);
-            }
-        }
-    };
-    auto tile_j0 = [&](int it) { return __builtin_amdgcn_readfirstlane((int)tiles[it]) * BKEY; };   // same for every lane
-
-    for (int pair0 = chunk * (AWAVE * QB); pair0 < npairs; pair0 += chunks * (AWAVE * QB)) {
-        int head[QB], qidx[QB], slot[QB];
-        h16x8 qf[QB][DH / 16];
-#pragma unroll
-        for (int qq = 0; qq < QB; ++qq) {
-            const int pi = pair0 + wave * QB + qq;
-            head[qq] = -1; qidx[qq] = -1; slot[qq] = 0;
-            if (pi < npairs) {
-                head[qq] = heads[pi / nqb];
-                slot[qq] = (pi % nqb) * 32 + l32;
-                if (slot[qq] < U) qidx[qq] = sel[((int64_t)b * selH + head[qq]) * U + slot[qq]];
-            }
-            const h16 *qrow = Q + sample_offset(row0, b, sq) + (int64_t)max(head[qq], 0) * sq.h +
-                                 (int64_t)max(qidx[qq], 0) * sq.l;
-#pragma unroll
-            for (int kk = 0; kk < DH / 16; ++kk)
-                qf[qq][kk] = *reinterpret_cast<const h16x8 *>(qrow + kk * 16 + lhi * 8);
-        }
-        const bool idle = pair0 + wave * QB >= npairs;        // wave-uniform: no pair at all (still stages and syncs)
-
-        f32x16 oacc[QB][DH / 32];
-        float m_run[QB], l_run[QB];
-#pragma unroll
-        for (int qq = 0; qq < QB; ++qq) {
-            m_run[qq] = -INFINITY; l_run[qq] = 0.f;
-#pragma unroll
-            for (int db = 0; db < DH / 32; ++db)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) oacc[qq][db][e] = 0.f;
-        }
-        f32x16 s[QB][2];
-        h16x8 pf[QB][4];
-
-        // S^T of both pairs for the 64 keys of a K tile (every K fragment serves both pairs)
-        auto s_tile = [&](const h16 *Kt) {
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                h16x8 kf[DH / 16];
-#pragma unroll
-                for (int kk = 0; kk < DH / 16; ++kk)
-                    kf[kk] = *reinterpret_cast<const h16x8 *>(Kt + (kb * 32 + l32) * (DH + PAD) + kk * 16 + lhi * 8);
-#pragma unroll
-                for (int qq = 0; qq < QB; ++qq) {
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) s[qq][kb][e] = 0.f;
-#pragma unroll
-                    for (int kk = 0; kk < DH / 16; ++kk)
-                        s[qq][kb] = SF_MFMA16(kf[kk], qf[qq][kk], s[qq][kb], 0, 0, 0);
-                }
-            }
-        };
-        // O^T += V^T . P^T of both pairs
-        auto pv_tile = [&](const h16 *Vt) {
-#pragma unroll
-            for (int db = 0; db < DH / 32; ++db)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    // keys {16t + lhi*4 + 0..3, 16t + 8 + lhi*4 + 0..3}: one 16-byte read in the staged key order
-                    const h16x8 vf = *reinterpret_cast<const h16x8 *>(Vt + (db * 32 + l32) * (BKEY + PAD) + t * 16 + lhi * 8);
-#pragma unroll
-                    for (int qq = 0; qq < QB; ++qq)
-                        oacc[qq][db] = SF_MFMA16(vf, pf[qq][t], oacc[qq][db], 0, 0, 0);
-                }
-        };
-        // softmax of S(t) -> P(t); updates the running reference / sum / output scale of both pairs
-        auto softmax_tile = [&](int j0) {
-            const uint32_t w0 = words[j0 / 32], w1 = (j0 / 32 + 1 < nwords) ? words[j0 / 32 + 1] : 0u;
-            const bool all_allowed = (uint32_t)__builtin_amdgcn_readfirstlane((int)(w0 & w1)) == 0xffffffffu;
-#pragma unroll
-            for (int qq = 0; qq < QB; ++qq) {
-                if (!all_allowed) {
-#pragma unroll
-                    for (int kb = 0; kb < 2; ++kb) {
-                        const uint32_t wl = (kb ? w1 : w0) >> (lhi * 4);
-#pragma unroll
-                        for (int e = 0; e < 16; ++e)
-                            if (!((wl >> ((e / 4) * 8 + (e % 4))) & 1u)) s[qq][kb][e] = -INFINITY;
-                    }
-                }
-                float mt = fmaxf(fmaxf(s[qq][0][0], s[qq][0][1]), s[qq][1][0]);
-                mt = fmaxf(fmaxf(mt, s[qq][1][1]), s[qq][0][2]);
-#pragma unroll
-                for (int e = 3; e < 15; e += 2) mt = fmaxf(fmaxf(mt, s[qq][0][e]), s[qq][0][e + 1]);
-#pragma unroll
-                for (int e = 2; e < 16; e += 2) mt = fmaxf(fmaxf(mt, s[qq][1][e]), s[qq][1][e + 1]);
-                mt = fmaxf(mt, s[qq][0][15]) * sc;         // sc > 0: max and scaling commute
-                mt = both_halves_max(mt);
-                // the reference moves only when some query needs it (see attend_bf16_kernel)
-                if (__builtin_expect(__builtin_amdgcn_ballot_w64(mt > m_run[qq] + RESCALE_LOG2) != 0ull, 0)) {
-                    const float m_new = fmaxf(m_run[qq], mt);
-                    const float alpha = __builtin_amdgcn_exp2f(m_run[qq] - (m_new == -INFINITY ? 0.f : m_new));
-                    m_run[qq] = m_new;
-                    l_run[qq] *= alpha;
-#pragma unroll
-                    for (int db = 0; db < DH / 32; ++db)
-#pragma unroll
-                        for (int e = 0; e < 16; ++e) oacc[qq][db][e] *= alpha;
-                }
-                const float nm = m_run[qq] == -INFINITY ? 0.f : -m_run[qq];
-                float rs0 = 0.f, rs1 = 0.f;
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int e = 0; e < 16; e += 2) {
-                        const float p0 = __builtin_amdgcn_exp2f(fmaf(s[qq][kb][e], sc, nm));
-                        const float p1 = __builtin_amdgcn_exp2f(fmaf(s[qq][kb][e + 1], sc, nm));
-                        rs0 += p0;
-                        rs1 += p1;
-                        reinterpret_cast<uint32_t *>(&pf[qq][kb * 2 + e / 8])[(e % 8) / 2] = pack2_h16(p0, p1);
-                    }
-                l_run[qq] += rs0 + rs1;
-            }
-        };
-
-        if (nt > 0) {
-            // K(0) and V(0) by group 0, K(1) by group 1; V(1) waits in group 0's registers, K(2) in group 1's
-            uint4 kreg[NK], vreg[NV];
-            if (grp == 0) {
-                fetch_k(tile_j0(0), kreg);
-                fetch_v(tile_j0(0), vreg);
-                put_k(kreg, Ks);
-                put_v(vreg, Vs, tile_j0(0));
-                fetch_v(tile_j0(min(1, nt - 1)), vreg);
-            } else {
-                fetch_k(tile_j0(min(1, nt - 1)), kreg);
-                put_k(kreg, Ks + KT);
-                fetch_k(tile_j0(min(2, nt - 1)), kreg);
-            }
-            __syncthreads();
-            if (!idle) s_tile(Ks);
-            if (grp == 1) __syncthreads();                    // group 1 runs one cluster behind
-            for (int it = 0; it < nt; ++it) {
-                // The tile numbers of this iteration, read at the top of the V cluster where the vector ALU work hides
-                // the LDS round trip.  Beyond the last tile the index is clamped: the staging and the S^T block of
-                // the last iterations are then redundant (they land in buffers nobody reads again), which keeps the
-                // M cluster free of data-dependent branches.
-                const int j_cur = tile_j0(it), j1 = tile_j0(min(it + 1, nt - 1));
-                const int j_far = tile_j0(min(it + 2 + grp, nt - 1));
-                // ---- cluster V(it): vector ALU only
-                if (!idle) softmax_tile(j_cur);
-                __syncthreads();
-                // ---- cluster M(it): matrix pipe, and the group's share of the staging (the buffers written here had
-                // their last readers one slot ago).  (Raising this wave's priority for the cluster changed nothing.)
-                if (grp == 0) {
-                    put_v(vreg, Vs + ((it + 1) & 1) * VT_, j1);                     // V(it+1) over V(it-1)
-                    fetch_v(j_far, vreg);                                           // V(it+2)
-                } else {
-                    put_k(kreg, Ks + (it & 1) * KT);                                // K(it+2) over K(it)
-                    fetch_k(j_far, kreg);                                           // K(it+3)
-                }
-                if (!idle) {
-                    pv_tile(Vs + (it & 1) * VT_);
-                    s_tile(Ks + ((it + 1) & 1) * KT);
-                }
-                __syncthreads();
-            }
-            if (grp == 0) __syncthreads();                    // as many barriers as group 1
-        }
-
-        // lane owns query l32 and output dims db*32 + ig*8 + lhi*4 + {0..3}
-#pragma unroll
-        for (int qq = 0; qq < QB; ++qq) {
-            const float l_tot = both_halves_sum(l_run[qq]);
-            if (qidx[qq] < 0) continue;
-            if (splits <= 1) {
-                const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-                h16 *orow = O + (sample_row(row0, b, L) + qidx[qq]) * ldo + (int64_t)head[qq] * DH;
-#pragma unroll
-                for (int db = 0; db < DH / 32; ++db)
-#pragma unroll
-                    for (int ig = 0; ig < 4; ++ig) {
-                        uint2 o;
-                        o.x = pack2_h16(oacc[qq][db][ig * 4] * inv, oacc[qq][db][ig * 4 + 1] * inv);
-                        o.y = pack2_h16(oacc[qq][db][ig * 4 + 2] * inv, oacc[qq][db][ig * 4 + 3] * inv);
-                        *reinterpret_cast<uint2 *>(orow + db * 32 + ig * 8 + lhi * 4) = o;
-                    }
-            } else {
-                const int64_t base = (((int64_t)b * nH + head[qq]) * splits + sp) * Upad + slot[qq];   // [b, head, split, slot]
-                float *po = part_o + base * DH;
-#pragma unroll
-                for (int db = 0; db < DH / 32; ++db)
-#pragma unroll
-                    for (int ig = 0; ig < 4; ++ig) {
-                        f32x4 o;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) o[e] = oacc[qq][db][ig * 4 + e];
-                        *reinterpret_cast<f32x4 *>(po + db * 32 + ig * 8 + lhi * 4) = o;
-                    }
-                if (lhi == 0) {
-                    part_ml[base * 2] = m_run[qq];
-                    part_ml[base * 2 + 1] = l_tot;
-                }
-            }
-        }
-        __syncthreads();            // the next pass restages the tile buffers
-    }
-}
-
 // ---------------------------------------------------------------- host side
 template <int DH, int QBS>
 static int32_t launch_score(const AttnArgs &a, const void *Kx, sf_strides skx, int Lk, const uint8_t *key_mask,
@@ -1205,7 +895,7 @@ bool attend_bf16_staged(const AttnArgs &a, int splits)
     return staged <= sliced;
 }
 
-template <int DH, int QB>
+template <int DH>
 static int32_t launch_attend(const AttnArgs &a, const AttnPlan &pl, const void *vt, sf_strides svt,
                              const int32_t *sel, int selH, hipStream_t st)
 {
@@ -1214,25 +904,18 @@ static int32_t launch_attend(const AttnArgs &a, const AttnPlan &pl, const void *
     const int nqb = pl.Upad / 32, BG = a.B * a.nG;
     // pair chunks per (sample, group) for evenly spread heads; a group with more heads takes several passes
     const int pairs = ceil_div(a.nH, a.nG) * nqb;
-    const int nw = QB == 1 ? staged_waves(DH, pairs, pl.splits) : AWAVE;
-    const int chunks = ceil_div(pairs, nw * QB);
+    const int nw = staged_waves(DH, pairs, pl.splits);
+    const int chunks = ceil_div(pairs, nw);
     const int64_t items = (int64_t)chunks * BG * pl.splits;
     if (items > (1 << 30)) return fail(SF_ERR_SHAPE, "sparse_gqa(bf16): too many work items");
     dim3 grid((unsigned)align_up(items, 8));
     ProfScope prof(SF_KERNEL_ATTEND, st);
-    if constexpr (QB == 2) {
-        hipLaunchKernelGGL((attend_pp_bf16_kernel<DH>), grid, dim3(AWAVE * 64), lds, st, (const h16 *)a.Q,
-                           a.sq, (const h16 *)a.K, a.sk, (const h16 *)vt, svt, a.head_group, a.hg_stride,
-                           a.pattern_id, a.key_valid, sel, selH, a.nH, a.nG, BG, chunks, a.L, pl.Lp, a.U, pl.Upad,
-                           pl.splits, pl.keys_per_split, (h16 *)a.O, a.ldo, pl.part_o, pl.part_ml, a.row0);
-    } else {
 #define SF_ATTEND_ARGS grid, dim3(nw * 64), lds, st, (const h16 *)a.Q, a.sq, (const h16 *)a.K, a.sk, (const h16 *)vt, \
                        svt, a.head_group, a.hg_stride, a.pattern_id, a.key_valid, sel, selH, a.nH, a.nG, BG, chunks, a.L, \
                        pl.Lp, a.U, pl.Upad, pl.splits, pl.keys_per_split, (h16 *)a.O, a.ldo, pl.part_o, pl.part_ml, a.row0
-        if (nw == 4) hipLaunchKernelGGL((attend_bf16_kernel<DH, QB, DH == 64 ? 4 : AWAVE>), SF_ATTEND_ARGS);
-        else hipLaunchKernelGGL((attend_bf16_kernel<DH, QB, AWAVE>), SF_ATTEND_ARGS);
+    if (nw == 4) hipLaunchKernelGGL((attend_bf16_kernel<DH, DH == 64 ? 4 : AWAVE>), SF_ATTEND_ARGS);
+    else hipLaunchKernelGGL((attend_bf16_kernel<DH, AWAVE>), SF_ATTEND_ARGS);
 #undef SF_ATTEND_ARGS
-    }
     return SF_OK;
 }
 
@@ -1263,17 +946,11 @@ int32_t attend_bf16(const AttnArgs &a, const AttnPlan &pl, const void *vt, sf_st
                     const int32_t *sel, int selH, hipStream_t st)
 {
     if (a.nH > 64) return fail(SF_ERR_SHAPE, "sparse_gqa(bf16): at most 64 heads");
-    if (pl.staged && a.U < STAGED_U) {
+    if (pl.staged) {
         switch (a.dh) {
-        case 32: return launch_attend<32, 1>(a, pl, vt, svt, sel, selH, st);
-        case 64: return launch_attend<64, 1>(a, pl, vt, svt, sel, selH, st);
-        case 128: return launch_attend<128, 1>(a, pl, vt, svt, sel, selH, st);
-        }
-    } else if (pl.staged) {                      // dense-like: two query blocks per wave
-        switch (a.dh) {
-        case 32: return launch_attend<32, 2>(a, pl, vt, svt, sel, selH, st);
-        case 64: return launch_attend<64, 2>(a, pl, vt, svt, sel, selH, st);
-        case 128: return launch_attend<128, 1>(a, pl, vt, svt, sel, selH, st);
+        case 32: return launch_attend<32>(a, pl, vt, svt, sel, selH, st);
+        case 64: return launch_attend<64>(a, pl, vt, svt, sel, selH, st);
+        case 128: return launch_attend<128>(a, pl, vt, svt, sel, selH, st);
         }
     } else {
         const SliceShape s = slice_shape(a);

@@ -7,6 +7,7 @@
 #include <type_traits>
 
 #include "attention.hpp"
+#include "gemm.hpp"
 #include "topk.hpp"
 
 namespace sf {
@@ -690,9 +691,18 @@ int32_t attention_forward(int dtype, const AttnArgs &a, hipStream_t st)
     sf_strides svu = a.sv;
     int vT = a.v_transposed;
     if (dtype == SF_BF16 && !a.v_transposed) {
-        dim3 grid(ceil_div(pl.Lp, 32), ceil_div(a.dh, 32), BG);
-        hipLaunchKernelGGL(transpose_v_kernel, grid, dim3(256), 0, st, (const uint16_t *)a.V, a.sv, a.nG,
-                           a.L, a.dh, pl.Lp, (uint16_t *)pl.vt, a.row0);
+        // whole chunks of 16 bytes where V is packed head by head or token by token (8 samples of 1777 keys, 4 groups of dh 64:
+        // 9.2 us, 6.7 so), else element by element
+        const bool whole = (uintptr_t)a.V % 16 == 0 && !a.row0;
+        if (whole && a.sv.h == a.L * a.sv.l && a.sv.b == a.nG * a.sv.h) {
+            transpose_v(a.V, a.sv.l, 0, a.dh, BG, a.L, pl.Lp, pl.vt, st);
+        } else if (whole && a.sv.h == a.dh && a.sv.b == a.L * a.sv.l) {
+            transpose_v(a.V, a.sv.l, 0, a.nG * a.dh, a.B, a.L, pl.Lp, pl.vt, st);
+        } else {
+            dim3 grid(ceil_div(pl.Lp, 32), ceil_div(a.dh, 32), BG);
+            hipLaunchKernelGGL(transpose_v_kernel, grid, dim3(256), 0, st, (const uint16_t *)a.V, a.sv, a.nG,
+                               a.L, a.dh, pl.Lp, (uint16_t *)pl.vt, a.row0);
+        }
         Vuse = pl.vt;
         svu.b = (int64_t)a.nG * a.dh * pl.Lp;
         svu.h = (int64_t)a.dh * pl.Lp;
@@ -713,8 +723,10 @@ int32_t attention_forward(int dtype, const AttnArgs &a, hipStream_t st)
         return check_launch("sparse_gqa_forward");
     }
 
-    // 1. statistics: mean key (for the score's mean term) and context vector
-    {
+    // 1. statistics: mean key (for the score's mean term) and context vector; nobody asks for them where every row is active
+    // and the choice is not the caller's
+    const bool all_active = a.U >= a.L && !a.key_valid && !a.forced_sel && !a.act_bits && !a.skip_fill && !a.row0;
+    if (!all_active) {
         const StatsOut so{pl.stats, pl.n_valid, a.act_bits};
         if (dtype == SF_BF16) {
             const int parts = pl.stat_parts;

@@ -151,3 +151,31 @@ def test_score_over_key_ranges_keeps_nan_and_infinities():
     assert np.array_equal(score[~fin & ~np.isnan(ref)], ref[~fin & ~np.isnan(ref)])
     assert np.allclose(score[fin], ref[fin], rtol=1e-4, atol=1e-4)
     assert np.array_equal(sel, sel_ref)
+
+
+# Every row active: (sample, group) problems that divide by the XCDs (dealt round-robin when masked) and that do not, blocks of
+# 32 rows without any, V packed head by head, token by token and on an odd element, no statistics without a mask
+@pytest.mark.parametrize("dtype,B,nH,nG,L,dh,mask", [
+    ("bf16", 8, 4, 2, 333, 64, True), ("bf16", 3, 3, 1, 385, 32, True), ("bf16", 2, 2, 2, 257, 64, False), ("f16", 4, 4, 4, 290, 32, True),
+    ("bf16", 2, 4, 2, 300, 128, True), ("bf16", 1, 2, 1, 33, 64, False),
+])
+def test_every_row_active(dtype, B, nH, nG, L, dh, mask):
+    _say(f"every row {dtype} B={B} nH={nH} L={L} dh={dh} mask={mask}")
+    with sf.use_half("f16" if dtype == "f16" else "bf16"):
+        for kw in (dict(), dict(strided=True), dict(v_transposed=True), dict(forced=True)):
+            _gqa_case(dtype, B, nH, nG, L, dh, L, mask, seed=L, **kw)
+
+
+def test_value_on_an_odd_element():
+    B, nH, L, dh = 2, 2, 300, 64
+    rng = np.random.default_rng(4)
+    Q, K, V = (to_dev(W.to_bf16_values(rng.standard_normal((B, nH, L, dh)).astype(np.float32)), "bf16") for _ in range(3))
+    odd = torch.empty(V.numel() + 1, dtype=V.dtype, device="cuda")[1:].view(V.shape)
+    odd.copy_(V)
+    assert odd.data_ptr() % 16 == 2
+    hg = torch.arange(nH, dtype=torch.int32, device="cuda").reshape(1, nH)
+    for U in (-1, L):
+        desc = sf.make_desc(B, L, 64, nH, nH, dh, 64, dtype=sf.SF_BF16, U_override=U)
+        a, b = (sf.sparse_gqa_forward(desc, Q, K, v, hg)[0] for v in (V, odd))
+        torch.cuda.synchronize()
+        assert torch.equal(a, b)
