@@ -686,8 +686,8 @@ int32_t sf_moe_ffn_forward(const sf_desc *desc, const sf_moe_compact *moe_host, 
  * Cost = c_fixed + sum_l (heads_l*c_head[l] + groups_l*c_group[l] +
  * channels_l*c_ffn[l]) in the caller's integer units (HOST arrays [nl], >= 0).
  * Finds the smallest score value whose keep set costs <= budget, i.e. the
- * largest network within the budget, by a weighted radix select over the
- * ordered bit patterns of the scores (exact, no sort).  Outputs (DEVICE memory):
+ * largest network within the budget, by a weighted selection over the scores
+ * (exact, no sort).  Outputs (DEVICE memory):
  *   tau (that score; +inf when nothing fits), k_head [nl], k_ffn [nl] (sizes
  *   of the keep set: pass them to sf_gate_scores_to_masks, whose top-k with
  *   these counts selects exactly the units >= tau), cost, feasible (1 / 0;
