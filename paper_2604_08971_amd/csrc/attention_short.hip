@@ -14,6 +14,7 @@
 
 #include "attention.hpp"
 #include "attention_dev.hpp"
+#include "attention_short_addr.hpp"
 #include "topk.hpp"
 
 namespace sf {
@@ -298,11 +299,10 @@ __global__ __launch_bounds__(NW * 64, 4) void attend_short_bf16_kernel(ShortArgs
         return t;
     };
     struct VTile { h16x8 v[DB][2]; } vx, vy;
-    const uint32_t v_row = (uint32_t)l32 * (uint32_t)a.svt.l * 2u + (uint32_t)lhi * 16u, v_last = (uint32_t)(a.Lp - 8) * 2u;
     auto load_v = [&](VTile &x, int t) {
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
-            const uint32_t off = v_row + min((uint32_t)(t * 64 + p * 32), v_last - (uint32_t)lhi * 16u);
+            const uint32_t off = short_v_off(t, p, l32, lhi, (uint32_t)a.svt.l, a.Lp);
 #pragma unroll
             for (int d = 0; d < DB; ++d)
                 x.v[d][p] = *reinterpret_cast<const h16x8 *>(reinterpret_cast<const char *>(Vb + (int64_t)(d * 32) * a.svt.l) + off);

@@ -32,6 +32,21 @@ def test_short_attention(dtype, B, nH, nG, L, dh, Uo, mask):
             _gqa_case(dtype, B, nH, nG, L, dh, Uo, mask, seed=L + dh, **kw)
 
 
+# rows of V^T of one and of two 16-byte chunks, less than the half tile that a wave reads at a time
+@pytest.mark.parametrize("L", [2, 7, 8, 9, 16, 17])
+@pytest.mark.parametrize("dtype,dh", [("bf16", 32), ("bf16", 64), ("f16", 64)])
+def test_shortest_sequences(dtype, dh, L):
+    for U in sorted({1, L - 1}):
+        _say(f"shortest sequences {dtype} L={L} dh={dh} U={U}")
+        with sf.use_half("f16" if dtype == "f16" else "bf16"):
+            assert _one_launch(3, 4, 2, L, dh, U, dtype)
+            for kw in (dict(), dict(v_transposed=True), dict(strided=True, v_transposed=True)):
+                _gqa_case(dtype, 3, 4, 2, L, dh, U, L > 2, seed=L + dh, **kw)
+            # a sample of ten keys and none masked: the score over a single key is zero but for rounding, which picks any query
+            if L >= 16:
+                _gqa_case(dtype, 3, 4, 2, L, dh, U, False, seed=L + dh, n_sample=14)
+
+
 def test_what_stays_with_the_separate_launches():
     """A caller's list, head dimension 128, every query active, long sequences of few heads."""
     assert not _one_launch(2, 4, 2, 300, 128, -1) and not _one_launch(2, 4, 2, 48, 64, 48)
