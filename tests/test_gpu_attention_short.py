@@ -21,7 +21,7 @@ def _one_launch(B, nH, nG, L, dh, Uo, dtype="bf16"):
     ("bf16", 1, 2, 2, 127, 64, 33, False), ("bf16", 2, 2, 1, 129, 64, 63, True), ("bf16", 130, 2, 2, 97, 64, 33, True),
     ("bf16", 130, 4, 2, 257, 32, 64, True), ("bf16", 130, 2, 2, 512, 32, 1, False), ("bf16", 2, 5, 1, 257, 64, -1, True),
     ("bf16", 2, 4, 2, 511, 64, 96, True), ("bf16", 1, 6, 2, 513, 64, -1, True), ("bf16", 2, 2, 2, 545, 32, -1, False),
-    ("bf16", 130, 2, 1, 1023, 32, 200, True), ("bf16", 1, 3, 1, 1024, 64, 300, False), ("bf16", 33, 2, 1, 1025, 32, -1, True),
+    ("bf16", 130, 2, 1, 1023, 32, 200, True), ("bf16", 33, 3, 1, 1024, 64, 300, False), ("bf16", 33, 2, 1, 1025, 32, -1, True),
     ("bf16", 2, 32, 4, 1900, 32, -1, False), ("f16", 3, 4, 2, 300, 64, -1, True), ("f16", 2, 4, 4, 700, 32, -1, True),
 ])
 def test_short_attention(dtype, B, nH, nG, L, dh, Uo, mask):
