@@ -801,13 +801,19 @@ int32_t launch_f32_threads(const ShortF32Args &s, int B, int nt, hipStream_t st)
 
 }  // namespace
 
-// Up to 128 queries whatever the number of heads; longer ones where there are heads enough, since the separate launches spread a
-// head over the chip (us, separate / this: 2 heads of 160 keys, dh 16 27 / 28, 64 heads 35 / 29, 64 heads of 300 58 / 56, of 400
-// 78 / 92).
+// Longer sequences only where there are heads enough, since the separate launches spread a head over the chip (us, separate / this:
+// 2 heads of 160 keys, dh 16 27 / 28, 64 heads 35 / 29; 48 heads of 220, dh 16 37 / 40, of 256, dh 8 34 / 44; 64 heads of 400 78 /
+// 92); and few heads only where the active rows are one pass of the workgroup, or the sequence is so short that two are
+// nothing (8 heads of 128 keys, dh 32, 64 active rows 30 / 60, 22 heads, 20 of them 31 / 30; 4 heads of 128, dh 16, 64 active rows 24
+// / 32, 32 of them 23 / 21).
 bool attend_short_f32(const AttnArgs &a)
 {
-    if ((a.dh != 8 && a.dh != 16 && a.dh != 32) || a.U < 1 || a.U >= a.L || a.L > ((int64_t)a.B * a.nH < 48 ? 128 : 300)) return false;
-    return short_f32_lds(a.L, a.dh, a.U, short_f32_threads(a)) <= SHORT_LDS;
+    if ((a.dh != 8 && a.dh != 16 && a.dh != 32) || a.U < 1 || a.U >= a.L) return false;
+    const int64_t heads = (int64_t)a.B * a.nH;
+    const int nt = short_f32_threads(a);
+    if (a.L > (heads < 48 ? 128 : heads < 96 ? 200 : 300)) return false;
+    if (heads < 48 && a.U + 1 > nt / 16 && a.L > (a.dh == 32 ? 48 : 64)) return false;
+    return short_f32_lds(a.L, a.dh, a.U, nt) <= SHORT_LDS;
 }
 
 int32_t attend_short_f32_run(const AttnArgs &a, hipStream_t st)
