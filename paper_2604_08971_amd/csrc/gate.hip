@@ -234,11 +234,10 @@ __global__ __launch_bounds__(BUDGET_NT) void budget_search_kernel(
     uint32_t v = 0u;
     bool exceeds = budget >= base;                                    // is there a key at which the budget is exceeded?
     bool open = exceeds;                                              // v still to be found
-    const float vlo = key_score(s_low), span = key_score(s_max) - vlo;      // NaN, or infinite: not a range
-    if (open && span > 0.f && span < 3.0e38f) {
-        const float step = ((float)BUDGET_BINS - 0.5f) / span;
-        // a key's score minus the smallest, times the step: both roundings keep the order
-        auto bin_of = [&](uint32_t key) { return min((int)((key_score(key) - vlo) * step), BUDGET_BINS - 1); };
+    const float vlo = key_score(s_low);
+    float per_unit;
+    if (open && cut_range(vlo, key_score(s_max), BUDGET_BINS, per_unit)) {
+        auto bin_of = [&](uint32_t key) { return step_of(key_score(key), vlo, per_unit, BUDGET_BINS); };
         if (tid == 0) s_found = 0;
         units([&](uint32_t key, bool in, int64_t cost) {
             if (in) atomicAdd(&hist[bin_of(key)], (unsigned long long)cost);

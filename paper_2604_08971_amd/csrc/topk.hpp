@@ -13,6 +13,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "value_steps.hpp"
 
 namespace sf {
 
@@ -116,11 +117,10 @@ __device__ void block_topk(uint32_t *keys, int n, int k, int *scratch, bool posi
         uint32_t hi = 0, lo = 0;
 #pragma unroll
         for (int i = 0; i < NWV; ++i) { hi = max(hi, ext[i]); lo = max(lo, ext[NWV + i]); }
-        const float vlo = key_value(~lo), span = key_value(hi) - vlo;      // NaN, or infinite: not a range
-        if (span > 0.f && span < 3.0e38f) {         // uniform
-            const float step = ((float)BINS - 0.5f) / span;
-            // a key's value minus the smallest, times the step: both roundings keep the order
-            auto bin_of = [&](uint32_t key) { return min((int)((key_value(key) - vlo) * step), BINS - 1); };
+        const float vlo = key_value(~lo);
+        float per_unit;
+        if (cut_range(vlo, key_value(hi), BINS, per_unit)) {                // uniform
+            auto bin_of = [&](uint32_t key) { return step_of(key_value(key), vlo, per_unit, BINS); };
             each([&](uint32_t key) {
                 if (key) atomicAdd(&scratch[bin_of(key)], 1);
             });

@@ -27,8 +27,8 @@ def test_budget_search_edges(nl, Hq, Hk, F, zero):
 
 
 # Scores that leave the histogram of equal steps: all equal, two values (more units in a step than its list holds), an outlier
-# that puts the others into one step, an infinity, and a layer that has only zeros
-@pytest.mark.parametrize("kind", ["equal", "two", "outlier", "inf", "zeros"])
+# that puts the others into one step, an infinity, a layer that has only zeros, and a range too narrow for steps
+@pytest.mark.parametrize("kind", ["equal", "two", "outlier", "inf", "zeros", "narrow"])
 @pytest.mark.parametrize("nl,Hq,Hk,F", [(3, 8, 4, 700), (20, 4, 2, 130), (2, 4, 2, 19000)])
 def test_budget_search_degenerate_scores(nl, Hq, Hk, F, kind):
     _say(f"budget_search nl={nl} F={F} {kind}")
@@ -43,6 +43,8 @@ def test_budget_search_degenerate_scores(nl, Hq, Hk, F, kind):
             a.reshape(-1)[a.size // 2] = 3e30
         elif kind == "inf":
             a.reshape(-1)[a.size // 2] = np.inf
+        elif kind == "narrow":
+            a *= np.float32(1e-37)
         else:
             a[0] = 0.0
     gh.copy_(torch.from_numpy(gh_h).reshape(gh.shape))

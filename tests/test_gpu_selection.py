@@ -58,7 +58,7 @@ def test_selection_of_degenerate_scores(dtype, L, dh, kind):
 
 
 @pytest.mark.parametrize("F", [1, 63, 700, 1024, 4096, 4097, 16384])
-@pytest.mark.parametrize("kind", ["random", "equal", "two", "outlier", "inf"])
+@pytest.mark.parametrize("kind", ["random", "equal", "two", "outlier", "inf", "narrow"])
 def test_keep_masks_of_degenerate_scores(F, kind):
     _say(f"keep masks F={F} {kind}")
     rng = np.random.default_rng(F)
@@ -71,6 +71,9 @@ def test_keep_masks_of_degenerate_scores(F, kind):
         g[:, :, F // 2] = 3e38
     elif kind == "inf":
         g[0, :, F // 2], g[1, :, F // 3] = np.inf, -np.inf
+    elif kind == "narrow":                       # ranges too narrow for steps: below the normal numbers, and of normal ones
+        g[0] *= np.float32(1e-38)
+        g[1] *= np.float32(1e-31)
     desc = sf.make_desc(1, 64, 64, 4, 2, 16, F, n_layers=2, dtype=sf.SF_F32)
     for k in {1, max(1, F // 2), F}:
         m = sf.gate_scores_to_masks(desc, torch.rand((2, 1, 4), device="cuda"), torch.from_numpy(g).cuda(), [1, 1], [k, k])
