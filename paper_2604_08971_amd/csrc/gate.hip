@@ -85,12 +85,14 @@ struct BudgetCosts { int64_t head[MAX_LAYERS_BUDGET], group[MAX_LAYERS_BUDGET], 
 // group with the largest key of its heads, one best unit of each kind and layer left out.  So the threshold is found
 // as a weighted selection: v, the largest key at which the cost exceeds the budget; the keep set is { key > v }.  One
 // histogram of costs over 1024 equal steps of the score's range finds the step that holds v, and its few units are summed
-// up pair by pair; where it has more than 64 of them, or the scores are no finite range, a radix select (eight bits per
-// pass over a histogram of costs) finds v.  Costs are integers: the order of the atomics does not matter.
+// up pair by pair; where it has more than 64 of them, a sample of the channels shows many in one step, or the scores are no
+// finite range, a radix select (eight bits per pass over a histogram of costs) finds v.  Costs are integers: the order of the
+// atomics does not matter.
 //
 // One block and latency-bound: the scores are read once, eight loads of a thread in flight, and kept in LDS where they
-// fit; layers are shared by all waves.  Six layers of 8 heads and 2048 channels: 39 -> 18.6 us in a kernel trace (the radix
-// passes, loads one after the other, a wave per layer).
+// fit; layers are shared by all waves.  us a call, the radix passes alone with loads one after the other and a wave per layer /
+// this: 6 layers of 8 heads and 2048 channels 38 / 18.5, their scores all equal 52 / 34, two values 42 / 39, nine zeros in
+// ten 54 / 39, an outlier 38 / 37; 64 layers of 64 heads, groups and 512 channels 156 / 67.
 constexpr int BUDGET_NT = 1024, BUDGET_BINS = 1024, BUDGET_LIST = 64;
 constexpr int BUDGET_LDS_KEYS = 38000;                                // keys in LDS (152 KB)
 
@@ -108,7 +110,7 @@ __global__ __launch_bounds__(BUDGET_NT) void budget_search_kernel(
     __shared__ uint32_t list_key[BUDGET_LIST];
     __shared__ uint32_t s_max, s_low, s_min, s_digit;
     __shared__ long long s_rest, s_cost;
-    __shared__ int s_found, s_list;
+    __shared__ int s_found, s_many, s_list;
     uint32_t *hkeys = gkey + nl * Hk, *fkeys = hkeys + (cached_h ? nl * Hq : 0);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr int NWAVES = BUDGET_NT / 64;
@@ -212,6 +214,25 @@ __global__ __launch_bounds__(BUDGET_NT) void budget_search_kernel(
     long long base = c_fixed;
     for (int l = 0; l < nl; ++l) base += costs.head[l] + costs.group[l] + costs.ffn[l];
 
+    // A unit in the histogram of a radix pass.  Atomics on one address run one after the other: where many scores meet in a bin
+    // (`crowded`), lanes with the bin and the cost of the first one are added by it, twice; the others by themselves.
+    bool crowded = true;
+    auto add = [&](bool use, int bin, int64_t cost) {
+        if (crowded)
+#pragma unroll
+            for (int it = 0; it < 2; ++it) {
+                const unsigned long long left = __ballot(use);
+                if (!left) return;
+                const int src = __ffsll((long long)left) - 1;
+                const int b = __builtin_amdgcn_readlane(bin, src);
+                const int64_t c = (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(cost >> 32), src) << 32 |
+                                            (uint32_t)__builtin_amdgcn_readlane((int)cost, src));
+                const unsigned long long same = __ballot(use && bin == b && cost == c);
+                if (lane == src) atomicAdd(&hist[b], (unsigned long long)c * (unsigned long long)__popcll(same));
+                use = use && !(bin == b && cost == c);
+            }
+        if (use) atomicAdd(&hist[bin], (unsigned long long)cost);
+    };
     // a wave's lane owns PER consecutive bins of a histogram: the bin in which the cost from the top passes `rest`
     auto scan = [&](auto per, long long rest) {
         constexpr int PER = decltype(per)::value;
@@ -236,9 +257,21 @@ __global__ __launch_bounds__(BUDGET_NT) void budget_search_kernel(
     bool open = exceeds;                                              // v still to be found
     const float vlo = key_score(s_low);
     float per_unit;
-    if (open && cut_range(vlo, key_score(s_max), BUDGET_BINS, per_unit)) {
-        auto bin_of = [&](uint32_t key) { return step_of(key_score(key), vlo, per_unit, BUDGET_BINS); };
-        if (tid == 0) s_found = 0;
+    bool steps = open && cut_range(vlo, key_score(s_max), BUDGET_BINS, per_unit);
+    auto bin_of = [&](uint32_t key) { return step_of(key_score(key), vlo, per_unit, BUDGET_BINS); };
+    if (steps) {
+        // a channel per thread, spread over the layers: where a quarter of a wave's meet in a step, the others do, in this histogram
+        // and in the list of a step
+        const int t = tid * max(1, nl * F / BUDGET_NT), bin = t < nl * F ? bin_of(key_f(t / F, t % F)) : -1;
+        if (tid == 0) { s_found = 0; s_many = 0; }
+        __syncthreads();
+        const int first = __builtin_amdgcn_readfirstlane(bin);
+        if (first >= 0 && __popcll(__ballot(bin == first)) > 16) s_many = 1;
+        __syncthreads();
+        crowded = s_many;
+        steps = !crowded;
+    }
+    if (steps) {
         units([&](uint32_t key, bool in, int64_t cost) {
             if (in) atomicAdd(&hist[bin_of(key)], (unsigned long long)cost);
         });
@@ -277,7 +310,7 @@ __global__ __launch_bounds__(BUDGET_NT) void budget_search_kernel(
             if (tid == 0) s_found = 0;
             __syncthreads();
             units([&](uint32_t key, bool in, int64_t cost) {
-                if (in && (key & mask) == v) atomicAdd(&hist[(key >> shift) & 255u], (unsigned long long)cost);
+                add(in && (key & mask) == v, (int)((key >> shift) & 255u), cost);
             });
             __syncthreads();
             if (tid < 64) scan(std::integral_constant<int, 4>(), s_rest);
@@ -390,11 +423,11 @@ extern "C" int32_t sf_budget_search(const sf_desc *desc, const float *g_head, co
             return fail(SF_ERR_INVALID_ARG, "budget_search: negative cost in layer %d", l);
         bc.head[l] = c_head_host[l]; bc.group[l] = c_group_host[l]; bc.ffn[l] = c_ffn_host[l];
     }
-    int64_t keys = (int64_t)D.nl * D.Hk;                              // the groups' always, then the heads', the channels' where they fit
-    const bool cached_h = keys + (int64_t)D.nl * D.Hq <= BUDGET_LDS_KEYS;
-    if (cached_h) keys += (int64_t)D.nl * D.Hq;
+    int64_t keys = (int64_t)D.nl * D.Hk;                              // the groups' always; the channels', then the heads' where they fit
     const bool cached = keys + (int64_t)D.nl * D.F <= BUDGET_LDS_KEYS;
     if (cached) keys += (int64_t)D.nl * D.F;
+    const bool cached_h = keys + (int64_t)D.nl * D.Hq <= BUDGET_LDS_KEYS;
+    if (cached_h) keys += (int64_t)D.nl * D.Hq;
     const size_t lds = (size_t)keys * sizeof(uint32_t);
     const uint32_t f_magic = (uint32_t)((((uint64_t)1 << 32) + D.F - 1) / D.F);      // t / F = umulhi(t, f_magic) for t F < 2^32
     static std::atomic<bool> attr_set{false};     // setting the attribute twice is harmless
