@@ -3,13 +3,15 @@
 // (Sec. 4.5) and for the top-U query choice of SentryAttend (Sec. 4.4).
 //
 // The k-th largest key is found from one histogram of 512 equal steps between the smallest and the largest value: the
-// step that holds it has a handful of keys, which every wave ranks for itself.  Where it has more than 64 (many equal
-// values, an outlier that leaves the others in one step) or the values are no finite range, a 4-pass radix select (8 bits
-// per pass, a 256-bin histogram per pass) finds it.  Counts come from integer atomics in LDS: they, hence the result, do
+// step that holds it has a handful of keys, which every wave ranks for itself.  Where it has more than 64, a sample shows many
+// of them in one step (equal values, an outlier that leaves the others in one step), the row is longer than 8192 and the
+// key not in its tail (a step near the mean of a bell curve has too many) or the values are no finite range, a 4-pass radix
+// select (8 bits per pass, a 256-bin histogram per pass) finds it.  Counts come from integer atomics in LDS: they, hence the result, do
 // not depend on the order of the atomics.  The kept indices are then emitted in ascending order from contiguous
-// per-thread index ranges with one block-wide prefix sum.  Barriers, cross-lane moves and lanes that meet in a bin are
-// what it costs on short rows.  us with the launch, radix passes alone / so: keep sets of 2048 channels 8.0 / 6.8, 4096 query
-// scores 12.1 / 9.8, 48 scores 5.0 / 4.2.
+// per-thread index ranges, or from the wave's counts of the keys in registers, with one block-wide prefix sum.  Barriers,
+// cross-lane moves and lanes that meet in a bin are what it costs on short rows.  us with the launch, radix passes alone / so:
+// keep sets of 2048 channels 7.6 / 6.7, of two values 9.3 / 10.4, with an outlier 7.6 / 8.4; of 4096 channels 9.5 / 7.9; of
+// 16384, half of them kept 27 / 29; 4096 query scores 12.1 / 9.8, 48 scores 5.0 / 4.2.
 #pragma once
 
 #include "common.hpp"
@@ -100,7 +102,8 @@ __device__ void block_topk(uint32_t *keys, int n, int k, int *scratch, bool posi
     uint32_t T = 0;                                 // k-th largest key
     int need = 0;                                   // how many keys == T are kept (lowest indices)
     bool found = positive;
-    if (!positive) {
+    const bool cut = !positive && (MAXE > 0 || n <= 8192 || k <= n / 8);
+    if (cut) {
 #pragma unroll
         for (int j = tid; j < BINS + 128; j += NT) scratch[j] = 0;
         uint32_t hi = 0, lo = 0;                    // lo: complement of the smallest key > 0
@@ -113,14 +116,24 @@ __device__ void block_topk(uint32_t *keys, int n, int k, int *scratch, bool posi
         if (lane == 0) { ext[w] = hi; ext[NWV + w] = lo; }
     }
     lds_barrier();
-    if (!positive) {
+    if (cut) {
         uint32_t hi = 0, lo = 0;
 #pragma unroll
         for (int i = 0; i < NWV; ++i) { hi = max(hi, ext[i]); lo = max(lo, ext[NWV + i]); }
         const float vlo = key_value(~lo);
         float per_unit;
-        if (cut_range(vlo, key_value(hi), BINS, per_unit)) {                // uniform
-            auto bin_of = [&](uint32_t key) { return step_of(key_value(key), vlo, per_unit, BINS); };
+        bool steps = cut_range(vlo, key_value(hi), BINS, per_unit);                    // uniform, as is all of this
+        auto bin_of = [&](uint32_t key) { return step_of(key_value(key), vlo, per_unit, BINS); };
+        if (steps) {
+            // 64 keys, the same for every wave: where a quarter of them meet in a step the histogram would be built on one address
+            const int at = n < 64 ? lane : lane * n >> 6;
+            const uint32_t key = at < n ? keys[at] : 0u;
+            const int bin = key ? bin_of(key) : -1;
+            const unsigned long long allowed = __ballot(key != 0u);
+            const int first = __builtin_amdgcn_readlane(bin, allowed ? __ffsll((long long)allowed) - 1 : 0);
+            steps = __popcll(__ballot(key && bin == first)) <= 16;
+        }
+        if (steps) {
             each([&](uint32_t key) {
                 if (key) atomicAdd(&scratch[bin_of(key)], 1);
             });
