@@ -16,6 +16,7 @@
 
 #include "attention.hpp"
 #include "attention_dev.hpp"
+#include "xcd_deal.hpp"
 
 namespace sf {
 
@@ -258,10 +259,11 @@ __global__ __launch_bounds__(NW * 64) void attend_bf16_kernel(
     if (item >= chunks * BG * splits) return;             // uniform
     const int chunk = item % chunks, sp = item / (chunks * BG);
     int bg = (item / chunks) % BG;
-    // masked samples differ in cost: each XCD gets every eighth problem instead of neighbours, which are one sample's groups
-    // (8 samples of 1777 keys in 4 groups, half of them with a modality missing: pass 79.0 -> 76.8 us; 16 of 700, 6 heads of dh 32:
-    // call 42.8 -> 38.4)
-    if (key_valid && BG % 8 == 0) bg = bg % (BG / 8) * 8 + bg / (BG / 8);
+    // Masked samples differ in cost: each XCD gets one of every eight problems instead of neighbours, which are one sample's groups.
+    // us a call, neighbours / so, kernel otherwise the same but for the first pair: 8 samples of 1777 keys in 4 groups, half of
+    // them at random with a modality missing, pass 79.0 / 76.8; 16 of 1500 in 4 groups, every second one so, 126 / 117 (132 with
+    // the same one of every eight, which is always an odd or always an even sample).
+    if (key_valid && BG % 8 == 0) bg = deal(bg / (BG / 8), bg % (BG / 8));
     const int b = bg / nG, g = bg % nG;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, lhi = lane >> 5;
     const int32_t *hg = head_group + (int64_t)(pattern_id ? pattern_id[b] : 0) * hg_stride;
