@@ -36,29 +36,6 @@ struct ShortArgs {
     h16 *O; int64_t ldo;
 };
 
-// LDS: keys of the head (later the partial results of the waves) | sum of every wave's queries | selection
-// keys | largest product of every query (with the keys of the score) | mask words | rows of the active queries (first the
-// mask words of the key sample) | partial sums of the mean key (later
-// the references of every wave's queries) | mean key | context vector (16 bits)
-template <int DH, int NW>
-struct ShortLds {
-    size_t keys_at, ml, sel_keys, qmax, words, rows, red, kbar, ctx, bytes;
-    __host__ __device__ ShortLds(int L, int U)
-    {
-        const size_t Lr = (size_t)(L + 31) / 32 * 32, k = Lr * DH * 2, p = (size_t)NW * 32 * DH * 4;
-        keys_at = 0;
-        ml = k > p ? k : p;
-        sel_keys = ml + NW * 32 * 4;
-        qmax = sel_keys + Lr * 4;
-        words = qmax + Lr * 4;
-        rows = words + Lr / 32 * 4;
-        red = rows + (size_t)(U > 64 ? (U + 31) / 32 * 32 : 64) * 4;
-        kbar = red + NW * DH * 4;
-        ctx = kbar + DH * 4;
-        bytes = ctx + DH * 2;
-    }
-};
-
 // Keys and partial results lie in LDS without padding, in lines of 256 bytes whose 16-byte slots are permuted by the line
 // number: 16 lanes are served together, and 16 consecutive rows fall into different slots whatever the chunk.  Padded rows
 // would be 86 KB for 512 keys of dh 64, one workgroup per compute unit instead of two (128 samples of 512 keys, 6 heads: 64 us padded, 53 so).

@@ -42,3 +42,31 @@ int main()
 
 def test_values_are_read_inside_their_row(tmp_path):
     _run(tmp_path, V_READS)
+
+
+# partial results, keys and the context vector are read and written 16 bytes at a time; the pieces do not overlap
+LAYOUT = r"""
+#include <cstdio>
+#include "attention_short_addr.hpp"
+
+template <int DH, int NW> int check()
+{
+    for (int L = 2; L <= 2048; ++L)
+        for (int U = 1; U < L && U < NW * 32; U += U < 40 ? 1 : 37) {
+            const sf::ShortLds<DH, NW> a(L, U);
+            const size_t nt = (L + 31) / 32, at[] = {a.keys_at, a.ml, a.sel_keys, a.qmax, a.words, a.rows, a.red, a.kbar, a.ctx, a.bytes},
+                         need[] = {nt * 32 * DH * 2, NW * 32 * 4, (size_t)L * 4, (size_t)L * 4, nt * 4, (size_t)(U > 64 ? U : 64) * 4,
+                                   NW * (DH > 32 ? DH : 32) * 4, DH * 4, DH * 2};
+            for (int i = 0; i < 9; ++i)
+                if (at[i] + need[i] > at[i + 1]) return std::printf("dh %d waves %d L %d U %d: piece %d\n", DH, NW, L, U, i), 1;
+            if (a.ml < (size_t)NW * 32 * DH * 4 || a.keys_at % 16 || a.ctx % 16) return std::printf("dh %d waves %d L %d U %d: %zu\n", DH, NW, L, U, a.ctx), 1;
+        }
+    return 0;
+}
+
+int main() { return check<32, 4>() || check<32, 8>() || check<32, 16>() || check<64, 4>() || check<64, 8>() || check<64, 16>(); }
+"""
+
+
+def test_layout_is_aligned(tmp_path):
+    _run(tmp_path, LAYOUT)
