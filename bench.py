@@ -236,17 +236,22 @@ def bench_config(name, steps, warmup, extras, cpu, use_graph=False, repeats=1):
     # per-kernel-class timing with HIP events on the launch stream (second pass of the same steps)
     prof = {}
     if s.dtype == "bf16":
-        for cls, key in ((sf.SF_KERNEL_GEMM, "gemm"), (sf.SF_KERNEL_SCORE, "score"), (sf.SF_KERNEL_ATTEND, "active")):
+        # "attention": score and active rows in one launch, where the sequence is short
+        for cls, key in ((sf.SF_KERNEL_GEMM, "gemm"), (sf.SF_KERNEL_SCORE, "score"), (sf.SF_KERNEL_ATTEND, "active"),
+                         (sf.SF_KERNEL_ATTENTION, "attention")):
             sf.profile_begin(cls, steps * 64 * s.n_layers)
             for _ in range(steps):
                 step()
             n, tot_ms, each = sf.profile_end(each=True)
             if n:
+                fl = flops["score"] + flops["active"] if key == "attention" else flops[key]
+                # layers may differ in heads, and so in their launches: no rate where the class serves some of them only
+                whole = key == "gemm" or n == steps * s.n_layers
                 prof[key] = {"launches_per_step": n / steps, "avg_launch_us": tot_ms * 1e3 / n,
                              "ms_per_step": tot_ms / steps,
-                             "tflops": flops[key] * steps / (tot_ms * 1e-3) / 1e12 if tot_ms > 0 else None}
+                             "tflops": fl * steps / (tot_ms * 1e-3) / 1e12 if whole and tot_ms > 0 else None}
                 prof[key]["frac_of_bf16_peak"] = prof[key]["tflops"] / PEAK_BF16_TFLOPS if prof[key]["tflops"] else None
-                if key == "active" and tot_ms > 0:
+                if key == "active" and whole and tot_ms > 0:
                     # the bound that matters for the sparse pattern: K and V of every referenced (sample, group) once
                     kv_bytes = sum(int(masks_host["n_groups"][l][wl.pattern_id].astype(np.int64).sum()) * 2 * L * s.dh * 2
                                    for l in range(s.n_layers))

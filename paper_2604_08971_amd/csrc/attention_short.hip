@@ -463,7 +463,7 @@ int32_t launch_short(const ShortArgs &s, hipStream_t st)
         attr_set = true;
     }
     const size_t lds = ShortLds<DH, NW>(s.L, s.U).bytes;
-    ProfScope prof(SF_KERNEL_ATTEND, st);
+    ProfScope prof(SF_KERNEL_ATTENTION, st);
     hipLaunchKernelGGL(kern, dim3((unsigned)align_up(s.n_items, 8)), dim3(NW * 64), lds, st, s);
     return SF_OK;
 }

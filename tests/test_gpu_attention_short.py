@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import pytest
+import torch
 
 from paper_2604_08971_amd import binding as sf
 from test_gpu_parity import _gqa_case, _say
@@ -45,6 +46,19 @@ def test_shortest_sequences(dtype, dh, L):
             # a sample of ten keys and none masked: the score over a single key is zero but for rounding, which picks any query
             if L >= 16:
                 _gqa_case(dtype, 3, 4, 2, L, dh, U, False, seed=L + dh, n_sample=14)
+
+
+def test_timed_as_a_class_of_its_own():
+    """One launch that is neither a score stream nor an active pass; a sequence that stays with the separate launches is both."""
+    for (B, L), want in (((2, 300), (0, 0, 1)), ((1, 3000), (1, 1, 0))):
+        Q, K, V = (torch.randn((B, 2, L, 64), device="cuda").bfloat16() for _ in range(3))
+        desc, hg = sf.make_desc(B, L, 64, 2, 2, 64, 64, dtype=sf.SF_BF16), torch.arange(2, dtype=torch.int32, device="cuda").reshape(1, 2)
+        seen = []
+        for cls in (sf.SF_KERNEL_SCORE, sf.SF_KERNEL_ATTEND, sf.SF_KERNEL_ATTENTION):
+            sf.profile_begin(cls, 4)
+            sf.sparse_gqa_forward(desc, Q, K, V, hg)
+            seen.append(sf.profile_end()[0])
+        assert tuple(seen) == want, (L, seen)
 
 
 def test_what_stays_with_the_separate_launches():
