@@ -38,7 +38,7 @@ def test_attention_edges(dtype, B, nH, nG, L, dh, Uo, mask):
 
 
 # Which of the two kernels takes fewer than 256 active rows is an estimate of their times: the plan is asserted, so that every
-# form stays covered.  Staged tiles: key splits with key groups inside a workgroup, four waves, a group with more pairs than
+# form stays covered (by the second of two calls, with an output that is not aligned, where one launch serves the first).  Staged tiles: key splits with key groups inside a workgroup, four waves, a group with more pairs than
 # waves, each head dimension; sliced keys: four waves with one query block each.
 @pytest.mark.parametrize("B,nH,nG,L,dh,Uo,mask,staged,splits", [
     (1, 2, 1, 4097, 64, -1, True, 1, 13),         # last tile of one key
@@ -74,11 +74,13 @@ def test_packed_rows_of_few_heads():
     _packed_case(make_wl(W.small_spec(dtype="bf16", d=64, Hq=2, Hk=1, dh=32, F=128, nl=1, seg=(2900, 1300), B=2, head_keep=1.0, dropout="upto:1")))
 
 
-# one sample whose only modality is a few tokens at the end: most key tiles are dead
+# one sample whose only modality is a few tokens at the end: most key tiles are dead; a length that one launch serves, and one
+# that keeps the separate ones
+@pytest.mark.parametrize("seg", [(600, 40, 7), (1300, 80, 7)])
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-def test_encoder_with_dead_tiles(dtype):
-    _say(f"dead tiles {dtype}")
-    spec = W.small_spec(dtype=dtype, B=7, seg=(600, 40, 7), d=64, Hq=2, Hk=1, dh=32, F=128, nl=1, head_keep=1.0,
+def test_encoder_with_dead_tiles(dtype, seg):
+    _say(f"dead tiles {dtype} {seg}")
+    spec = W.small_spec(dtype=dtype, B=7, seg=seg, d=64, Hq=2, Hk=1, dh=32, F=128, nl=1, head_keep=1.0,
                         dropout="upto:2", c=3)
     with sf.use_half("f16" if dtype == "f16" else "bf16"):
         _encoder_parity(make_wl(spec))
@@ -127,7 +129,7 @@ def test_allowed_query_whose_score_has_every_bit_set():
 def test_score_over_key_ranges_keeps_nan_and_infinities():
     """The score of one sample comes in ranges of keys, the same sample in a batch of 64 without: NaN, both infinities and
     finite values fall on the same queries (one range has no allowed key, one key overflows its products)."""
-    B, nH, L, dh = 64, 2, 600, 64
+    B, nH, L, dh = 64, 2, 600, 128
     rng = np.random.default_rng(8)
     Q, K, V = (W.to_bf16_values(rng.standard_normal((1, nH, L, dh)).astype(np.float32)) for _ in range(3))
     K[0, :, 350, 0] = 3e38
@@ -140,6 +142,8 @@ def test_score_over_key_ranges_keeps_nan_and_infinities():
     got = []
     for n in (1, B):
         desc = sf.make_desc(n, L, 64, nH, nH, dh, 64, dtype=sf.SF_BF16)
+        parts = sf.sparse_gqa_plan(desc, nH, nH)["score_parts"]
+        assert parts > 1 if n == 1 else parts == 1, parts
         q, k, v = (to_dev(np.repeat(x, n, axis=0), "bf16") for x in (Q, K, V))
         _, sel, score = sf.sparse_gqa_forward(desc, q, k, v, hg, key_valid=torch.from_numpy(np.repeat(kv, n, axis=0)).cuda(), want_score=True)
         torch.cuda.synchronize()

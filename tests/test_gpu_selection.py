@@ -21,8 +21,8 @@ def _expected(score, allowed, U):
 
 # The selection against the device's own scores: all equal (a range of one value), two values, an outlier that leaves the others
 # in one step of the histogram, an infinity.  One to four queries per thread
-# in registers, and more of them read from LDS.
-@pytest.mark.parametrize("dtype,L,dh", [("bf16", 300, 64), ("bf16", 700, 32), ("bf16", 3000, 64), ("bf16", 5000, 128), ("f32", 90, 16), ("f32", 700, 16)])
+# in registers, and more of them read from LDS, in the one launch of a short sequence (300 and 700 keys) and in one of their own.
+@pytest.mark.parametrize("dtype,L,dh", [("bf16", 300, 64), ("bf16", 700, 32), ("bf16", 200, 128), ("bf16", 300, 128), ("bf16", 3000, 64), ("bf16", 5000, 128), ("f32", 90, 16), ("f32", 700, 16)])
 @pytest.mark.parametrize("kind", ["equal", "two", "outlier", "inf", "random"])
 def test_selection_of_degenerate_scores(dtype, L, dh, kind):
     _say(f"selection {dtype} L={L} {kind}")

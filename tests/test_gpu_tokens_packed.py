@@ -262,6 +262,8 @@ def _packed_case(wl, samples=None, tight=True, n_sample=0):
     # runs of several 256-row blocks, blocks that straddle samples, more samples than one scan chunk has lanes
     (dict(dtype="bf16", d=64, dh=32, Hq=4, Hk=2, F=192, seg=(260, 140, 120, 60), B=23, nl=2, dropout="upto:2", c=1), True),
     (dict(dtype="bf16", d=256, dh=64, Hq=4, Hk=2, F=512, seg=(130, 70, 60), B=40, dropout="upto:2"), True),
+    # a head dimension that keeps the attention's separate launches at any length
+    (dict(dtype="bf16", d=256, dh=128, Hq=4, Hk=2, F=192, seg=(260, 140, 120, 60), B=9, dropout="upto:2"), True),
 ])
 def test_encoder_packed_parity_small(kw, tight):
     _say(f"packed encoder {kw}")
@@ -273,6 +275,7 @@ def test_encoder_packed_parity_with_sampled_score():
     _say("packed encoder, sampled score")
     _packed_case(make_wl(W.small_spec(dtype="bf16", d=128, dh=64, Hq=8, Hk=2, F=300, seg=(100, 33, 64, 120), B=7, nl=2,
                                       dropout="upto:3", act=1)), n_sample=40)
+    _packed_case(make_wl(W.small_spec(dtype="bf16", d=256, dh=128, Hq=4, Hk=2, F=192, seg=(100, 33, 64, 120), B=5, dropout="upto:3")), n_sample=40)
     _packed_case(make_wl(W.small_spec(dtype="f32", dropout="upto:2", B=5)), n_sample=9)
 
 
