@@ -218,9 +218,9 @@ __global__ __launch_bounds__(NWAVE * 64) SF_SCORE_OCC void score_bf16_kernel(
 
 // ---------------------------------------------------------------- active pass
 // A "pair" is (head of the group, block of 32 active queries).  A workgroup of
-// AWAVE waves serves one (sample, K/V group, key split): each wave owns QB
-// pairs and all waves share the K / V^T tiles staged in LDS; a group with more
-// pairs than AWAVE*QB is served in several passes over the key range.
+// AWAVE waves serves one (sample, K/V group, key split): each wave owns a
+// pair and all waves share the K / V^T tiles staged in LDS; a group with more
+// pairs than AWAVE is served in several passes over the key range.
 // 1-D grid; the launch index is folded so that consecutive work items (the
 // pair chunks of one (sample, group), which read the same K/V) run on the same
 // XCD and share its L2, and the items are spread evenly over the XCDs.
@@ -229,10 +229,12 @@ constexpr int AWAVE = 8;
 // NW = waves per workgroup.  Four instead of eight where a (sample, group) has at most four pairs: the same registers
 // per wave then leave room for three workgroups per compute unit, and no wave is without a pair.
 // Many active rows (dense-like patterns): at 126 registers (dh 64; 102 at dh 32) two workgroups share a compute unit, and one runs
-// its softmax on the vector ALU while the other has the matrix pipe.  What bounds it is the vector ALU.  us for a call, every
-// query active: a kernel of two query blocks per wave that kept the waves of a SIMD in opposite phases by barriers, one
-// workgroup per compute unit / this (with nothing else changed): 8 samples of 1777 keys, 8 heads 115 / 110; 16 of 4096 720 / 694;
-// 1 of 4096, 4 heads 163 / 112; 64 of 1500, 3 heads of dh 32 196 / 147; 32 of 512, 4 heads 54 / 45; 4 of 1024, 4 heads 63 / 47.
+// its softmax on the vector ALU while the other has the matrix pipe.  (128 are the limit for that.  As a minimum in the launch
+// bounds it makes the compiler spill, so a test of the build watches the number.)  us for this launch, every query active, a
+// kernel of two query blocks per wave that kept the waves of a SIMD in opposite phases by barriers, one workgroup per compute
+// unit / this: 16 samples of 4096 keys, 8 heads 696 / 710; 8 of 1777 82 / 82; 1 of 4096, 4 heads 143 / 101; 64 of 1500, 3 heads of
+// dh 32 165 / 124; 32 of 512, 4 heads 29 / 22; 4 of 1024, 4 heads 44 / 30.  Few long problems gain, many are level: there the
+// calls gained by statistics that are not formed and a faster transposition (746 / 731, 109 / 95).
 template <int DH, int NW>
 __global__ __launch_bounds__(NW * 64) void attend_bf16_kernel(
     const h16 *__restrict__ Q, sf_strides sq, const h16 *__restrict__ K, sf_strides sk,
@@ -242,7 +244,6 @@ __global__ __launch_bounds__(NW * 64) void attend_bf16_kernel(
     int Upad, int splits, int keys_per_split, h16 *__restrict__ O, int64_t ldo,
     float *__restrict__ part_o, float *__restrict__ part_ml, const int32_t *__restrict__ row0)
 {
-    constexpr int QB = 1;                                          // query blocks per wave
     constexpr int NT = NW * 64;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int KT = BKEY * (DH + PAD), VT_ = DH * (BKEY + PAD);          // elements of one K / V^T tile
@@ -326,56 +327,44 @@ __global__ __launch_bounds__(NW * 64) void attend_bf16_kernel(
     using KT_ = KTile<DH, NT>;
     auto tile_j0 = [&](int it) { return __builtin_amdgcn_readfirstlane((int)tiles[it]) * BKEY; };   // same for every lane
 
-    for (int pair0 = chunk * (NW * QB); pair0 < npairs; pair0 += chunks * (NW * QB)) {
+    for (int pair0 = chunk * NW; pair0 < npairs; pair0 += chunks * NW) {
         // When this pass has pairs for at most half of the waves (few active rows: U = c*ceil(ln L) gives one or two
         // blocks of 32 per head), the others would only help with the staging: instead KG groups of waves take the
         // same pairs and every KG-th key tile each, and their partial results are merged through LDS at the end.
         int kg = 1;
         {
-            const int waves_used = (min(npairs - pair0, NW * QB) + QB - 1) / QB;
+            const int waves_used = min(npairs - pair0, NW);
             // only where the launch is short of workgroups (the host split the keys for that reason): with a
             // (sample, group) problem per compute unit or more the idle waves cost nothing and the merge does
             while (splits > 1 && waves_used * kg * 2 <= NW) kg *= 2;
         }
         const int pslots = NW / kg;                  // waves that hold distinct pairs
         const int pw = wave % pslots, kgi = wave / pslots;
-        int head[QB], qidx[QB], slot[QB];
-        h16x8 qf[QB][DH / 16];
-        auto locate = [&](int qq, int lane32) {
-            const int pi = pair0 + pw * QB + qq;
-            head[qq] = -1; qidx[qq] = -1; slot[qq] = 0;
+        int head, qidx, slot;
+        auto locate = [&](int lane32) {
+            const int pi = pair0 + pw;
+            head = -1; qidx = -1; slot = 0;
             if (pi < npairs) {
-                head[qq] = heads[pi / nqb];
-                slot[qq] = (pi % nqb) * 32 + lane32;
-                if (slot[qq] < U) qidx[qq] = sel[((int64_t)b * selH + head[qq]) * U + slot[qq]];
+                head = heads[pi / nqb];
+                slot = (pi % nqb) * 32 + lane32;
+                if (slot < U) qidx = sel[((int64_t)b * selH + head) * U + slot];
             }
         };
+        locate(l32);
+        const h16 *qrow = Q + sample_offset(row0, b, sq) + (int64_t)max(head, 0) * sq.h + (int64_t)max(qidx, 0) * sq.l;
+        h16x8 qf[DH / 16];
 #pragma unroll
-        for (int qq = 0; qq < QB; ++qq) {
-            locate(qq, l32);
-            const h16 *qrow = Q + sample_offset(row0, b, sq) + (int64_t)max(head[qq], 0) * sq.h +
-                                 (int64_t)max(qidx[qq], 0) * sq.l;
-#pragma unroll
-            for (int kk = 0; kk < DH / 16; ++kk)
-                qf[qq][kk] = *reinterpret_cast<const h16x8 *>(qrow + kk * 16 + lhi * 8);
-        }
+        for (int kk = 0; kk < DH / 16; ++kk) qf[kk] = *reinterpret_cast<const h16x8 *>(qrow + kk * 16 + lhi * 8);
         // no pair, or none of its slots names a row (masked queries leave whole blocks empty): uniform over the wave
-        bool row = qidx[0] >= 0;
-#pragma unroll
-        for (int qq = 1; qq < QB; ++qq) row |= qidx[qq] >= 0;
-        const bool idle = __builtin_amdgcn_ballot_w64(row) == 0ull;
+        const bool idle = __builtin_amdgcn_ballot_w64(qidx >= 0) == 0ull;
         if (!__syncthreads_or(!idle)) continue;               // nobody in the workgroup has one
 
-        f32x16 oacc[QB][DH / 32];
-        float m_run[QB], l_run[QB];
+        f32x16 oacc[DH / 32];
+        float m_run = -INFINITY, l_run = 0.f;
 #pragma unroll
-        for (int qq = 0; qq < QB; ++qq) {
-            m_run[qq] = -INFINITY; l_run[qq] = 0.f;
+        for (int db = 0; db < DH / 32; ++db)
 #pragma unroll
-            for (int db = 0; db < DH / 32; ++db)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) oacc[qq][db][e] = 0.f;
-        }
+            for (int e = 0; e < 16; ++e) oacc[db][e] = 0.f;
 
         uint4 kreg[KT_::N], vreg[NV];
         if (nt > 0) { KT_::fetch(Kb, sk.l, tile_j0(0), L, kreg); fetch_v(tile_j0(0), vreg); }
@@ -393,7 +382,7 @@ __global__ __launch_bounds__(NW * 64) void attend_bf16_kernel(
             const bool all_allowed = (uint32_t)__builtin_amdgcn_readfirstlane((int)(w0 & w1)) == 0xffffffffu;
 
             // S^T blocks for the two 32-key halves
-            f32x16 s[QB][2];
+            f32x16 s[2];
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb) {
                 h16x8 kf[DH / 16];
@@ -401,66 +390,59 @@ __global__ __launch_bounds__(NW * 64) void attend_bf16_kernel(
                 for (int kk = 0; kk < DH / 16; ++kk)
                     kf[kk] = *reinterpret_cast<const h16x8 *>(Kt + (kb * 32 + l32) * (DH + PAD) + kk * 16 + lhi * 8);
 #pragma unroll
-                for (int qq = 0; qq < QB; ++qq) {
+                for (int e = 0; e < 16; ++e) s[kb][e] = 0.f;
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) s[qq][kb][e] = 0.f;
-#pragma unroll
-                    for (int kk = 0; kk < DH / 16; ++kk)
-                        s[qq][kb] = SF_MFMA16(kf[kk], qf[qq][kk], s[qq][kb], 0, 0, 0);
-                }
+                for (int kk = 0; kk < DH / 16; ++kk) s[kb] = SF_MFMA16(kf[kk], qf[kk], s[kb], 0, 0, 0);
             }
 
             // online softmax per query (per lane), log2 domain
-            h16x8 pf[QB][4];
+            if (!all_allowed) {
 #pragma unroll
-            for (int qq = 0; qq < QB; ++qq) {
-                if (!all_allowed) {
+                for (int kb = 0; kb < 2; ++kb) {
+                    const uint32_t wl = (kb ? w1 : w0) >> (lhi * 4);
 #pragma unroll
-                    for (int kb = 0; kb < 2; ++kb) {
-                        const uint32_t wl = (kb ? w1 : w0) >> (lhi * 4);
-#pragma unroll
-                        for (int e = 0; e < 16; ++e)
-                            if (!((wl >> ((e / 4) * 8 + (e % 4))) & 1u)) s[qq][kb][e] = -INFINITY;
-                    }
+                    for (int e = 0; e < 16; ++e)
+                        if (!((wl >> ((e / 4) * 8 + (e % 4))) & 1u)) s[kb][e] = -INFINITY;
                 }
-                float mt = fmaxf(fmaxf(s[qq][0][0], s[qq][0][1]), s[qq][1][0]);
-                mt = fmaxf(fmaxf(mt, s[qq][1][1]), s[qq][0][2]);
-#pragma unroll
-                for (int e = 3; e < 15; e += 2) mt = fmaxf(fmaxf(mt, s[qq][0][e]), s[qq][0][e + 1]);
-#pragma unroll
-                for (int e = 2; e < 16; e += 2) mt = fmaxf(fmaxf(mt, s[qq][1][e]), s[qq][1][e + 1]);
-                mt = fmaxf(mt, s[qq][0][15]) * sc;         // sc > 0: max and scaling commute
-                mt = both_halves_max(mt);                  // the other 16 keys of each 32-key block sit in lane ^ 32
-                // The reference m_run of the exponentials only has to stay within 2^RESCALE_LOG2 of the true running
-                // maximum (sums and outputs are relative to the same reference, so the result does not depend on
-                // it): it moves, and the accumulators are rescaled, only when some query of the wave needs it.
-                // After the first tiles of a row that is rare, which removes the rescaling from the common path.
-                if (__builtin_expect(__builtin_amdgcn_ballot_w64(mt > m_run[qq] + RESCALE_LOG2) != 0ull, 0)) {
-                    const float m_new = fmaxf(m_run[qq], mt);
-                    const float alpha = __builtin_amdgcn_exp2f(m_run[qq] - (m_new == -INFINITY ? 0.f : m_new));
-                    m_run[qq] = m_new;
-                    l_run[qq] *= alpha;
-#pragma unroll
-                    for (int db = 0; db < DH / 32; ++db)
-#pragma unroll
-                        for (int e = 0; e < 16; ++e) oacc[qq][db][e] *= alpha;
-                }
-                const float nm = m_run[qq] == -INFINITY ? 0.f : -m_run[qq];
-                float rs0 = 0.f, rs1 = 0.f;
-                // k-step t covers keys 16t..16t+15; this lane supplies keys
-                // {16t + lhi*4 + 0..3, 16t + 8 + lhi*4 + 0..3} = accumulator entries (t%2)*8 + 0..7 of block t/2
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int e = 0; e < 16; e += 2) {
-                        const float p0 = __builtin_amdgcn_exp2f(fmaf(s[qq][kb][e], sc, nm));
-                        const float p1 = __builtin_amdgcn_exp2f(fmaf(s[qq][kb][e + 1], sc, nm));
-                        rs0 += p0;
-                        rs1 += p1;
-                        reinterpret_cast<uint32_t *>(&pf[qq][kb * 2 + e / 8])[(e % 8) / 2] = pack2_h16(p0, p1);
-                    }
-                l_run[qq] += rs0 + rs1;
             }
+            float mt = fmaxf(fmaxf(s[0][0], s[0][1]), s[1][0]);
+            mt = fmaxf(fmaxf(mt, s[1][1]), s[0][2]);
+#pragma unroll
+            for (int e = 3; e < 15; e += 2) mt = fmaxf(fmaxf(mt, s[0][e]), s[0][e + 1]);
+#pragma unroll
+            for (int e = 2; e < 16; e += 2) mt = fmaxf(fmaxf(mt, s[1][e]), s[1][e + 1]);
+            mt = fmaxf(mt, s[0][15]) * sc;             // sc > 0: max and scaling commute
+            mt = both_halves_max(mt);                  // the other 16 keys of each 32-key block sit in lane ^ 32
+            // The reference m_run of the exponentials only has to stay within 2^RESCALE_LOG2 of the true running
+            // maximum (sums and outputs are relative to the same reference, so the result does not depend on
+            // it): it moves, and the accumulators are rescaled, only when some query of the wave needs it.
+            // After the first tiles of a row that is rare, which removes the rescaling from the common path.
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(mt > m_run + RESCALE_LOG2) != 0ull, 0)) {
+                const float m_new = fmaxf(m_run, mt);
+                const float alpha = __builtin_amdgcn_exp2f(m_run - (m_new == -INFINITY ? 0.f : m_new));
+                m_run = m_new;
+                l_run *= alpha;
+#pragma unroll
+                for (int db = 0; db < DH / 32; ++db)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
+            }
+            const float nm = m_run == -INFINITY ? 0.f : -m_run;
+            float rs0 = 0.f, rs1 = 0.f;
+            h16x8 pf[4];
+            // k-step t covers keys 16t..16t+15; this lane supplies keys
+            // {16t + lhi*4 + 0..3, 16t + 8 + lhi*4 + 0..3} = accumulator entries (t%2)*8 + 0..7 of block t/2
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int e = 0; e < 16; e += 2) {
+                    const float p0 = __builtin_amdgcn_exp2f(fmaf(s[kb][e], sc, nm));
+                    const float p1 = __builtin_amdgcn_exp2f(fmaf(s[kb][e + 1], sc, nm));
+                    rs0 += p0;
+                    rs1 += p1;
+                    reinterpret_cast<uint32_t *>(&pf[kb * 2 + e / 8])[(e % 8) / 2] = pack2_h16(p0, p1);
+                }
+            l_run += rs0 + rs1;
 
             // O^T += V^T . P^T
 #pragma unroll
@@ -473,9 +455,7 @@ __global__ __launch_bounds__(NW * 64) void attend_bf16_kernel(
                     h16x8 vf;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) { vf[e] = lo[e]; vf[4 + e] = hi[e]; }
-#pragma unroll
-                    for (int qq = 0; qq < QB; ++qq)
-                        oacc[qq][db] = SF_MFMA16(vf, pf[qq][t], oacc[qq][db], 0, 0, 0);
+                    oacc[db] = SF_MFMA16(vf, pf[t], oacc[db], 0, 0, 0);
                 }
             }
         }
@@ -483,66 +463,57 @@ __global__ __launch_bounds__(NW * 64) void attend_bf16_kernel(
         // merge of the key groups: in log2(KG) rounds the upper half of the groups hands its running reference, sum
         // and accumulator over through the tile buffers (free now) and the lower half folds them into its own
         if (kg > 1) {
-            float *mrg = reinterpret_cast<float *>(smem);              // [writer wave][QB * (DH/2 + 2)][64 lanes]
-            constexpr int PER = QB * ((DH / 32) * 16 + 2);
+            float *mrg = reinterpret_cast<float *>(smem);              // [writer wave][DH/2 + 2][64 lanes]
+            constexpr int PER = (DH / 32) * 16 + 2;
             static_assert((NW / 2) * PER * 64 * 4 <= 2 * KT * 2 + 2 * VT_ * 2, "merge scratch must fit in the tile buffers");
             for (int step = kg / 2; step >= 1; step /= 2) {
                 __syncthreads();                                       // tile buffers (or the last round's slots) are free
                 if (kgi >= step && kgi < 2 * step) {
                     float *dst = mrg + (size_t)(wave - step * pslots) * PER * 64 + lane;
 #pragma unroll
-                    for (int qq = 0; qq < QB; ++qq) {
+                    for (int db = 0; db < DH / 32; ++db)
 #pragma unroll
-                        for (int db = 0; db < DH / 32; ++db)
-#pragma unroll
-                            for (int e = 0; e < 16; ++e) dst[((qq * (DH / 32) + db) * 16 + e) * 64] = oacc[qq][db][e];
-                        dst[(QB * (DH / 32) * 16 + qq * 2) * 64] = m_run[qq];
-                        dst[(QB * (DH / 32) * 16 + qq * 2 + 1) * 64] = l_run[qq];
-                    }
+                        for (int e = 0; e < 16; ++e) dst[(db * 16 + e) * 64] = oacc[db][e];
+                    dst[(DH / 32) * 16 * 64] = m_run;
+                    dst[((DH / 32) * 16 + 1) * 64] = l_run;
                 }
                 __syncthreads();
                 if (kgi < step) {
                     const float *src = mrg + (size_t)wave * PER * 64 + lane;
+                    const float m_o = src[(DH / 32) * 16 * 64], l_o = src[((DH / 32) * 16 + 1) * 64];
+                    const float m_new = fmaxf(m_run, m_o);
+                    const float m_safe = m_new == -INFINITY ? 0.f : m_new;
+                    const float a_me = __builtin_amdgcn_exp2f(m_run - m_safe), a_o = __builtin_amdgcn_exp2f(m_o - m_safe);
+                    m_run = m_new;
+                    l_run = l_run * a_me + l_o * a_o;
 #pragma unroll
-                    for (int qq = 0; qq < QB; ++qq) {
-                        const float m_o = src[(QB * (DH / 32) * 16 + qq * 2) * 64], l_o = src[(QB * (DH / 32) * 16 + qq * 2 + 1) * 64];
-                        const float m_new = fmaxf(m_run[qq], m_o);
-                        const float m_safe = m_new == -INFINITY ? 0.f : m_new;
-                        const float a_me = __builtin_amdgcn_exp2f(m_run[qq] - m_safe), a_o = __builtin_amdgcn_exp2f(m_o - m_safe);
-                        m_run[qq] = m_new;
-                        l_run[qq] = l_run[qq] * a_me + l_o * a_o;
+                    for (int db = 0; db < DH / 32; ++db)
 #pragma unroll
-                        for (int db = 0; db < DH / 32; ++db)
-#pragma unroll
-                            for (int e = 0; e < 16; ++e)
-                                oacc[qq][db][e] = oacc[qq][db][e] * a_me + src[((qq * (DH / 32) + db) * 16 + e) * 64] * a_o;
-                    }
+                        for (int e = 0; e < 16; ++e) oacc[db][e] = oacc[db][e] * a_me + src[(db * 16 + e) * 64] * a_o;
                 }
             }
         }
 
         // lane owns query l32 and output dims db*32 + ig*8 + lhi*4 + {0..3}
-#pragma unroll
-        for (int qq = 0; qq < QB; ++qq) {
-            const float l_tot = both_halves_sum(l_run[qq]);
-            int lane32 = l32;
-            asm volatile("" : "+v"(lane32));     // the row is looked up again: live across the loop it costs registers
-            locate(qq, lane32);
-            if (qidx[qq] < 0 || kgi != 0) continue;
+        const float l_tot = both_halves_sum(l_run);
+        int lane32 = l32;
+        asm volatile("" : "+v"(lane32));     // the row is looked up again: live across the loop it costs registers
+        locate(lane32);
+        if (qidx >= 0 && kgi == 0) {
             if (splits <= 1) {
                 const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-                h16 *orow = O + (sample_row(row0, b, L) + qidx[qq]) * ldo + (int64_t)head[qq] * DH;
+                h16 *orow = O + (sample_row(row0, b, L) + qidx) * ldo + (int64_t)head * DH;
 #pragma unroll
                 for (int db = 0; db < DH / 32; ++db)
 #pragma unroll
                     for (int ig = 0; ig < 4; ++ig) {
                         h16x4 o;
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) o[e] = (h16)(oacc[qq][db][ig * 4 + e] * inv);
+                        for (int e = 0; e < 4; ++e) o[e] = (h16)(oacc[db][ig * 4 + e] * inv);
                         *reinterpret_cast<h16x4 *>(orow + db * 32 + ig * 8 + lhi * 4) = o;
                     }
             } else {
-                const int64_t base = (((int64_t)b * nH + head[qq]) * splits + sp) * Upad + slot[qq];   // [b, head, split, slot]
+                const int64_t base = (((int64_t)b * nH + head) * splits + sp) * Upad + slot;   // [b, head, split, slot]
                 float *po = part_o + base * DH;
 #pragma unroll
                 for (int db = 0; db < DH / 32; ++db)
@@ -550,11 +521,11 @@ __global__ __launch_bounds__(NW * 64) void attend_bf16_kernel(
                     for (int ig = 0; ig < 4; ++ig) {
                         f32x4 o;
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) o[e] = oacc[qq][db][ig * 4 + e];
+                        for (int e = 0; e < 4; ++e) o[e] = oacc[db][ig * 4 + e];
                         *reinterpret_cast<f32x4 *>(po + db * 32 + ig * 8 + lhi * 4) = o;
                     }
                 if (lhi == 0) {
-                    part_ml[base * 2] = m_run[qq];
+                    part_ml[base * 2] = m_run;
                     part_ml[base * 2 + 1] = l_tot;
                 }
             }
@@ -868,7 +839,8 @@ static SliceShape slice_shape(const AttnArgs &a)
 // or the traffic, each item's own where it is sliced).  Its constants are a fit to 2400 calls drawn at random (1 to 512
 // samples of 48 to 16384 keys, 1 to 8 groups of 1 to 16 heads, 1 to 255 active rows, a third of them masked): over those the
 // choice costs 0.4 % of a call against the better kernel, 20 % at worst (all sliced: 6 %, a factor of 1.9; all staged: 11 %,
-// 2.1).
+// 2.1).  Since then the staged kernel has come to share a compute unit between two workgroups: over 110 calls of 1100 to 16384
+// keys the choice costs 1.5 %, 13 % at worst (all sliced: 5.6 %, all staged: 5.5 %).
 bool attend_bf16_staged(const AttnArgs &a, int splits)
 {
     if (a.U >= STAGED_U) return true;

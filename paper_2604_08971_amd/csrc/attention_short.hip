@@ -110,11 +110,7 @@ __global__ __launch_bounds__(NW * 64, 4) void attend_short_bf16_kernel(ShortArgs
         }
     };
     fetch_q(wave * QBS);
-    for (int j0 = 0; j0 < nt * 32; j0 += NT) {                            // the same trip count for every wave
-        const int j = j0 + tid;
-        const unsigned long long bal = __ballot(j < L && (!kv || kv[j]));
-        if ((lane & 31) == 0 && j < nt * 32) words[j >> 5] = (uint32_t)(bal >> (lane & 32));
-    }
+    build_mask_words(kv, L, words, nt);
     uint32_t *const set = SAMPLED ? reinterpret_cast<uint32_t *>(rows) : words;           // the keys of the score
     uint16_t *const list = reinterpret_cast<uint16_t *>(scratch);
     uint32_t set_word = 0u;
@@ -468,8 +464,10 @@ int32_t launch_short(const ShortArgs &s, hipStream_t st)
     return SF_OK;
 }
 
-// Waves of a workgroup.  Four where four workgroups fit a compute unit and there are heads for them (161 x 12 heads of 78 keys:
-// 20 us, 34 with eight waves), and for up to 128 keys, four blocks of queries; eight where two fit (128 x 6 heads of 512 keys,
+// Waves of a workgroup.  Four where at least three workgroups fit a compute unit (four but for the last few lengths: 41 KB at 256
+// keys of dh 64 or 512 of dh 32) and there are heads for them (161 x 12 heads of 78 keys: 20 us, 34 with eight waves; 256 x 6 of
+// 225, dh 64 49 / 58; 130 x 12 of 256, dh 64 71 / 75; 256 x 12 of 512, dh 32 113 / 121; with 260 to 520 heads of 288 and more,
+// dh 32, eight are 5 to 10 % ahead), and for up to 128 keys, four blocks of queries; eight where two fit (128 x 6 heads of 512 keys,
 // dh 64: 63 / 53 / 69 with four, eight, sixteen); sixteen for long sequences, whose score is a wave's longest step (24 x 6
 // heads of 628 keys 38 / 31 / 29), once fewer than two workgroups fit or there are no more heads than compute units.
 int short_waves(const AttnArgs &a)
@@ -601,11 +599,7 @@ __global__ __launch_bounds__(NT) void attend_short_f32_kernel(ShortF32Args a)
             Vs[r * LD + e] = Vb[(int64_t)r * a.v_sj + (int64_t)e * a.v_se];
         }
     }
-    for (int j0 = 0; j0 < F32_WORDS * 32; j0 += NT) {                     // the same trip count for every wave
-        const int j = j0 + tid;
-        const unsigned long long bal = __ballot(j < L && (!kv || kv[j]));
-        if ((lane & 31) == 0 && j < F32_WORDS * 32) words[j >> 5] = (uint32_t)(bal >> (lane & 32));
-    }
+    build_mask_words(kv, L, words, F32_WORDS);
     lds_barrier();
     const uint32_t word = lane < F32_WORDS ? words[lane] : 0u;
     const int n = __builtin_amdgcn_readlane(wave_incl_scan(__popc(word)), 63);      // allowed keys

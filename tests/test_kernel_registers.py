@@ -1,0 +1,26 @@
+"""What the compiler reports of kernels whose speed rests on their registers."""
+from __future__ import annotations
+
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2604_08971_amd import build
+
+
+# The staged active pass: two workgroups of eight waves share a compute unit up to 128 registers a lane, without scratch
+@pytest.mark.parametrize("half", ["bf16", "f16"])
+def test_two_workgroups_of_the_staged_active_pass(half, tmp_path):
+    cmd = ["hipcc"] + build.FLAGS + (["-DSF_HALF_F16"] if half == "f16" else []) + ["--cuda-device-only", "-Rpass-analysis=kernel-resource-usage",
+           "-c", os.path.join(build.CSRC, "attention_bf16.hip"), "-o", str(tmp_path / "a.o")]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    found = 0
+    for part in r.stderr.split("Function Name: ")[1:]:
+        if re.match(r"\S*attend_bf16_kernelILi(32|64)ELi8E", part):
+            total = sum(int(re.search(rf" {n}: (\d+)", part).group(1)) for n in ("VGPRs", "AGPRs"))
+            assert total <= 128 and re.search(r"ScratchSize \[bytes/lane\]: 0 ", part), part.split("\n")[0]
+            found += 1
+    assert found == 2
