@@ -547,7 +547,7 @@ int32_t attend_short_bf16(const AttnArgs &a, const void *vt, sf_strides svt, int
 // The same in fp32, for the small models that the fp32 path is there for: a workgroup per (sample, head) holds its queries, keys
 // and values in LDS; sixteen threads share a query (or an active row), as in score_f32_kernel, whose sums it keeps.  What
 // bounds it is the chain of phases, and in each the latency of LDS: four keys are on their way per thread.  us, launches of their
-// own / this one: 2 x 2 heads of 48 keys, dh 16 18.6 / 11.7; 128 heads of 90, dh 32 66 / 25; 128 of 256, dh 16 74 / 46.
+// own / this one: 2 x 2 heads of 48 keys, dh 16 17.1 / 12.2; 128 heads of 90, dh 32 64 / 25; 128 of 256, dh 16 72 / 45.
 namespace {
 
 struct ShortF32Args {
@@ -694,12 +694,17 @@ __global__ __launch_bounds__(NT) void attend_short_f32_kernel(ShortF32Args a)
         }
 #pragma unroll
         for (int o = 8; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-        float den = 0.f;
-        for (int j = kl; j < L; j += 16) {
-            const float s = p[j], pj = s == -INFINITY ? 0.f : expf(s - mx);
-            p[j] = pj;
-            den += pj;
+        float dn[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int j = kl; j < L; j += 64) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (j + u * 16 >= L) break;
+                const float s = p[j + u * 16], pj = s == -INFINITY ? 0.f : expf(s - mx);
+                p[j + u * 16] = pj;
+                dn[u] += pj;
+            }
         }
+        float den = (dn[0] + dn[1]) + (dn[2] + dn[3]);
 #pragma unroll
         for (int o = 8; o > 0; o >>= 1) den += __shfl_xor(den, o);
         // the sixteen threads are in one wave: its LDS accesses are in order
@@ -708,20 +713,33 @@ __global__ __launch_bounds__(NT) void attend_short_f32_kernel(ShortF32Args a)
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
         const float inv = den > 0.f ? 1.0f / den : 0.f;
         constexpr int SHARE = DH < 16 ? 16 / DH : 1, PER = DH < 16 ? 1 : DH / 16;      // threads of a dimension, dimensions of a thread
-        float acc[PER];
+        // Eight sums of a dimension next to each other: one of all keys is 1.4 times as far from the sum in 64 bits as the separate
+        // launches are (256 keys; the context vector 2.4 times)
+        constexpr int SUMS = 8;
+        float part[PER][SUMS];
 #pragma unroll
-        for (int u = 0; u < PER; ++u) acc[u] = 0.f;
-#pragma unroll 8
-        for (int j = kl / (16 / SHARE); j < L; j += SHARE) {
+        for (int u = 0; u < PER; ++u)
+#pragma unroll
+            for (int c = 0; c < SUMS; ++c) part[u][c] = 0.f;
+        auto add = [&](int j, int c) {
             const float pj = p[j];
 #pragma unroll
             for (int u = 0; u < PER; ++u) {
                 const float v = Vs[j * LD + kl % (16 / SHARE) + u * 16];
-                acc[u] = pj != 0.f ? fmaf(pj, v, acc[u]) : acc[u];        // masked rows may hold anything
+                part[u][c] = pj != 0.f ? fmaf(pj, v, part[u][c]) : part[u][c];        // masked rows may hold anything
             }
-        }
+        };
+        int j = kl / (16 / SHARE);
+        for (; j + (SUMS - 1) * SHARE < L; j += SUMS * SHARE)
+#pragma unroll
+            for (int c = 0; c < SUMS; ++c) add(j + c * SHARE, c);
+#pragma unroll
+        for (int c = 0; c < SUMS - 1; ++c)
+            if (j + c * SHARE < L) add(j + c * SHARE, c);
+        float acc[PER];
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
+            acc[u] = ((part[u][0] + part[u][1]) + (part[u][2] + part[u][3])) + ((part[u][4] + part[u][5]) + (part[u][6] + part[u][7]));
 #pragma unroll
             for (int o = 16 / SHARE; o < 16; o <<= 1) acc[u] += __shfl_xor(acc[u], o);
             const int e = kl % (16 / SHARE) + u * 16;

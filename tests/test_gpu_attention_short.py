@@ -81,3 +81,23 @@ def test_short_attention_f32(B, nH, nG, L, dh, Uo, mask):
     _say(f"short attention f32 B={B} nH={nH} L={L} dh={dh} U={Uo} mask={mask}")
     for kw in (dict(), dict(strided=True, per_sample_map=True), dict(v_transposed=True), dict(forced=True), dict(n_sample=min(24, L))):
         _gqa_case("f32", B, nH, nG, L, dh, Uo, mask, seed=L + dh, **kw)
+
+
+# Against 64 bits, where the oracle's own sums in 32 bits would hide the difference.  A sum of n terms in a row is off by a random
+# walk of n roundings, and so by about a factor of sqrt(n) more than one: eight sums of 32 to 38 keys next to each other measure
+# 1.2e-7 of the context vector (as do the separate launches), one of 256 keys 3.0e-7; the bound lies between them.  With the
+# exponentials on top the active rows measure 2.4e-7 and 3.6e-7.
+@pytest.mark.parametrize("dh,L", [(16, 256), (16, 300), (8, 256), (32, 200)])
+def test_fp32_sums_against_64_bits(dh, L):
+    B, H, U = 64, 2, 30
+    _say(f"fp32 sums L={L} dh={dh}")
+    Q, K, V = (torch.randn((B, H, L, dh), generator=torch.Generator(device="cuda").manual_seed(s), device="cuda") for s in (1, 2, 3))
+    desc = sf.make_desc(B, L, 64, H, H, dh, 64, dtype=sf.SF_F32, U_override=U)
+    O, sel, _ = sf.sparse_gqa_forward(desc, Q, K, V, torch.arange(H, dtype=torch.int32, device="cuda").reshape(1, H))
+    q, k, v, sel = Q.cpu().double(), K.cpu().double(), V.cpu().double(), sel.cpu().long()
+    rows = torch.softmax((q @ k.transpose(2, 3)) * dh ** -0.5, 3) @ v
+    o = O.cpu().double().view(B, L, H, dh).transpose(1, 2)
+    active = torch.zeros((B, H, L), dtype=torch.bool).scatter_(2, sel, True)
+    ctx = v.mean(2, keepdim=True).expand(B, H, L, dh)
+    err = [((o - ref)[m].norm() / ref[m].norm()).item() for ref, m in ((ctx, ~active), (rows, active))]
+    assert err[0] <= 2e-7 and err[1] <= 3e-7, err
