@@ -60,8 +60,9 @@ __device__ __forceinline__ float rows_sum(float x)
 }
 
 // NW waves; a wave scores QBS blocks of 32 queries at a time; at most EPT queries per thread in the selection.  SAMPLED: the
-// score looks at the allowed keys of a sample only, listed in ascending order.
-template <int DH, int NW, int QBS, int EPT, bool SAMPLED>
+// score looks at the allowed keys of a sample only, listed in ascending order.  OWN: waves with one tile of keys have their own
+// reference of the exponentials.
+template <int DH, int NW, int QBS, int EPT, bool SAMPLED, bool OWN>
 __global__ __launch_bounds__(NW * 64, 4) void attend_short_bf16_kernel(ShortArgs a)
 {
     constexpr int NT = NW * 64, CH = DH / 8, RP = NT / CH, UN = 8, KF = DH / 16, DB = DH / 32;
@@ -316,9 +317,11 @@ __global__ __launch_bounds__(NW * 64, 4) void attend_short_bf16_kernel(ShortArgs
             qa[kk] = h16x8{};
             if (slot < k) qa[kk] = *at(Qb, (uint32_t)rows[slot] * (uint32_t)a.sq.l + (uint32_t)(kk * 16 + lhi * 8));
         }
-        // the largest product of the row is the reference of its exponentials; of a key sample it is a first guess, which moves
-        // when a product exceeds it by 2^RESCALE_LOG2 (results are relative to it and do not depend on it)
-        top = slot < k ? qmax[rows[slot]] * sc : 0.f;
+        // The reference of the exponentials: the largest product of the row; of the wave's tile where it has one only (OWN); of the
+        // tiles so far, with a slack, where only a key sample was scored.  The results are relative to it, but the rounding to 16
+        // bits is least next to it: the row's for waves of one tile is 4 to 8 % more error, the first tile's for waves of several 5 %.
+        const bool single = OWN && ty >= nt;
+        if (!SAMPLED) top = slot < k ? qmax[rows[slot]] * sc : 0.f;
         auto process = [&](VTile &x, int t) {
             f32x16 s;
 #pragma unroll
@@ -347,12 +350,14 @@ __global__ __launch_bounds__(NW * 64, 4) void attend_short_bf16_kernel(ShortArgs
                         for (int i = 0; i < 8; ++i)
                             if (!((wl >> (p * 16 + i)) & 1u)) x.v[d][p][i] = (h16)0.f;
             }
-            if constexpr (SAMPLED) {
+            if (SAMPLED || single) {
                 float mt = fmaxf(s[0], s[1]);
 #pragma unroll
                 for (int e = 2; e < 16; e += 2) mt = fmaxf(fmaxf(mt, s[e]), s[e + 1]);
                 mt = both_halves_max(mt) * sc;                            // sc > 0: max and scaling commute
-                if (__builtin_amdgcn_ballot_w64(mt > top + RESCALE_LOG2) != 0ull) {
+                if (!SAMPLED) {
+                    top = mt;
+                } else if (__builtin_amdgcn_ballot_w64(mt > top + RESCALE_LOG2) != 0ull) {
                     const float to = fmaxf(top, mt), alpha = __builtin_amdgcn_exp2f(top - (to == -INFINITY ? 0.f : to));
                     top = to;
                     l_run *= alpha;
@@ -397,7 +402,7 @@ __global__ __launch_bounds__(NW * 64, 4) void attend_short_bf16_kernel(ShortArgs
         const float l_tot = both_halves_sum(l_run);
         if (lhi == 0) {
             ml[wave * 32 + l32] = l_tot;
-            if constexpr (SAMPLED) refs[wave * 32 + l32] = top;
+            if constexpr (SAMPLED || OWN) refs[wave * 32 + l32] = top;
         }
 #pragma unroll
         for (int d = 0; d < DB; ++d)
@@ -415,19 +420,19 @@ __global__ __launch_bounds__(NW * 64, 4) void attend_short_bf16_kernel(ShortArgs
     for (int x = tid; x < (k + 1) * CH; x += NT) {
         const int s = x / CH, d8 = (x % CH) * 8, w0 = (s >> 5) * spb, q = s & 31;
         float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, den = 0.f, ref = -INFINITY;
-        if constexpr (SAMPLED) {
+        if constexpr (SAMPLED || OWN) {
             for (int w = w0; w < w0 + spb; ++w) ref = fmaxf(ref, refs[w * 32 + q]);
             if (ref == -INFINITY) ref = 0.f;
         }
 #pragma unroll 4
         for (int w = w0; w < w0 + spb; ++w) {
-            const float wgt = SAMPLED ? __builtin_amdgcn_exp2f(refs[w * 32 + q] - ref) : 1.0f;
-            den += SAMPLED ? wgt * ml[w * 32 + q] : ml[w * 32 + q];
+            const float wgt = SAMPLED || OWN ? __builtin_amdgcn_exp2f(refs[w * 32 + q] - ref) : 1.0f;
+            den += wgt * ml[w * 32 + q];
             const f32x4 v0 = *part(w, q, d8 / 4), v1 = *part(w, q, d8 / 4 + 1);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                acc[e] += SAMPLED ? wgt * v0[e] : v0[e];
-                acc[4 + e] += SAMPLED ? wgt * v1[e] : v1[e];
+                acc[e] += wgt * v0[e];
+                acc[4 + e] += wgt * v1[e];
             }
         }
         const float norm = den > 0.f ? 1.0f / den : 0.f;
@@ -448,10 +453,10 @@ __global__ __launch_bounds__(NW * 64, 4) void attend_short_bf16_kernel(ShortArgs
     }
 }
 
-template <int DH, int NW, int QBS, int EPT, bool SAMPLED>
+template <int DH, int NW, int QBS, int EPT, bool SAMPLED, bool OWN = false>
 int32_t launch_short(const ShortArgs &s, hipStream_t st)
 {
-    auto kern = attend_short_bf16_kernel<DH, NW, QBS, EPT, SAMPLED>;
+    auto kern = attend_short_bf16_kernel<DH, NW, QBS, EPT, SAMPLED, OWN>;
     static std::atomic<bool> attr_set{false};     // setting the attribute twice is harmless
     if (!attr_set) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, SHORT_LDS) != hipSuccess)
@@ -486,6 +491,11 @@ size_t short_lds(const AttnArgs &a, int nw)
 template <int DH, int NW, bool SAMPLED>
 int32_t launch_waves(const ShortArgs &s, hipStream_t st)
 {
+    int slots = 1;                                                        // as in the kernel, for U active rows
+    while (slots < (s.U + 32) / 32) slots *= 2;
+    if constexpr (!SAMPLED)
+        if (ceil_div(s.L, 32) < 2 * (NW / slots))                         // some wave has one tile: fewer than 64 NW queries
+            return s.L <= NW * 32 ? launch_short<DH, NW, 1, 1, false, true>(s, st) : launch_short<DH, NW, 2, 1, false, true>(s, st);
     if (s.L <= NW * 32) return launch_short<DH, NW, 1, 1, SAMPLED>(s, st);
     return s.L <= NW * 64 ? launch_short<DH, NW, 2, 1, SAMPLED>(s, st) : launch_short<DH, NW, 2, 4, SAMPLED>(s, st);
 }

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_2604_08971_amd import binding as sf
-from test_gpu_parity import _gqa_case, _say
+from test_gpu_parity import SF_DTYPE, _gqa_case, _say, _separate_launches
 
 pytestmark = pytest.mark.gpu
 
@@ -101,3 +101,26 @@ def test_fp32_sums_against_64_bits(dh, L):
     ctx = v.mean(2, keepdim=True).expand(B, H, L, dh)
     err = [((o - ref)[m].norm() / ref[m].norm()).item() for ref, m in ((ctx, ~active), (rows, active))]
     assert err[0] <= 2e-7 and err[1] <= 3e-7, err
+
+
+# The active rows against 64 bits: the one launch rounds the same exponentials to 16 bits as the separate ones, relative to another
+# reference at most, so it is as far off as they are.  128 heads of about 30 rows are a quarter of a million values, and the ratio
+# of two such errors scatters by 1 % (0.98 to 1.012 over 80 shapes); a reference per row for waves of one tile measures 1.04 to 1.09.
+@pytest.mark.parametrize("dtype,L,dh", [("bf16", 64, 64), ("bf16", 128, 32), ("bf16", 200, 64), ("bf16", 256, 32), ("f16", 200, 32), ("bf16", 500, 64)])
+def test_active_rows_against_64_bits(dtype, L, dh):
+    B, H = 32, 4
+    _say(f"active rows against 64 bits {dtype} L={L} dh={dh}")
+    with sf.use_half(dtype):
+        td = torch.float16 if dtype == "f16" else torch.bfloat16
+        Q, K, V = (torch.randn((B, H, L, dh), generator=torch.Generator(device="cuda").manual_seed(s), device="cuda").to(td) for s in (4, 5, 6))
+        desc, hg = sf.make_desc(B, L, 64, H, H, dh, 64, dtype=SF_DTYPE[dtype]), torch.arange(H, dtype=torch.int32, device="cuda").reshape(1, H)
+        assert _one_launch(B, H, H, L, dh, -1, dtype)
+        calls = sf.sparse_gqa_forward(desc, Q, K, V, hg), _separate_launches(desc, Q, K, V, hg, None, None, False, None)
+    q, k, v = (x.cpu().double() for x in (Q, K, V))
+    rows = torch.softmax((q @ k.transpose(2, 3)) * dh ** -0.5, 3) @ v
+    err = []
+    for O, sel, _ in calls:
+        active = torch.zeros((B, H, L), dtype=torch.bool).scatter_(2, sel.cpu().long(), True)
+        o = O.cpu().double().reshape(B, L, H, dh).transpose(1, 2)
+        err.append(((o - rows)[active].norm() / rows[active].norm()).item())
+    assert err[0] <= 1.03 * err[1], err
