@@ -508,14 +508,15 @@ int32_t launch_dim(const ShortArgs &s, int nw, hipStream_t st)
 
 }  // namespace
 
-// By length, heads and active rows, over 1516 calls drawn at random (1 to 512 samples of 130 to 2000 keys, 1 to 12 heads of dh 32
-// or 64, 20 to 511 active rows, half of them masked): the 1359 that are taken cost 0.74 of the separate launches, five of them
+// By length, heads and active rows, over 1706 calls drawn at random (1 to 512 samples of 130 to 2000 keys, 1 to 12 heads of dh 32
+// or 64, 20 to 511 active rows, half of them masked): the 1512 that are taken cost 0.75 of the separate launches, five of them
 // more than 1.05 and none more than 1.10.
 // What the separate launches do better:
 //   - few heads: they spread a head over the chip, while one workgroup's chain is as long as its score (tiles of keys x blocks of
 //     queries) and its active rows (tiles x blocks, eight times as long a step, since each wave brings V for itself).  us, separate /
 //     this: 6 heads of 1000 keys, dh 32, 256 active rows 35 / 41; 4 of 700, dh 64, 200 of them 31 / 40; 8 of 1024, dh 64, 380 of
-//     them 44 / 75; 8 of 512, dh 64, 200 of them 26 / 30; but 4 of 600, dh 64, 127 of them 29 / 28.  Beyond 1024 keys, 14 heads of
+//     them 44 / 75; 8 of 512, dh 64, 200 of them 26 / 30; but 4 of 600, dh 64, 127 of them 29 / 28, 64 of
+//     1000, dh 64, 35 of them 44 / 37.  Beyond 1024 keys, 14 heads of
 //     1564 37 / 43;
 //   - several rounds of heads with a compute unit to themselves (sixteen waves), and rows enough for the staged kernel, in which the
 //     heads of a group share K and V: 3072 heads of 600 keys, dh 64, 256 active rows 410 / 481; 1560 of 700, 160 of them 236 /
@@ -529,7 +530,7 @@ bool attend_short(const AttnArgs &a)
     if (a.L > 1024 && heads < 64) return false;
     const int nw = short_waves(a), nt = ceil_div(a.L, 32), nb = (a.U + 32) / 32;      // nb: with the context vector
     if (heads <= (a.dh == 32 ? 48 : 64)) {
-        if (nt * (nt + 8 * nb) > (a.dh == 32 ? 1540 : 1020)) return false;
+        if (nt * (nt + 8 * nb) > (a.dh == 32 ? 1540 : heads <= 32 ? 1120 : heads <= 48 ? 1500 : 2000)) return false;
     } else if (nw == 16 && (a.dh == 32 ? nb > 5 && a.L > 1500 : heads > 512 && (nb > 8 || heads > 800))) {
         return false;
     }

@@ -284,7 +284,7 @@ def test_active_pass_kernel_follows_length_and_pairs():
         assert plan(2, 4, 2, 700, dh, 0) == dict(staged=0, splits=1, score_parts=1, stat_parts=6 if dh == 128 else 1)
     # the whole call in one launch (no score stream of its own): short sequences, but neither few heads whose score or active
     # rows are a long chain nor, with a compute unit per head, many heads of many active rows
-    for B, nH, L, dh, U, one in ((1, 6, 512, 64, 35, True), (8, 1, 480, 64, 127, True), (4, 1, 600, 64, 127, True), (16, 6, 1000, 64, 380, True),
+    for B, nH, L, dh, U, one in ((1, 6, 512, 64, 35, True), (8, 1, 480, 64, 127, True), (4, 1, 600, 64, 127, True), (8, 8, 1000, 64, 35, True), (16, 6, 1000, 64, 380, True),
                                  (256, 2, 800, 64, 255, True), (64, 4, 1300, 32, 300, True), (6, 1, 1024, 32, 64, False),
                                  (8, 1, 512, 64, 200, False), (4, 1, 700, 64, 200, False), (8, 1, 1024, 64, 255, False), (64, 1, 1024, 64, 127, False), (1, 2, 900, 64, 511, False),
                                  (6, 2, 900, 32, 200, False), (130, 12, 700, 64, 160, False), (256, 12, 600, 64, 96, False), (256, 8, 700, 64, 511, False), (33, 8, 2000, 32, 255, False)):
