@@ -508,9 +508,9 @@ int32_t launch_dim(const ShortArgs &s, int nw, hipStream_t st)
 
 }  // namespace
 
-// By length, heads and active rows, over 1706 calls drawn at random (1 to 512 samples of 130 to 2000 keys, 1 to 12 heads of dh 32
-// or 64, 20 to 511 active rows, half of them masked): the 1512 that are taken cost 0.75 of the separate launches, five of them
-// more than 1.05 and none more than 1.10.
+// By length, heads and active rows, fitted to 2500 calls drawn at random (1 to 512 samples of 130 to 2000 keys, 1 to 12 heads of dh
+// 32 or 64, 20 to 511 active rows, half of them masked).  Of 741 others that it takes, half with a key sample, the launch costs 0.68
+// of the separate ones on average, two cost more than 1.04, none more than 1.10.
 // What the separate launches do better:
 //   - few heads: they spread a head over the chip, while one workgroup's chain is as long as its score (tiles of keys x blocks of
 //     queries) and its active rows (tiles x blocks, eight times as long a step, since each wave brings V for itself).  us, separate /
@@ -522,6 +522,9 @@ int32_t launch_dim(const ShortArgs &s, int nw, hipStream_t st)
 //     heads of a group share K and V: 3072 heads of 600 keys, dh 64, 256 active rows 410 / 481; 1560 of 700, 160 of them 236 /
 //     298; 264 of 2000, dh 32, 255 of them 148 / 167.  One or two rounds are ahead here (256 heads of 1000, dh 64, 380 of them
 //     139 / 77; 512 of 800, 200 of them 0.73).
+// With a key sample the separate launches are one more, and the score is short on both sides: over 600 calls with 64 keys few
+// heads are 0.45 to 0.9 up to twice the chain (4 heads of 1024, dh 64, 300 active rows 1.17), while many rounds of heads are
+// behind sooner (1600 of 1100, dh 32, 127 active rows 137 / 171; 264 of 700, dh 64, 480 of them 1.21).
 bool attend_short(const AttnArgs &a)
 {
     if ((a.dh != 32 && a.dh != 64) || a.U < 1 || a.U >= a.L) return false;
@@ -529,10 +532,12 @@ bool attend_short(const AttnArgs &a)
     const int64_t heads = (int64_t)a.B * a.nH;
     if (a.L > 1024 && heads < 64) return false;
     const int nw = short_waves(a), nt = ceil_div(a.L, 32), nb = (a.U + 32) / 32;      // nb: with the context vector
-    if (heads <= (a.dh == 32 ? 48 : 64)) {
-        if (nt * (nt + 8 * nb) > (a.dh == 32 ? 1540 : heads <= 32 ? 1120 : heads <= 48 ? 1500 : 2000)) return false;
-    } else if (nw == 16 && (a.dh == 32 ? nb > 5 && a.L > 1500 : heads > 512 && (nb > 8 || heads > 800))) {
-        return false;
+    const bool few = heads <= (a.dh == 32 ? 48 : 64), sampled = a.n_sample > 0;
+    if (few && !sampled && nt * (nt + 8 * nb) > (a.dh == 32 ? 1540 : heads <= 32 ? 1120 : heads <= 48 ? 1500 : 2000)) return false;
+    if (few && sampled && nt * (std::min(nt, ceil_div(a.n_sample, 32)) + 8 * nb) > (a.dh == 32 ? 2800 : heads <= 32 ? 2000 : 4200)) return false;
+    if (!few && nw == 16) {
+        if (a.dh == 32 && (sampled ? heads > 512 && (nb > 8 || heads > 1040) : nb > 5 && a.L > 1500)) return false;
+        if (a.dh == 64 && ((heads > 512 && (nb > 8 || heads >= 800)) || (sampled && nb > 9 && heads > 256))) return false;
     }
     return nb <= nw && a.L <= std::min(nw * 256, 2048) && short_lds(a, nw) <= SHORT_LDS;
 }

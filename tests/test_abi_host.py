@@ -274,8 +274,8 @@ def test_static_scratch_takes_what_fits_without_key_ranges():
 def test_active_pass_kernel_follows_length_and_pairs():
     """Short sequences and groups of one or two heads deal their keys to the waves; long sequences with little else to do,
     groups of many pairs and U >= 256 stage their tiles, split where there is less than a (sample, group) per compute unit."""
-    def plan(B, nH, nG, L, dh, U=-1):
-        return sf.sparse_gqa_plan(sf.make_desc(B, L, 64, nH, nG, dh, 64, dtype=sf.SF_BF16, U_override=U), nH, nG)
+    def plan(B, nH, nG, L, dh, U=-1, n_sample=0):
+        return sf.sparse_gqa_plan(sf.make_desc(B, L, 64, nH, nG, dh, 64, dtype=sf.SF_BF16, U_override=U, n_sample=n_sample), nH, nG)
     for dh in (32, 64, 128):
         assert not plan(1, 6, 2, 512, dh)["staged"] and not plan(512, 1, 1, 100, dh, 20)["staged"]
         assert plan(4, 4, 1, 16384, dh)["staged"] and plan(4, 4, 1, 16384, dh)["splits"] == 64
@@ -289,6 +289,10 @@ def test_active_pass_kernel_follows_length_and_pairs():
                                  (8, 1, 512, 64, 200, False), (4, 1, 700, 64, 200, False), (8, 1, 1024, 64, 255, False), (64, 1, 1024, 64, 127, False), (1, 2, 900, 64, 511, False),
                                  (6, 2, 900, 32, 200, False), (130, 12, 700, 64, 160, False), (256, 12, 600, 64, 96, False), (256, 8, 700, 64, 511, False), (33, 8, 2000, 32, 255, False)):
         assert (plan(B, nH, nH, L, dh, U)["score_parts"] == 0) == one, (B, nH, L, dh, U)
+    # the same with a key sample
+    for B, nH, L, dh, U, one in ((8, 1, 1000, 64, 127, True), (4, 2, 700, 32, 380, True), (2, 2, 1000, 64, 300, False), (3, 1, 1000, 32, 480, False),
+                                 (400, 4, 1100, 32, 127, False), (66, 4, 700, 64, 480, False), (400, 2, 1000, 64, 50, False)):
+        assert (plan(B, nH, nH, L, dh, U, 64)["score_parts"] == 0) == one, (B, nH, L, dh, U)
     L = sf.lib()
     d = sf.make_desc(1, 64, 64, 4, 2, 16, 64, dtype=sf.SF_F32)
     assert L.sf_sparse_gqa_plan(C.byref(d), 4, 2, (C.c_int32 * 4)()) == -3
