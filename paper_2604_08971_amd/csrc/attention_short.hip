@@ -317,11 +317,13 @@ __global__ __launch_bounds__(NW * 64, 4) void attend_short_bf16_kernel(ShortArgs
             qa[kk] = h16x8{};
             if (slot < k) qa[kk] = *at(Qb, (uint32_t)rows[slot] * (uint32_t)a.sq.l + (uint32_t)(kk * 16 + lhi * 8));
         }
-        // The reference of the exponentials: the largest product of the row; of the wave's tile where it has one only (OWN); of the
-        // tiles so far, with a slack, where only a key sample was scored.  The results are relative to it, but the rounding to 16
-        // bits is least next to it: the row's for waves of one tile is 4 to 8 % more error, the first tile's for waves of several 5 %.
+        // The reference of the exponentials: the largest product of the row, or of the wave's tile where it has one only (OWN).  Of a
+        // key sample the former is a first guess: the wave's first tile may raise it, the others do when a product exceeds it by
+        // 2^RESCALE_LOG2.  The results are relative to it, but the rounding to 16 bits is least next to it: the row's for waves of
+        // one tile is 4 to 8 % more error, the first tile's for waves of several 5 %.
         const bool single = OWN && ty >= nt;
-        if (!SAMPLED) top = slot < k ? qmax[rows[slot]] * sc : 0.f;
+        top = slot < k ? qmax[rows[slot]] * sc : 0.f;
+        float slack = 0.f;
         auto process = [&](VTile &x, int t) {
             f32x16 s;
 #pragma unroll
@@ -355,9 +357,9 @@ __global__ __launch_bounds__(NW * 64, 4) void attend_short_bf16_kernel(ShortArgs
 #pragma unroll
                 for (int e = 2; e < 16; e += 2) mt = fmaxf(fmaxf(mt, s[e]), s[e + 1]);
                 mt = both_halves_max(mt) * sc;                            // sc > 0: max and scaling commute
-                if (!SAMPLED) {
+                if (single) {
                     top = mt;
-                } else if (__builtin_amdgcn_ballot_w64(mt > top + RESCALE_LOG2) != 0ull) {
+                } else if (__builtin_amdgcn_ballot_w64(mt > top + slack) != 0ull) {
                     const float to = fmaxf(top, mt), alpha = __builtin_amdgcn_exp2f(top - (to == -INFINITY ? 0.f : to));
                     top = to;
                     l_run *= alpha;
@@ -366,6 +368,7 @@ __global__ __launch_bounds__(NW * 64, 4) void attend_short_bf16_kernel(ShortArgs
 #pragma unroll
                         for (int e = 0; e < 16; ++e) o[d][e] *= alpha;
                 }
+                slack = RESCALE_LOG2;
             }
             const float nm = top == -INFINITY ? 0.f : -top;
             float rs0 = 0.f, rs1 = 0.f;
@@ -493,9 +496,8 @@ int32_t launch_waves(const ShortArgs &s, hipStream_t st)
 {
     int slots = 1;                                                        // as in the kernel, for U active rows
     while (slots < (s.U + 32) / 32) slots *= 2;
-    if constexpr (!SAMPLED)
-        if (ceil_div(s.L, 32) < 2 * (NW / slots))                         // some wave has one tile: fewer than 64 NW queries
-            return s.L <= NW * 32 ? launch_short<DH, NW, 1, 1, false, true>(s, st) : launch_short<DH, NW, 2, 1, false, true>(s, st);
+    if (ceil_div(s.L, 32) < 2 * (NW / slots))                             // some wave has one tile: fewer than 64 NW queries
+        return s.L <= NW * 32 ? launch_short<DH, NW, 1, 1, SAMPLED, true>(s, st) : launch_short<DH, NW, 2, 1, SAMPLED, true>(s, st);
     if (s.L <= NW * 32) return launch_short<DH, NW, 1, 1, SAMPLED>(s, st);
     return s.L <= NW * 64 ? launch_short<DH, NW, 2, 1, SAMPLED>(s, st) : launch_short<DH, NW, 2, 4, SAMPLED>(s, st);
 }
