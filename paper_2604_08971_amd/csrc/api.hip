@@ -114,11 +114,32 @@ static void normalised(int dtype, GemmArgs &g, bool x_f32, const void *x, const 
     else layernorm(dtype, x_f32, x, gamma, beta, eps, (int64_t)g.B * g.L, g.K, xn, st);
 }
 
+// The product of g is a row of the residual stream, whose LayerNorm goes to y next: written with it where the product owns whole
+// rows, else `done` stays false.  without_stream: nobody else reads the stream, so that it need not be written then.
+struct NormOut { const void *gamma, *beta; void *y; bool without_stream; bool done; };
+static GemmArgs with_norm(GemmArgs g, float eps, const NormOut &n)
+{
+    g.lno_g = n.gamma; g.lno_b = n.beta; g.lno_eps = eps; g.lno_y = n.y;
+    if (n.without_stream) g.C = nullptr;
+    return g;
+}
+static int32_t gemm_then_norm(int dtype, GemmArgs &g, float eps, NormOut *n, hipStream_t st)
+{
+    if (n && n->y) {
+        const GemmArgs t = with_norm(g, eps, *n);
+        if (gemm_takes_ln_out(dtype, t)) {
+            n->done = true;
+            return gemm(dtype, t, st);
+        }
+    }
+    return gemm(dtype, g, st);
+}
+
 // x_f32 / y_f32: X / Y hold fp32 although the model dtype is bf16 (the
 // encoder's residual stream).  With x_f32, pre_ln is required (the GEMM reads bf16).
 static int32_t ffn_forward(const Dims &D, const sf_compact_layer &ly, const void *X, bool x_f32,
                            const int32_t *pattern_id, bool pre_ln, bool add_residual, void *Y, bool y_f32,
-                           void *xn, void *hid, hipStream_t st, bool xn_ready = false)
+                           void *xn, void *hid, hipStream_t st, bool xn_ready = false, NormOut *next = nullptr)
 {
     const int Fp = (int)align_up(ly.k_ffn, D.ffn_pad);
     GemmArgs g{};
@@ -128,7 +149,6 @@ static int32_t ffn_forward(const Dims &D, const sf_compact_layer &ly, const void
     g.C = hid; g.ldc = Fp;
     // xn_ready: LN2(X) is already there (written together with X)
     if (pre_ln && !xn_ready) normalised(D.dtype, g, x_f32, X, ly.ln2_g, ly.ln2_b, D.eps, xn, st);
-    if (int32_t rc = gemm(D.dtype, g, st)) return rc;
 
     GemmArgs h{};
     h.A = hid; h.lda = Fp; h.W = ly.W2T; h.ldw = Fp; h.w_pstride = (int64_t)D.d * Fp;
@@ -136,7 +156,13 @@ static int32_t ffn_forward(const Dims &D, const sf_compact_layer &ly, const void
     h.B = D.B; h.L = D.L; h.N = D.d; h.K = Fp; h.epi = EPI_ROWMAJOR; h.act = ACT_NONE;
     h.R = add_residual ? X : nullptr; h.ldr = D.d; h.r_f32 = x_f32;
     h.C = Y; h.ldc = D.d; h.c_f32 = y_f32;
-    return gemm(D.dtype, h, st);
+    const GemmArgs one = next && next->y ? with_norm(h, D.eps, *next) : h;
+    if (ffn_in_one(D.dtype, g, one)) {
+        if (next) next->done = next->y != nullptr;
+        return ffn_one_launch(g, one, st);
+    }
+    if (int32_t rc = gemm(D.dtype, g, st)) return rc;
+    return gemm_then_norm(D.dtype, h, D.eps, next, st);
 }
 
 // ---- encoder ----------------------------------------------------------------------
@@ -403,6 +429,7 @@ static int32_t encoder_forward_impl(const sf_desc *desc, const sf_compact_layer 
     const void *in = X;
     bool in_f32 = !bf;
     const bool final_ln = (D.flags & SF_FLAG_FINAL_LN) != 0;
+    bool xn_ready = false, y_ready = false;      // LN1 of this layer, the final LayerNorm: written together with the stream
     for (int l = 0; l < D.nl; ++l) {
         const sf_compact_layer &ly = layers[l];
         const int kh = ly.k_head, dh = D.dh, Hk = D.Hk;
@@ -428,7 +455,9 @@ static int32_t encoder_forward_impl(const sf_desc *desc, const sf_compact_layer 
             g.bias = ly.bqkv; g.bias_pstride = Nqkv; g.pattern_id = gpat;
             g.B = Dg.B; g.L = Dg.L; g.K = D.d; g.act = ACT_NONE; g.epi = EPI_ROWMAJOR;
             g.C = w.qkv; g.ldc = ldq; g.n0 = 0; g.N = bf && !pk ? Nqk : Nqkv;
-            if (!bf || pk) normalised(D.dtype, g, in_f32, in, ly.ln1_g, ly.ln1_b, D.eps, w.xn, st);
+            if (xn_ready) {
+                // w.xn holds it
+            } else if (!bf || pk) normalised(D.dtype, g, in_f32, in, ly.ln1_g, ly.ln1_b, D.eps, w.xn, st);
             if (bf && pk) {
                 // Q, K, V token-major in one launch; V^T per sample (what the attention kernels read) by a pass of
                 // its own, since a 256-row block of packed rows may straddle samples
@@ -440,10 +469,10 @@ static int32_t encoder_forward_impl(const sf_desc *desc, const sf_compact_layer 
                 GemmArgs q3 = g;
                 q3.N = Nqkv; q3.VT = w.vt; q3.vt_from = Nqk; q3.vt_b = (int64_t)Hk * dh * w.Lp; q3.vt_n = w.Lp;
                 if (gemm_takes_vt_split(D.dtype, q3)) {
-                    normalised(D.dtype, q3, in_f32, in, ly.ln1_g, ly.ln1_b, D.eps, w.xn, st);
+                    if (!xn_ready) normalised(D.dtype, q3, in_f32, in, ly.ln1_g, ly.ln1_b, D.eps, w.xn, st);
                     if (int32_t rc = gemm(D.dtype, q3, st)) return rc;
                 } else {
-                    layernorm(D.dtype, in_f32, in, ly.ln1_g, ly.ln1_b, D.eps, rows, D.d, w.xn, st);
+                    if (!xn_ready) layernorm(D.dtype, in_f32, in, ly.ln1_g, ly.ln1_b, D.eps, rows, D.d, w.xn, st);
                     if (int32_t rc = gemm(D.dtype, g, st)) return rc;
                     g.n0 = Nqk; g.N = Hk * dh; g.epi = EPI_VT; g.C = w.vt;
                     g.vt_b = q3.vt_b; g.vt_n = q3.vt_n;
@@ -453,6 +482,19 @@ static int32_t encoder_forward_impl(const sf_desc *desc, const sf_compact_layer 
                 if (int32_t rc = gemm(D.dtype, g, st)) return rc;
             }
         }
+
+        // What reads the layer's output next: LN1 of the following layer (its Q/K/V in 16 bits) or the final LayerNorm
+        NormOut next{};
+        if (l + 1 < D.nl) {
+            if (!proj8) next = NormOut{layers[l + 1].ln1_g, layers[l + 1].ln1_b, w.xn, false, false};
+        } else if (final_ln) {
+            next = NormOut{final_g, final_b, Y, true, false};
+        }
+        auto after_layer = [&]() {
+            in = w.x2;
+            in_f32 = true;
+            (l + 1 < D.nl ? xn_ready : y_ready) = next.done;
+        };
 
         // SentryAttend over the kept heads
         AttnArgs a = enc_attn_args(D, kh);
@@ -531,15 +573,15 @@ static int32_t encoder_forward_impl(const sf_desc *desc, const sf_compact_layer 
                 lazy_combine_ln(in, in_f32, w.lz_pos, w.lz_C, ly.bo, w.lz_c, D.B, D.L, capA, ly.ln2_g, ly.ln2_b, D.eps,
                                 D.d, static_cast<float *>(w.x1), w.xn, 0.f, st);
                 if (int32_t rc = ffn_forward(D, ly, w.x1, true, pattern_id, true, true, to_y ? Y : w.x2, !to_y, w.xn,
-                                             w.hid, st, true))
+                                             w.hid, st, true, &next))
                     return rc;
             }
-            in = w.x2;
-            in_f32 = true;
+            after_layer();
             continue;
         }
 
-        // x1 = x + att Wo' + bo   (only the kept heads' rows of Wo exist)
+        // x1 = x + att Wo' + bo   (only the kept heads' rows of Wo exist), with LN2(x1) for an FFN in 16 bits where that is possible
+        NormOut ln2{};
         if (proj8) {
             const sf_proj_fp8 &pj = proj8[l];
             const int Kh = kh * dh;
@@ -559,7 +601,8 @@ static int32_t encoder_forward_impl(const sf_desc *desc, const sf_compact_layer 
             o.w_pstride = (int64_t)D.d * kh * dh; o.bias = ly.bo; o.bias_pstride = 0; o.pattern_id = gpat;
             o.B = Dg.B; o.L = Dg.L; o.N = D.d; o.K = kh * dh; o.epi = EPI_ROWMAJOR; o.act = ACT_NONE;
             o.R = in; o.ldr = D.d; o.r_f32 = in_f32; o.C = w.x1; o.ldc = D.d; o.c_f32 = 1;
-            if (int32_t rc = gemm(D.dtype, o, st)) return rc;
+            if (!ffn8) ln2 = NormOut{ly.ln2_g, ly.ln2_b, w.xn, false, false};
+            if (int32_t rc = gemm_then_norm(D.dtype, o, D.eps, &ln2, st)) return rc;
         }
 
         // x2 = x1 + FFN(LN2(x1)); the last layer without a final LN writes Y directly
@@ -573,12 +616,11 @@ static int32_t encoder_forward_impl(const sf_desc *desc, const sf_compact_layer 
                                              xq, hq, st))
                 return rc;
         } else if (int32_t rc = ffn_forward(Dg, ly, w.x1, true, gpat, true, true, to_y ? Y : w.x2, !to_y, w.xn,
-                                            w.hid, st))
+                                            w.hid, st, ln2.done, &next))
             return rc;
-        in = w.x2;
-        in_f32 = true;
+        after_layer();
     }
-    if (final_ln) layernorm(D.dtype, 1, w.x2, final_g, final_b, D.eps, rows, D.d, Y, st);
+    if (final_ln && !y_ready) layernorm(D.dtype, 1, w.x2, final_g, final_b, D.eps, rows, D.d, Y, st);
     return check_launch("encoder_forward");
 }
 

@@ -39,6 +39,8 @@ struct GemmArgs {
     int c_f8; float c_scale;                             // f8: C receives E4M3 codes of act(value) * c_scale (ldc in bytes)
     const void *ln_g, *ln_b; float ln_eps; int ln_x32;   // bf16 GEMM only, ln_g != NULL (gemm_takes_ln): A holds rows x (fp32 when
                                                          // ln_x32) and the operand is LayerNorm(x) rounded to 16 bits
+    const void *lno_g, *lno_b; float lno_eps; void *lno_y;  // bf16 GEMM only, lno_y != NULL (gemm_takes_ln_out): lno_y [B*L, N] receives
+                                                         // LayerNorm of the finished output rows, rounded to 16 bits; C may then be NULL
     void *VT; int vt_from;                               // bf16 row-major problems only (gemm_takes_vt_split):
                                                          // features n >= vt_from go to VT[b, n - vt_from, i] (strides
                                                          // vt_b, vt_n, both % 8 == 0; vt_from % 8 == 0) instead of C
@@ -93,6 +95,17 @@ bool gemm_takes_vt_split(int dtype, const GemmArgs &a);
 // True when gemm() takes the LayerNorm of its operand along (a.ln_g) and that is the faster way, else the caller runs layernorm().
 bool gemm_takes_ln(int dtype, const GemmArgs &a);
 bool gemm_bf16_tile_takes_ln(const GemmArgs &a);
+
+// True when gemm() writes the LayerNorm of its output rows (a.lno_y) and that is the faster way (gemm_bf16_rows.hip).
+bool gemm_takes_ln_out(int dtype, const GemmArgs &a);
+bool gemm_bf16_rows_eligible(const GemmArgs &a);
+int32_t gemm_bf16_rows(const GemmArgs &a, hipStream_t st);
+
+// The two products of an FFN (down.A is not read): in one launch where that is possible and the faster way.
+bool ffn_in_one(int dtype, const GemmArgs &up, const GemmArgs &down);
+int32_t ffn_one_launch(const GemmArgs &up, const GemmArgs &down, hipStream_t st);
+bool ffn_bf16_rows_eligible(const GemmArgs &up, const GemmArgs &down);
+int32_t ffn_bf16_rows(const GemmArgs &up, const GemmArgs &down, hipStream_t st);
 
 // LayerNorm over rows of d elements (biased variance).  gamma/beta are in the
 // model dtype; x is fp32 when x_f32 (or dtype is SF_F32), y is in the model dtype.

@@ -276,6 +276,50 @@ bool gemm_takes_ln(int dtype, const GemmArgs &a0)
     return gemm_bf16_tile_eligible(a) && gemm_bf16_tile_takes_ln(a);
 }
 
+// Row tiles of gemm_bf16_rows.hip: 64 rows and two workgroups per compute unit up to N 256, 128 rows and one beyond, where a last
+// round that is not full costs nearly a whole one.
+static int64_t row_tiles(const GemmArgs &a) { return a.B * (int64_t)ceil_div(a.L, a.N <= 256 ? 64 : 128); }
+static bool rounds_filled(int64_t tiles, double share) { return tiles >= share * 256 * ((tiles + 255) / 256); }
+
+// The product with the LayerNorm of its rows against the two launches, us: 12 288 rows, N 128, K 64 6.2 / 12.1; 24 576 rows in samples of 384,
+// N 256, K 192 17.3 / 22; 65 536 rows, N 512, K 384 86 / 111; 122 880 in samples of 480, K 256 138 / 193.  Beyond N 256 by how full
+// the rounds are: 1.7 of them 0.86 of the two launches, 1.46 1.00, 1.1 1.09.  Below 32 tiles the LayerNorm rides along with the
+// product that follows, which costs less than this kernel's epilogue.
+bool gemm_takes_ln_out(int dtype, const GemmArgs &a0)
+{
+    GemmArgs a = a0;
+    if (dtype != SF_BF16 || !gemm_bf16_rows_eligible(a)) return false;
+    join_samples(a);
+    return a.N <= 256 ? row_tiles(a) >= 32 : rounds_filled(row_tiles(a), 0.77);
+}
+
+// Both products see the samples joined where the up-projection does
+static void join_ffn(GemmArgs &up, GemmArgs &down)
+{
+    join_samples(up);
+    down.B = up.B;
+    down.L = up.L;
+}
+
+// The FFN in one launch against two (and a LayerNorm of its rows), us: 24 576 rows in samples of 384, d 256, 640 channels 34 / 37 (37 / 47);
+// 65 536 rows, d 256, 640 channels 72 / 90 (78 / 115); 65 536 rows, d 512, 1280 channels 196 / 208 (208 / 238); 122 880 in
+// samples of 480, 1024 channels 317 / 345 (338 / 408).  d 256 from half a round on (0.4 of one 1.05, 0.2 1.24).
+bool ffn_in_one(int dtype, const GemmArgs &up0, const GemmArgs &down0)
+{
+    GemmArgs up = up0, down = down0;
+    if (dtype != SF_BF16 || !ffn_bf16_rows_eligible(up, down)) return false;
+    join_ffn(up, down);
+    const int64_t tiles = row_tiles(down);
+    return down.N == 128 ? tiles >= 32 : down.N == 256 ? tiles >= 128 : rounds_filled(tiles, down.lno_y ? 0.8 : 0.93);
+}
+
+int32_t ffn_one_launch(const GemmArgs &up0, const GemmArgs &down0, hipStream_t st)
+{
+    GemmArgs up = up0, down = down0;
+    join_ffn(up, down);
+    return ffn_bf16_rows(up, down, st);
+}
+
 int32_t gemm_bf16(const GemmArgs &a0, hipStream_t st)
 {
     GemmArgs a = a0;
@@ -286,6 +330,11 @@ int32_t gemm_bf16(const GemmArgs &a0, hipStream_t st)
         if (!gemm_takes_ln(SF_BF16, a)) return fail(SF_ERR_UNSUPPORTED, "gemm(bf16): LayerNorm on a problem that does not take it along");
         join_samples(a);
         return gemm_bf16_tile(GEMM_SLICE8, a, st);
+    }
+    if (a.lno_y) {
+        if (!gemm_takes_ln_out(SF_BF16, a)) return fail(SF_ERR_UNSUPPORTED, "gemm(bf16): LayerNorm of the output on a problem that does not write it");
+        join_samples(a);
+        return gemm_bf16_rows(a, st);
     }
     const GemmKind kind = choose(a);
     if (kind == GEMM_WS) return gemm_bf16_ws(a, st);

@@ -1,4 +1,4 @@
-// Addresses of the operand loads of gemm_bf16_tile.hip, apart from the kernels so that a host program can walk them.
+// Addresses of the operand loads of gemm_bf16_tile.hip and gemm_bf16_rows.hip, apart from the kernels so that a host program can walk them.
 #pragma once
 
 #include <cstdint>

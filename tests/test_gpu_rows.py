@@ -1,0 +1,58 @@
+"""The kernels whose tile owns whole rows (gemm_bf16_rows.hip): the FFN in one launch and the output projection with its LayerNorm, at the
+edges of their tiles and chunks, against the oracle."""
+from __future__ import annotations
+
+import pytest
+import torch
+
+from paper_2604_08971_amd import binding as sf
+from paper_2604_08971_amd import workloads as W
+from gpu_utils import DeviceModel
+from helpers import make_wl
+from test_gpu_parity import _encoder_parity, _ffn_case, _say
+
+pytestmark = pytest.mark.gpu
+
+
+def _gemm_launches(run):
+    torch.cuda.synchronize()
+    sf.profile_begin(sf.SF_KERNEL_GEMM, 64)
+    run()
+    torch.cuda.synchronize()
+    return sf.profile_end()[0]
+
+
+# Each width; one row past a tile and one short of it; hidden channels of one and a half chunks (192 of 128, 384 of 256), of one tile
+# of 64, and of a chunk and a tile; the last is one round short of full and keeps two launches
+@pytest.mark.parametrize("dtype,act,B,L,d,F,keep,launches", [
+    ("bf16", 0, 33, 65, 128, 200, 0.7, 1), ("f16", 1, 130, 63, 256, 300, 1.0, 1), ("bf16", 1, 120, 129, 384, 328, 1.0, 1),
+    ("f16", 0, 60, 385, 512, 64, 1.0, 1), ("bf16", 0, 80, 383, 512, 576, 0.55, 1), ("bf16", 0, 75, 383, 512, 576, 0.55, 2),
+])
+def test_ffn_in_one_launch(monkeypatch, dtype, act, B, L, d, F, keep, launches):
+    _say(f"ffn of whole rows {dtype} act={act} B={B} L={L} d={d} F={F}")
+    run, counts = sf.pruned_ffn_forward, []
+
+    def counted(*a):
+        out = []
+        counts.append(_gemm_launches(lambda: out.append(run(*a))))
+        return out[0]
+
+    monkeypatch.setattr(sf, "pruned_ffn_forward", counted)
+    with sf.use_half(dtype):
+        _ffn_case(dtype, act, B, L, d, F, keep)          # three weight sets, with and without LayerNorm and residual
+    assert counts == [launches] * 2
+
+
+# Two layers and a final LayerNorm: LN2 written by the output projection, the next layer's LN1 and the final one by the FFN (three launches
+# a layer); missing sensors, ragged tiles, no bias to spare
+@pytest.mark.parametrize("dtype,B,seg,d,Hq,Hk,dh,F", [("bf16", 20, (70, 50, 90), 128, 4, 2, 32, 256), ("f16", 65, (70, 60), 256, 4, 2, 64, 384),
+                                                      ("bf16", 103, (70, 50, 90), 384, 6, 2, 64, 512), ("bf16", 103, (99, 80, 61), 512, 8, 2, 64, 640)])
+def test_encoder_writes_its_layernorms_along(dtype, B, seg, d, Hq, Hk, dh, F):
+    _say(f"layernorm written along {dtype} B={B} d={d}")
+    spec = W.small_spec(dtype=dtype, B=B, seg=seg, d=d, Hq=Hq, Hk=Hk, dh=dh, F=F, head_keep=0.5 if d < 384 else 0.67, nl=2, c=5)
+    with sf.use_half(dtype):
+        wl = make_wl(spec)
+        dm = DeviceModel(wl).build_plan()
+        dm.forward()
+        assert _gemm_launches(lambda: dm.forward()) == 6
+        _encoder_parity(wl, samples=[0, B // 2, B - 1])
