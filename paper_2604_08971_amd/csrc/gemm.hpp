@@ -37,13 +37,13 @@ struct GemmArgs {
                                                          // elements = bytes), K % 128 == 0
     float out_scale;                                     // f8: factor of the sum of code products (the two tensor scales)
     int c_f8; float c_scale;                             // f8: C receives E4M3 codes of act(value) * c_scale (ldc in bytes)
-    const void *ln_g, *ln_b; float ln_eps; int ln_x32;   // bf16 GEMM only, ln_g != NULL (gemm_takes_ln): A holds rows x (fp32 when
-                                                         // ln_x32) and the operand is LayerNorm(x) rounded to 16 bits
-    const void *lno_g, *lno_b; float lno_eps; void *lno_y;  // bf16 GEMM only, lno_y != NULL (gemm_takes_ln_out): lno_y [B*L, N] receives
-                                                         // LayerNorm of the finished output rows, rounded to 16 bits; C may then be NULL
+    const void *ln_g, *ln_b; float ln_eps; int ln_x32;   // ln_g != NULL (gemm_takes_ln): A holds rows x (16-bit models: fp32 when
+                                                         // ln_x32) and the operand is LayerNorm(x), rounded to 16 bits in those
     void *VT; int vt_from;                               // bf16 row-major problems only (gemm_takes_vt_split):
                                                          // features n >= vt_from go to VT[b, n - vt_from, i] (strides
                                                          // vt_b, vt_n, both % 8 == 0; vt_from % 8 == 0) instead of C
+    const void *lno_g, *lno_b; float lno_eps; void *lno_y;  // bf16 GEMM only, lno_y != NULL (gemm_takes_ln_out): lno_y [B*L, N] receives
+                                                         // LayerNorm of the finished output rows, rounded to 16 bits; C may then be NULL
 };
 
 // dtype SF_BF16: bf16 MFMA, fp32 accumulate (K % 8 == 0, lda/ldw/ldr % 8 == 0,
@@ -95,6 +95,7 @@ bool gemm_takes_vt_split(int dtype, const GemmArgs &a);
 // True when gemm() takes the LayerNorm of its operand along (a.ln_g) and that is the faster way, else the caller runs layernorm().
 bool gemm_takes_ln(int dtype, const GemmArgs &a);
 bool gemm_bf16_tile_takes_ln(const GemmArgs &a);
+bool gemm_f32_takes_ln(const GemmArgs &a);
 
 // True when gemm() writes the LayerNorm of its output rows (a.lno_y) and that is the faster way (gemm_bf16_rows.hip).
 bool gemm_takes_ln_out(int dtype, const GemmArgs &a);

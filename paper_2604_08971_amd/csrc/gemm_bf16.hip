@@ -271,6 +271,7 @@ static GemmKind choose(GemmArgs &a)
 bool gemm_takes_ln(int dtype, const GemmArgs &a0)
 {
     GemmArgs a = a0;
+    if (dtype == SF_F32) return gemm_f32_takes_ln(a);
     if (dtype != SF_BF16 || a.epi != EPI_ROWMAJOR || (a.VT && !gemm_takes_vt_split(dtype, a))) return false;
     join_samples(a);
     return gemm_bf16_tile_eligible(a) && gemm_bf16_tile_takes_ln(a);

@@ -17,12 +17,29 @@ __device__ __forceinline__ float act_f32(float z, int act)
     return z;
 }
 
-// 256 threads; thread (tx,ty) of a 16x16 grid owns a 2x2 patch of the 32x32 tile.  Small problems are a chain of memory
-// round trips, one per K step: a step is 64 of K, all 16 loads of a thread are in flight before the first is used, and
-// those of the next step are issued before this one's products.  2 samples of 48 rows, N 64 to 128, K 32 to 128: 7.0-8.4 us with steps of 16, 6.1-7.2 us now.
+// Sum over the eight lanes 8 i .. 8 i + 7, in each of them
+__device__ __forceinline__ float sum8(float x)
+{
+    x += __shfl_xor(x, 1);
+    x += __shfl_xor(x, 2);
+    return x + __shfl_xor(x, 4);
+}
+
+constexpr int FLN = 256;    // longest row whose LayerNorm the product takes along
+
+// 256 threads; thread (tx,ty) of a 16x16 grid owns rows ty, ty + 16 and columns tx, tx + 16 of the 32x32 tile: any 16 lanes then read
+// 16 different 16-byte slots of LDS (rows of 272 bytes).  Small problems are a chain of memory round trips, one per K step: a step
+// is 64 of K, all 16 loads of a thread are in flight before the first is used, and those of the next step are issued before this one's
+// products.  Four values of K per LDS read; every sum runs over K in order.  2 samples of 48 rows, N 64 to 128, K 32 to 128: 6.1-7.2 us
+// with single values, 4.6-7.0 now (the small encoder of those 43.9 -> 38.9 us with the LayerNorms along).
+// LN: the rows of A come unnormalised.  Eight threads hold a row (K <= FLN) and take mean and deviations as layernorm_vec_kernel
+// does, from loads that are in flight with the first step's; every column of tiles does so again, which costs less than the
+// launch it replaces (3.2 us) while there are few of them.
+template <bool LN>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a)
 {
-    __shared__ float Xs[FT][FK + 1], Ws[FT][FK + 1];
+    __shared__ __attribute__((aligned(16))) float Xs[FT][FK + 4], Ws[FT][FK + 4];
+    __shared__ float mean[FT], inv[FT];
     const int tiles_m = (a.L + FT - 1) / FT;
     const int b = blockIdx.x / tiles_m;
     const int m0 = (blockIdx.x % tiles_m) * FT;
@@ -38,53 +55,103 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a)
     float acc[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
 
     constexpr int NL = FT * FK / 256;
-    float xv[NL], wv[NL];
+    float xv[NL], wv[NL], gk = 1.f, bk = 0.f;                      // column k0 + threadIdx.x % FK is the same in all NL loads
     auto fetch = [&](int k0) {
+        const int k = k0 + threadIdx.x % FK;
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
-            const int e = threadIdx.x + u * 256, r = e / FK, k = k0 + e % FK;
-            const int i = m0 + r, n = nt0 + r;
+            const int r = (threadIdx.x + u * 256) / FK, i = m0 + r, n = nt0 + r;
             xv[u] = (i < a.L && k < a.K) ? A[(int64_t)i * a.lda + k] : 0.f;
             wv[u] = (n < a.N && k < a.K) ? W[(int64_t)n * a.ldw + k] : 0.f;
         }
+        if (LN && k < a.K) {
+            gk = static_cast<const float *>(a.ln_g)[k];
+            bk = static_cast<const float *>(a.ln_b)[k];
+        }
     };
     fetch(0);
+    // what the epilogue adds is on its way with the first step: read at the end it is a memory round trip of its own
+    const float *bias = a.bias ? static_cast<const float *>(a.bias) + (int64_t)p * a.bias_pstride + a.n0 : nullptr;
+    const float *R = static_cast<const float *>(a.R);
+    float bv[2], rv[2][2];
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+        const int n = nt0 + tx + v * 16;
+        bv[v] = bias && n < a.N ? bias[n] : 0.f;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int i = m0 + ty + u * 16;
+            rv[u][v] = R && i < a.L && n < a.N ? R[((int64_t)b * a.L + i) * a.ldr + a.r0 + n] : 0.f;
+        }
+    }
+    if constexpr (LN) {
+        const int r = threadIdx.x / 8, c = threadIdx.x % 8;
+        const float *x = A + (int64_t)min(m0 + r, a.L - 1) * a.lda;
+        float v[FLN / 8], s = 0.f, q = 0.f;
+#pragma unroll
+        for (int i = 0; i < FLN / 8; ++i) v[i] = i * 8 + c < a.K ? x[i * 8 + c] : 0.f;
+#pragma unroll
+        for (int i = 0; i < FLN / 8; ++i) s += v[i];
+        const float m = sum8(s) / a.K;
+#pragma unroll
+        for (int i = 0; i < FLN / 8; ++i) {
+            const float t = i * 8 + c < a.K ? v[i] - m : 0.f;
+            q += t * t;
+        }
+        q = sum8(q);
+        if (c == 0) {
+            mean[r] = m;
+            inv[r] = 1.0f / sqrtf(q / a.K + a.ln_eps);
+        }
+        __syncthreads();
+    }
     for (int k0 = 0; k0 < a.K; k0 += FK) {
+        const int k = threadIdx.x % FK;
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
-            const int e = threadIdx.x + u * 256;
-            Xs[e / FK][e % FK] = xv[u];
-            Ws[e / FK][e % FK] = wv[u];
+            const int r = (threadIdx.x + u * 256) / FK;
+            Xs[r][k] = LN ? (xv[u] - mean[r]) * inv[r] * gk + bk : xv[u];
+            Ws[r][k] = wv[u];
         }
         __syncthreads();
         if (k0 + FK < a.K) fetch(k0 + FK);
         for (int kq = 0; kq < min(FK, a.K - k0); kq += 16)       // K of 16 or 40 has no use for the rest of the step
 #pragma unroll
-            for (int k = kq; k < kq + 16; ++k) {
+            for (int kk = kq; kk < kq + 16; kk += 4) {
+                f32x4 x[2], w[2];
 #pragma unroll
-                for (int u = 0; u < 2; ++u)
+                for (int u = 0; u < 2; ++u) {
+                    x[u] = *reinterpret_cast<const f32x4 *>(&Xs[ty + u * 16][kk]);
+                    w[u] = *reinterpret_cast<const f32x4 *>(&Ws[tx + u * 16][kk]);
+                }
 #pragma unroll
-                    for (int v = 0; v < 2; ++v)
-                        acc[u][v] = fmaf(Xs[ty * 2 + u][k], Ws[tx * 2 + v][k], acc[u][v]);
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+#pragma unroll
+                        for (int v = 0; v < 2; ++v) acc[u][v] = fmaf(x[u][e], w[v][e], acc[u][v]);
             }
         __syncthreads();
     }
-    const float *bias = a.bias ? static_cast<const float *>(a.bias) + (int64_t)p * a.bias_pstride + a.n0 : nullptr;
-    const float *R = static_cast<const float *>(a.R);
     float *C = static_cast<float *>(a.C);
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
         for (int v = 0; v < 2; ++v) {
-            const int i = m0 + ty * 2 + u, n = nt0 + tx * 2 + v;
+            const int i = m0 + ty + u * 16, n = nt0 + tx + v * 16;
             if (i >= a.L || n >= a.N) continue;
             const int64_t row = (int64_t)b * a.L + i;
-            float z = acc[u][v] + (bias ? bias[n] : 0.f);
-            z = act_f32(z, a.act);
-            if (R) z += R[row * a.ldr + a.r0 + n];
+            float z = act_f32(acc[u][v] + bv[v], a.act);
+            if (R) z += rv[u][v];
             if (a.epi == EPI_VT) C[(int64_t)b * a.vt_b + (int64_t)n * a.vt_n + i] = z;
             else C[row * a.ldc + a.c0 + n] = z;
         }
+}
+
+// Few columns of tiles only: each forms the statistics of its rows again
+bool gemm_f32_takes_ln(const GemmArgs &a)
+{
+    return a.K <= FLN && !a.k_lim && !a.n_lim && (int64_t)a.B * ceil_div(a.L, FT) * ceil_div(a.N, FT) <= 1024;
 }
 
 int32_t gemm(int dtype, const GemmArgs &a, hipStream_t st)
@@ -93,7 +160,12 @@ int32_t gemm(int dtype, const GemmArgs &a, hipStream_t st)
     if (a.row_map || a.VT) return fail(SF_ERR_UNSUPPORTED, "gemm(f32): row_map / transposed column range are not supported");
     if (a.B <= 0 || a.N <= 0) return SF_OK;
     dim3 grid(ceil_div(a.L, FT) * a.B, ceil_div(a.N, FT));
-    hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, st, a);
+    if (a.ln_g) {
+        if (!gemm_f32_takes_ln(a)) return fail(SF_ERR_UNSUPPORTED, "gemm(f32): LayerNorm on a problem that does not take it along");
+        hipLaunchKernelGGL(gemm_f32_kernel<true>, grid, dim3(256), 0, st, a);
+    } else {
+        hipLaunchKernelGGL(gemm_f32_kernel<false>, grid, dim3(256), 0, st, a);
+    }
     return SF_OK;
 }
 

@@ -109,3 +109,24 @@ def test_ffn_with_layernorm_along(dtype, B, L, d, F):
         ref = sf.pruned_ffn_forward(dm.desc, lay, xn, dm.pattern_id, False, False)
         torch.cuda.synchronize()
         assert err_metric(to_host(got), to_host(ref)) <= (2.0 ** -6 if dtype == "bf16" else 2.0 ** -9)
+
+
+# The same in fp32 (rows of at most 256, at most 1024 tiles of 32 x 32): one row, one past a tile, one and several K steps, a last step
+# that is not full; the longest row that takes it, the first that does not, and a launch with too many tiles.  Rows far from zero:
+# their mean of 50 is exact to 50 * 2^-24, and so is every normalised value to about that; eight of those bound what the two
+# products, whose weights have unit norm, make of it next to their own rounding.
+@pytest.mark.parametrize("B,L,d,F", [(1, 1, 8, 16), (2, 33, 64, 128), (1, 65, 200, 72), (3, 31, 256, 64), (2, 40, 264, 64), (40, 130, 64, 200)])
+def test_f32_ffn_with_layernorm_along(B, L, d, F):
+    _say(f"layernorm along f32 B={B} L={L} d={d} F={F}")
+    wl = make_wl(W.small_spec(dtype="f32", B=B, seg=(max(1, L - 1),), extra=int(L > 1), d=d, Hq=2, Hk=1, dh=8, F=F, nl=1, ffn_keep=1.0,
+                              dropout="none", final_ln=False))
+    dm = DeviceModel(wl).build_plan()
+    lay = dm.layers[0]
+    g = torch.Generator(device="cuda").manual_seed(L)
+    x = torch.randn((B * L, d), generator=g, device="cuda") + torch.randn((B * L, 1), generator=g, device="cuda").sign() * 50
+    got = sf.pruned_ffn_forward(dm.desc, lay, x, dm.pattern_id, True, False)
+    w = {n: lay.dense[n].double() for n in ("ln2_g", "ln2_b", "W1", "b1", "W2", "b2")}
+    xn = torch.nn.functional.layer_norm(x.double(), (d,), w["ln2_g"], w["ln2_b"], 1e-5)
+    ref = torch.relu(xn @ w["W1"].T + w["b1"]) @ w["W2"] + w["b2"]
+    torch.cuda.synchronize()
+    assert err_metric(to_host(got), ref.cpu().numpy()) <= 8 * 50 * 2.0 ** -24
