@@ -284,14 +284,16 @@ static bool rounds_filled(int64_t tiles, double share) { return tiles >= share *
 
 // The product with the LayerNorm of its rows against the two launches, us: 12 288 rows, N 128, K 64 6.2 / 12.1; 24 576 rows in samples of 384,
 // N 256, K 192 17.3 / 22; 65 536 rows, N 512, K 384 86 / 111; 122 880 in samples of 480, K 256 138 / 193.  Beyond N 256 by how full
-// the rounds are: 1.7 of them 0.86 of the two launches, 1.46 1.00, 1.1 1.09.  Below 32 tiles the LayerNorm rides along with the
-// product that follows, which costs less than this kernel's epilogue.
+// the rounds are: 1.7 of them 0.86 of the two launches, 1.46 1.00, 1.1 1.09.  Up to N 256 a few tiles take a few steps only, since a
+// tile walks K alone (41 tiles, N 256: K 128 0.81; 34 samples of 53 rows, four layers: 205 us with K 640 so, 192 without), and
+// below 32 tiles the LayerNorm rides along with the product that follows, which costs less than this kernel's epilogue.
 bool gemm_takes_ln_out(int dtype, const GemmArgs &a0)
 {
     GemmArgs a = a0;
     if (dtype != SF_BF16 || !gemm_bf16_rows_eligible(a)) return false;
     join_samples(a);
-    return a.N <= 256 ? row_tiles(a) >= 32 : rounds_filled(row_tiles(a), 0.77);
+    const int64_t tiles = row_tiles(a);
+    return a.N <= 256 ? tiles >= 32 && a.K <= (a.N == 128 ? 4 : 2) * tiles + 64 : rounds_filled(tiles, 0.77);
 }
 
 // Both products see the samples joined where the up-projection does
