@@ -209,6 +209,7 @@ struct Fill {
     T *O; int64_t ldo;
     const float *stats; const int32_t *head_group; int hg_stride; const int32_t *pattern_id; int nG, dh;
     const int32_t *row0, *ext;
+    const float *part; int parts;      // or NULL: the context vector is the sum of `parts` pieces [B*nG, parts, dh] over the allowed keys
 };
 
 // The thread's share of the context vector (VEC consecutive elements), read ahead of the selection, and the rows it writes:
@@ -226,11 +227,24 @@ struct HeadFill {
         step = NT / qv;
         if (!f.O || (int)threadIdx.x >= step * qv) return;
         rows = f.ext ? f.ext[b] : L;
-        const int g = f.head_group[(int64_t)(f.pattern_id ? f.pattern_id[b] : 0) * f.hg_stride + h];
-        const float *ctx = f.stats + (((int64_t)b * f.nG + g) * 2 + 1) * f.dh + c * VEC;
+        if (!f.part) {
+            const float *ctx = f.stats + (((int64_t)b * f.nG + group(f, b, h)) * 2 + 1) * f.dh + c * VEC;
 #pragma unroll
-        for (int t = 0; t < VEC; ++t) v[t] = from_f32<T>(ctx[t]);
+            for (int t = 0; t < VEC; ++t) v[t] = from_f32<T>(ctx[t]);
+        }
         o = f.O + sample_row(f.row0, b, L) * f.ldo + (int64_t)h * f.dh + c * VEC;
+    }
+    static __device__ __forceinline__ int group(const Fill<T> &f, int b, int h)
+    {
+        return f.head_group[(int64_t)(f.pattern_id ? f.pattern_id[b] : 0) * f.hg_stride + h];
+    }
+    // the context vector from its sum over n allowed keys (dh values in LDS)
+    __device__ __forceinline__ void mean_of(const Fill<T> &f, const float *sum, int n)
+    {
+        const float inv = n > 0 ? 1.0f / (float)n : 0.f;
+        const int c = threadIdx.x % (f.dh / VEC);
+#pragma unroll
+        for (int t = 0; t < VEC; ++t) v[t] = from_f32<T>(sum[c * VEC + t] * inv);
     }
     __device__ __forceinline__ void put(const Fill<T> &f, int r) const { *reinterpret_cast<vec *>(o + (int64_t)r * f.ldo) = v; }
     __device__ __forceinline__ void write(const Fill<T> &f, int L, const uint32_t *kept) const
@@ -274,7 +288,15 @@ __global__ __launch_bounds__(NT) void select_kernel(
     const int64_t m0 = ((int64_t)b * sc.H + h) * L;
     int32_t *sl = slot ? slot + (int64_t)bh * L : nullptr;      // only the active-row projection reads it
     int32_t *se = sel + ((int64_t)b * selH + h) * U;
-    const HeadFill<NT, VEC, T> hf(fill, b, h, L);
+    HeadFill<NT, VEC, T> hf(fill, b, h, L);
+    __shared__ float ctx[256];
+    if (fill.part && threadIdx.x < fill.dh) {                   // with a key mask only: its count orders these writes
+        const float *p = fill.part + ((int64_t)b * fill.nG + HeadFill<NT, VEC, T>::group(fill, b, h)) * fill.parts * fill.dh + threadIdx.x;
+        float s = 0.f;
+#pragma unroll 8
+        for (int i = 0; i < fill.parts; ++i) s += p[(int64_t)i * fill.dh];
+        ctx[threadIdx.x] = s;
+    }
     const bool no_key = sc.n > 1 && sc.n_keys[b] == 0;
     int c = 0;
     for (int i = threadIdx.x; i < L; i += NT) {
@@ -296,6 +318,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
         c += ok;
     }
     const int n_ok = kv ? block_sum<NT>(c, red) : L;
+    if (fill.part) hf.mean_of(fill, ctx, n_ok);
     // u_active: this sample's own number of active queries (samples of different length in one batch)
     const int k = min(u_active ? min(max(u_active[b], 0), U) : U, n_ok);
     if (k == 0) {
@@ -690,14 +713,23 @@ int32_t attention_forward(int dtype, const AttnArgs &a, hipStream_t st)
     const void *Vuse = a.V;
     sf_strides svu = a.sv;
     int vT = a.v_transposed;
+    // Every allowed query active: no score asks for the mean key, and the context vector of the masked rows is summed from what the
+    // transposition of V leaves per 64 tokens (in the place of the score) by the blocks that write those rows.
+    VSums sums{};
+    if (a.U >= a.L && a.key_valid && !a.forced_sel && !a.act_bits && !a.skip_fill &&
+        (int64_t)BG * ceil_div(pl.Lp, 64) * a.dh <= (int64_t)BH * a.L)
+        sums = VSums{a.key_valid, a.nG, a.dh, pl.score};
+    bool summed = false;
     if (dtype == SF_BF16 && !a.v_transposed) {
         // whole chunks of 16 bytes where V is packed head by head or token by token (8 samples of 1777 keys, 4 groups of dh 64:
         // 9.2 us, 6.7 so), else element by element
         const bool whole = (uintptr_t)a.V % 16 == 0 && !a.row0;
         if (whole && a.sv.h == a.L * a.sv.l && a.sv.b == a.nG * a.sv.h) {
-            transpose_v(a.V, a.sv.l, 0, a.dh, BG, a.L, pl.Lp, pl.vt, st);
+            transpose_v(a.V, a.sv.l, 0, a.dh, BG, a.L, pl.Lp, pl.vt, st, nullptr, sums);
+            summed = sums.part != nullptr;
         } else if (whole && a.sv.h == a.dh && a.sv.b == a.L * a.sv.l) {
-            transpose_v(a.V, a.sv.l, 0, a.nG * a.dh, a.B, a.L, pl.Lp, pl.vt, st);
+            transpose_v(a.V, a.sv.l, 0, a.nG * a.dh, a.B, a.L, pl.Lp, pl.vt, st, nullptr, sums);
+            summed = sums.part != nullptr;
         } else {
             dim3 grid(ceil_div(pl.Lp, 32), ceil_div(a.dh, 32), BG);
             hipLaunchKernelGGL(transpose_v_kernel, grid, dim3(256), 0, st, (const uint16_t *)a.V, a.sv, a.nG,
@@ -726,7 +758,7 @@ int32_t attention_forward(int dtype, const AttnArgs &a, hipStream_t st)
     // 1. statistics: mean key (for the score's mean term) and context vector; nobody asks for them where every row is active
     // and the choice is not the caller's
     const bool all_active = a.U >= a.L && !a.key_valid && !a.forced_sel && !a.act_bits && !a.skip_fill && !a.row0;
-    if (!all_active) {
+    if (!all_active && !summed) {
         const StatsOut so{pl.stats, pl.n_valid, a.act_bits};
         if (dtype == SF_BF16) {
             const int parts = pl.stat_parts;
@@ -770,6 +802,7 @@ int32_t attention_forward(int dtype, const AttnArgs &a, hipStream_t st)
         Fill<std::remove_pointer_t<decltype(O)>> f{};
         f.O = a.skip_fill || beside == spread ? nullptr : O; f.ldo = a.ldo; f.stats = pl.stats; f.head_group = a.head_group; f.hg_stride = a.hg_stride;
         f.pattern_id = a.pattern_id; f.nG = a.nG; f.dh = a.dh; f.row0 = a.row0; f.ext = a.ext;
+        if (summed) { f.part = pl.score; f.parts = ceil_div(pl.Lp, 64); }
         return f;
     };
     const Fill<h16> fill16 = fill_args((h16 *)a.O, true);

@@ -74,8 +74,10 @@ int32_t proj_fp8_check(const char *who, const Dims &D, const sf_proj_fp8 *p, int
 // bf16 buffer into the key-contiguous layout the attention kernels read.
 // codes[r, 0:K] = E4M3(x[r, 0:K] * inv_scale), codes[r, K:Kp] = 0 (x bf16 with row stride ld; K, Kp, ld % 8 == 0)
 void quantize_rows_fp8(const void *x, int64_t ld, int64_t rows, int K, int Kp, float inv_scale, uint8_t *codes, hipStream_t st);
+// sums.part [groups, ceil(Lp/64), dh] (samples b-strided, ncols = groups of a row * dh): also the sums of each 64 tokens' allowed rows.
+struct VSums { const uint8_t *key_valid; int nG, dh; float *part; };
 void transpose_v(const void *src, int64_t ld, int col0, int ncols, int B, int L, int Lp, void *vt, hipStream_t st,
-                 const int32_t *row0 = nullptr);
+                 const int32_t *row0 = nullptr, VSums sums = VSums{});
 
 // The bf16 GEMM kernels: 256 x 256 tiles (gemm_bf16_ws.hip), 128 x 128 tiles and K slices (gemm_bf16_tile.hip), and the one
 // for sizes and alignments that those refuse (gemm_bf16.hip).  Numbered in sentryfuse.h (sf_gemm_kernel).

@@ -170,6 +170,17 @@ def test_every_row_active(dtype, B, nH, nG, L, dh, mask):
             _gqa_case(dtype, B, nH, nG, L, dh, L, mask, seed=L, **kw)
 
 
+# Masked rows of a call whose every allowed row is active: their context vector is summed from what the transposition of V leaves per
+# 64 keys; a tile short of and past full, one key, several groups in a row of V, the widest head
+@pytest.mark.parametrize("dtype,B,nH,nG,L,dh", [("bf16", 3, 2, 1, 63, 64), ("f16", 5, 3, 3, 64, 32), ("bf16", 5, 6, 3, 65, 32), ("bf16", 2, 4, 4, 129, 64),
+                                                ("f16", 2, 4, 2, 191, 128), ("bf16", 9, 8, 2, 1100, 64)])
+def test_context_where_every_allowed_row_is_active(dtype, B, nH, nG, L, dh):
+    _say(f"context of masked rows {dtype} B={B} nH={nH} nG={nG} L={L} dh={dh}")
+    with sf.use_half(dtype):
+        for kw in (dict(), dict(strided=True)):
+            _gqa_case(dtype, B, nH, nG, L, dh, L, True, seed=L, **kw)
+
+
 def test_value_on_an_odd_element():
     B, nH, L, dh = 2, 2, 300, 64
     rng = np.random.default_rng(4)
