@@ -104,6 +104,27 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// x of lane ^ O summed with the lane's own: between halves and rows of 16 by a swap, inside a row as a rotation or a permutation of four
+// lanes (vector instructions; through LDS an exchange takes over 100 clocks, and a row's mean and deviations are twelve in a chain).
+// O 4 only where lanes ^ 8 hold the same.
+template <int O>
+__device__ __forceinline__ float pair_sum(float x)
+{
+    if constexpr (O == 32 || O == 16) {
+        const auto r = O == 32 ? __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false)
+                               : __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    } else {
+        constexpr int ctrl = O == 8 ? 0x128 : O == 4 ? 0x124 : O == 2 ? 0x4e : 0xb1;      // row_ror:8, row_ror:4, quad_perm
+        return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), ctrl, 0xf, 0xf, false));
+    }
+}
+// Sum over the lanes of a wave, in each of them
+__device__ __forceinline__ float wave_sum(float x)
+{
+    return pair_sum<1>(pair_sum<2>(pair_sum<4>(pair_sum<8>(pair_sum<16>(pair_sum<32>(x))))));
+}
+
 // Order-preserving map of fp32 to uint32 (larger float <=> larger key).
 __device__ __forceinline__ uint32_t sortable_key(float f)
 {

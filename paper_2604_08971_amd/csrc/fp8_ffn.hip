@@ -74,8 +74,7 @@ __global__ __launch_bounds__(256) void layernorm_q8_kernel(const TI *__restrict_
             for (int e = 0; e < 8; ++e) v[c][e] = 0.f;
         }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    s = wave_sum(s);
     const float mean = s / d;
     float q = 0.f;
 #pragma unroll
@@ -84,8 +83,7 @@ __global__ __launch_bounds__(256) void layernorm_q8_kernel(const TI *__restrict_
 #pragma unroll
             for (int e = 0; e < 8; ++e) { const float t = v[c][e] - mean; q += t * t; }
         }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o);
+    q = wave_sum(q);
     const float inv = 1.0f / sqrtf(q / d + eps);
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {

@@ -184,13 +184,11 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const TI *x, const TP *_
     TO *yr = y + row * d;
     float s = 0.f;
     for (int k = lane; k < d; k += 64) s += to_f32(xr[k]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    s = wave_sum(s);
     const float mean = s / d;
     float v = 0.f;
     for (int k = lane; k < d; k += 64) { const float c = to_f32(xr[k]) - mean; v += c * c; }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    v = wave_sum(v);
     const float inv = 1.0f / sqrtf(v / d + eps);
     for (int k = lane; k < d; k += 64) {
         float z = (to_f32(xr[k]) - mean) * inv;
@@ -255,8 +253,7 @@ __global__ __launch_bounds__(256) void layernorm_vec_kernel(const TI *x, const T
             for (int e = 0; e < 8; ++e) v[c][e] = 0.f;
         }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    s = wave_sum(s);
     const float mean = s / d;
     float q = 0.f;
 #pragma unroll
@@ -265,8 +262,7 @@ __global__ __launch_bounds__(256) void layernorm_vec_kernel(const TI *x, const T
 #pragma unroll
             for (int e = 0; e < 8; ++e) { const float t = v[c][e] - mean; q += t * t; }
         }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o);
+    q = wave_sum(q);
     const float inv = 1.0f / sqrtf(q / d + eps);
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {

@@ -127,8 +127,7 @@ __device__ __forceinline__ void ctx_proj_rows(int block, const float *__restrict
 #pragma unroll
         for (int t = 0; t < 8; ++t) acc = fmaf((float)x[t], (float)wv[t], acc);
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+    acc = wave_sum(acc);
     if (lane == 0) cvec[r] = acc + (bo ? (float)bo[n] : 0.f);
 }
 
@@ -189,8 +188,7 @@ __global__ __launch_bounds__(256) void ctx_proj_q8_kernel(const float *__restric
             acc = fmaf(e4m3_value((q1 >> (8 * t)) & 0xFFu), e4m3_value((wv.y >> (8 * t)) & 0xFFu), acc);
         }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+    acc = wave_sum(acc);
     if (lane == 0) cvec[r] = acc * out_scale + (bo ? (float)bo[n] : 0.f);
 }
 
@@ -257,8 +255,7 @@ __global__ __launch_bounds__(256) void combine_ln_kernel(const TI *__restrict__ 
             for (int e = 0; e < 8; ++e) v[c][e] = 0.f;
         }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    s = wave_sum(s);
     const float mean = s / d;
     float q = 0.f;
 #pragma unroll
@@ -267,8 +264,7 @@ __global__ __launch_bounds__(256) void combine_ln_kernel(const TI *__restrict__ 
 #pragma unroll
             for (int e = 0; e < 8; ++e) { const float t = v[c][e] - mean; q += t * t; }
         }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o);
+    q = wave_sum(q);
     const float inv = 1.0f / sqrtf(q / d + eps);
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {

@@ -48,19 +48,34 @@ template <> struct Vec16<h16> {
 // lane per token: Top-k and the softmax over the chosen logits.
 constexpr int TOK_PER_BLOCK = 64;
 
-template <class T, int EB, bool WLDS>
+// What the launch does besides: the LayerNorm of the rows (16-bit, d % 8 == 0, d <= 512 * LN), as layernorm_vec_kernel computes it, for
+// which the rows come unnormalised in `xn` and go to `y` (a row is in the wave's registers anyway; the next one is on its way
+// meanwhile); and the zeros that the sort of the pairs starts from.  What bounds it is memory then.  65 536 tokens of d 768, 8
+// experts: LayerNorm 38 + router 62 + zeros 5 + 5 us as launches of their own, 64 so (87 with the sums over a wave through LDS);
+// blocks of few tokens: 435, d 384, 4 experts, 63.6 / 41.2; 891, d 256, 16 experts 112 / 54, where a wave took sixteen tokens in a row.
+struct RouterAlso {
+    const h16 *ln_g, *ln_b; float eps; h16 *y;
+    int32_t *zero[2]; int n_zero[2];
+    int tokens;                         // per block: up to TOK_PER_BLOCK, a multiple of 4
+};
+
+template <class T, int EB, bool WLDS, int LN>
 __global__ __launch_bounds__(256) void moe_router_kernel(
     const T *__restrict__ xn, const T *__restrict__ Wr, const T *__restrict__ br, int64_t rows, int d, int E,
     int top_k, const int32_t *__restrict__ forced_route, int32_t *__restrict__ route, float *__restrict__ weight,
-    float *__restrict__ logit_out)
+    float *__restrict__ logit_out, RouterAlso also)
 {
     constexpr int VN = Vec16<T>::N;
+    const int tpb = also.tokens;
+#pragma unroll
+    for (int z = 0; z < 2; ++z)
+        for (int i = blockIdx.x * 256 + threadIdx.x; i < also.n_zero[z]; i += gridDim.x * 256) also.zero[z][i] = 0;
     extern __shared__ __attribute__((aligned(16))) char router_lds[];
-    float *lg = reinterpret_cast<float *>(router_lds);      // [TOK_PER_BLOCK][E + 1]
+    float *lg = reinterpret_cast<float *>(router_lds);      // [tokens][E + 1]
     const int lgs = E + 1;
     const T *Wl = Wr;
     if constexpr (WLDS) {
-        char *wbase = router_lds + (((size_t)TOK_PER_BLOCK * lgs * sizeof(float) + 15) & ~(size_t)15);
+        char *wbase = router_lds + (((size_t)tpb * lgs * sizeof(float) + 15) & ~(size_t)15);
         uint4 *dst = reinterpret_cast<uint4 *>(wbase);
         const uint4 *src = reinterpret_cast<const uint4 *>(Wr);
         const int n16 = E * d / VN;
@@ -69,13 +84,74 @@ __global__ __launch_bounds__(256) void moe_router_kernel(
         Wl = reinterpret_cast<const T *>(wbase);
     }
     const int lane = threadIdx.x & 63;
-    for (int tt = threadIdx.x >> 6; tt < TOK_PER_BLOCK; tt += 4) {
-        const int64_t t = (int64_t)blockIdx.x * TOK_PER_BLOCK + tt;
+    constexpr int NCH = LN > 0 ? LN : 1;
+    uint4 next[NCH];
+    h16x8 gm[NCH], bt[NCH];
+    auto fetch = [&](int64_t t) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            next[c] = make_uint4(0, 0, 0, 0);
+            if (t < rows && (lane + c * 64) * 8 < d) next[c] = *reinterpret_cast<const uint4 *>(xn + t * d + (lane + c * 64) * 8);
+        }
+    };
+    if constexpr (LN > 0) {
+        fetch((int64_t)blockIdx.x * tpb + (threadIdx.x >> 6));
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            gm[c] = bt[c] = h16x8{};
+            if ((lane + c * 64) * 8 >= d) continue;
+            gm[c] = *reinterpret_cast<const h16x8 *>(also.ln_g + (lane + c * 64) * 8);
+            bt[c] = *reinterpret_cast<const h16x8 *>(also.ln_b + (lane + c * 64) * 8);
+        }
+    }
+    for (int tt = threadIdx.x >> 6; tt < tpb; tt += 4) {
+        const int64_t t = (int64_t)blockIdx.x * tpb + tt;
         if (t >= rows) break;
         const T *x = xn + t * d;
         float acc[EB];
 #pragma unroll
         for (int e = 0; e < EB; ++e) acc[e] = 0.f;
+        if constexpr (LN > 0) {
+            float v[NCH][8], sum = 0.f, q = 0.f;
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) {
+                const h16x8 r = __builtin_bit_cast(h16x8, next[c]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) { v[c][e] = (float)r[e]; sum += v[c][e]; }
+            }
+            if (tt + 4 < tpb) fetch(t + 4);
+            sum = wave_sum(sum);
+            const float mean = sum / d;
+#pragma unroll
+            for (int c = 0; c < NCH; ++c)
+                if ((lane + c * 64) * 8 < d) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) { const float z = v[c][e] - mean; q += z * z; }
+                }
+            q = wave_sum(q);
+            const float inv = 1.0f / sqrtf(q / d + also.eps);
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) {
+                const int at = (lane + c * 64) * 8;
+                if (at >= d) continue;
+                h16x8 o;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[e] = (h16)((v[c][e] - mean) * inv * (float)gm[c][e] + (float)bt[c][e]);
+                *reinterpret_cast<h16x8 *>(also.y + t * d + at) = o;
+                const uint4 xq = __builtin_bit_cast(uint4, o);
+                const uint32_t xw[4] = {xq.x, xq.y, xq.z, xq.w};
+#pragma unroll
+                for (int e = 0; e < EB; ++e) {
+                    if (e < E) {
+                        const uint4 wq = *reinterpret_cast<const uint4 *>(Wl + e * d + at);
+                        const uint32_t ww[4] = {wq.x, wq.y, wq.z, wq.w};
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            acc[e] = SF_FDOT2(__builtin_bit_cast(h16x2, xw[i]), __builtin_bit_cast(h16x2, ww[i]), acc[e], false);
+                    }
+                }
+            }
+        } else
         for (int c = lane * VN; c < d; c += 64 * VN) {
             if constexpr (VN == 8) {
                 // 16-bit: two products per instruction, fp32 accumulate, no unpacking
@@ -109,22 +185,34 @@ __global__ __launch_bounds__(256) void moe_router_kernel(
         // bit `o` is set keep the upper half) until one is left, which the remaining steps sum up; lane l then
         // holds the logit of expert l >> SH.  EB - 1 + log2(64 / EB) exchanges instead of 6 * EB.
         constexpr int SH = EB == 64 ? 0 : (EB == 16 ? 2 : 3);
-        int n = EB;
+        // The first two exchanges are swaps of halves and of rows of 16: [a, b] and [a', b'] become the pairs that are summed.
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
+        for (int i = 0; i < EB / 2; ++i) {
+            const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[i]), __float_as_uint(acc[i + EB / 2]), false, false);
+            acc[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        }
+#pragma unroll
+        for (int i = 0; i < EB / 4; ++i) {
+            const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[i]), __float_as_uint(acc[i + EB / 4]), false, false);
+            acc[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        }
+        int n = EB / 4;
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) {
             if (n > 1) {
                 n >>= 1;
                 const bool up = (lane & o) != 0;
 #pragma unroll
-                for (int i = 0; i < EB / 2; ++i) {
+                for (int i = 0; i < EB / 8; ++i) {
                     if (i < n) {
                         const float send = up ? acc[i] : acc[i + n];
                         const float keep = up ? acc[i + n] : acc[i];
-                        acc[i] = keep + __shfl_xor(send, o);
+                        acc[i] = keep + (o == 8 ? __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(send), 0x128, 0xf, 0xf, false))
+                                                : __shfl_xor(send, o));
                     }
                 }
             } else {
-                acc[0] += __shfl_xor(acc[0], o);
+                acc[0] = o == 2 ? pair_sum<2>(acc[0]) : o == 1 ? pair_sum<1>(acc[0]) : acc[0] + __shfl_xor(acc[0], o);
             }
         }
         const int e = lane >> SH;
@@ -133,8 +221,8 @@ __global__ __launch_bounds__(256) void moe_router_kernel(
     __syncthreads();
     // Phase 2: lane tt of the first wave owns token tt.  Top-k by repeated scan over the experts not taken yet
     // (ties: lower expert index; a NaN logit ranks below every number), or the caller's experts.
-    if (threadIdx.x >= TOK_PER_BLOCK) return;
-    const int64_t t = (int64_t)blockIdx.x * TOK_PER_BLOCK + threadIdx.x;
+    if (threadIdx.x >= tpb) return;
+    const int64_t t = (int64_t)blockIdx.x * tpb + threadIdx.x;
     if (t >= rows) return;
     const float *my = lg + threadIdx.x * lgs;
     if (logit_out)
@@ -188,12 +276,6 @@ __global__ __launch_bounds__(256) void moe_router_kernel(
             weight[t * top_k + s] = ex[s] / den;
         }
     }
-}
-
-__global__ void moe_zero_kernel(int32_t *p, int n)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
 }
 
 constexpr int MAX_SEG = 4096;           // (pattern, expert) pairs: their counters fit in LDS
@@ -460,44 +542,48 @@ extern "C" int32_t sf_moe_ffn_forward(const sf_desc *desc, const sf_moe_compact 
     const bool bf = D.dtype == SF_BF16;
 
     const void *xin = X;
-    if (pre_ln) {
-        layernorm(D.dtype, 0, X, m->ln_g, m->ln_b, D.eps, rows, D.d, w.xn, st);
-        xin = w.xn;
-    }
-    // router
+    // router, with the LayerNorm where a wave holds a row and the router rows are in LDS
     {
-        dim3 grid((unsigned)((rows + TOK_PER_BLOCK - 1) / TOK_PER_BLOCK));
+        // a wave takes its tokens one after the other: few of them where there are not four blocks per compute unit of many
+        const int tokens = rows <= 256 * TOK_PER_BLOCK ? 16 : TOK_PER_BLOCK;
+        dim3 grid((unsigned)((rows + tokens - 1) / tokens));
         const size_t wbytes = (size_t)E * D.d * es;
         const size_t lgbytes = ((size_t)TOK_PER_BLOCK * (E + 1) * sizeof(float) + 15) & ~(size_t)15;
         const bool wlds = lgbytes + wbytes <= 64 * 1024;
-#define SF_ROUTER(T, EB)                                                                                              \
-    do {                                                                                                              \
-        if (wlds)                                                                                                     \
-            hipLaunchKernelGGL((moe_router_kernel<T, EB, true>), grid, dim3(256), lgbytes + wbytes, st, (const T *)xin,         \
-                               (const T *)m->Wr, (const T *)m->br, rows, D.d, E, k, forced_route, w.route, w.weight,  \
-                               logit_out);                                                                            \
-        else                                                                                                          \
-            hipLaunchKernelGGL((moe_router_kernel<T, EB, false>), grid, dim3(256), lgbytes, st, (const T *)xin,             \
-                               (const T *)m->Wr, (const T *)m->br, rows, D.d, E, k, forced_route, w.route, w.weight,  \
-                               logit_out);                                                                            \
-    } while (0)
-        if (bf) {
-            if (E <= 8) SF_ROUTER(h16, 8);
-            else if (E <= 16) SF_ROUTER(h16, 16);
-            else SF_ROUTER(h16, 64);
-        } else {
-            if (E <= 8) SF_ROUTER(float, 8);
-            else if (E <= 16) SF_ROUTER(float, 16);
-            else SF_ROUTER(float, 64);
+        const bool along = pre_ln && bf && wlds && E <= 16 && D.d <= 1024 && !(((uintptr_t)m->ln_g | (uintptr_t)m->ln_b) & 15);
+        if (pre_ln) {
+            if (!along) layernorm(D.dtype, 0, X, m->ln_g, m->ln_b, D.eps, rows, D.d, w.xn, st);
+            xin = w.xn;
         }
+        RouterAlso also{};
+        also.tokens = tokens;
+        also.ln_g = (const h16 *)m->ln_g; also.ln_b = (const h16 *)m->ln_b; also.eps = D.eps; also.y = (h16 *)w.xn;
+        also.zero[0] = w.counts; also.n_zero[0] = n_seg;
+        // rows of padding read token 0 (their results are never used)
+        also.zero[1] = w.src_row; also.n_zero[1] = w.n_blocks_max * SEG_ROWS;
+        const void *in = along ? X : xin;
+#define SF_ROUTER(T, EB, WLDS, LN)                                                                                    \
+    hipLaunchKernelGGL((moe_router_kernel<T, EB, WLDS, LN>), grid, dim3(256), lgbytes + (WLDS ? wbytes : 0), st, (const T *)in, \
+                       (const T *)m->Wr, (const T *)m->br, rows, D.d, E, k, forced_route, w.route, w.weight, logit_out, also)
+#define SF_ROUTER_EB(EB)                                                                                              \
+    do {                                                                                                              \
+        if (bf && wlds) SF_ROUTER(h16, EB, true, 0);                                                             \
+        else if (bf) SF_ROUTER(h16, EB, false, 0);                                                                    \
+        else if (wlds) SF_ROUTER(float, EB, true, 0);                                                                 \
+        else SF_ROUTER(float, EB, false, 0);                                                                          \
+    } while (0)
+        if (along && E <= 8 && D.d <= 512) SF_ROUTER(h16, 8, true, 1);
+        else if (along && E <= 8) SF_ROUTER(h16, 8, true, 2);
+        else if (along && D.d <= 512) SF_ROUTER(h16, 16, true, 1);
+        else if (along) SF_ROUTER(h16, 16, true, 2);
+        else if (E <= 8) SF_ROUTER_EB(8);
+        else if (E <= 16) SF_ROUTER_EB(16);
+        else SF_ROUTER_EB(64);
+#undef SF_ROUTER_EB
 #undef SF_ROUTER
     }
     // counting sort of the (token, slot) pairs by (pattern, expert)
     const unsigned sort_blocks = (unsigned)((pairs + PAIRS_PER_BLOCK - 1) / PAIRS_PER_BLOCK);
-    hipLaunchKernelGGL(moe_zero_kernel, dim3(ceil_div(n_seg, 256)), dim3(256), 0, st, w.counts, n_seg);
-    // rows of padding read token 0 (their results are never used)
-    hipLaunchKernelGGL(moe_zero_kernel, dim3(ceil_div(w.n_blocks_max * SEG_ROWS, 256)), dim3(256), 0, st, w.src_row,
-                       w.n_blocks_max * SEG_ROWS);
     hipLaunchKernelGGL(moe_count_kernel, dim3(sort_blocks), dim3(256), 0, st, w.route, pattern_id, pairs, D.L, D.P, E, k,
                        w.counts);
     hipLaunchKernelGGL(moe_layout_kernel, dim3(1), dim3(256), 0, st, w.counts, n_seg, w.n_blocks_max, m->k_ffn, E,

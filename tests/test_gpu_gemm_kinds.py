@@ -130,3 +130,14 @@ def test_f32_ffn_with_layernorm_along(B, L, d, F):
     ref = torch.relu(xn @ w["W1"].T + w["b1"]) @ w["W2"] + w["b2"]
     torch.cuda.synchronize()
     assert err_metric(to_host(got), ref.cpu().numpy()) <= 8 * 50 * 2.0 ** -24
+
+
+# The router that takes the LayerNorm along: rows of one and two chunks of 512 and just beyond (a launch of its own), up to 8 and 16 experts
+# and beyond, blocks of 16 tokens (one short of full, full, one more) and of 64
+@pytest.mark.parametrize("dtype,B,L,d,E,k", [("bf16", 1, 15, 512, 8, 2), ("f16", 1, 16, 520, 9, 2), ("bf16", 1, 17, 1024, 16, 3), ("f16", 3, 33, 1032, 4, 1),
+                                             ("bf16", 2, 50, 64, 17, 2), ("bf16", 129, 128, 64, 8, 2)])
+def test_moe_router_with_layernorm_along(dtype, B, L, d, E, k):
+    _say(f"moe router {dtype} B={B} L={L} d={d} E={E}")
+    wl = make_wl(W.small_spec(dtype=dtype, B=B, seg=(L - 5, 3), extra=2, d=d, Hq=2, Hk=1, dh=32, F=128, dropout="upto:1"))
+    with sf.use_half(dtype):
+        _moe_case(wl, E, k)
