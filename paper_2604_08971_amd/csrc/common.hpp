@@ -125,6 +125,35 @@ __device__ __forceinline__ float wave_sum(float x)
     return pair_sum<1>(pair_sum<2>(pair_sum<4>(pair_sum<8>(pair_sum<16>(pair_sum<32>(x))))));
 }
 
+// The first four squares of a row's deviations, in the order that every sum of them begins with (one product rounded by itself)
+__device__ __forceinline__ float squares4(const float *t)
+{
+    return __builtin_fmaf(t[3], t[3], __builtin_fmaf(t[2], t[2], __builtin_fmaf(t[0], t[0], t[1] * t[1])));
+}
+
+// n * g + b in 16 bits.  binary16: layernorm_vec_kernel is compiled to the product that rounds to 16 bits itself; an fp32 product and
+// a conversion, which the compiler may take elsewhere, differ from it in a last place now and then.  The wait is for a vector
+// instruction that reads the register next: the compiler does not see that its halves are written one at a time.
+__device__ __forceinline__ h16x4 scale_shift(const float *n, h16x4 g, h16x4 b)
+{
+#ifdef SF_HALF_F16
+    const uint2 gu = __builtin_bit_cast(uint2, g), bu = __builtin_bit_cast(uint2, b);
+    uint2 o;
+#define SF_MIX2(D, N0, N1, G, B)                                                                                     \
+    asm("v_fma_mixlo_f16 %0, %1, %3, %4 op_sel_hi:[0,1,1]\n\tv_fma_mixhi_f16 %0, %2, %3, %4 op_sel:[0,1,1] op_sel_hi:[0,1,1]\n\ts_nop 0" \
+        : "=&v"(D) : "v"(N0), "v"(N1), "v"(G), "v"(B))
+    SF_MIX2(o.x, n[0], n[1], gu.x, bu.x);
+    SF_MIX2(o.y, n[2], n[3], gu.y, bu.y);
+#undef SF_MIX2
+    return __builtin_bit_cast(h16x4, o);
+#else
+    h16x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = (h16)(n[e] * (float)g[e] + (float)b[e]);
+    return o;
+#endif
+}
+
 // Order-preserving map of fp32 to uint32 (larger float <=> larger key).
 __device__ __forceinline__ uint32_t sortable_key(float f)
 {

@@ -34,12 +34,39 @@ __device__ __forceinline__ int lay(int row, int chunk)
     return sr * 128 + ((((row & 1) << 3) | chunk) ^ (sr & 7)) * 8;
 }
 
-// Sum over the eight lanes 8 i .. 8 i + 7, in each of them
-__device__ __forceinline__ float sum8(float x)
+// x of another lane of a row's eight (er, ec = 0 .. 7): the one next to it, the one opposite (7 - ec)
+__device__ __forceinline__ float beside(float x) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xb1, 0xf, 0xf, false)); }      // quad_perm
+__device__ __forceinline__ float opposite(float x) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x141, 0xf, 0xf, false)); }     // row_half_mirror
+
+// A row's sum in the order of layernorm_vec_kernel, so that both give the same bits: there lane l adds columns 8 l .. 8 l + 7 one
+// after the other, then lanes 32, 16, 8, 4, 2 and 1 apart are joined.  Here column 32 wn + 128 tn + 4 ec + e is with lane ec of wave column
+// wn, so that l = 16 tn + 4 wn + ec / 2: an odd lane goes on where the even one before it ends, tiles two and one apart
+// follow, then wave columns two and one apart (through LDS), then lanes.
+// row_part: what an odd lane holds before the wave columns are joined, of the terms x(tn, e) of column e of tile tn or (SQ) their squares.
+// The contraction of a square and a sum is written out: left to the compiler it is another one here than there.
+template <int TN, bool SQ, class X>
+__device__ __forceinline__ float row_part(X x)
 {
-    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xb1, 0xf, 0xf, false));      // quad_perm: lane ^ 1
-    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x4e, 0xf, 0xf, false));      // quad_perm: lane ^ 2
-    return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x141, 0xf, 0xf, false));      // row_half_mirror: lane 7 - i
+    float p[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int tn = 0; tn < TN; ++tn) {
+        float t[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] = x(tn, e);
+        p[tn] = beside(SQ ? squares4(t) : ((t[0] + t[1]) + t[2]) + t[3]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[tn] = SQ ? __builtin_fmaf(t[e], t[e], p[tn]) : p[tn] + t[e];
+    }
+    return TN == 1 ? p[0] : TN == 2 ? p[0] + p[1] : TN == 3 ? (p[0] + p[2]) + p[1] : (p[0] + p[2]) + (p[1] + p[3]);
+}
+// red: [row][ec / 2][wave column].  Lane ec joins the wave columns of pair (ec / 2) ^ (ec / 4), so that the opposite lane holds the pair
+// two away and, after that, the lane two away the other two.
+__device__ __forceinline__ float row_total(const float *red, int row, int ec)
+{
+    const f32x4 v = *reinterpret_cast<const f32x4 *>(red + (row * 4 + ((ec >> 1) ^ (ec >> 2))) * 4);
+    float s = (v[0] + v[2]) + (v[1] + v[3]);
+    s += opposite(s);
+    return s + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s), 0x4e, 0xf, 0xf, false));       // quad_perm: lane ^ 2
 }
 
 // A step begins: its operands have landed, and every wave is done with the step before
@@ -189,7 +216,7 @@ __device__ __forceinline__ void finish_rows(const GemmArgs &a, const Place &t, f
     f32x4 rr[NR][JR];
     fetch_r(0, rr[0]);
     char *stg = smem + t.wave * (TM * 4096);
-    float *red = reinterpret_cast<float *>(smem + NWV * TM * 4096);         // [2][row][wave column]
+    float *red = reinterpret_cast<float *>(smem + NWV * TM * 4096);         // [2][row][16]
     const uint32_t wb = (uint32_t)lay(t.l32, t.lhi) * 2u;
     f32x4 z[TN][JR];
     const int64_t co = a.C ? (grow0 + mrow0 + er) * a.ldc + a.c0 + ncol0 + ec * 4 : 0;
@@ -231,38 +258,24 @@ __device__ __forceinline__ void finish_rows(const GemmArgs &a, const Place &t, f
     }
     if (!a.lno_y) return;
 
-    // ---- LayerNorm of the rows (two passes over the registers, as layernorm_vec_kernel)
-    const int r0 = t.wm * TM * 32 + er;
+    // ---- LayerNorm of the rows (two passes over the registers)
+    const int r0 = t.wm * TM * 32 + er, slot = (ec >> 1) * 4 + t.wn;
     float mean[JR], inv[JR];
 #pragma unroll
     for (int j = 0; j < JR; ++j) {
-        float s = 0.f;
-#pragma unroll
-        for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) s += z[tn][j][e];
-        s = sum8(s);
-        if (ec == 0) red[(r0 + j * 8) * 4 + t.wn] = s;
+        const float s = row_part<TN, false>([&](int tn, int e) { return z[tn][j][e]; });
+        if (ec & 1) red[(r0 + j * 8) * 16 + slot] = s;
     }
     lds_barrier();
 #pragma unroll
     for (int j = 0; j < JR; ++j) {
-        const f32x4 v = *reinterpret_cast<const f32x4 *>(red + (r0 + j * 8) * 4);
-        mean[j] = ((v[0] + v[1]) + (v[2] + v[3])) / BN;
-        float s = 0.f;
-#pragma unroll
-        for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { const float d = z[tn][j][e] - mean[j]; s += d * d; }
-        s = sum8(s);
-        if (ec == 0) red[BM * 4 + (r0 + j * 8) * 4 + t.wn] = s;
+        mean[j] = row_total(red, r0 + j * 8, ec) / BN;
+        const float s = row_part<TN, true>([&](int tn, int e) { return z[tn][j][e] - mean[j]; });
+        if (ec & 1) red[BM * 16 + (r0 + j * 8) * 16 + slot] = s;
     }
     lds_barrier();
 #pragma unroll
-    for (int j = 0; j < JR; ++j) {
-        const f32x4 v = *reinterpret_cast<const f32x4 *>(red + BM * 4 + (r0 + j * 8) * 4);
-        inv[j] = 1.0f / sqrtf(((v[0] + v[1]) + (v[2] + v[3])) / BN + a.lno_eps);
-    }
+    for (int j = 0; j < JR; ++j) inv[j] = 1.0f / sqrtf(row_total(red + BM * 16, r0 + j * 8, ec) / BN + a.lno_eps);
     h16 *yp = static_cast<h16 *>(a.lno_y) + (grow0 + mrow0 + er) * (int64_t)BN + ncol0 + ec * 4;
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
@@ -270,15 +283,16 @@ __device__ __forceinline__ void finish_rows(const GemmArgs &a, const Place &t, f
         const h16x4 bt = *reinterpret_cast<const h16x4 *>(static_cast<const h16 *>(a.lno_b) + ncol0 + tn * 128 + ec * 4);
 #pragma unroll
         for (int j = 0; j < JR; ++j) {
-            h16x4 o;
+            float n[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (h16)((z[tn][j][e] - mean[j]) * inv[j] * (float)g[e] + (float)bt[e]);
+            for (int e = 0; e < 4; ++e) n[e] = (z[tn][j][e] - mean[j]) * inv[j];
+            const h16x4 o = scale_shift(n, g, bt);
             if (j * 8 < rows_left) *reinterpret_cast<h16x4 *>(yp + (int64_t)(j * 8) * BN + tn * 128) = o;
         }
     }
 }
 
-constexpr size_t after_of(int TM) { return (size_t)NWV * TM * 4096 + 64 * TM * 4 * 2 * 4; }      // staging and row sums of finish_rows()
+constexpr size_t after_of(int TM) { return (size_t)NWV * TM * 4096 + 64 * TM * 16 * 2 * 4; }      // staging and row sums of finish_rows()
 constexpr size_t at_least(size_t a, size_t b) { return a > b ? a : b; }
 
 // (64 * TM) x (128 * TN) tile; a wave owns 32 * TM rows of TN tiles of 32 columns, 128 apart.  Two buffers: the operands of a step
@@ -481,7 +495,9 @@ bool gemm_bf16_rows_eligible(const GemmArgs &a)
     if (a.N % 128 || a.N > 512 || a.K % SK || a.K < SK || a.lda % 8 || a.ldw % 8 || a.ldr % 4 || a.r0 % 4 || a.ldc % 4 || a.c0 % 4) return false;
     // whole aligned chunks: 16 bytes of the operands, the residual and the stream, 8 of 16-bit rows, 4 of the bias
     if (((uintptr_t)a.A | (uintptr_t)a.W | (a.r_f32 ? (uintptr_t)a.R : 0) | (a.c_f32 ? (uintptr_t)a.C : 0)) & 15) return false;
-    if (((uintptr_t)a.R | (uintptr_t)a.C | (uintptr_t)a.lno_g | (uintptr_t)a.lno_b | (uintptr_t)a.lno_y) & 7) return false;
+    if (((uintptr_t)a.R | (uintptr_t)a.C) & 7) return false;
+    // layernorm() takes rows off their 16 bytes by a kernel that adds in another order
+    if (((uintptr_t)a.lno_g | (uintptr_t)a.lno_b | (uintptr_t)a.lno_y) & 15) return false;
     if (((uintptr_t)a.bias & 3) || a.bias_pstride % 2) return false;
     return a.lda < ((int64_t)1 << 23) && a.ldw < ((int64_t)1 << 20);        // 32-bit byte offsets within a tile
 }

@@ -259,8 +259,12 @@ __global__ __launch_bounds__(256) void layernorm_vec_kernel(const TI *x, const T
 #pragma unroll
     for (int c = 0; c < NCH; ++c)
         if (lane + c * 64 < nch) {
+            float t[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) { const float t = v[c][e] - mean; q += t * t; }
+            for (int e = 0; e < 8; ++e) t[e] = v[c][e] - mean;
+            if (c == 0) q = squares4(t);
+#pragma unroll
+            for (int e = c == 0 ? 4 : 0; e < 8; ++e) q = __builtin_fmaf(t[e], t[e], q);
         }
     q = wave_sum(q);
     const float inv = 1.0f / sqrtf(q / d + eps);

@@ -2,6 +2,8 @@
 edges of their tiles and chunks, against the oracle."""
 from __future__ import annotations
 
+import dataclasses
+
 import pytest
 import torch
 
@@ -56,3 +58,29 @@ def test_encoder_writes_its_layernorms_along(dtype, B, seg, d, Hq, Hk, dh, F):
         dm.forward()
         assert _gemm_launches(lambda: dm.forward()) == 6
         _encoder_parity(wl, samples=[0, B // 2, B - 1])
+
+
+def _first_samples(wl, n):
+    return dataclasses.replace(wl, x=wl.x[:n], presence=wl.presence[:n], pattern_id=wl.pattern_id[:n])
+
+
+# A sample's output does not depend on how many others there are, to the bit: few of them go through separate launches, all of them
+# through the whole-row kernels (three GEMM launches a layer), whose products and row sums run in the same order.  Two layers, so that
+# LN2, the next layer's LN1 and the final LayerNorm are all written along.
+@pytest.mark.parametrize("dtype,few,B,L,d,Hq,Hk,dh,F,act", [
+    ("bf16", 60, 80, 383, 384, 6, 2, 64, 512, 0), ("f16", 60, 80, 383, 512, 8, 2, 64, 320, 1),
+])
+def test_same_bits_as_separate_launches(dtype, few, B, L, d, Hq, Hk, dh, F, act):
+    _say(f"bits of whole rows {dtype} few={few} B={B} L={L} d={d} F={F}")
+    spec = W.small_spec(dtype=dtype, B=B, seg=(L // 2, L - L // 2), extra=0, d=d, Hq=Hq, Hk=Hk, dh=dh, F=F, head_keep=0.75, ffn_keep=1.0, nl=2,
+                        act=act, final_ln=True)
+    with sf.use_half(dtype):
+        wl = W.make_workload(spec)
+        got = []
+        for n in (few, B):
+            dm = DeviceModel(_first_samples(wl, n)).build_plan()
+            dm.forward()
+            launches = _gemm_launches(lambda: got.append(dm.forward()[0][:few].clone()))
+            assert (launches == 6) == (n == B), launches
+        assert bool(torch.isfinite(got[0]).all())
+        assert int((got[0] != got[1]).sum()) == 0
