@@ -125,8 +125,12 @@ __global__ __launch_bounds__(256) void moe_router_kernel(
 #pragma unroll
             for (int c = 0; c < NCH; ++c)
                 if ((lane + c * 64) * 8 < d) {
+                    float z[8];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) { const float z = v[c][e] - mean; q += z * z; }
+                    for (int e = 0; e < 8; ++e) z[e] = v[c][e] - mean;
+                    if (c == 0) q = squares4(z);
+#pragma unroll
+                    for (int e = c == 0 ? 4 : 0; e < 8; ++e) q = __builtin_fmaf(z[e], z[e], q);
                 }
             q = wave_sum(q);
             const float inv = 1.0f / sqrtf(q / d + also.eps);
@@ -134,9 +138,12 @@ __global__ __launch_bounds__(256) void moe_router_kernel(
             for (int c = 0; c < NCH; ++c) {
                 const int at = (lane + c * 64) * 8;
                 if (at >= d) continue;
-                h16x8 o;
+                float n[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) o[e] = (h16)((v[c][e] - mean) * inv * (float)gm[c][e] + (float)bt[c][e]);
+                for (int e = 0; e < 8; ++e) n[e] = (v[c][e] - mean) * inv;
+                const h16x4 lo = scale_shift(n, __builtin_shufflevector(gm[c], gm[c], 0, 1, 2, 3), __builtin_shufflevector(bt[c], bt[c], 0, 1, 2, 3));
+                const h16x4 hi = scale_shift(n + 4, __builtin_shufflevector(gm[c], gm[c], 4, 5, 6, 7), __builtin_shufflevector(bt[c], bt[c], 4, 5, 6, 7));
+                const h16x8 o = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
                 *reinterpret_cast<h16x8 *>(also.y + t * d + at) = o;
                 const uint4 xq = __builtin_bit_cast(uint4, o);
                 const uint32_t xw[4] = {xq.x, xq.y, xq.z, xq.w};

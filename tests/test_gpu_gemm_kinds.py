@@ -2,12 +2,13 @@
 edges of their tiles and at a K tail of half a K tile, through the pruned FFN and the encoder against the oracle."""
 from __future__ import annotations
 
+import numpy as np
 import pytest
 import torch
 
 from paper_2604_08971_amd import binding as sf
 from paper_2604_08971_amd import workloads as W
-from gpu_utils import DeviceModel, to_host
+from gpu_utils import SF_DTYPE, DeviceModel, layernorm_as_launched, to_dev, to_host
 from helpers import err_metric, make_wl
 from test_gpu_parity import _encoder_parity, _ffn_case, _moe_case, _say
 
@@ -141,3 +142,27 @@ def test_moe_router_with_layernorm_along(dtype, B, L, d, E, k):
     wl = make_wl(W.small_spec(dtype=dtype, B=B, seg=(L - 5, 3), extra=2, d=d, Hq=2, Hk=1, dh=32, F=128, dropout="upto:1"))
     with sf.use_half(dtype):
         _moe_case(wl, E, k)
+
+
+# A LayerNorm that rides along with the router gives the bits of the launch it replaces (17 experts: that launch): the block without one on
+# rows normalised like it.  Means of 30, so that a row's sums decide its last bits.
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("d,E", [(384, 4), (768, 16), (384, 17)])
+def test_moe_layernorm_along_has_the_bits_of_the_launch(dtype, d, E):
+    _say(f"moe layernorm bits {dtype} d={d} E={E}")
+    B, L, F, k = 3, 700, 64, 2
+    wl = make_wl(W.small_spec(dtype=dtype, B=B, seg=(L - 5, 3), extra=2, d=d, Hq=2, Hk=1, dh=32, F=F, dropout="none"))
+    mb = W.make_moe_block(wl, E, k)
+    rnd = W.storage_rounding(dtype)
+    X = rnd(wl.x.reshape(B * L, d) + np.random.default_rng(d).normal(0, 30, (B * L, 1)))
+    with sf.use_half(dtype):
+        dt = SF_DTYPE[dtype]
+        masks = sf.gate_scores_to_masks(sf.make_desc(B, L, d, 8, 2, 8, F, n_layers=E, P=1, dtype=dt), to_dev(np.zeros((E, 1, 8), np.float32), "f32"),
+                                        to_dev(mb.g_ffn, "f32"), [1] * E, mb.k_ffn.tolist())
+        desc = sf.make_desc(B, L, d, 8, 2, 8, F, n_layers=1, P=1, dtype=dt)
+        cm = sf.compact_moe_experts(desc, {n: to_dev(v, dtype) for n, v in mb.dense.items()}, masks["ffn_idx"], k, mb.k_ffn.tolist())
+        got = sf.moe_ffn_forward(desc, cm, to_dev(X, dtype), None, pre_ln=True, add_residual=False, want_route=True)
+        xn = layernorm_as_launched(X, mb.dense["ln_g"], mb.dense["ln_b"], dtype)
+        ref = sf.moe_ffn_forward(desc, cm, to_dev(xn, dtype), None, pre_ln=False, add_residual=False, want_route=True)
+        torch.cuda.synchronize()
+    assert [int((a != b).sum()) for a, b in zip(got, ref)] == [0, 0, 0, 0]
