@@ -102,13 +102,13 @@ bool gemm_f32_takes_ln(const GemmArgs &a);
 // True when gemm() writes the LayerNorm of its output rows (a.lno_y) and that is the faster way (gemm_bf16_rows.hip).
 bool gemm_takes_ln_out(int dtype, const GemmArgs &a);
 bool gemm_bf16_rows_eligible(const GemmArgs &a);
-int32_t gemm_bf16_rows(const GemmArgs &a, hipStream_t st);
+int32_t gemm_bf16_rows(const GemmArgs &a, GemmKind kind, hipStream_t st);
 
 // The two products of an FFN (down.A is not read): in one launch where that is possible and the faster way.
 bool ffn_in_one(int dtype, const GemmArgs &up, const GemmArgs &down);
 int32_t ffn_one_launch(const GemmArgs &up, const GemmArgs &down, hipStream_t st);
 bool ffn_bf16_rows_eligible(const GemmArgs &up, const GemmArgs &down);
-int32_t ffn_bf16_rows(const GemmArgs &up, const GemmArgs &down, hipStream_t st);
+int32_t ffn_bf16_rows(const GemmArgs &up, GemmKind up_kind, const GemmArgs &down, GemmKind down_kind, hipStream_t st);
 
 // LayerNorm over rows of d elements (biased variance).  gamma/beta are in the
 // model dtype; x is fp32 when x_f32 (or dtype is SF_F32), y is in the model dtype.

@@ -320,7 +320,8 @@ int32_t ffn_one_launch(const GemmArgs &up0, const GemmArgs &down0, hipStream_t s
 {
     GemmArgs up = up0, down = down0;
     join_ffn(up, down);
-    return ffn_bf16_rows(up, down, st);
+    GemmArgs u = up, d = down;
+    return ffn_bf16_rows(up, choose(u), down, choose(d), st);
 }
 
 int32_t gemm_bf16(const GemmArgs &a0, hipStream_t st)
@@ -336,8 +337,8 @@ int32_t gemm_bf16(const GemmArgs &a0, hipStream_t st)
     }
     if (a.lno_y) {
         if (!gemm_takes_ln_out(SF_BF16, a)) return fail(SF_ERR_UNSUPPORTED, "gemm(bf16): LayerNorm of the output on a problem that does not write it");
-        join_samples(a);
-        return gemm_bf16_rows(a, st);
+        const GemmKind kind = choose(a);
+        return gemm_bf16_rows(a, kind, st);
     }
     const GemmKind kind = choose(a);
     if (kind == GEMM_WS) return gemm_bf16_ws(a, st);

@@ -295,11 +295,42 @@ __device__ __forceinline__ void finish_rows(const GemmArgs &a, const Place &t, f
 constexpr size_t after_of(int TM) { return (size_t)NWV * TM * 4096 + 64 * TM * 16 * 2 * 4; }      // staging and row sums of finish_rows()
 constexpr size_t at_least(size_t a, size_t b) { return a > b ? a : b; }
 
+// Where gemm() would slice K over S waves (gemm_slice_kernel: wave s takes K tiles s, s + S, .. from zero, and the slices are added to
+// the bias one after the other), a tile here walks K in that order too and keeps a sum per slice, so that the bits do not depend on
+// which kernel runs.  S is 4 or 8, or 1: all of K in one chain that begins with the bias, as in the other kernels.
+struct Slices {
+    int nk, S;                                                              // K tiles, slices
+    __device__ __forceinline__ bool ends(int t) const { return t + S >= nk; }
+    __device__ __forceinline__ int after(int t) const { return ends(t) ? (t & (S - 1)) + 1 : t + S; }
+};
+template <int TN, int TM>
+__device__ __forceinline__ void clear(f32x16 (&acc)[TN][TM])
+{
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+}
+// acc += slice, slice = 0
+template <int TN, int TM>
+__device__ __forceinline__ void join(f32x16 (&acc)[TN][TM], f32x16 (&slice)[TN][TM])
+{
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] += slice[i][j][e];
+    clear(slice);
+}
+
 // (64 * TM) x (128 * TN) tile; a wave owns 32 * TM rows of TN tiles of 32 columns, 128 apart.  Two buffers: the operands of a step
 // are on their way while the step before is multiplied.
-template <int TM, int TN>
+template <int TM, int TN, bool SL>
 __global__ __launch_bounds__(64 * NWV, TN <= 2 ? 4 : 2)
-void gemm_rows_kernel(GemmArgs a, int tiles_m, int total_tiles, int per_xcd)
+void gemm_rows_kernel(GemmArgs a, int slices, int tiles_m, int total_tiles, int per_xcd)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int BM = 64 * TM, BN = 128 * TN, BUF = (TM + 2 * TN) * PIECE;      // X, then W
@@ -329,13 +360,24 @@ void gemm_rows_kernel(GemmArgs a, int tiles_m, int total_tiles, int per_xcd)
     start_at(acc, a.bias ? static_cast<const h16 *>(a.bias) + (int64_t)t.p * a.bias_pstride : static_cast<const h16 *>(a.W), t.wn * 32, BN - 32,
              a.bias != nullptr, t.lhi);
     const uint32_t xbase = (uint32_t)lay(t.wm * TM * 32 + t.l32, t.lhi) * 2u, wbase = (uint32_t)lay(t.wn * 32 + t.l32, t.lhi) * 2u + TM * PIECE;
-    for (int k = 0; k < nk; ++k) {
+    const Slices order{nk, slices};
+    f32x16 slice[SL ? TN : 1][SL ? TM : 1];
+    if constexpr (SL) clear(slice);
+    for (int k = 0, tile = 0; k < nk; ++k) {
         next_step();
         const char *buf = smem + (k & 1) * BUF;
+        const int next = SL ? order.after(tile) : k + 1;
         h16x8 xf[SK / 16][TM];
-        step_mma<TN, 0, false>(acc, xf, buf + xbase, buf + wbase, t.wm == 0, [&] {
-            if (k + 1 < nk) load(k + 1, (k + 1) & 1);
-        });
+        auto issue = [&] {
+            if (k + 1 < nk) load(next, (k + 1) & 1);
+        };
+        if constexpr (SL) {
+            step_mma<TN, 0, false>(slice, xf, buf + xbase, buf + wbase, t.wm == 0, issue);
+            if (order.ends(tile)) join(acc, slice);
+        } else {
+            step_mma<TN, 0, false>(acc, xf, buf + xbase, buf + wbase, t.wm == 0, issue);
+        }
+        tile = next;
     }
     next_step();
     finish_rows(a, t, acc, smem);
@@ -344,14 +386,17 @@ void gemm_rows_kernel(GemmArgs a, int tiles_m, int total_tiles, int per_xcd)
 
 // The whole FFN of a row block: H = act(xn W1^T + b1) is formed in chunks of HC hidden channels, which stay in LDS as the second
 // product's operand: the hidden activations (2.5 KB a row, written and read again by two launches) never reach memory.
-struct FfnUp { const void *xn, *W1, *b1; int64_t w1_pstride, b1_pstride; };
+// SL: the bits of a sliced first product (up_sliced: at most four K tiles, each a slice) or second one (`slices` as above: the
+// chunks then take the tiles of 64 channels in that order).  Chunks of two tiles only, and registers for one workgroup per compute unit:
+// a problem that gemm() slices has no more tiles than that, or hardly.
+struct FfnUp { const void *xn, *W1, *b1; int64_t w1_pstride, b1_pstride; int up_sliced, slices; };
 
 constexpr int ffn_g(int TN) { return TN == 4 ? 2 : TN; }               // the second product takes 128 g columns at a time
 constexpr size_t ffn_buf(int TM, int TN, int TH) { return at_least(TM + 2 * TH, 2 * ffn_g(TN)) * PIECE; }
 constexpr size_t ffn_lds(int TM, int TN, int TH) { return (size_t)TM * TH * 16384 + 2 * ffn_buf(TM, TN, TH); }
 
-template <int TM, int TN, int TH, int ACT>
-__global__ __launch_bounds__(64 * NWV, TH == 2 ? 2 : 4)
+template <int TM, int TN, int TH, int ACT, bool SL>
+__global__ __launch_bounds__(64 * NWV, TH == 2 || (SL && TN == 2) ? 2 : 4)
 void ffn_rows_kernel(GemmArgs a, FfnUp u, int tiles_m, int total_tiles, int per_xcd)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -372,14 +417,14 @@ void ffn_rows_kernel(GemmArgs a, FfnUp u, int tiles_m, int total_tiles, int per_
     const uint32_t w1off = lane_off(t.wave, t.lane, 128, BN, nullptr), w2off = lane_off(t.wave, t.lane, 128, F, nullptr);
     char *const bufs = smem + HC * BM * 2;
     int buf = 0;                                                            // of the step to come
-    auto load1 = [&](int c0, int s, int bf) {                               // X and W1 of a step of the first product
+    auto load1 = [&](int c0, int cb, int s, int bf) {                       // X and W1 of a step of the first product; cb: SL, the second tile
         char *to = bufs + bf * BUF + t.wave * 1024;
 #pragma unroll
         for (int j = 0; j < TM; ++j)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_void *)(to + j * PIECE), 16, xoff[j], s * (SK * 2), 0, 0);
 #pragma unroll
         for (int j = 0; j < 2 * TH; ++j)                                    // rows behind the last channel: zeros, never used
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(w1r, (lds_void *)(to + (TM + j) * PIECE), 16, w1off, (c0 + j * 64) * (BN * 2) + s * (SK * 2), 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(w1r, (lds_void *)(to + (TM + j) * PIECE), 16, w1off, (SL && j ? cb : c0 + j * 64) * (BN * 2) + s * (SK * 2), 0, 0);
     };
     auto load2 = [&](int c, int part, int bf) {                             // W2 of 64 channels from c
         char *to = bufs + bf * BUF + t.wave * 1024;
@@ -387,27 +432,45 @@ void ffn_rows_kernel(GemmArgs a, FfnUp u, int tiles_m, int total_tiles, int per_
         for (int j = 0; j < 2 * G; ++j)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(w2r, (lds_void *)(to + j * PIECE), 16, w2off, c * 2 + (part * G * 128 + j * 64) * F * 2, 0, 0);
     };
-    load1(0, 0, 0);
+    static_assert(!SL || (TH == 1 && PARTS == 1), "two tiles of channels a chunk");
+    const Slices order{F / SK, u.slices};
+    int ca = 0, cb = SL && F > SK ? order.after(0) * SK : F;                // SL: the channels of the two tiles of a chunk (F: none)
+    load1(0, cb, 0, 0);
 
-    f32x16 acc[TN][TM];
+    f32x16 acc[TN][TM], slice[SL ? TN : 1][SL ? TM : 1];
     start_at(acc, a.bias ? static_cast<const h16 *>(a.bias) + (int64_t)t.p * a.bias_pstride : static_cast<const h16 *>(a.W), t.wn * 32, BN - 32,
              a.bias != nullptr, t.lhi);
+    const bool down_sliced = SL && u.slices > 1;
+    if constexpr (SL) {
+        clear(slice);
+        if (!down_sliced) join(slice, acc);                                 // the chain begins with the bias
+    }
     const uint32_t xbase = (uint32_t)lay(t.wm * TM * 32 + t.l32, t.lhi) * 2u, wbase = (uint32_t)lay(t.wn * 32 + t.l32, t.lhi) * 2u;
     // H: channels 128 i + 32 wn + 8 q + 4 lhi .. are chunk (wn & 1) * 4 + q of tile 2 i + wn / 2 of 64 channels
     const uint32_t hwrite = (uint32_t)lay(t.wm * TM * 32 + t.l32, (t.wn & 1) * 4) * 2u + t.lhi * 8u;
     for (int c0 = 0; c0 < F; c0 += HC) {
-        f32x16 h[TH][TM];
+        f32x16 h[TH][TM], hs[SL ? TH : 1][SL ? TM : 1];
         // channels behind the last: any finite start, never used
-        start_at(h, u.b1 ? static_cast<const h16 *>(u.b1) + (int64_t)t.p * u.b1_pstride : static_cast<const h16 *>(u.W1), c0 + t.wn * 32, F - 32,
-                 u.b1 != nullptr, t.lhi);
+        start_at(h, u.b1 ? static_cast<const h16 *>(u.b1) + (int64_t)t.p * u.b1_pstride : static_cast<const h16 *>(u.W1),
+                 SL ? (t.wn < 2 ? ca + t.wn * 32 : cb + t.wn * 32 - 64) : c0 + t.wn * 32, F - 32, u.b1 != nullptr, t.lhi);
+        if constexpr (SL) {
+            clear(hs);
+            if (!u.up_sliced) join(hs, h);
+        }
         for (int s = 0; s < s1; ++s) {
             next_step();
             const char *b = bufs + buf * BUF;
             h16x8 xf[SK / 16][TM];
-            step_mma<TH, 0, false>(h, xf, b + xbase, b + TM * PIECE + wbase, t.wm == 0, [&] {
-                if (s + 1 < s1) load1(c0, s + 1, buf ^ 1);
-                else load2(c0, 0, buf ^ 1);
-            });
+            auto issue = [&] {
+                if (s + 1 < s1) load1(SL ? ca : c0, cb, s + 1, buf ^ 1);
+                else load2(SL ? ca : c0, 0, buf ^ 1);
+            };
+            if constexpr (SL) {
+                step_mma<TH, 0, false>(hs, xf, b + xbase, b + TM * PIECE + wbase, t.wm == 0, issue);
+                if (u.up_sliced || s + 1 == s1) join(h, hs);
+            } else {
+                step_mma<TH, 0, false>(h, xf, b + xbase, b + TM * PIECE + wbase, t.wm == 0, issue);
+            }
             buf ^= 1;
         }
         // H to LDS: every wave has passed a barrier behind its last read of the chunk before
@@ -423,18 +486,25 @@ void ffn_rows_kernel(GemmArgs a, FfnUp u, int tiles_m, int total_tiles, int per_
                     *reinterpret_cast<uint2 *>(smem + (2 * i + t.wn / 2) * HT + (hwrite ^ (q << 4)) + j * 4096) = pw;
                 }
         const int c1 = min(c0 + HC, F);
+        const int na = SL && c1 < F ? order.after(cb / SK) * SK : c1, nb = SL && c1 + SK < F ? order.after(na / SK) * SK : F;
         for (int c = c0; c < c1; c += SK) {
             h16x8 xf[SK / 16][TM];
             auto after = [&] {                                              // what follows these 64 channels
-                if (c + SK < c1) load2(c + SK, 0, buf ^ 1);
-                else if (c1 < F) load1(c1, 0, buf ^ 1);
+                if (c + SK < c1) load2(SL ? cb : c + SK, 0, buf ^ 1);
+                else if (c1 < F) load1(na, nb, 0, buf ^ 1);
             };
             next_step();
             const char *x = smem + (c - c0) / SK * HT + xbase;
-            step_mma<G, 0, false>(acc, xf, x, bufs + buf * BUF + wbase, t.wm == 0, [&] {
+            auto issue = [&] {
                 if constexpr (PARTS == 2) load2(c, 1, buf ^ 1);
                 else after();
-            });
+            };
+            if constexpr (SL) {
+                step_mma<G, 0, false>(slice, xf, x, bufs + buf * BUF + wbase, t.wm == 0, issue);
+                if (order.ends((c == c0 ? ca : cb) / SK)) join(acc, slice);
+            } else {
+                step_mma<G, 0, false>(acc, xf, x, bufs + buf * BUF + wbase, t.wm == 0, issue);
+            }
             buf ^= 1;
             if constexpr (PARTS == 2) {                                     // the same channels, the other columns
                 next_step();
@@ -442,6 +512,8 @@ void ffn_rows_kernel(GemmArgs a, FfnUp u, int tiles_m, int total_tiles, int per_
                 buf ^= 1;
             }
         }
+        ca = na;
+        cb = nb;
     }
     next_step();
     finish_rows(a, t, acc, smem);
@@ -462,30 +534,34 @@ int32_t launch(Kern kern, std::atomic<bool> &attr_set, size_t lds, int bm, const
     return SF_OK;
 }
 
-template <int TM, int TN>
-int32_t launch_rows(const GemmArgs &a, hipStream_t st)
+template <int TM, int TN, bool SL>
+int32_t launch_rows(const GemmArgs &a, int slices, hipStream_t st)
 {
     static std::atomic<bool> set{false};
-    return launch(gemm_rows_kernel<TM, TN>, set, at_least((size_t)2 * (TM + 2 * TN) * PIECE, after_of(TM)), 64 * TM, a, st);
+    return launch(gemm_rows_kernel<TM, TN, SL>, set, at_least((size_t)2 * (TM + 2 * TN) * PIECE, after_of(TM)), 64 * TM, a, st, slices);
 }
 
-template <int TM, int TN, int TH, int ACT>
+template <int TM, int TN, int TH, int ACT, bool SL>
 int32_t launch_ffn(const GemmArgs &a, const FfnUp &u, hipStream_t st)
 {
     static std::atomic<bool> set{false};
-    return launch(ffn_rows_kernel<TM, TN, TH, ACT>, set, at_least(ffn_lds(TM, TN, TH), after_of(TM)), 64 * TM, a, st, u);
+    return launch(ffn_rows_kernel<TM, TN, TH, ACT, SL>, set, at_least(ffn_lds(TM, TN, TH), after_of(TM)), 64 * TM, a, st, u);
 }
 
 template <int ACT>
 int32_t launch_ffn_act(const GemmArgs &a, const FfnUp &u, hipStream_t st)
 {
+    const bool sliced = u.up_sliced || u.slices > 1;
     switch (a.N / 128) {
-    case 1: return launch_ffn<1, 1, 1, ACT>(a, u, st);
-    case 2: return launch_ffn<1, 2, 1, ACT>(a, u, st);
-    case 3: return launch_ffn<2, 3, 2, ACT>(a, u, st);
-    default: return launch_ffn<2, 4, 2, ACT>(a, u, st);
+    case 1: return sliced ? launch_ffn<1, 1, 1, ACT, true>(a, u, st) : launch_ffn<1, 1, 1, ACT, false>(a, u, st);
+    case 2: return sliced ? launch_ffn<1, 2, 1, ACT, true>(a, u, st) : launch_ffn<1, 2, 1, ACT, false>(a, u, st);
+    case 3: return launch_ffn<2, 3, 2, ACT, false>(a, u, st);
+    default: return launch_ffn<2, 4, 2, ACT, false>(a, u, st);
     }
 }
+
+// K slices of the kernel that gemm() takes; 1: one chain
+int slices_of(GemmKind kind) { return kind == GEMM_SLICE8 ? 8 : kind == GEMM_SLICE4 ? 4 : 1; }
 
 }  // namespace
 
@@ -502,13 +578,15 @@ bool gemm_bf16_rows_eligible(const GemmArgs &a)
     return a.lda < ((int64_t)1 << 23) && a.ldw < ((int64_t)1 << 20);        // 32-bit byte offsets within a tile
 }
 
-int32_t gemm_bf16_rows(const GemmArgs &a, hipStream_t st)
+// kind: the kernel that gemm() takes without the LayerNorm
+int32_t gemm_bf16_rows(const GemmArgs &a, GemmKind kind, hipStream_t st)
 {
+    const int slices = slices_of(kind);
     switch (a.N / 128) {
-    case 1: return launch_rows<1, 1>(a, st);
-    case 2: return launch_rows<1, 2>(a, st);
-    case 3: return launch_rows<2, 3>(a, st);
-    default: return launch_rows<2, 4>(a, st);
+    case 1: return slices > 1 ? launch_rows<1, 1, true>(a, slices, st) : launch_rows<1, 1, false>(a, 1, st);
+    case 2: return slices > 1 ? launch_rows<1, 2, true>(a, slices, st) : launch_rows<1, 2, false>(a, 1, st);
+    case 3: return launch_rows<2, 3, false>(a, 1, st);
+    default: return launch_rows<2, 4, false>(a, 1, st);
     }
 }
 
@@ -520,9 +598,9 @@ bool ffn_bf16_rows_eligible(const GemmArgs &up, const GemmArgs &down)
     return (int64_t)up.N * up.K * 2 < ((int64_t)1 << 31);
 }
 
-int32_t ffn_bf16_rows(const GemmArgs &up, const GemmArgs &down, hipStream_t st)
+int32_t ffn_bf16_rows(const GemmArgs &up, GemmKind up_kind, const GemmArgs &down, GemmKind down_kind, hipStream_t st)
 {
-    const FfnUp u{up.A, up.W, up.bias, up.w_pstride, up.bias_pstride};
+    const FfnUp u{up.A, up.W, up.bias, up.w_pstride, up.bias_pstride, slices_of(up_kind) > 1, slices_of(down_kind)};
     return up.act == ACT_GELU ? launch_ffn_act<ACT_GELU>(down, u, st) : launch_ffn_act<ACT_RELU>(down, u, st);
 }
 
