@@ -103,13 +103,18 @@ static FfnWs ffn_ws(const Dims &D, int Fp, bool pre_ln, void *ws)
     return w;
 }
 
-// The operand of g is LayerNorm(x), rows of g.K elements: the product takes it along where it can (g.A = x then), else it
-// is formed in xn.
+// g with LayerNorm(x) as its operand, rows of g.K elements
+static GemmArgs of_normalised(GemmArgs g, bool x_f32, const void *x, const void *gamma, const void *beta, float eps)
+{
+    g.A = x; g.ln_g = gamma; g.ln_b = beta; g.ln_eps = eps; g.ln_x32 = x_f32;
+    return g;
+}
+
+// The operand of g is LayerNorm(x): the product takes it along where it can (g.A = x then), else it is formed in xn.
 static void normalised(int dtype, GemmArgs &g, bool x_f32, const void *x, const void *gamma, const void *beta, float eps, void *xn,
                        hipStream_t st)
 {
-    GemmArgs t = g;
-    t.A = x; t.ln_g = gamma; t.ln_b = beta; t.ln_eps = eps; t.ln_x32 = x_f32;
+    const GemmArgs t = of_normalised(g, x_f32, x, gamma, beta, eps);
     if (gamma && beta && gemm_takes_ln(dtype, t)) g = t;
     else layernorm(dtype, x_f32, x, gamma, beta, eps, (int64_t)g.B * g.L, g.K, xn, st);
 }
@@ -135,6 +140,17 @@ static int32_t gemm_then_norm(int dtype, GemmArgs &g, float eps, NormOut *n, hip
     return gemm(dtype, g, st);
 }
 
+static GemmArgs ffn_up(const Dims &D, const sf_compact_layer &ly, const int32_t *pattern_id, const void *x, void *hid)
+{
+    const int Fp = (int)align_up(ly.k_ffn, D.ffn_pad);
+    GemmArgs g{};
+    g.A = x; g.lda = D.d; g.W = ly.W1; g.ldw = D.d; g.w_pstride = (int64_t)Fp * D.d;
+    g.bias = ly.b1; g.bias_pstride = Fp; g.pattern_id = pattern_id;
+    g.B = D.B; g.L = D.L; g.N = Fp; g.K = D.d; g.epi = EPI_ROWMAJOR; g.act = gemm_act(D.act);
+    g.C = hid; g.ldc = Fp;
+    return g;
+}
+
 // x_f32 / y_f32: X / Y hold fp32 although the model dtype is bf16 (the
 // encoder's residual stream).  With x_f32, pre_ln is required (the GEMM reads bf16).
 static int32_t ffn_forward(const Dims &D, const sf_compact_layer &ly, const void *X, bool x_f32,
@@ -142,11 +158,7 @@ static int32_t ffn_forward(const Dims &D, const sf_compact_layer &ly, const void
                            void *xn, void *hid, hipStream_t st, bool xn_ready = false, NormOut *next = nullptr)
 {
     const int Fp = (int)align_up(ly.k_ffn, D.ffn_pad);
-    GemmArgs g{};
-    g.A = xn_ready || pre_ln ? xn : X; g.lda = D.d; g.W = ly.W1; g.ldw = D.d; g.w_pstride = (int64_t)Fp * D.d;
-    g.bias = ly.b1; g.bias_pstride = Fp; g.pattern_id = pattern_id;
-    g.B = D.B; g.L = D.L; g.N = Fp; g.K = D.d; g.epi = EPI_ROWMAJOR; g.act = gemm_act(D.act);
-    g.C = hid; g.ldc = Fp;
+    GemmArgs g = ffn_up(D, ly, pattern_id, xn_ready || pre_ln ? xn : X, hid);
     // xn_ready: LN2(X) is already there (written together with X)
     if (pre_ln && !xn_ready) normalised(D.dtype, g, x_f32, X, ly.ln2_g, ly.ln2_b, D.eps, xn, st);
 
@@ -430,6 +442,19 @@ static int32_t encoder_forward_impl(const sf_desc *desc, const sf_compact_layer 
     bool in_f32 = !bf;
     const bool final_ln = (D.flags & SF_FLAG_FINAL_LN) != 0;
     bool xn_ready = false, y_ready = false;      // LN1 of this layer, the final LayerNorm: written together with the stream
+    // Q, K, V of layer i from w.xn: token-major, or (16 bits, not packed) V as the transposed column range, if a kernel takes that
+    auto qkv_of = [&](int i) {
+        const sf_compact_layer &ly = layers[i];
+        const int Nqk = (ly.k_head + D.Hk) * D.dh, Nqkv = Nqk + D.Hk * D.dh;
+        const bool vt = bf && !pk;
+        GemmArgs g{};
+        g.A = w.xn; g.lda = D.d; g.W = ly.Wqkv; g.ldw = D.d; g.w_pstride = (int64_t)Nqkv * D.d;
+        g.bias = ly.bqkv; g.bias_pstride = Nqkv; g.pattern_id = gpat;
+        g.B = Dg.B; g.L = Dg.L; g.N = Nqkv; g.K = D.d; g.act = ACT_NONE; g.epi = EPI_ROWMAJOR;
+        g.C = w.qkv; g.ldc = vt ? Nqk : Nqkv;
+        if (vt) { g.VT = w.vt; g.vt_from = Nqk; g.vt_b = (int64_t)D.Hk * D.dh * w.Lp; g.vt_n = w.Lp; }
+        return g;
+    };
     for (int l = 0; l < D.nl; ++l) {
         const sf_compact_layer &ly = layers[l];
         const int kh = ly.k_head, dh = D.dh, Hk = D.Hk;
@@ -450,43 +475,30 @@ static int32_t encoder_forward_impl(const sf_desc *desc, const sf_compact_layer 
             if (int32_t rc = gemm_fp8(q8, st)) return rc;
             transpose_v(w.qkv, Nqkv, Nqk, Hk * dh, D.B, D.L, w.Lp, w.vt, st);
         } else {
-            GemmArgs g{};
-            g.A = w.xn; g.lda = D.d; g.W = ly.Wqkv; g.ldw = D.d; g.w_pstride = (int64_t)Nqkv * D.d;
-            g.bias = ly.bqkv; g.bias_pstride = Nqkv; g.pattern_id = gpat;
-            g.B = Dg.B; g.L = Dg.L; g.K = D.d; g.act = ACT_NONE; g.epi = EPI_ROWMAJOR;
-            g.C = w.qkv; g.ldc = ldq; g.n0 = 0; g.N = bf && !pk ? Nqk : Nqkv;
-            if (xn_ready) {
-                // w.xn holds it
-            } else if (!bf || pk) normalised(D.dtype, g, in_f32, in, ly.ln1_g, ly.ln1_b, D.eps, w.xn, st);
-            if (bf && pk) {
-                // Q, K, V token-major in one launch; V^T per sample (what the attention kernels read) by a pass of
-                // its own, since a 256-row block of packed rows may straddle samples
+            GemmArgs g = qkv_of(l);
+            if (g.VT && !gemm_takes_vt_split(D.dtype, g)) {
+                if (!xn_ready) layernorm(D.dtype, in_f32, in, ly.ln1_g, ly.ln1_b, D.eps, rows, D.d, w.xn, st);
+                GemmArgs v = g;
+                g.N = Nqk; g.VT = nullptr; g.vt_from = 0;
                 if (int32_t rc = gemm(D.dtype, g, st)) return rc;
-                transpose_v(w.qkv, Nqkv, Nqk, Hk * dh, D.B, D.L, w.Lp, w.vt, st, pk->row0);
-            } else if (bf) {
-                // one launch for Q, K and V when the large-tile kernel takes it (V is the transposed column range:
-                // the normalised input is read once); otherwise Q/K and V separately
-                GemmArgs q3 = g;
-                q3.N = Nqkv; q3.VT = w.vt; q3.vt_from = Nqk; q3.vt_b = (int64_t)Hk * dh * w.Lp; q3.vt_n = w.Lp;
-                if (gemm_takes_vt_split(D.dtype, q3)) {
-                    if (!xn_ready) normalised(D.dtype, q3, in_f32, in, ly.ln1_g, ly.ln1_b, D.eps, w.xn, st);
-                    if (int32_t rc = gemm(D.dtype, q3, st)) return rc;
-                } else {
-                    if (!xn_ready) layernorm(D.dtype, in_f32, in, ly.ln1_g, ly.ln1_b, D.eps, rows, D.d, w.xn, st);
-                    if (int32_t rc = gemm(D.dtype, g, st)) return rc;
-                    g.n0 = Nqk; g.N = Hk * dh; g.epi = EPI_VT; g.C = w.vt;
-                    g.vt_b = q3.vt_b; g.vt_n = q3.vt_n;
-                    if (int32_t rc = gemm(D.dtype, g, st)) return rc;
-                }
+                v.n0 = Nqk; v.N = Hk * dh; v.epi = EPI_VT; v.C = w.vt; v.VT = nullptr; v.vt_from = 0;
+                if (int32_t rc = gemm(D.dtype, v, st)) return rc;
             } else {
+                if (!xn_ready) normalised(D.dtype, g, in_f32, in, ly.ln1_g, ly.ln1_b, D.eps, w.xn, st);
                 if (int32_t rc = gemm(D.dtype, g, st)) return rc;
+                // packed: V^T per sample (what the attention kernels read) by a pass of its own, since a 256-row block of
+                // packed rows may straddle samples
+                if (bf && pk) transpose_v(w.qkv, Nqkv, Nqk, Hk * dh, D.B, D.L, w.Lp, w.vt, st, pk->row0);
             }
         }
 
-        // What reads the layer's output next: LN1 of the following layer (its Q/K/V in 16 bits) or the final LayerNorm
+        // What reads the layer's output next: LN1 of the following layer (its Q/K/V in 16 bits; not where that product takes the
+        // LayerNorm along) or the final LayerNorm
         NormOut next{};
         if (l + 1 < D.nl) {
-            if (!proj8) next = NormOut{layers[l + 1].ln1_g, layers[l + 1].ln1_b, w.xn, false, false};
+            const sf_compact_layer &ln = layers[l + 1];
+            if (!proj8 && !gemm_takes_ln(D.dtype, of_normalised(qkv_of(l + 1), true, w.x2, ln.ln1_g, ln.ln1_b, D.eps)))
+                next = NormOut{ln.ln1_g, ln.ln1_b, w.xn, false, false};
         } else if (final_ln) {
             next = NormOut{final_g, final_b, Y, true, false};
         }
@@ -580,7 +592,8 @@ static int32_t encoder_forward_impl(const sf_desc *desc, const sf_compact_layer 
             continue;
         }
 
-        // x1 = x + att Wo' + bo   (only the kept heads' rows of Wo exist), with LN2(x1) for an FFN in 16 bits where that is possible
+        // x1 = x + att Wo' + bo   (only the kept heads' rows of Wo exist), with LN2(x1) for an FFN in 16 bits where that is possible and
+        // the FFN does not take it along itself
         NormOut ln2{};
         if (proj8) {
             const sf_proj_fp8 &pj = proj8[l];
@@ -601,7 +614,8 @@ static int32_t encoder_forward_impl(const sf_desc *desc, const sf_compact_layer 
             o.w_pstride = (int64_t)D.d * kh * dh; o.bias = ly.bo; o.bias_pstride = 0; o.pattern_id = gpat;
             o.B = Dg.B; o.L = Dg.L; o.N = D.d; o.K = kh * dh; o.epi = EPI_ROWMAJOR; o.act = ACT_NONE;
             o.R = in; o.ldr = D.d; o.r_f32 = in_f32; o.C = w.x1; o.ldc = D.d; o.c_f32 = 1;
-            if (!ffn8) ln2 = NormOut{ly.ln2_g, ly.ln2_b, w.xn, false, false};
+            if (!ffn8 && !gemm_takes_ln(D.dtype, of_normalised(ffn_up(Dg, ly, gpat, w.xn, w.hid), true, w.x1, ly.ln2_g, ly.ln2_b, D.eps)))
+                ln2 = NormOut{ly.ln2_g, ly.ln2_b, w.xn, false, false};
             if (int32_t rc = gemm_then_norm(D.dtype, o, D.eps, &ln2, st)) return rc;
         }
 
