@@ -17,12 +17,12 @@ __device__ __forceinline__ float act_f32(float z, int act)
     return z;
 }
 
-// Sum over the eight lanes 8 i .. 8 i + 7, in each of them
+// Sum over the eight lanes 8 i .. 8 i + 7, in each of them, joined as by the last steps of wave_sum()
 __device__ __forceinline__ float sum8(float x)
 {
-    x += __shfl_xor(x, 1);
+    x += __shfl_xor(x, 4);
     x += __shfl_xor(x, 2);
-    return x + __shfl_xor(x, 4);
+    return x + __shfl_xor(x, 1);
 }
 
 constexpr int FLN = 256;    // longest row whose LayerNorm the product takes along
@@ -32,10 +32,13 @@ constexpr int FLN = 256;    // longest row whose LayerNorm the product takes alo
 // is 64 of K, all 16 loads of a thread are in flight before the first is used, and those of the next step are issued before this one's
 // products.  Four values of K per LDS read; every sum runs over K in order.  2 samples of 48 rows, N 64 to 128, K 32 to 128: 6.1-7.2 us
 // with single values, 4.6-7.0 now (the small encoder of those 43.9 -> 38.9 us with the LayerNorms along).
-// LN: the rows of A come unnormalised.  Eight threads hold a row (K <= FLN) and take mean and deviations as layernorm_vec_kernel
-// does, from loads that are in flight with the first step's; every column of tiles does so again, which costs less than the
-// launch it replaces (3.2 us) while there are few of them.
-template <bool LN>
+// LN: the rows of A come unnormalised.  Eight threads hold a row (K <= FLN) and take mean and deviations from loads that are in
+// flight with the first step's; every column of tiles does so again, which costs less than the launch it replaces (3.2 us) while there
+// are few of them.  Thread c of the eight stands for lanes c, c + 8, .. of the launch and adds in its order, so that both give the
+// same bits: as layernorm_vec_kernel (LN_VEC: eight columns in a row per lane) or, where rows are no whole chunks of 16 bytes,
+// layernorm_kernel (LN_ONE: columns 64 apart).
+enum { LN_NONE, LN_VEC, LN_ONE };
+template <int LN>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a)
 {
     __shared__ __attribute__((aligned(16))) float Xs[FT][FK + 4], Ws[FT][FK + 4];
@@ -64,7 +67,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a)
             xv[u] = (i < a.L && k < a.K) ? A[(int64_t)i * a.lda + k] : 0.f;
             wv[u] = (n < a.N && k < a.K) ? W[(int64_t)n * a.ldw + k] : 0.f;
         }
-        if (LN && k < a.K) {
+        if (LN != LN_NONE && k < a.K) {
             gk = static_cast<const float *>(a.ln_g)[k];
             bk = static_cast<const float *>(a.ln_b)[k];
         }
@@ -84,33 +87,70 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a)
             rv[u][v] = R && i < a.L && n < a.N ? R[((int64_t)b * a.L + i) * a.ldr + a.r0 + n] : 0.f;
         }
     }
-    if constexpr (LN) {
+    if constexpr (LN != LN_NONE) {
+        constexpr int NP = LN == LN_VEC ? 4 : 8, PL = FLN / 8 / NP;         // lanes of the launch per thread, columns per lane
         const int r = threadIdx.x / 8, c = threadIdx.x % 8;
         const float *x = A + (int64_t)min(m0 + r, a.L - 1) * a.lda;
-        float v[FLN / 8], s = 0.f, q = 0.f;
+        auto column = [&](int i, int j) { return LN == LN_VEC ? (c + 8 * i) * 8 + j : c + 8 * i + 64 * j; };
+        float v[NP][PL], part[NP];
 #pragma unroll
-        for (int i = 0; i < FLN / 8; ++i) v[i] = i * 8 + c < a.K ? x[i * 8 + c] : 0.f;
+        for (int i = 0; i < NP; ++i)
+            if constexpr (LN == LN_VEC) {
 #pragma unroll
-        for (int i = 0; i < FLN / 8; ++i) s += v[i];
-        const float m = sum8(s) / a.K;
+                for (int j = 0; j < PL; j += 4) {
+                    f32x4 t = {0.f, 0.f, 0.f, 0.f};
+                    if (column(i, 0) < a.K) t = *reinterpret_cast<const f32x4 *>(x + column(i, j));
 #pragma unroll
-        for (int i = 0; i < FLN / 8; ++i) {
-            const float t = i * 8 + c < a.K ? v[i] - m : 0.f;
-            q += t * t;
+                    for (int e = 0; e < 4; ++e) v[i][j + e] = t[e];
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < PL; ++j) v[i][j] = column(i, j) < a.K ? x[column(i, j)] : 0.f;
+            }
+        // lanes 32, 16 and 8 apart are with the same thread (none 32 apart of rows of up to 256 columns by eights)
+        auto joined = [&]() {
+            if constexpr (LN == LN_VEC) return sum8((part[0] + part[2]) + (part[1] + part[3]));
+            else return sum8(((part[0] + part[4]) + (part[2] + part[6])) + ((part[1] + part[5]) + (part[3] + part[7])));
+        };
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            part[i] = v[i][0];
+#pragma unroll
+            for (int j = 1; j < PL; ++j) part[i] += v[i][j];
         }
-        q = sum8(q);
+        const float m = joined() / a.K;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            float t[PL];
+#pragma unroll
+            for (int j = 0; j < PL; ++j) t[j] = column(i, j) < a.K ? v[i][j] - m : 0.f;
+            part[i] = LN == LN_VEC ? squares4(t) : t[0] * t[0];
+#pragma unroll
+            for (int j = LN == LN_VEC ? 4 : 1; j < PL; ++j) part[i] = __builtin_fmaf(t[j], t[j], part[i]);
+        }
+        const float q = joined();
         if (c == 0) {
             mean[r] = m;
             inv[r] = 1.0f / sqrtf(q / a.K + a.ln_eps);
         }
         __syncthreads();
     }
+    auto operand = [&](float x, int r) {
+        if constexpr (LN == LN_NONE) return x;
+        const float n = (x - mean[r]) * inv[r];
+        if constexpr (LN == LN_VEC) return __builtin_fmaf(n, gk, bk);
+        {
+#pragma clang fp contract(off)
+            const float scaled = n * gk;
+            return scaled + bk;
+        }
+    };
     for (int k0 = 0; k0 < a.K; k0 += FK) {
         const int k = threadIdx.x % FK;
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
             const int r = (threadIdx.x + u * 256) / FK;
-            Xs[r][k] = LN ? (xv[u] - mean[r]) * inv[r] * gk + bk : xv[u];
+            Xs[r][k] = operand(xv[u], r);
             Ws[r][k] = wv[u];
         }
         __syncthreads();
@@ -162,9 +202,12 @@ int32_t gemm(int dtype, const GemmArgs &a, hipStream_t st)
     dim3 grid(ceil_div(a.L, FT) * a.B, ceil_div(a.N, FT));
     if (a.ln_g) {
         if (!gemm_f32_takes_ln(a)) return fail(SF_ERR_UNSUPPORTED, "gemm(f32): LayerNorm on a problem that does not take it along");
-        hipLaunchKernelGGL(gemm_f32_kernel<true>, grid, dim3(256), 0, st, a);
+        // as launch_ln() chooses; the launch would write rows of its own that are aligned
+        const bool vec = a.K % 8 == 0 && a.lda % 4 == 0 && !(((uintptr_t)a.A | (uintptr_t)a.ln_g | (uintptr_t)a.ln_b) & 15);
+        if (vec) hipLaunchKernelGGL(gemm_f32_kernel<LN_VEC>, grid, dim3(256), 0, st, a);
+        else hipLaunchKernelGGL(gemm_f32_kernel<LN_ONE>, grid, dim3(256), 0, st, a);
     } else {
-        hipLaunchKernelGGL(gemm_f32_kernel<false>, grid, dim3(256), 0, st, a);
+        hipLaunchKernelGGL(gemm_f32_kernel<LN_NONE>, grid, dim3(256), 0, st, a);
     }
     return SF_OK;
 }

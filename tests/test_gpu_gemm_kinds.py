@@ -8,7 +8,7 @@ import torch
 
 from paper_2604_08971_amd import binding as sf
 from paper_2604_08971_amd import workloads as W
-from gpu_utils import SF_DTYPE, DeviceModel, layernorm_as_launched, to_dev, to_host
+from gpu_utils import SF_DTYPE, DeviceModel, desc_for, layernorm_as_launched, to_dev, to_host
 from helpers import err_metric, make_wl
 from test_gpu_parity import _encoder_parity, _ffn_case, _moe_case, _say
 
@@ -131,6 +131,20 @@ def test_f32_ffn_with_layernorm_along(B, L, d, F):
     ref = torch.relu(xn @ w["W1"].T + w["b1"]) @ w["W2"] + w["b2"]
     torch.cuda.synchronize()
     assert err_metric(to_host(got), ref.cpu().numpy()) <= 8 * 50 * 2.0 ** -24
+
+
+# ... with the bits of the launch: few rows take it along, many (more than 1024 tiles) do not.  Chunks of eight columns of which a lane has
+# one, some lanes none, all four; rows that are no whole chunks, and longer than one, two and three columns per lane
+@pytest.mark.parametrize("d", [24, 64, 200, 256, 36, 250, 190, 100])
+def test_f32_layernorm_along_has_the_bits_of_the_launch(d):
+    _say(f"layernorm along f32 bits d={d}")
+    few, B, L, F = 2, 36, 130, 192
+    wl = make_wl(W.small_spec(dtype="f32", B=B, seg=(L,), extra=0, d=d, Hq=2, Hk=1, dh=8, F=F, nl=1, ffn_keep=1.0, dropout="none", final_ln=False))
+    dm = DeviceModel(wl).build_plan()
+    g = torch.Generator(device="cuda").manual_seed(d)
+    x = torch.randn((B * L, d), generator=g, device="cuda") + 50 * torch.randn((B * L, 1), generator=g, device="cuda")
+    got = [sf.pruned_ffn_forward(desc_for(wl, B=n), dm.layers[0], x[:n * L], dm.pattern_id[:n], True, False)[:few * L] for n in (few, B)]
+    assert int((got[0] != got[1]).sum()) == 0
 
 
 # The router that takes the LayerNorm along: rows of one and two chunks of 512 and just beyond (a launch of its own), up to 8 and 16 experts
