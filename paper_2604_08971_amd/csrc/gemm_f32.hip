@@ -150,7 +150,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a)
 #pragma unroll
         for (int u = 0; u < NL; ++u) {
             const int r = (threadIdx.x + u * 256) / FK;
-            Xs[r][k] = operand(xv[u], r);
+            Xs[r][k] = LN == LN_NONE || k0 + k < a.K ? operand(xv[u], r) : 0.f;       // behind K: no multiple of the mean
             Ws[r][k] = wv[u];
         }
         __syncthreads();

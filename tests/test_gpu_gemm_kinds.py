@@ -147,6 +147,19 @@ def test_f32_layernorm_along_has_the_bits_of_the_launch(d):
     assert int((got[0] != got[1]).sum()) == 0
 
 
+# Behind the last column nothing is added up: a constant row is its mean (2^122: every sum of 24 or 36 is exact), whose multiple by 1 / sqrt(eps)
+# would overflow there, and its output is what the bias of the LayerNorm gives
+@pytest.mark.parametrize("d", [24, 36])
+def test_f32_layernorm_along_of_a_constant_row(d):
+    _say(f"layernorm along f32 constant row d={d}")
+    wl = make_wl(W.small_spec(dtype="f32", B=1, seg=(3,), extra=0, d=d, Hq=2, Hk=1, dh=8, F=64, nl=1, ffn_keep=1.0, dropout="none", final_ln=False))
+    dm = DeviceModel(wl).build_plan()
+    x = torch.zeros((3, d), device="cuda")
+    x[1] = 2.0 ** 122
+    got = sf.pruned_ffn_forward(dm.desc, dm.layers[0], x, dm.pattern_id, True, False)
+    assert bool(torch.isfinite(got).all()) and torch.equal(got[1], got[0])
+
+
 # The router that takes the LayerNorm along: rows of one and two chunks of 512 and just beyond (a launch of its own), up to 8 and 16 experts
 # and beyond, blocks of 16 tokens (one short of full, full, one more) and of 64
 @pytest.mark.parametrize("dtype,B,L,d,E,k", [("bf16", 1, 15, 512, 8, 2), ("f16", 1, 16, 520, 9, 2), ("bf16", 1, 17, 1024, 16, 3), ("f16", 3, 33, 1032, 4, 1),
