@@ -14,6 +14,7 @@
 // stores are 8-byte vectors.  With SWAP = true the roles flip and a lane holds
 // one feature and 4 consecutive tokens: that is the store pattern of the
 // transposed V layout the attention kernels read.
+#include <algorithm>
 #include <atomic>
 
 #include "gemm.hpp"
@@ -306,14 +307,28 @@ static void join_ffn(GemmArgs &up, GemmArgs &down)
 
 // The FFN in one launch against two (and a LayerNorm of its rows), us: 24 576 rows in samples of 384, d 256, 640 channels 34 / 37 (37 / 47);
 // 65 536 rows, d 256, 640 channels 72 / 90 (78 / 115); 65 536 rows, d 512, 1280 channels 196 / 208 (208 / 238); 122 880 in
-// samples of 480, 1024 channels 317 / 345 (338 / 408).  d 256 from half a round on (0.4 of one 1.05, 0.2 1.24).
+// samples of 480, 1024 channels 317 / 345 (338 / 408).  A tile walks its hidden channels alone, 1.9 us per 128 of them at d 128 and
+// 3.3 at d 256 however few tiles there are, where the two launches spread them over columns and K slices: few tiles take few channels.
+// One launch / two, with the LayerNorm:
+//   d 128   channels   256  512  1024  2048  4096        d 256   channels   512  1024  2048  4096  8192
+//    32 tiles         0.77 1.04  1.52  2.27  2.87        128 tiles         0.95  1.12  1.17  1.74  1.89
+//    64               0.72 0.99  1.39  1.81  1.88        160               0.82  0.86  0.99  1.19  1.20
+//    96               0.63 0.81  1.05  1.22  1.51        192               0.75  0.87  0.93  1.15  1.14
+//   128               0.61 0.77  0.97  0.96  1.17        256               0.74  0.73  0.84  1.08  1.03
+//   192               0.56 0.66  0.74  0.87  0.88        320               0.77  0.93  0.84  0.95  0.94
+// (99 tiles of d 256, 448 channels 0.92), without it 0.05 to 0.15 more below 192 tiles.  At d 256 a few compute units with two tiles cost as
+// much as all (GELU, samples of 61 rows: 256 tiles, 2048 channels 0.72, 270 1.18, 300 1.21, 320 1.05, 360 0.94; 1024 channels 1.00 at 270,
+// 1.00 at 300, 0.94 at 330).  Beyond d 256 by how full the rounds are.
 bool ffn_in_one(int dtype, const GemmArgs &up0, const GemmArgs &down0)
 {
     GemmArgs up = up0, down = down0;
     if (dtype != SF_BF16 || !ffn_bf16_rows_eligible(up, down)) return false;
     join_ffn(up, down);
-    const int64_t tiles = row_tiles(down);
-    return down.N == 128 ? tiles >= 32 : down.N == 256 ? tiles >= 128 : rounds_filled(tiles, down.lno_y ? 0.8 : 0.93);
+    const int64_t tiles = row_tiles(down), F = up.N;
+    const bool ln = down.lno_y;
+    if (down.N == 128) return tiles >= 32 && (tiles >= 192 || F <= (ln ? 6 * tiles + 192 : 5 * tiles + 96));
+    if (down.N == 256) return tiles >= 128 && (tiles >= 340 || F <= std::min<int64_t>(tiles > 256 ? 1024 : 2048, 32 * (tiles - (ln ? 112 : 116))));
+    return rounds_filled(tiles, ln ? 0.8 : 0.93);
 }
 
 int32_t ffn_one_launch(const GemmArgs &up0, const GemmArgs &down0, hipStream_t st)
