@@ -16,6 +16,8 @@
 //   -> weighted combination of each token's top_k rows (+ residual).
 // The order of rows inside a segment depends on integer atomics and may vary
 // from run to run; no result depends on it (every row is computed on its own).
+#include <algorithm>
+
 #include "gemm.hpp"
 
 namespace sf {
@@ -70,6 +72,7 @@ __global__ __launch_bounds__(256) void moe_router_kernel(
 #pragma unroll
     for (int z = 0; z < 2; ++z)
         for (int i = blockIdx.x * 256 + threadIdx.x; i < also.n_zero[z]; i += gridDim.x * 256) also.zero[z][i] = 0;
+    if ((int64_t)blockIdx.x * tpb >= rows) return;          // blocks for the zeros only
     extern __shared__ __attribute__((aligned(16))) char router_lds[];
     float *lg = reinterpret_cast<float *>(router_lds);      // [tokens][E + 1]
     const int lgs = E + 1;
@@ -551,9 +554,12 @@ extern "C" int32_t sf_moe_ffn_forward(const sf_desc *desc, const sf_moe_compact 
     const void *xin = X;
     // router, with the LayerNorm where a wave holds a row and the router rows are in LDS
     {
-        // a wave takes its tokens one after the other: few of them where there are not four blocks per compute unit of many
+        // a wave takes its tokens one after the other: 4 instead of 16 where blocks of 64 would be one per compute unit or fewer
         const int tokens = rows <= 256 * TOK_PER_BLOCK ? 16 : TOK_PER_BLOCK;
-        dim3 grid((unsigned)((rows + tokens - 1) / tokens));
+        // The zeros grow with the (pattern, expert) pairs, not with the tokens: at most 16 KB of them per block.  The whole call, d 64,
+        // 16 tokens, 4096 / 1024 pairs: 226 / 79 us with the tokens' own block alone, 98 / 48 so
+        const int n_rows = w.n_blocks_max * SEG_ROWS;
+        dim3 grid(std::max((unsigned)((rows + tokens - 1) / tokens), (unsigned)ceil_div(n_rows, 4096)));
         const size_t wbytes = (size_t)E * D.d * es;
         const size_t lgbytes = ((size_t)TOK_PER_BLOCK * (E + 1) * sizeof(float) + 15) & ~(size_t)15;
         const bool wlds = lgbytes + wbytes <= 64 * 1024;
@@ -567,7 +573,7 @@ extern "C" int32_t sf_moe_ffn_forward(const sf_desc *desc, const sf_moe_compact 
         also.ln_g = (const h16 *)m->ln_g; also.ln_b = (const h16 *)m->ln_b; also.eps = D.eps; also.y = (h16 *)w.xn;
         also.zero[0] = w.counts; also.n_zero[0] = n_seg;
         // rows of padding read token 0 (their results are never used)
-        also.zero[1] = w.src_row; also.n_zero[1] = w.n_blocks_max * SEG_ROWS;
+        also.zero[1] = w.src_row; also.n_zero[1] = n_rows;
         const void *in = along ? X : xin;
 #define SF_ROUTER(T, EB, WLDS, LN)                                                                                    \
     hipLaunchKernelGGL((moe_router_kernel<T, EB, WLDS, LN>), grid, dim3(256), lgbytes + (WLDS ? wbytes : 0), st, (const T *)in, \

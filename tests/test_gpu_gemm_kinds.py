@@ -171,6 +171,16 @@ def test_moe_router_with_layernorm_along(dtype, B, L, d, E, k):
         _moe_case(wl, E, k)
 
 
+# Few tokens and many (pattern, expert) pairs: most of the router's blocks only clear what the sort starts from
+@pytest.mark.parametrize("B,seg,P,E", [(3, (1,) * 6, 64, 16), (40, (2, 1, 1, 2, 1, 2), 40, 5)])
+def test_moe_of_few_tokens_and_many_pairs(B, seg, P, E):
+    _say(f"moe of few tokens B={B} P={P} E={E}")
+    wl = make_wl(W.small_spec(dtype="bf16", B=B, seg=seg, extra=0, d=64, Hq=2, Hk=1, dh=32, F=64, dropout="none"))
+    wl.pattern_bits = np.arange(P)
+    wl.pattern_id = np.random.default_rng(P).integers(0, P, B).astype(np.int32)
+    _moe_case(wl, E, 2)
+
+
 # A LayerNorm that rides along with the router gives the bits of the launch it replaces (17 experts: that launch): the block without one on
 # rows normalised like it.  Means of 30, so that a row's sums decide its last bits.
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
