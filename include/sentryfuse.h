@@ -724,8 +724,9 @@ int32_t sf_budget_search(const sf_desc *desc, const float *g_head, const float *
 enum { SF_KERNEL_GEMM = 0,      /* bf16 MFMA GEMM (all projections and both FFN GEMMs) */
        SF_KERNEL_SCORE = 1,     /* sparsity-score stream (QK^T with running max) */
        SF_KERNEL_ATTEND = 2,    /* active-row attention (Eq. (6)) */
-       SF_KERNEL_ATTENTION = 3 };  /* score, selection, active rows and fill in one launch (short sequences of 16-bit models, see
-                                      sf_sparse_gqa_plan); SCORE and ATTEND see none of it */
+       SF_KERNEL_ATTENTION = 3, /* score, selection, active rows and fill in one launch (short sequences of 16-bit models, see
+                                   sf_sparse_gqa_plan); SCORE and ATTEND see none of it */
+       SF_KERNEL_LAYERNORM = 4 };  /* LayerNorm in a launch of its own (not: in or after a product, in the router, to E4M3) */
 int32_t sf_profile_begin(int32_t kernel_class, int32_t max_launches);
 int32_t sf_profile_end(int32_t *n_launches_host, float *total_ms_host, float *each_ms_host);
 

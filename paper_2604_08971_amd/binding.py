@@ -40,7 +40,7 @@ EXPORTS = ["sf_last_error", "sf_num_active", "sf_ffn_padded", "sf_gate_scores_to
            "sf_encoder_packed_workspace_bytes", "sf_encoder_forward_packed", "sf_sparse_gqa_plan",
            "sf_gemm_kernel"]
 SF_GATE_RELU, SF_GATE_TANH = 0, 1
-SF_KERNEL_GEMM, SF_KERNEL_SCORE, SF_KERNEL_ATTEND, SF_KERNEL_ATTENTION = 0, 1, 2, 3
+SF_KERNEL_GEMM, SF_KERNEL_SCORE, SF_KERNEL_ATTEND, SF_KERNEL_ATTENTION, SF_KERNEL_LAYERNORM = 0, 1, 2, 3, 4
 
 
 class SfDesc(C.Structure):

@@ -261,7 +261,7 @@ extern "C" const char *sf_last_error(void) { return err_buf(); }
 extern "C" int32_t sf_profile_begin(int32_t kernel_class, int32_t max_launches)
 {
     if (g_prof.kernel_class >= 0) return fail(SF_ERR_INVALID_ARG, "profile: already profiling");
-    if (kernel_class < 0 || kernel_class > SF_KERNEL_ATTENTION || max_launches < 1 || max_launches > (1 << 20))
+    if (kernel_class < 0 || kernel_class > SF_KERNEL_LAYERNORM || max_launches < 1 || max_launches > (1 << 20))
         return fail(SF_ERR_INVALID_ARG, "profile: bad kernel class or launch count");
     g_prof.start = new hipEvent_t[max_launches];
     g_prof.stop = new hipEvent_t[max_launches];

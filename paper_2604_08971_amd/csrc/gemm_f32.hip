@@ -354,6 +354,7 @@ void layernorm(int dtype, int x_f32, const void *x, const void *gamma, const voi
                int64_t rows, int d, void *y, hipStream_t st)
 {
     if (rows <= 0) return;
+    ProfScope prof(SF_KERNEL_LAYERNORM, st);
     if (dtype == SF_BF16 && !x_f32) launch_ln<h16, h16, h16>(x, gamma, beta, eps, rows, d, y, st);
     else if (dtype == SF_BF16) launch_ln<float, h16, h16>(x, gamma, beta, eps, rows, d, y, st);
     else launch_ln<float, float, float>(x, gamma, beta, eps, rows, d, y, st);

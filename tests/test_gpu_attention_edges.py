@@ -10,7 +10,7 @@ from oracle import cpu_oracle as orc
 from oracle.packs import err_metric
 from paper_2604_08971_amd import binding as sf
 from paper_2604_08971_amd import workloads as W
-from gpu_utils import to_dev, to_host
+from gpu_utils import SF_DTYPE, to_dev, to_host
 from helpers import make_wl
 from test_gpu_tokens_packed import _packed_case
 from test_gpu_parity import TOL, _encoder_parity, _gqa_case, _say, test_sparse_gqa_parity as gqa_case
@@ -179,6 +179,29 @@ def test_context_where_every_allowed_row_is_active(dtype, B, nH, nG, L, dh):
     with sf.use_half(dtype):
         for kw in (dict(), dict(strided=True)):
             _gqa_case(dtype, B, nH, nG, L, dh, L, True, seed=L, **kw)
+
+
+# ... which does not look at the masked rows of V
+@pytest.mark.parametrize("dtype,token_major", [("bf16", False), ("f16", True)])
+def test_context_leaves_masked_values_alone(dtype, token_major):
+    _say(f"masked values {dtype} token-major={token_major}")
+    B, nH, nG, L, dh = 3, 4, 2, 321, 64
+    g = torch.Generator(device="cuda").manual_seed(6)
+    with sf.use_half(dtype):
+        t = torch.bfloat16 if dtype == "bf16" else torch.float16
+        Q, K, V = (torch.randn((B, n, L, dh), generator=g, device="cuda").to(t) for n in (nH, nG, nG))
+        if token_major:
+            V = V.transpose(1, 2).contiguous().transpose(1, 2)
+        kv = (torch.rand((B, L), generator=g, device="cuda") < 0.6).to(torch.uint8)
+        kv[1] = 0                                                  # no key at all: rows of zeros
+        desc = sf.make_desc(B, L, nH * dh, nH, nG, dh, 64, dtype=SF_DTYPE[dtype], U_override=L)
+        hg = torch.arange(nH, dtype=torch.int32, device="cuda").div(nH // nG, rounding_mode="floor").to(torch.int32).reshape(1, nH)
+        clean = sf.sparse_gqa_forward(desc, Q, K, V, hg, None, kv, want_sel=False)[0]
+        V[(kv == 0)[:, None, :].expand(B, nG, L)] = float("nan")
+        got = sf.sparse_gqa_forward(desc, Q, K, V, hg, None, kv, want_sel=False)[0]
+        torch.cuda.synchronize()
+    got, clean = got[kv == 0], clean[kv == 0]
+    assert bool(torch.isfinite(got).all()) and torch.equal(got, clean) and not bool(got[int((kv[0] == 0).sum()):][:L].any())
 
 
 def test_value_on_an_odd_element():

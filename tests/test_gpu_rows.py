@@ -13,16 +13,21 @@ from paper_2604_08971_amd import workloads as W
 from gpu_utils import DeviceModel
 from helpers import make_wl
 from test_gpu_parity import _encoder_parity, _ffn_case, _say
+from test_gpu_tokens_packed import _packed_case
 
 pytestmark = pytest.mark.gpu
 
 
-def _gemm_launches(run):
+def _launches(kernel_class, run):
     torch.cuda.synchronize()
-    sf.profile_begin(sf.SF_KERNEL_GEMM, 64)
+    sf.profile_begin(kernel_class, 64)
     run()
     torch.cuda.synchronize()
     return sf.profile_end()[0]
+
+
+def _gemm_launches(run):
+    return _launches(sf.SF_KERNEL_GEMM, run)
 
 
 # Each width; one row past a tile and one short of it; hidden channels of one and a half chunks (192 of 128, 384 of 256), of one tile
@@ -49,8 +54,8 @@ def test_ffn_in_one_launch(monkeypatch, dtype, act, B, L, d, F, keep, launches):
     assert counts == [launches] * 2
 
 
-# Two layers and a final LayerNorm: LN2 written by the output projection, the next layer's LN1 and the final one by the FFN (three launches
-# a layer); missing sensors, ragged tiles, no bias to spare
+# Two layers and a final LayerNorm: LN2 written by the output projection, the next layer's LN1 and the final one by the FFN (three GEMM launches
+# a layer, one LayerNorm for the input); missing sensors, ragged tiles, no bias to spare
 @pytest.mark.parametrize("dtype,B,seg,d,Hq,Hk,dh,F", [("bf16", 20, (70, 50, 90), 128, 4, 2, 32, 256), ("f16", 65, (70, 60), 256, 4, 2, 64, 384),
                                                       ("bf16", 103, (70, 50, 90), 384, 6, 2, 64, 512), ("bf16", 103, (99, 80, 61), 512, 8, 2, 64, 640)])
 def test_encoder_writes_its_layernorms_along(dtype, B, seg, d, Hq, Hk, dh, F):
@@ -60,7 +65,7 @@ def test_encoder_writes_its_layernorms_along(dtype, B, seg, d, Hq, Hk, dh, F):
         wl = make_wl(spec)
         dm = DeviceModel(wl).build_plan()
         dm.forward()
-        assert _gemm_launches(lambda: dm.forward()) == 6
+        assert _gemm_launches(dm.forward) == 6 and _launches(sf.SF_KERNEL_LAYERNORM, dm.forward) == 1
         _encoder_parity(wl, samples=[0, B // 2, B - 1])
 
 
@@ -71,8 +76,9 @@ def _first_samples(wl, n):
 # A sample's output does not depend on how many others there are, to the bit: few of them go through separate launches, all of them
 # through the whole-row kernels, whose products and row sums run in the same order.  Two layers, so that LN2, the next layer's LN1 and the
 # final LayerNorm are all written along.  Sizes at which both sides' separate launches would slice K alike and no LayerNorm
-# rides along with the product that reads it (in the last case all do, as they do among few): one chain (d 384, 512); projection and FFN in eight slices, of up to two tiles, up-
-# projection of one chain and sliced; four slices of an odd number of tiles; four in the projection alone.
+# rides along with the product that reads it (in the last case all do, as they do among few): one chain (d 384, 512; the second without
+# biases); projection and FFN in slices, of up to three tiles, up-projection of one chain and sliced; four slices of an odd number of
+# tiles; four in the projection alone.
 @pytest.mark.parametrize("dtype,few,B,L,d,Hq,Hk,dh,F,act,keep,launches", [
     ("bf16", 60, 80, 383, 384, 6, 2, 64, 512, 0, 0.75, (8, 6)), ("f16", 60, 80, 383, 512, 8, 2, 64, 320, 1, 0.75, (8, 6)),
     ("bf16", 74, 75, 50, 128, 8, 1, 32, 640, 0, 0.75, (8, 6)), ("f16", 31, 32, 50, 128, 8, 1, 32, 320, 1, 0.75, (8, 6)),
@@ -90,9 +96,90 @@ def test_same_bits_as_separate_launches(dtype, few, B, L, d, Hq, Hk, dh, F, act,
         wl = dataclasses.replace(wl, x=W.storage_rounding(dtype)(wl.x + np.random.default_rng(L).normal(0, 30, (B, L, 1))))
         got, seen = [], []
         for n in (few, B):
-            dm = DeviceModel(_first_samples(wl, n)).build_plan()
+            dm = DeviceModel(_first_samples(wl, n))
+            if d == 512:
+                dm.dense = [{k: v for k, v in w.items() if k not in ("bq", "bk", "bv", "bo", "b1", "b2")} for w in dm.dense]
+            dm.build_plan()
             dm.forward()
             seen.append(_gemm_launches(lambda: got.append(dm.forward()[0][:few].clone())))
         assert tuple(seen) == launches
         assert bool(torch.isfinite(got[0]).all())
         assert int((got[0] != got[1]).sum()) == 0
+
+
+# One weight set and no pattern numbers: the samples are one long one, and tiles cross their ends.  The same bits as sample by sample (products
+# of one chain on both sides), a last tile of 44 and of 53 rows; and a NaN, an infinity and a value whose square overflows stay
+# in their own sample.
+@pytest.mark.parametrize("dtype,B,L,d,Hq,Hk,dh,F", [("bf16", 100, 131, 256, 4, 2, 64, 320), ("f16", 83, 383, 512, 8, 2, 64, 320)])
+def test_samples_joined(dtype, B, L, d, Hq, Hk, dh, F):
+    _say(f"whole rows of joined samples {dtype} B={B} L={L} d={d}")
+    spec = W.small_spec(dtype=dtype, B=B, seg=(L - 60, 60), extra=0, d=d, Hq=Hq, Hk=Hk, dh=dh, F=F, head_keep=0.5, ffn_keep=1.0, nl=2, dropout="none")
+    with sf.use_half(dtype):
+        dm = DeviceModel(W.make_workload(spec)).build_plan()
+        one_by_one = dm.forward()[0].clone()
+        dm.pattern_id = None
+        assert _gemm_launches(dm.forward) == 6 and _launches(sf.SF_KERNEL_LAYERNORM, dm.forward) == 1
+        joined = dm.forward()[0].clone()
+        assert bool(torch.isfinite(joined).all()) and int((joined != one_by_one).sum()) == 0
+        bad = {B // 3: float("nan"), B // 2: float("inf"), B - 1: 6e4 if dtype == "f16" else 2e38}
+        for b, v in bad.items():
+            dm.x[b, 7, 3] = v
+        Y = dm.forward()[0]
+        others = [b for b in range(B) if b not in bad]
+        assert int((Y[others] != joined[others]).sum()) == 0
+
+
+# Packed rows, whose blocks of 256 may be unused or straddle samples: the widths with one workgroup per compute unit
+@pytest.mark.parametrize("dtype,B,d,Hq", [("bf16", 165, 384, 6), ("bf16", 165, 512, 8)])
+def test_packed_rows(monkeypatch, dtype, B, d, Hq):
+    _say(f"whole rows packed {dtype} B={B} d={d}")
+    run, counts = sf.encoder_forward_packed, []
+
+    def counted(*a, **kw):
+        counts.extend(_launches(c, lambda: run(*a, **kw)) for c in (sf.SF_KERNEL_GEMM, sf.SF_KERNEL_LAYERNORM))
+        return run(*a, **kw)
+
+    monkeypatch.setattr(sf, "encoder_forward_packed", counted)
+    _packed_case(make_wl(W.small_spec(dtype=dtype, d=d, Hq=Hq, Hk=2, dh=64, F=320, seg=(130, 70, 60), B=B, nl=2, dropout="upto:2", c=5)),
+                 samples=[0, B // 2, B - 1])
+    assert counts == [6, 1]
+
+
+# What the whole-row kernels refuse: an output, or the vectors of LN2 or the final LayerNorm, off their 16 bytes.  The launches take over; rows
+# beside the output stay as they are.
+@pytest.mark.parametrize("dtype,B,L,d,dh", [("bf16", 12, 300, 128, 32), ("f16", 80, 383, 512, 64)])
+@pytest.mark.parametrize("what,layernorms", [("Y", 2), ("ln2_g", 2), ("ln2_b", 2), ("final", 2)])
+def test_off_alignment(dtype, B, L, d, dh, what, layernorms):
+    _say(f"whole rows off alignment {what} {dtype} B={B} L={L} d={d}")
+    spec = W.small_spec(dtype=dtype, B=B, seg=(L - 60, 60), extra=0, d=d, Hq=d // dh, Hk=1, dh=dh, F=320, head_keep=0.5, ffn_keep=1.0, nl=1, dropout="none")
+
+    def moved(t, by):
+        buf = torch.full((t.numel() + 16,), 7.0, dtype=t.dtype, device="cuda")
+        v = buf[by:by + t.numel()].view(t.shape)
+        v.copy_(t)
+        return buf, v
+
+    with sf.use_half(dtype):
+        dm = DeviceModel(W.make_workload(spec)).build_plan()
+        assert _launches(sf.SF_KERNEL_LAYERNORM, dm.forward) == 1
+        ref = dm.forward()[0]
+        for by in (1, 4):                                          # 2 and 8 bytes
+            out, hold = None, []
+            if what == "Y":
+                buf, out = moved(ref, by)
+            else:
+                dm = DeviceModel(W.make_workload(spec))
+                vectors = dm.final_ln if what == "final" else dm.dense[0]
+                for n in (("g", "b") if what == "final" else (what,)):
+                    b, vectors[n] = moved(vectors[n], by)
+                    hold.append(b)
+                dm.build_plan()
+            assert _launches(sf.SF_KERNEL_LAYERNORM, lambda: dm.forward(out=out)) == layernorms
+            got = dm.forward(out=out)[0]
+            # the LayerNorm of rows off their alignment adds in another order: one code in some thousand moves by a place, and what a moved
+            # LN2 code moves in the FFN is less than that of the sum
+            place = 2.0 ** (-7 if dtype == "bf16" else -10)
+            diff = (got.float() - ref.float()).abs()
+            assert float((diff / ref.float().abs().clamp(min=1)).max()) <= 2 * place and float((diff != 0).float().mean()) < 0.01
+            if what == "Y":
+                assert bool((buf[:by] == 7).all()) and bool((buf[by + ref.numel():] == 7).all())
