@@ -24,12 +24,14 @@ METRIC = "encoder tokens/sec + sparse-GQA TFLOP/s (% of bf16 MFMA peak), 1 MI355
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA, published
 PEAK_HBM_GBS = 8000.0
 
-# kernel behind each of the five GEMM launches of a layer (large shapes; small ones fall back, see gemm_bf16.hip)
+# kernel behind each of the three to five GEMM launches of a layer (large shapes; small ones fall back, see gemm_bf16.hip)
 GEMM_KERNEL_NAMES = {
     "qkv_proj": "gemm_bf16_ws_kernel<0> (Q/K/V projection, V as the transposed column range)",
     "qk_proj": "gemm_bf16_ws_kernel<0> (Q/K projection)",
     "v_proj": "gemm_bf16_kernel<128, 128, 2, 2, true> (V projection, transposed output)",
-    "o_proj": "gemm_bf16_ws_kernel<0> (output projection + residual), or gemm_pipe_kernel<0> on the active rows only",
+    "o_proj": "gemm_bf16_ws_kernel<0> (output projection + residual), gemm_rows_kernel (with LN2; d up to 512) or gemm_pipe_kernel<0> on "
+              "the active rows only",
+    "ffn": "ffn_rows_kernel (the whole FFN + residual, with the LayerNorm that follows; d up to 512)",
     "ffn_up": "gemm_bf16_ws_kernel<1> (FFN up-projection + ReLU)",
     "ffn_down": "gemm_bf16_ws_kernel<0> (FFN down-projection + residual)",
 }
@@ -258,14 +260,16 @@ def bench_config(name, steps, warmup, extras, cpu, use_graph=False, repeats=1):
                     prof[key]["kv_algorithmic_bytes_per_step"] = kv_bytes
                     prof[key]["kv_GBs"] = kv_bytes * steps / (tot_ms * 1e-3) / 1e9
                     prof[key]["kv_frac_of_hbm_peak"] = prof[key]["kv_GBs"] / PEAK_HBM_GBS
-            if key == "gemm" and n and n % steps == 0 and n // steps in (4 * s.n_layers, 5 * s.n_layers):
+            if key == "gemm" and n and n % steps == 0 and n // steps in (3 * s.n_layers, 4 * s.n_layers, 5 * s.n_layers):
                 # the GEMM launches of a layer, in launch order, averaged over steps and layers: four when the
-                # Q/K/V projection is one launch (large shapes), five when V is projected separately
+                # Q/K/V projection is one launch (large shapes), three when the FFN is one as well, five when V is projected
+                # separately
                 per = n // steps
                 nper = per // s.n_layers
-                names = (["qkv_proj"] if nper == 4 else ["qk_proj", "v_proj"]) + ["o_proj", "ffn_up", "ffn_down"]
+                names = (["qk_proj", "v_proj"] if nper == 5 else ["qkv_proj"]) + ["o_proj"] + (["ffn"] if nper == 3 else ["ffn_up", "ffn_down"])
                 fl = gemm_flops_by_launch(wl, masks_host, oproj_rows)
                 fl["qkv_proj"] = fl["qk_proj"] + fl["v_proj"]
+                fl["ffn"] = fl["ffn_up"] + fl["ffn_down"]
                 by = {}
                 for j, nm in enumerate(names):
                     d = [each[i] for i in range(n) if (i % per) % nper == j]
@@ -604,7 +608,8 @@ def bench_ffn_fp8(wl, dm, steps, warmup):
         for _ in range(steps):
             fn()
         _, _, e = sf.profile_end(each=True)
-        each[name] = [sum(e[i::2]) / len(e[i::2]) * 1e3 for i in range(2)]      # us: up, down
+        per = len(e) // steps                                                   # 1: the whole FFN in one launch
+        each[name] = [sum(e[i::per]) / len(e[i::per]) * 1e3 for i in range(per)]      # us: up, down
     # the whole encoder step with the FFN in FP8 arithmetic (single-layer workloads: one calibrated FFN is all it needs)
     enc = None
     if s.n_layers == 1:
@@ -658,7 +663,7 @@ def bench_ffn_fp8(wl, dm, steps, warmup):
     flop = 2.0 * B * L * d * kf                      # per GEMM, unpadded
     out = {"k_ffn": kf, "ms_block_fp8": ms8, "ms_block_bf16": ms16,
            "gemm_launch_us_fp8": {"ffn_up": each["fp8"][0], "ffn_down": each["fp8"][1]},
-           "gemm_launch_us_bf16": {"ffn_up": each["bf16"][0], "ffn_down": each["bf16"][1]},
+           "gemm_launch_us_bf16": dict(zip(("ffn_up", "ffn_down") if len(each["bf16"]) == 2 else ("ffn",), each["bf16"])),
            "tflops_fp8": {"ffn_up": flop / each["fp8"][0] / 1e6, "ffn_down": flop / each["fp8"][1] / 1e6},
            "frac_of_fp8_peak": {"ffn_up": flop / each["fp8"][0] / 1e6 / 5000.0,
                                 "ffn_down": flop / each["fp8"][1] / 1e6 / 5000.0},

@@ -456,7 +456,10 @@ int32_t sf_pruned_ffn_forward(const sf_desc *desc, const sf_compact_layer *layer
                               size_t workspace_bytes, void *stream);
 
 /* Which GEMM kernel a 16-bit model runs for desc->B samples of desc->L rows, N
- * outputs and K inputs (a reporting aid; host only, nothing is launched): 0 =
+ * outputs and K inputs as a product on its own (a reporting aid; host only, nothing
+ * is launched; with N = 128, 256, 384 or 512 an output projection may be run together
+ * with the LayerNorm that follows it and the two products of an FFN in one launch, by
+ * kernels of their own that sum K in the order of the one named here): 0 =
  * 256 x 256 tiles, 1 = 128 x 128 tiles, 2 / 3 = four / eight K slices, 4 = the
  * kernel for sizes the others refuse.  act 0 none, 1 ReLU, 2 GELU; residual: fp32
  * output added to an fp32 residual; desc->P > 1: each sample has its own weights. */
