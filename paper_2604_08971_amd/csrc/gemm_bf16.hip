@@ -285,9 +285,13 @@ static bool rounds_filled(int64_t tiles, double share) { return tiles >= share *
 
 // The product with the LayerNorm of its rows against the two launches, us: 12 288 rows, N 128, K 64 6.2 / 12.1; 24 576 rows in samples of 384,
 // N 256, K 192 17.3 / 22; 65 536 rows, N 512, K 384 86 / 111; 122 880 in samples of 480, K 256 138 / 193.  Beyond N 256 by how full
-// the rounds are: 1.7 of them 0.86 of the two launches, 1.46 1.00, 1.1 1.09.  Up to N 256 a few tiles take a few steps only, since a
-// tile walks K alone (41 tiles, N 256: K 128 0.81; 34 samples of 53 rows, four layers: 205 us with K 640 so, 192 without), and
-// below 32 tiles the LayerNorm rides along with the product that follows, which costs less than this kernel's epilogue.
+// the rounds are, one line for both widths, where the slower of them is ahead in one round and even in two.  This / two launches, rounds
+// filled 0.63 0.69 0.75 0.81 0.91 1.0 (one) and 0.55 0.63 0.72 0.78 0.86 1.0 (two):
+//   N 384, K 192   1.07 0.87 0.86 0.85 0.85 0.86    1.13 1.08 1.00 0.97 0.95 0.92
+//   N 512, K 320   0.95 0.94 0.91 0.92 0.91 0.90    1.18 1.11 1.04 0.99 0.87 0.80
+// Up to N 256 a few tiles take a few steps only, since a tile walks K alone (N 256, 128 tiles: K 512 0.80, 1024 0.96, 2048 1.25; N 128, 32
+// tiles: K 128 0.80, 512 0.97, 1024 1.18; with the sums of K slices 34 samples of 53 rows, four layers, 205 us with K 640 so, 192
+// without), and below 32 tiles the LayerNorm rides along with the product that follows, which costs less than this kernel's epilogue.
 bool gemm_takes_ln_out(int dtype, const GemmArgs &a0)
 {
     GemmArgs a = a0;
@@ -318,7 +322,11 @@ static void join_ffn(GemmArgs &up, GemmArgs &down)
 //   192               0.56 0.66  0.74  0.87  0.88        320               0.77  0.93  0.84  0.95  0.94
 // (99 tiles of d 256, 448 channels 0.92), without it 0.05 to 0.15 more below 192 tiles.  At d 256 a few compute units with two tiles cost as
 // much as all (GELU, samples of 61 rows: 256 tiles, 2048 channels 0.72, 270 1.18, 300 1.21, 320 1.05, 360 0.94; 1024 channels 1.00 at 270,
-// 1.00 at 300, 0.94 at 330).  Beyond d 256 by how full the rounds are.
+// 1.00 at 300, 0.94 at 330).  Beyond d 256 by how full the rounds are, with one line for both widths, which leaves the narrower one some
+// of its gain.  With the LayerNorm, rounds filled as above:
+//   d 384,  960 channels   0.96 0.78 0.70 0.71 0.71 0.69    0.98 0.89 0.84 0.77 0.76 0.71
+//   d 512, 1280 channels   0.90 0.91 0.87 0.82 0.80 0.79    1.08 0.97 0.97 0.95 0.87 0.87
+// and without it 1.03 0.81 0.73 0.74 0.74 0.73, 1.04 0.95 0.90 0.83 0.81 0.76 and 0.94 0.97 0.93 0.87 0.84 0.85, 1.14 1.02 1.04 1.01 0.93 0.95.
 bool ffn_in_one(int dtype, const GemmArgs &up0, const GemmArgs &down0)
 {
     GemmArgs up = up0, down = down0;
