@@ -292,10 +292,13 @@ __global__ __launch_bounds__(NT) void select_kernel(
     __shared__ float ctx[256];
     if (fill.part && threadIdx.x < fill.dh) {                   // with a key mask only: its count orders these writes
         const float *p = fill.part + ((int64_t)b * fill.nG + HeadFill<NT, VEC, T>::group(fill, b, h)) * fill.parts * fill.dh + threadIdx.x;
-        float s = 0.f;
-#pragma unroll 8
-        for (int i = 0; i < fill.parts; ++i) s += p[(int64_t)i * fill.dh];
-        ctx[threadIdx.x] = s;
+        // in eight chains: one of 28 (1777 keys of mean 1) errs by 6.8e-8 of the sum, these by 2.9e-8, the statistics launch by 4.9e-8
+        float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < fill.parts; i += 8) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) s[k] += i + k < fill.parts ? p[(int64_t)(i + k) * fill.dh] : 0.f;
+        }
+        ctx[threadIdx.x] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
     }
     const bool no_key = sc.n > 1 && sc.n_keys[b] == 0;
     int c = 0;
