@@ -13,8 +13,8 @@
 // of them loads, with 128-byte rows 75-115, since the L2 moves whole lines.
 //
 // Bits: products, row sums and roundings run in the order of the launches that these replace (K in slices where gemm() would slice it, a
-// row as layernorm_vec_kernel adds it), so that a sample's output does not depend on which of them its batch takes.  What that costs:
-// 1 % of an encoder of d 128 where K is sliced, nothing measurable elsewhere.
+// row as layernorm_vec_kernel adds it), so that a sample's output does not depend on which of them its batch takes.  What that costs
+// against a free order: 1 % of an encoder of d 128 where K is sliced, 0.7 % of one of d 512 (128 x 512 rows, six layers 2787 / 2808 us).
 #include <atomic>
 #include <type_traits>
 
@@ -333,8 +333,7 @@ __device__ __forceinline__ void join(f32x16 (&acc)[TN][TM], f32x16 (&slice)[TN][
 // (64 * TM) x (128 * TN) tile; a wave owns 32 * TM rows of TN tiles of 32 columns, 128 apart.  Two buffers: the operands of a step
 // are on their way while the step before is multiplied.
 template <int TM, int TN, bool SL>
-__global__ __launch_bounds__(64 * NWV, TN <= 2 ? 4 : 2)
-void gemm_rows_kernel(GemmArgs a, int slices, int tiles_m, int total_tiles, int per_xcd)
+__device__ __forceinline__ void gemm_rows(const GemmArgs &a, int slices, int tiles_m, int total_tiles, int per_xcd)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int BM = 64 * TM, BN = 128 * TN, BUF = (TM + 2 * TN) * PIECE;      // X, then W
@@ -387,6 +386,16 @@ void gemm_rows_kernel(GemmArgs a, int slices, int tiles_m, int total_tiles, int 
     finish_rows(a, t, acc, smem);
 #endif
 }
+template <int TM, int TN>
+__global__ __launch_bounds__(64 * NWV, TN <= 2 ? 4 : 2) void gemm_rows_kernel(GemmArgs a, int tiles_m, int total_tiles, int per_xcd)
+{
+    gemm_rows<TM, TN, false>(a, 1, tiles_m, total_tiles, per_xcd);
+}
+template <int TM, int TN>
+__global__ __launch_bounds__(64 * NWV, 4) void gemm_rows_sliced_kernel(GemmArgs a, int slices, int tiles_m, int total_tiles, int per_xcd)
+{
+    gemm_rows<TM, TN, true>(a, slices, tiles_m, total_tiles, per_xcd);
+}
 
 // The whole FFN of a row block: H = act(xn W1^T + b1) is formed in chunks of HC hidden channels, which stay in LDS as the second
 // product's operand: the hidden activations (2.5 KB a row, written and read again by two launches) never reach memory.
@@ -400,8 +409,7 @@ constexpr size_t ffn_buf(int TM, int TN, int TH) { return at_least(TM + 2 * TH, 
 constexpr size_t ffn_lds(int TM, int TN, int TH) { return (size_t)TM * TH * 16384 + 2 * ffn_buf(TM, TN, TH); }
 
 template <int TM, int TN, int TH, int ACT, bool SL>
-__global__ __launch_bounds__(64 * NWV, TH == 2 || (SL && TN == 2) ? 2 : 4)
-void ffn_rows_kernel(GemmArgs a, FfnUp u, int tiles_m, int total_tiles, int per_xcd)
+__device__ __forceinline__ void ffn_rows(const GemmArgs &a, const FfnUp &u, int tiles_m, int total_tiles, int per_xcd)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int BM = 64 * TM, BN = 128 * TN, HC = 128 * TH, HT = BM * SK * 2;      // HT: bytes of 64 channels of H
@@ -523,6 +531,16 @@ void ffn_rows_kernel(GemmArgs a, FfnUp u, int tiles_m, int total_tiles, int per_
     finish_rows(a, t, acc, smem);
 #endif
 }
+template <int TM, int TN, int TH, int ACT>
+__global__ __launch_bounds__(64 * NWV, TH == 2 ? 2 : 4) void ffn_rows_kernel(GemmArgs a, FfnUp u, int tiles_m, int total_tiles, int per_xcd)
+{
+    ffn_rows<TM, TN, TH, ACT, false>(a, u, tiles_m, total_tiles, per_xcd);
+}
+template <int TM, int TN, int TH, int ACT>
+__global__ __launch_bounds__(64 * NWV, TN == 2 ? 2 : 4) void ffn_rows_sliced_kernel(GemmArgs a, FfnUp u, int tiles_m, int total_tiles, int per_xcd)
+{
+    ffn_rows<TM, TN, TH, ACT, true>(a, u, tiles_m, total_tiles, per_xcd);
+}
 
 template <class Kern, class... Extra>
 int32_t launch(Kern kern, std::atomic<bool> &attr_set, size_t lds, int bm, const GemmArgs &a, hipStream_t st, Extra... extra)
@@ -542,14 +560,18 @@ template <int TM, int TN, bool SL>
 int32_t launch_rows(const GemmArgs &a, int slices, hipStream_t st)
 {
     static std::atomic<bool> set{false};
-    return launch(gemm_rows_kernel<TM, TN, SL>, set, at_least((size_t)2 * (TM + 2 * TN) * PIECE, after_of(TM)), 64 * TM, a, st, slices);
+    constexpr size_t lds = at_least((size_t)2 * (TM + 2 * TN) * PIECE, after_of(TM));
+    if constexpr (SL) return launch(gemm_rows_sliced_kernel<TM, TN>, set, lds, 64 * TM, a, st, slices);
+    else return launch(gemm_rows_kernel<TM, TN>, set, lds, 64 * TM, a, st);
 }
 
 template <int TM, int TN, int TH, int ACT, bool SL>
 int32_t launch_ffn(const GemmArgs &a, const FfnUp &u, hipStream_t st)
 {
     static std::atomic<bool> set{false};
-    return launch(ffn_rows_kernel<TM, TN, TH, ACT, SL>, set, at_least(ffn_lds(TM, TN, TH), after_of(TM)), 64 * TM, a, st, u);
+    constexpr size_t lds = at_least(ffn_lds(TM, TN, TH), after_of(TM));
+    if constexpr (SL) return launch(ffn_rows_sliced_kernel<TM, TN, TH, ACT>, set, lds, 64 * TM, a, st, u);
+    else return launch(ffn_rows_kernel<TM, TN, TH, ACT>, set, lds, 64 * TM, a, st, u);
 }
 
 template <int ACT>

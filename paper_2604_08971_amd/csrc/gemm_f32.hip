@@ -31,7 +31,7 @@ constexpr int FLN = 256;    // longest row whose LayerNorm the product takes alo
 // 16 different 16-byte slots of LDS (rows of 272 bytes).  Small problems are a chain of memory round trips, one per K step: a step
 // is 64 of K, all 16 loads of a thread are in flight before the first is used, and those of the next step are issued before this one's
 // products.  Four values of K per LDS read; every sum runs over K in order.  2 samples of 48 rows, N 64 to 128, K 32 to 128: 6.1-7.2 us
-// with single values, 4.6-7.0 now (the small encoder of those 43.9 -> 38.9 us with the LayerNorms along).
+// with single values, 4.6-7.0 now (the small encoder of those 43.7 -> 37.1 us with the LayerNorms along).
 // LN: the rows of A come unnormalised.  Eight threads hold a row (K <= FLN) and take mean and deviations from loads that are in
 // flight with the first step's; every column of tiles does so again, which costs less than the launch it replaces (3.2 us) while there
 // are few of them.  Thread c of the eight stands for lanes c, c + 8, .. of the launch and adds in its order, so that both give the

@@ -26,8 +26,8 @@ def test_two_workgroups_of_the_staged_active_pass(half, tmp_path):
     assert found == 2
 
 
-# The whole-row kernels: 64-row tiles share a compute unit (sixteen waves, 128 registers; not the FFN of 256 columns with a sum per K slice),
-# and only the widest FFN spills, ten registers a lane and chunk of channels
+# The whole-row kernels: 64-row tiles share a compute unit (sixteen waves, 128 registers), and only the widest FFN spills, ten registers
+# a lane and chunk of channels
 @pytest.mark.parametrize("half", ["bf16", "f16"])
 def test_whole_row_kernels(half, tmp_path):
     cmd = ["hipcc"] + build.FLAGS + (["-DSF_HALF_F16"] if half == "f16" else []) + ["--cuda-device-only", "-Rpass-analysis=kernel-resource-usage",
@@ -36,12 +36,29 @@ def test_whole_row_kernels(half, tmp_path):
     assert r.returncode == 0, r.stderr
     found = 0
     for part in r.stderr.split("Function Name: ")[1:]:
-        m = re.match(r"\S*(gemm|ffn)_rows_kernelILi(\d)ELi(\d)E\S*?Lb(\d)E", part)
+        m = re.match(r"\S*(gemm|ffn)_rows_kernelILi(\d)ELi(\d)E", part)
         if m:
             total = sum(int(re.search(rf" {n}: (\d+)", part).group(1)) for n in ("VGPRs", "AGPRs"))
             scratch = int(re.search(r"ScratchSize \[bytes/lane\]: (\d+)", part).group(1))
-            alone = m.group(2) == "2" or m.groups() == ("ffn", "1", "2", "1")
-            assert total <= (256 if alone else 128), part.split("\n")[0]
-            assert scratch <= (40 if m.groups()[:3] == ("ffn", "2", "4") else 0), part.split("\n")[0]
+            assert total <= (128 if m.group(2) == "1" else 256), part.split("\n")[0]
+            assert scratch <= (40 if m.groups() == ("ffn", "2", "4") else 0), part.split("\n")[0]
             found += 1
-    assert found == 18
+    assert found == 12
+
+
+# Those that keep a sum per K slice: no scratch, and two workgroups per compute unit but for the FFN of 256 columns
+@pytest.mark.parametrize("half", ["bf16", "f16"])
+def test_whole_row_kernels_with_k_slices(half, tmp_path):
+    cmd = ["hipcc"] + build.FLAGS + (["-DSF_HALF_F16"] if half == "f16" else []) + ["--cuda-device-only", "-Rpass-analysis=kernel-resource-usage",
+           "-c", os.path.join(build.CSRC, "gemm_bf16_rows.hip"), "-o", str(tmp_path / "a.o")]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    found = 0
+    for part in r.stderr.split("Function Name: ")[1:]:
+        m = re.match(r"\S*(gemm|ffn)_rows_sliced_kernelILi1ELi(\d)E", part)
+        if m:
+            total = sum(int(re.search(rf" {n}: (\d+)", part).group(1)) for n in ("VGPRs", "AGPRs"))
+            assert total <= (256 if m.groups() == ("ffn", "2") else 128), part.split("\n")[0]
+            assert re.search(r"ScratchSize \[bytes/lane\]: 0 ", part), part.split("\n")[0]
+            found += 1
+    assert found == 6
