@@ -282,6 +282,14 @@ bool gemm_takes_ln(int dtype, const GemmArgs &a0)
 // round that is not full costs nearly a whole one.
 static int64_t row_tiles(const GemmArgs &a) { return a.B * (int64_t)ceil_div(a.L, a.N <= 256 ? 64 : 128); }
 static bool rounds_filled(int64_t tiles, double share) { return tiles >= share * 256 * ((tiles + 255) / 256); }
+// Whole rows give the bits of the kernel that gemm() takes for the product on its own: beyond N 256 there are no registers for a sum per K
+// slice (a batch of many short samples, whose 128-row tiles are mostly empty, would be sliced).
+static bool rows_keep_bits(const GemmArgs &a0, int64_t N)
+{
+    GemmArgs a = a0;
+    const GemmKind kind = choose(a);
+    return kind == GEMM_WS || kind == GEMM_PIPE || (N <= 256 && kind != GEMM_GENERIC);
+}
 
 // The product with the LayerNorm of its rows against the two launches, us: 12 288 rows, N 128, K 64 6.2 / 12.1; 24 576 rows in samples of 384,
 // N 256, K 192 17.3 / 22; 65 536 rows, N 512, K 384 86 / 111; 122 880 in samples of 480, K 256 138 / 193.  Beyond N 256 by how full
@@ -298,6 +306,7 @@ bool gemm_takes_ln_out(int dtype, const GemmArgs &a0)
     if (dtype != SF_BF16 || !gemm_bf16_rows_eligible(a)) return false;
     join_samples(a);
     const int64_t tiles = row_tiles(a);
+    if (!rows_keep_bits(a0, a.N)) return false;
     return a.N <= 256 ? tiles >= 32 && a.K <= (a.N == 128 ? 4 : 2) * tiles + 64 : rounds_filled(tiles, 0.77);
 }
 
@@ -332,6 +341,7 @@ bool ffn_in_one(int dtype, const GemmArgs &up0, const GemmArgs &down0)
     GemmArgs up = up0, down = down0;
     if (dtype != SF_BF16 || !ffn_bf16_rows_eligible(up, down)) return false;
     join_ffn(up, down);
+    if (!rows_keep_bits(up, down.N) || !rows_keep_bits(down, down.N)) return false;
     const int64_t tiles = row_tiles(down), F = up.N;
     const bool ln = down.lno_y;
     if (down.N == 128) return tiles >= 32 && (tiles >= 192 || F <= (ln ? 6 * tiles + 192 : 5 * tiles + 96));

@@ -99,13 +99,13 @@ def _first_samples(wl, n):
 # final LayerNorm are all written along.  Sizes at which both sides' separate launches would slice K alike and no LayerNorm
 # rides along with the product that reads it (in the last case all do, as they do among few): one chain (d 384, 512; the second without
 # biases); projection and FFN in slices, of up to three tiles, up-projection of one chain and sliced; four slices of an odd number of
-# tiles; four in the projection alone.
+# tiles; four in the projection alone; short samples of d 384, which are sliced, for which the wide tiles have no registers.
 @pytest.mark.parametrize("dtype,few,B,L,d,Hq,Hk,dh,F,act,keep,launches", [
     ("bf16", 60, 80, 383, 384, 6, 2, 64, 512, 0, 0.75, (8, 6)), ("f16", 60, 80, 383, 512, 8, 2, 64, 320, 1, 0.75, (8, 6)),
     ("bf16", 74, 75, 50, 128, 8, 1, 32, 640, 0, 0.75, (8, 6)), ("f16", 31, 32, 50, 128, 8, 1, 32, 320, 1, 0.75, (8, 6)),
     ("bf16", 127, 128, 61, 256, 8, 1, 32, 448, 1, 0.25, (8, 6)), ("f16", 127, 128, 50, 256, 8, 1, 32, 256, 0, 0.25, (8, 6)),
     ("bf16", 127, 128, 50, 256, 8, 1, 32, 192, 1, 0.25, (8, 6)), ("bf16", 63, 64, 50, 256, 8, 1, 32, 192, 0, 0.75, (8, 8)),
-    ("bf16", 31, 32, 50, 128, 8, 1, 32, 64, 0, 0.25, (8, 8)),
+    ("bf16", 31, 32, 50, 128, 8, 1, 32, 64, 0, 0.25, (8, 8)), ("f16", 180, 220, 35, 384, 6, 2, 64, 2048, 0, 0.75, (8, 8)),
 ])
 def test_same_bits_as_separate_launches(dtype, few, B, L, d, Hq, Hk, dh, F, act, keep, launches):
     _say(f"bits of whole rows {dtype} few={few} B={B} L={L} d={d} F={F}")
