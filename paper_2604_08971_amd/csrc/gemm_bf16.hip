@@ -281,6 +281,8 @@ bool gemm_takes_ln(int dtype, const GemmArgs &a0)
 // Row tiles of gemm_bf16_rows.hip: 64 rows and two workgroups per compute unit up to N 256, 128 rows and one beyond, where a last
 // round that is not full costs nearly a whole one.
 static int64_t row_tiles(const GemmArgs &a) { return a.B * (int64_t)ceil_div(a.L, a.N <= 256 ? 64 : 128); }
+// Share of their rows that are there: short samples with weights of their own leave most of a tile empty
+static double tile_fill(const GemmArgs &a) { return (double)a.B * a.L / (row_tiles(a) * (a.N <= 256 ? 64. : 128.)); }
 static bool rounds_filled(int64_t tiles, double share) { return tiles >= share * 256 * ((tiles + 255) / 256); }
 // Whole rows give the bits of the kernel that gemm() takes for the product on its own: beyond N 256 there are no registers for a sum per K
 // slice (a batch of many short samples, whose 128-row tiles are mostly empty, would be sliced).
@@ -300,14 +302,19 @@ static bool rows_keep_bits(const GemmArgs &a0, int64_t N)
 // Up to N 256 a few tiles take a few steps only, since a tile walks K alone (N 256, 128 tiles: K 512 0.80, 1024 0.96, 2048 1.25; N 128, 32
 // tiles: K 128 0.80, 512 0.97, 1024 1.18; with the sums of K slices 34 samples of 53 rows, four layers, 205 us with K 640 so, 192
 // without), and below 32 tiles the LayerNorm rides along with the product that follows, which costs less than this kernel's epilogue.
+// An empty row costs a tile here what a full one does, the smaller tiles and K slices of gemm() less.  A layer without / with this, us:
+// 253 samples of 18 rows, d 512, K 768 117 / 132; 227 of 67 rows, d 384, K 128 73 / 80; 160 of 12 rows, d 256, K 192 39.6 / 40.9.  Of 408
+// layers drawn at random (samples of 8 to 700 rows) 34 took over 2 % longer, the worst 1.13, and of the 336 that a bound on the empty rows
+// leaves 5, the worst 1.03.
 bool gemm_takes_ln_out(int dtype, const GemmArgs &a0)
 {
     GemmArgs a = a0;
     if (dtype != SF_BF16 || !gemm_bf16_rows_eligible(a)) return false;
     join_samples(a);
     const int64_t tiles = row_tiles(a);
-    if (!rows_keep_bits(a0, a.N)) return false;
-    return a.N <= 256 ? tiles >= 32 && a.K <= (a.N == 128 ? 4 : 2) * tiles + 64 : rounds_filled(tiles, 0.77);
+    if (tile_fill(a) < (a.N <= 256 ? 0.25 : 0.75)) return false;
+    if (a.N <= 256 ? tiles < 32 || a.K > (a.N == 128 ? 4 : 2) * tiles + 64 : !rounds_filled(tiles, 0.77)) return false;
+    return rows_keep_bits(a0, a.N);
 }
 
 // Both products see the samples joined where the up-projection does
@@ -329,10 +336,16 @@ static void join_ffn(GemmArgs &up, GemmArgs &down)
 //    96               0.63 0.81  1.05  1.22  1.51        192               0.75  0.87  0.93  1.15  1.14
 //   128               0.61 0.77  0.97  0.96  1.17        256               0.74  0.73  0.84  1.08  1.03
 //   192               0.56 0.66  0.74  0.87  0.88        320               0.77  0.93  0.84  0.95  0.94
-// (99 tiles of d 256, 448 channels 0.92), without it 0.05 to 0.15 more below 192 tiles.  At d 256 a few compute units with two tiles cost as
-// much as all (GELU, samples of 61 rows: 256 tiles, 2048 channels 0.72, 270 1.18, 300 1.21, 320 1.05, 360 0.94; 1024 channels 1.00 at 270,
-// 1.00 at 300, 0.94 at 330).  Beyond d 256 by how full the rounds are, with one line for both widths, which leaves the narrower one some
-// of its gain.  With the LayerNorm, rounds filled as above:
+// (ReLU, full tiles; without the LayerNorm 0.05 to 0.15 more below 192 tiles).  GELU stands between the two products here and costs as much
+// as a third more channels; a tile with empty rows costs what a full one does, where the separate launches have smaller tiles: both are
+// counted as channels.  us, two launches / one: 247 samples of 24 rows, d 512, 3776 channels, GELU 90 / 244; 227 of 9 rows, d 128, 2048 channels 16 / 49;
+// 189 of 31, d 256, 1408 channels 28 / 45.  At d 256 a few compute units with two tiles, and a few with two more, cost as much as all:
+// 60 samples of 646 rows (660 tiles), 3904 channels 292 / 325; 33 072 rows (517 tiles), 2112 channels 150 / 169; 91 samples of 195 rows (364), 896
+// channels 50 / 57 (all GELU).  Of 1169 calls and layers
+// drawn at random (samples of 8 to 700 rows, 64 to 4096 channels) 165 took over 2 % longer by the tiles alone, the worst 3.1 times as long; of the
+// 813 that these bounds leave 12, the worst 1.06.
+// Beyond d 256 by how full the rounds are, with one line for both widths, which leaves the narrower one some of its gain.  With the
+// LayerNorm, rounds filled as above:
 //   d 384,  960 channels   0.96 0.78 0.70 0.71 0.71 0.69    0.98 0.89 0.84 0.77 0.76 0.71
 //   d 512, 1280 channels   0.90 0.91 0.87 0.82 0.80 0.79    1.08 0.97 0.97 0.95 0.87 0.87
 // and without it 1.03 0.81 0.73 0.74 0.74 0.73, 1.04 0.95 0.90 0.83 0.81 0.76 and 0.94 0.97 0.93 0.87 0.84 0.85, 1.14 1.02 1.04 1.01 0.93 0.95.
@@ -341,12 +354,20 @@ bool ffn_in_one(int dtype, const GemmArgs &up0, const GemmArgs &down0)
     GemmArgs up = up0, down = down0;
     if (dtype != SF_BF16 || !ffn_bf16_rows_eligible(up, down)) return false;
     join_ffn(up, down);
-    if (!rows_keep_bits(up, down.N) || !rows_keep_bits(down, down.N)) return false;
-    const int64_t tiles = row_tiles(down), F = up.N;
-    const bool ln = down.lno_y;
-    if (down.N == 128) return tiles >= 32 && (tiles >= 192 || F <= (ln ? 6 * tiles + 192 : 5 * tiles + 96));
-    if (down.N == 256) return tiles >= 128 && (tiles >= 340 || F <= std::min<int64_t>(tiles > 256 ? 1024 : 2048, 32 * (tiles - (ln ? 112 : 116))));
-    return rounds_filled(tiles, ln ? 0.8 : 0.93);
+    const int64_t tiles = row_tiles(down);
+    const bool ln = down.lno_y, gelu = up.act == ACT_GELU;
+    const double fill = tile_fill(down), F = up.N * (gelu ? 4. / 3 : 1.) / fill;
+    if (fill < (down.N <= 256 ? 1. / 3 : 0.5)) return false;
+    if (down.N == 128) {
+        if (tiles < 32 || F > (tiles > 256 ? 4096 : tiles >= 192 ? 2048 : ln ? 6 * tiles + 192 : 5 * tiles + 96)) return false;
+    } else if (down.N == 256) {
+        const int64_t one_round = std::min<int64_t>(2048, ln ? 20 * (tiles - 104) : 32 * (tiles - 116));
+        const int64_t more = tiles < (gelu ? 400 : 340) ? 1365 : tiles > 512 && tiles <= 640 ? 1792 : 2816;
+        if (tiles < 128 || F > (tiles > 256 ? more : one_round)) return false;
+    } else if (!rounds_filled(tiles, ln ? 0.8 : 0.93) || F / fill > 3840 || (fill < 0.6 && F > 1536)) {
+        return false;
+    }
+    return rows_keep_bits(up, down.N) && rows_keep_bits(down, down.N);
 }
 
 int32_t ffn_one_launch(const GemmArgs &up0, const GemmArgs &down0, hipStream_t st)
