@@ -10,22 +10,24 @@ namespace {
 
 // 64 tokens x 64 features per block through LDS, 16 bytes per lane on both sides: 8 features of a token on the way
 // in, 8 tokens of a feature on the way out (ld, col0, ncols, Lp multiples of 8).
-// sums.part: the block also leaves the sums of its allowed tokens, feature by feature, which the mean of V is made of: the tile is in
+// SUMS: the block also leaves the sums of its allowed tokens, feature by feature, which the mean of V is made of: the tile is in
 // LDS already, where a pass of its own over V and one that joins its ranges were 11 us of a call (8 samples of 1777 keys, 4 groups).
+// Calls without a mask do not carry it along (8 samples of 380 keys, one head: 22.7 us with it, 22.4 without).
+template <bool SUMS>
 __global__ __launch_bounds__(256) void transpose_v_kernel(const h16 *__restrict__ src, int64_t ld, int col0, int ncols,
                                                           int L, int Lp, h16 *__restrict__ vt,
                                                           const int32_t *__restrict__ row0, VSums sums)
 {
     __shared__ uint16_t tile[64][66];                          // row stride 33 words: the column reads spread over the banks
-    __shared__ float quarter[4][64];
+    [[maybe_unused]] __shared__ float quarter[4][64];
     const int b = blockIdx.z, j0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
     // row0: samples packed back to back (sample b starts at row row0[b]); the transposed copy stays b-strided
     const uint16_t *s = reinterpret_cast<const uint16_t *>(src) + (row0 ? (int64_t)row0[b] : (int64_t)b * L) * ld + col0;
     uint16_t *dst = reinterpret_cast<uint16_t *>(vt) + (int64_t)b * ncols * Lp;
     const int ch = threadIdx.x & 7, r = threadIdx.x >> 3;      // 8 chunks x 32 rows per pass
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, per = sums.part ? ncols / sums.dh : 1;     // per: groups in a row of src
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, per = SUMS ? ncols / sums.dh : 1;          // per: groups in a row of src
     unsigned long long allowed = 0;                            // bit i: token j0 + i
-    if (sums.part) allowed = __ballot(j0 + lane < L && sums.key_valid[(int64_t)(b * per / sums.nG) * L + j0 + lane]);
+    if constexpr (SUMS) allowed = __ballot(j0 + lane < L && sums.key_valid[(int64_t)(b * per / sums.nG) * L + j0 + lane]);
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
         const int jj = r + pass * 32, j = j0 + jj, c = c0 + ch * 8;
@@ -45,20 +47,21 @@ __global__ __launch_bounds__(256) void transpose_v_kernel(const h16 *__restrict_
             w[k] = (uint32_t)tile[ch * 8 + 2 * k][cc] | ((uint32_t)tile[ch * 8 + 2 * k + 1][cc] << 16);
         *reinterpret_cast<uint4 *>(dst + (int64_t)c * Lp + j) = make_uint4(w[0], w[1], w[2], w[3]);
     }
-    if (!sums.part) return;
-    // wave w: tokens 16 w .. 16 w + 15 of feature c0 + lane; a select, since masked rows may hold anything
-    float sum = 0.f;
+    if constexpr (SUMS) {
+        // wave w: tokens 16 w .. 16 w + 15 of feature c0 + lane; a select, since masked rows may hold anything
+        float sum = 0.f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const float v = (float)__builtin_bit_cast(h16, tile[wave * 16 + i][lane]);
-        sum += (allowed >> (wave * 16 + i)) & 1u ? v : 0.f;
+        for (int i = 0; i < 16; ++i) {
+            const float v = (float)__builtin_bit_cast(h16, tile[wave * 16 + i][lane]);
+            sum += (allowed >> (wave * 16 + i)) & 1u ? v : 0.f;
+        }
+        quarter[wave][lane] = sum;
+        __syncthreads();
+        const int c = c0 + lane;
+        if (wave == 0 && c < ncols)
+            sums.part[((int64_t)(b * per + c / sums.dh) * gridDim.x + blockIdx.x) * sums.dh + c % sums.dh] =
+                (quarter[0][lane] + quarter[1][lane]) + (quarter[2][lane] + quarter[3][lane]);
     }
-    quarter[wave][lane] = sum;
-    __syncthreads();
-    const int c = c0 + lane;
-    if (wave == 0 && c < ncols)
-        sums.part[((int64_t)(b * per + c / sums.dh) * gridDim.x + blockIdx.x) * sums.dh + c % sums.dh] =
-            (quarter[0][lane] + quarter[1][lane]) + (quarter[2][lane] + quarter[3][lane]);
 }
 
 // codes[r, c] = E4M3(x[r, c] * inv_scale) for c < K, 0 for K <= c < Kp: rows of a bf16 matrix into code rows padded to
@@ -95,8 +98,12 @@ void transpose_v(const void *src, int64_t ld, int col0, int ncols, int B, int L,
 {
     if (B == 0 || ncols == 0) return;
     dim3 grid((unsigned)ceil_div(Lp, 64), (unsigned)ceil_div(ncols, 64), (unsigned)B);
-    hipLaunchKernelGGL(transpose_v_kernel, grid, dim3(256), 0, st, (const h16 *)src, ld, col0, ncols, L, Lp,
-                       (h16 *)vt, row0, sums);
+    if (sums.part)
+        hipLaunchKernelGGL(transpose_v_kernel<true>, grid, dim3(256), 0, st, (const h16 *)src, ld, col0, ncols, L, Lp,
+                           (h16 *)vt, row0, sums);
+    else
+        hipLaunchKernelGGL(transpose_v_kernel<false>, grid, dim3(256), 0, st, (const h16 *)src, ld, col0, ncols, L, Lp,
+                           (h16 *)vt, row0, sums);
 }
 
 int32_t proj_fp8_check(const char *who, const Dims &D, const sf_proj_fp8 *p, int k_head)
