@@ -50,6 +50,28 @@ template <> struct Vec16<h16> {
 // lane per token: Top-k and the softmax over the chosen logits.
 constexpr int TOK_PER_BLOCK = 64;
 
+// The steps of the router's transposing reduction inside rows of 16 lanes: N partial sums a lane, exchanged with lane ^ O.  N and O are
+// constants, so that the sums are never looked up by a number that the compiler does not know: 64 of them then live in scratch memory
+// (34 158 tokens of d 256, 32 experts: 348 us so, 316 with exchanges through LDS alone, 82 now; 17 experts, 19 040 of d 512 233 / 60).
+template <int N, int O, int EB>
+__device__ __forceinline__ void fold_rows(float (&acc)[EB], int lane)
+{
+    if constexpr (N > 1) {
+        const bool up = (lane & O) != 0;
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i) {
+            const float send = up ? acc[i] : acc[i + N / 2];
+            const float keep = up ? acc[i + N / 2] : acc[i];
+            acc[i] = keep + (O == 8 ? __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(send), 0x128, 0xf, 0xf, false))
+                                    : __shfl_xor(send, O));
+        }
+        if constexpr (O > 1) fold_rows<N / 2, O / 2>(acc, lane);
+    } else {
+        acc[0] = O == 2 || O == 1 ? pair_sum<O>(acc[0]) : acc[0] + __shfl_xor(acc[0], O);
+        if constexpr (O > 1) fold_rows<1, O / 2>(acc, lane);
+    }
+}
+
 // What the launch does besides: the LayerNorm of the rows (16-bit, d % 8 == 0, d <= 512 * LN), as layernorm_vec_kernel computes it, for
 // which the rows come unnormalised in `xn` and go to `y` (a row is in the wave's registers anyway; the next one is on its way
 // meanwhile); and the zeros that the sort of the pairs starts from.  What bounds it is memory then.  65 536 tokens of d 768, 8
@@ -206,25 +228,7 @@ __global__ __launch_bounds__(256) void moe_router_kernel(
             const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[i]), __float_as_uint(acc[i + EB / 4]), false, false);
             acc[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
         }
-        int n = EB / 4;
-#pragma unroll
-        for (int o = 8; o > 0; o >>= 1) {
-            if (n > 1) {
-                n >>= 1;
-                const bool up = (lane & o) != 0;
-#pragma unroll
-                for (int i = 0; i < EB / 8; ++i) {
-                    if (i < n) {
-                        const float send = up ? acc[i] : acc[i + n];
-                        const float keep = up ? acc[i + n] : acc[i];
-                        acc[i] = keep + (o == 8 ? __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(send), 0x128, 0xf, 0xf, false))
-                                                : __shfl_xor(send, o));
-                    }
-                }
-            } else {
-                acc[0] = o == 2 ? pair_sum<2>(acc[0]) : o == 1 ? pair_sum<1>(acc[0]) : acc[0] + __shfl_xor(acc[0], o);
-            }
-        }
+        fold_rows<EB / 4, 8>(acc, lane);
         const int e = lane >> SH;
         if ((lane & ((1 << SH) - 1)) == 0 && e < E) lg[tt * lgs + e] = acc[0] + (br ? to_f32(br[e]) : 0.f);
     }

@@ -62,3 +62,18 @@ def test_whole_row_kernels_with_k_slices(half, tmp_path):
             assert re.search(r"ScratchSize \[bytes/lane\]: 0 ", part), part.split("\n")[0]
             found += 1
     assert found == 6
+
+
+# The router's partial sums (up to 64 a lane) stay in registers
+@pytest.mark.parametrize("half", ["bf16", "f16"])
+def test_router_without_scratch(half, tmp_path):
+    cmd = ["hipcc"] + build.FLAGS + (["-DSF_HALF_F16"] if half == "f16" else []) + ["--cuda-device-only", "-Rpass-analysis=kernel-resource-usage",
+           "-c", os.path.join(build.CSRC, "moe.hip"), "-o", str(tmp_path / "a.o")]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    found = 0
+    for part in r.stderr.split("Function Name: ")[1:]:
+        if "moe_router_kernel" in part.split("\n")[0]:
+            assert re.search(r"ScratchSize \[bytes/lane\]: 0 ", part), part.split("\n")[0]
+            found += 1
+    assert found == 16
