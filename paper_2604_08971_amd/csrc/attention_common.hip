@@ -214,8 +214,8 @@ struct Fill {
 
 // The thread's share of the context vector (VEC consecutive elements), read ahead of the selection, and the rows it writes:
 // kept[i] != 0: row i < L is active.  Packed samples also own the padding rows behind their tokens (ext[b] >= the
-// sample's length; rows at or beyond L are padding).
-template <int NT, int VEC, class T>
+// sample's length; rows at or beyond L are padding).  PART: the context vector follows with mean_of().
+template <int NT, int VEC, class T, bool PART = false>
 struct HeadFill {
     typedef __attribute__((ext_vector_type(VEC))) T vec;
     vec v;
@@ -227,7 +227,7 @@ struct HeadFill {
         step = NT / qv;
         if (!f.O || (int)threadIdx.x >= step * qv) return;
         rows = f.ext ? f.ext[b] : L;
-        if (!f.part) {
+        if constexpr (!PART) {
             const float *ctx = f.stats + (((int64_t)b * f.nG + group(f, b, h)) * 2 + 1) * f.dh + c * VEC;
 #pragma unroll
             for (int t = 0; t < VEC; ++t) v[t] = from_f32<T>(ctx[t]);
@@ -274,7 +274,8 @@ __global__ __launch_bounds__(256) void fill_rows_kernel(int nH, int L, Fill<T> f
 // sample without a key to score by (n_keys), and `out` then receives it.
 struct ScoreParts { const float *score; int64_t stride; int n, H; const int32_t *n_keys; float scale; float *out; int outH; };     // H: heads per sample
 
-template <int NT, int VEC, class T>
+// PART: fill.part is there, in an instance of its own (a call without it waited for the context vector where it asked: 0.1 to 0.3 us).
+template <int NT, int VEC, class T, bool PART>
 __global__ __launch_bounds__(NT) void select_kernel(
     ScoreParts sc, const uint8_t *__restrict__ key_valid, int nH, int L,
     int U, const int32_t *__restrict__ u_active, int32_t *__restrict__ sel, int selH, int32_t *__restrict__ slot,
@@ -288,10 +289,10 @@ __global__ __launch_bounds__(NT) void select_kernel(
     const int64_t m0 = ((int64_t)b * sc.H + h) * L;
     int32_t *sl = slot ? slot + (int64_t)bh * L : nullptr;      // only the active-row projection reads it
     int32_t *se = sel + ((int64_t)b * selH + h) * U;
-    HeadFill<NT, VEC, T> hf(fill, b, h, L);
-    __shared__ float ctx[256];
-    if (fill.part && threadIdx.x < fill.dh) {                   // with a key mask only: its count orders these writes
-        const float *p = fill.part + ((int64_t)b * fill.nG + HeadFill<NT, VEC, T>::group(fill, b, h)) * fill.parts * fill.dh + threadIdx.x;
+    HeadFill<NT, VEC, T, PART> hf(fill, b, h, L);
+    __shared__ float ctx[PART ? 256 : 1];
+    if (PART && threadIdx.x < fill.dh) {                        // with a key mask only: its count orders these writes
+        const float *p = fill.part + ((int64_t)b * fill.nG + hf.group(fill, b, h)) * fill.parts * fill.dh + threadIdx.x;
         // in eight chains: one of 28 (1777 keys of mean 1) errs by 6.8e-8 of the sum, these by 2.9e-8, the statistics launch by 4.9e-8
         float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         for (int i = 0; i < fill.parts; i += 8) {
@@ -321,7 +322,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
         c += ok;
     }
     const int n_ok = kv ? block_sum<NT>(c, red) : L;
-    if (fill.part) hf.mean_of(fill, ctx, n_ok);
+    if constexpr (PART) hf.mean_of(fill, ctx, n_ok);
     // u_active: this sample's own number of active queries (samples of different length in one batch)
     const int k = min(u_active ? min(max(u_active[b], 0), U) : U, n_ok);
     if (k == 0) {
@@ -870,14 +871,16 @@ int32_t attention_forward(int dtype, const AttnArgs &a, hipStream_t st)
         // get 1024 threads
         const bool wide = a.L >= 2048 || (a.L >= 512 && BH <= 256);
 #define SF_SELECT_ARGS(NT) dim3(BH), dim3(NT), key_bytes, st, parts, a.key_valid, a.nH, a.L, a.U, a.u_active, sel, selH, slot, a.act_bits
-#define SF_SELECT_LAUNCH(VEC, T, F)                                                                              \
+#define SF_SELECT_LAUNCH(VEC, T, PART, F)                                                                        \
     do {                                                                                                         \
-        if (wide) hipLaunchKernelGGL((select_kernel<1024, VEC, T>), SF_SELECT_ARGS(1024), F);                     \
-        else hipLaunchKernelGGL((select_kernel<256, VEC, T>), SF_SELECT_ARGS(256), F);                            \
+        if (wide) hipLaunchKernelGGL((select_kernel<1024, VEC, T, PART>), SF_SELECT_ARGS(1024), F);               \
+        else hipLaunchKernelGGL((select_kernel<256, VEC, T, PART>), SF_SELECT_ARGS(256), F);                      \
     } while (0)
-        if (dtype != SF_BF16) SF_SELECT_LAUNCH(4, float, fill32);
-        else if (v8) SF_SELECT_LAUNCH(8, h16, fill16);
-        else SF_SELECT_LAUNCH(4, h16, fill16);
+        if (dtype != SF_BF16) SF_SELECT_LAUNCH(4, float, false, fill32);
+        else if (v8 && summed) SF_SELECT_LAUNCH(8, h16, true, fill16);
+        else if (v8) SF_SELECT_LAUNCH(8, h16, false, fill16);
+        else if (summed) SF_SELECT_LAUNCH(4, h16, true, fill16);
+        else SF_SELECT_LAUNCH(4, h16, false, fill16);
 #undef SF_SELECT_LAUNCH
 #undef SF_SELECT_ARGS
     }
